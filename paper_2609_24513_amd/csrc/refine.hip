@@ -1542,6 +1542,438 @@ __global__ __launch_bounds__(kBlock, SCHED == 1 ? 6 : 5) void k_trace(RefineArgs
   flush_stats(st, ra);
 }
 
+// ---- packet traversal of the default schedule (wave-per-pair) ---------------------
+//
+// One wave traces one surviving group: its 64 segments, one per lane, against
+// the target tree, depth first (a hit ends the pair, and the first hit is
+// found soonest by going down).  A fresh group starts below the root: lane
+// j W + d holds child d of second-level node j (all addressed from the root's
+// index alone), the children whose boxes meet the group's box are tested by
+// every lane and pushed.  Then one entry at a time: a node read in one burst
+// through the scalar cache, each present child tested by every lane; a leaf's
+// triangles likewise.
+//
+// Long runs are bound by vector instructions, short ones by the chain of
+// dependent loads of a group.  Against k_trace's form of the same walk
+// everything but the tests is scalar (one traversal in the code for popped
+// groups and handed-over subtrees, no spilled pointers, no 64-bit remainder a
+// pop, no cross-lane sums a group): 50,000 mixed pairs W = 8, L = 1 cull +
+// trace 677 -> 622 us, 2,000 touching pairs 319 -> 211 us, 4,999 nested pairs
+// 323 -> 260 us, 16,727 nucleus-vessel pairs 167 -> 150 us.  Measured slower:
+// taking up to 64 / W pending nodes at once (boxes one per lane, broadcast
+// when they meet the group box).  The latency of a step is shared by its
+// nodes, but the order is no longer depth first, hits come later and twice
+// the nodes and triangles are tested (touching pairs 1.7 times the time).
+
+__device__ __forceinline__ void push_node(WaveStack& s, int32_t ref, uint64_t m) {
+  if (s.top < kRegStack) {
+    s.ref = lane_write(ref, s.top, s.ref);
+    s.mlo = lane_write((int32_t)(uint32_t)m, s.top, s.mlo);
+    s.mhi = lane_write((int32_t)(uint32_t)(m >> 32), s.top, s.mhi);
+  } else if ((threadIdx.x & 63) == 0) {
+    s.lref[s.top - kRegStack] = ref;
+    s.lmask[s.top - kRegStack] = m;
+  }
+  ++s.top;
+}
+
+// Reciprocal direction of the slab test, from the hardware reciprocal (1 ulp):
+// t then carries a relative error of at most gamma_5 on either side, within
+// the 2^-19 that the slab test allows.  FP32-safe coordinates differ by 0 or
+// by 2^-63 ... 2^41, so neither operand nor result is subnormal.
+__device__ __forceinline__ void axis_rcp(float d, bool safe, float& inv, float& bias) {
+  const bool zero = d == 0.f;
+  inv = zero ? kZeroInv : __builtin_amdgcn_rcpf(d);
+  bias = zero ? kZeroBias : 0.f;
+  if (!safe) { inv = 0.f; bias = INFINITY; }
+}
+
+// Waits for a task of the block's list.  Returns false when no wave of the
+// block is on its queues or tracing a task and the list is drained (or, never
+// for a valid launch, after kHelpSpinLimit looks: status PR_E_DEVICE).
+__device__ bool take_task(BlockShare* sh, int32_t* status, int4& t, uint64_t& m) {
+  const int lane = threadIdx.x & 63;
+  for (uint32_t spin = 0; spin < kHelpSpinLimit; ++spin) {
+    const uint32_t tail = lds_load(&sh->tail), head = lds_load(&sh->head);
+    const uint32_t n = tail < kBlkTasks ? tail : kBlkTasks;
+    if (uni((int32_t)(head < n))) {
+      // announce the attempt before claiming: a wave deciding whether to
+      // leave reads the busy count before the list
+      if (lane == 0) __hip_atomic_fetch_add(&sh->busy, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+      uint32_t got = ~0u;
+      if (lane == 0) {
+        uint32_t h = lds_load(&sh->head);
+        for (int k = 0; k < 64; ++k) {
+          const uint32_t tl = lds_load(&sh->tail);
+          if (h >= (tl < kBlkTasks ? tl : kBlkTasks)) break;
+          uint32_t e = h;
+          if (__hip_atomic_compare_exchange_strong(&sh->head, &e, h + 1, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP)) {
+            got = h;
+            break;
+          }
+          h = e;
+        }
+      }
+      got = (uint32_t)uni((int32_t)got);
+      if (got == ~0u) {
+        if (lane == 0) __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        continue;
+      }
+      if (lane == 0) __hip_atomic_fetch_add(&sh->idle, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      // the slot was reserved by a wave of this block that writes it next
+      uint32_t ok = 0;
+      for (uint32_t w = 0; w < kHelpSpinLimit && !ok; ++w) {
+        ok = (uint32_t)uni((int32_t)__hip_atomic_load(&sh->ready[got], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+        if (!ok) __builtin_amdgcn_s_sleep(1);
+      }
+      if (!ok) {
+        if (lane == 0) __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        break;
+      }
+      const int4 e = sh->task[got];
+      t = make_int4(uni(e.x), uni(e.y), uni(e.z), uni(e.w));
+      m = uni64(sh->mask[got]);
+      return true;
+    }
+    // nothing to take: leave once no wave of the block is on its queues or
+    // tracing a task (read first) and the list is drained (read after)
+    if (uni((int32_t)(__hip_atomic_load(&sh->active, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u &&
+                      __hip_atomic_load(&sh->busy, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u))) {
+      const uint32_t tl = lds_load(&sh->tail);
+      if (uni((int32_t)(lds_load(&sh->head) >= (tl < kBlkTasks ? tl : kBlkTasks)))) return false;
+    }
+    __builtin_amdgcn_s_sleep(2);
+  }
+  if (lane == 0) atomicMin(status, (int32_t)PR_E_DEVICE);
+  return false;
+}
+
+// Survivors popped at a time from a queue of n entries that `waves` waves
+// drain, as a shift.  A wave holds a batch while others find the hits that
+// cancel it, and the last batches are the end of the run, so small batches
+// pay until a queue holds over a hundred entries a wave (2,000 touching
+// pairs: cull + trace 260 us with these limits halved, 211 us so; at a
+// further doubling and more 16,727 nucleus-vessel pairs go from 150 to
+// 172 us, the pops' own cost).
+__device__ __forceinline__ int pop_shift(uint32_t n, uint32_t waves) {
+  return n >= 128u * waves ? 3 : (n >= 32u * waves ? 2 : (n >= 8u * waves ? 1 : 0));
+}
+// Columns of the pop order: the slots of a pair, side by side in its queue,
+// are popped a 1/16th of the run apart (50,000 mixed pairs: 622 us; 4
+// columns 657 us, 64 columns 682 us).
+constexpr uint32_t kPopCols = 16;
+
+template <int W, int PREC>
+__global__ __launch_bounds__(kBlock, 6) void k_packet(RefineArgs ra) {
+  __shared__ int32_t s_ref[kWaves][lds_stack_cap<W>()];
+  __shared__ uint64_t s_mask[kWaves][lds_stack_cap<W>()];
+  __shared__ BlockShare s_share;
+  const int wv = uni((int32_t)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  if (threadIdx.x < kBlkTasks) s_share.ready[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) {
+    s_share.tail = 0u;
+    s_share.head = 0u;
+    s_share.idle = 0u;
+    s_share.active = kWaves;
+    s_share.busy = 0u;
+  }
+  __syncthreads();
+  const cptr_t<BlobHeader> ha = cview(reinterpret_cast<const BlobHeader*>(ra.blob_a));
+  const cptr_t<BlobHeader> hb = cview(reinterpret_cast<const BlobHeader*>(ra.blob_b));
+  if (ha->magic != kMagic || hb->magic != kMagic || ha->width != W || hb->width != W ||
+      ha->n_meshes != ra.n_meshes_a || hb->n_meshes != ra.n_meshes_b)
+    return;
+
+  uint64_t acc = 0;   // lane k: counter k of the wave's statistics
+  uint32_t accm = 0;  // lane k: maximum k
+  uint32_t n32 = 0, ngrid = 0;  // per lane: FP32-uncertain tests, those decided in place
+
+  // The wave's queues: its block's own first, then the others of its XCD (with
+  // fewer blocks than queues: blockIdx, blockIdx + gridDim, ...).  Their fill
+  // counts are read together, lane j for the j-th.
+  const uint32_t home = blockIdx.x % kQueues;
+  const bool few = gridDim.x < (unsigned)kQueues;
+  const int nq = few ? (int)((kQueues - 1 - home) / gridDim.x) + 1 : kQueues / kSlices;
+  uint32_t fill = 0;
+  if (lane < nq) {
+    const uint32_t c = few ? home + lane * gridDim.x : (home + lane * kSlices) % kQueues;
+    const uint64_t f = ra.surv_cnt[kCtrStride * c];
+    fill = (uint32_t)(f < ra.surv_cap ? f : ra.surv_cap);
+  }
+  uint64_t queues = ballot(fill != 0);  // queues not yet seen empty
+  // With fewer survivors on the XCD than two for each wave of its blocks, only
+  // some waves of a block pop; the others take the subtrees that those hand
+  // over (24 pairs of 320-triangle meshes, cull + trace: 33 us, 44 us with
+  // every wave popping, which leaves most blocks without work and the others
+  // without helpers).
+  if (ra.share && !few) {
+    const uint32_t total = wave_sum(fill), nblk = gridDim.x / kSlices;
+    const uint32_t poppers = (total + 2 * nblk - 1) / (2 * nblk);
+    if ((uint32_t)wv >= max(poppers, 1u)) queues = 0;
+  }
+  const uint32_t qwaves = gridDim.x * kWaves / kQueues + 1;
+
+  int4 ent = make_int4(0, 0, 0, 0);  // lane j: entry j of the popped batch
+  uint64_t todo = 0;                 // entries of the batch still to trace
+  int32_t helping = 0;               // 1: the queues are drained, tasks of the block's list come next
+  // Wave-uniform values that travel round the loops go through uni(): the
+  // compiler then keeps them, and the branches on them, on the scalar side.
+  for (;;) {
+    todo = uni64(todo);
+    queues = uni64(queues);
+    helping = uni(helping);
+    // ---- the next piece of work: a group, or a subtree of one handed over ----
+    int4 it;
+    uint64_t start = 0;
+    if (todo) {
+      const int j = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      it = make_int4(__builtin_amdgcn_readlane(ent.x, j), __builtin_amdgcn_readlane(ent.y, j),
+                     __builtin_amdgcn_readlane(ent.z, j), __builtin_amdgcn_readlane(ent.w, j));
+    } else if (queues) {
+      const int j = __builtin_ctzll(queues);
+      const uint32_t cid = few ? home + j * gridDim.x : (home + j * kSlices) % kQueues;
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)fill, j);
+      const int sh = pop_shift(n, qwaves);
+      const uint32_t slots = (n + (1u << sh) - 1) >> sh;
+      const uint32_t rows = (slots + kPopCols - 1) / kPopCols;
+      unsigned long long k0 = 0;
+      if (lane == 0) k0 = atomicAdd(ra.surv_pop + kCtrStride * cid, 1ull);
+      const uint32_t k = (uint32_t)uni64(k0);
+      if (k >= rows * kPopCols) {
+        queues &= queues - 1;
+        continue;
+      }
+      // pop k takes slot (k mod rows) kPopCols + k / rows: the queue holds each
+      // pair's groups side by side, and a hit found in one of them cancels
+      // those popped a column later
+      uint32_t col = 0;
+      for (uint32_t b = rows; k >= b; b += rows) ++col;
+      const uint32_t slot = (k - col * rows) * kPopCols + col;
+      if (slot >= slots) continue;
+      const uint32_t e0 = slot << sh;
+      const uint32_t cnt = min(1u << sh, n - e0);
+      bool open = false;
+      if ((uint32_t)lane < cnt) {
+        ent = ra.surv[(int64_t)cid * ra.surv_cap + e0 + lane];
+        // groups of pairs already decided are dropped before their segments load
+        open = load_state(ra.state + (ent.y >> 1)) == 0u;
+      }
+      todo = ballot(open);
+      continue;
+    } else {
+      if (!ra.share) break;
+      if (!helping) {
+        helping = 1;
+        if (lane == 0) {
+          __hip_atomic_fetch_add(&s_share.idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&s_share.active, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+      if (!uni(take_task(&s_share, ra.status, it, start) ? 1 : 0)) break;
+    }
+
+    // ---- trace it ----
+    const int32_t gc = uni(it.x), unit = uni(it.y), ref0 = uni(it.z), word = uni(it.w);
+    start = uni64(start);
+    const bool dirb = (unit & 1) != 0;
+    const bool safe = (word & 256) != 0;
+    const int32_t live = word & 0xff;
+    const int32_t n_nodes = (int32_t)((uint32_t)word >> 11);
+    // source and target sections, read from the headers through the scalar cache
+    const char* const sblob = dirb ? ra.blob_b : ra.blob_a;
+    const char* const tblob = dirb ? ra.blob_a : ra.blob_b;
+    const cptr_t<BlobHeader> hs = cview(reinterpret_cast<const BlobHeader*>(sblob));
+    const cptr_t<BlobHeader> ht = cview(reinterpret_cast<const BlobHeader*>(tblob));
+    const char* const tnodes = tblob + ht->off_node;
+    const float* const ttris = reinterpret_cast<const float*>(tblob + ht->off_tri);
+    uint32_t* const pstate = ra.state + (unit >> 1);
+    const bool fresh = start == 0;
+    const uint64_t m0 = fresh ? (live >= 64 ? ~0ull : (1ull << live) - 1ull) : start;
+    const bool below = fresh && n_nodes > 1;
+    const uint32_t decided = load_state(pstate);  // by another wave, since the entry was popped
+    const float* sp = reinterpret_cast<const float*>(sblob + hs->off_seg) + (int64_t)gc * (6 * kChunk);
+    const f3 p{sp[lane], sp[kChunk + lane], sp[2 * kChunk + lane]};
+    const f3 q{sp[3 * kChunk + lane], sp[4 * kChunk + lane], sp[5 * kChunk + lane]};
+    float e[6];
+    int32_t eref = kEmpty, rref = kEmpty;
+    if (below) {
+      const int j = min(lane / W, min(W, n_nodes - 1) - 1);
+      const float* nd = reinterpret_cast<const float*>(tnodes + sizeof(Node<W>) * ((int64_t)ref0 + 1 + j));
+#pragma unroll
+      for (int a = 0; a < 6; ++a) e[a] = nd[a * W + lane % W];
+      eref = reinterpret_cast<const int32_t*>(nd)[6 * W + lane % W];
+      rref = reinterpret_cast<const int32_t*>(tnodes + sizeof(Node<W>) * (int64_t)ref0)[6 * W + lane % W];
+    }
+    float cb[6];
+    {
+      const cptr_t<float> cbp = cview(reinterpret_cast<const float*>(sblob + hs->off_cbox)) + 8 * (int64_t)gc;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) cb[k] = cbp[k];
+    }
+    if (uni((int32_t)decided)) {
+      if (helping && lane == 0) {
+        __hip_atomic_fetch_add(&s_share.idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&s_share.busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      continue;
+    }
+    Ray r;
+    r.px = p.x; r.py = p.y; r.pz = p.z;
+    axis_rcp(q.x - p.x, safe, r.ix, r.bx);
+    axis_rcp(q.y - p.y, safe, r.iy, r.by);
+    axis_rcp(q.z - p.z, safe, r.iz, r.bz);
+    WaveStack stk;
+    stk.ref = 0; stk.mlo = 0; stk.mhi = 0;
+    stk.lref = s_ref[wv]; stk.lmask = s_mask[wv]; stk.top = 0;
+    uint32_t visits = 0, leaf_tris = 0, tests = 0;
+    int32_t from_root = 1;
+    if (below) {
+      // second-level nodes are the root's inner children only; a root with a
+      // leaf child (small meshes) starts at the root itself, as a group that
+      // meets more entries than the stack's bound allows
+      const uint32_t inner = (uint32_t)__popcll(ballot(lane < W && rref >= 0 && rref != kEmpty));
+      uint64_t f = ballot(lane < (int)inner * W && eref != kEmpty && meet6(cb, e[0], e[1], e[2], e[3], e[4], e[5]));
+      if (!ballot(rref < 0) && __popcll(f) <= frontier_start_max<W>()) {
+        from_root = 0;
+        // visits: the second-level nodes whose child boxes are tested here
+#pragma unroll
+        for (int i = 0; i < W; ++i) visits += ((f >> (i * W)) & ((1ull << W) - 1ull)) ? 1u : 0u;
+        while (f) {
+          stk.top = uni(stk.top);
+          const int k = __builtin_ctzll(f);
+          f = uni64(f & (f - 1));
+          const uint64_t m = ballot(slab(r, lane_f(e[0], k), lane_f(e[1], k), lane_f(e[2], k), lane_f(e[3], k),
+                                         lane_f(e[4], k), lane_f(e[5], k))) & m0;
+          if (m) push_node(stk, __builtin_amdgcn_readlane(eref, k), m);
+        }
+      }
+    }
+    if (uni(from_root)) push_node(stk, ref0, m0);
+    const cptr_t<Node<W>> nodes = cview(reinterpret_cast<const Node<W>*>(tnodes));
+    uint32_t poll = 0;
+    int step = 0;
+    int32_t done = 0;  // the pair is decided (or the walk given up)
+    while (uni(stk.top) > 0) {
+      stk.top = uni(stk.top) - 1;
+      int32_t ref;
+      uint64_t nm;
+      if (stk.top < kRegStack) {
+        ref = __builtin_amdgcn_readlane(stk.ref, stk.top);
+        nm = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(stk.mhi, stk.top) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane(stk.mlo, stk.top);
+      } else {
+        ref = uni(stk.lref[stk.top - kRegStack]);
+        nm = uni64(stk.lmask[stk.top - kRegStack]);
+      }
+      ref = uni(ref);
+      nm = uni64(nm);
+      // the pair's state is polled every 8 entries, the load issued one poll ahead
+      step = uni(step + 1);
+      if ((step & 7) == 0) {
+        if (uni((int32_t)poll)) break;
+        poll = load_state(pstate);
+      }
+      // waves of the block waiting for work, beyond the tasks already waiting
+      if (ra.share && stk.top >= 1 && stk.top <= kRegStack) {
+        const uint32_t idle = lds_load(&s_share.idle), tail = lds_load(&s_share.tail), head = lds_load(&s_share.head);
+        const uint32_t n = tail < kBlkTasks ? tail : kBlkTasks;
+        const uint32_t waiting = n > head ? n - head : 0u;
+        const int want = uni((int32_t)(tail < kBlkTasks && idle > waiting ? idle - waiting : 0u));
+        if (want > 0) share_out(stk, &s_share, gc, unit, word & 0x1ff, want < stk.top ? want : stk.top);
+      }
+      if (ref < 0) {
+        // a leaf: the lanes of the mask test their segment against its triangles
+        const int32_t first = ~ref >> 3;
+        const int cnt = (~ref & 7) + 1;
+        const bool on = (nm >> lane) & 1ull;
+        leaf_tris = (uint32_t)uni((int32_t)leaf_tris + cnt);
+        tests = (uint32_t)uni((int32_t)tests + __popcll(nm) * cnt);
+        uint32_t hitbits = 0, ambbits = 0;
+        const cptr_t<float> tp = cview(ttris) + 9 * (int64_t)first;
+        // the next triangle's coordinates load while one is tested (the array
+        // has three triangles of slack at its end)
+        float tv[9], tn[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) tv[k] = tp[k];
+#pragma unroll 1
+        for (int t = 0; t < cnt; t = uni(t + 1)) {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) tn[k] = tp[9 * (t + 1) + k];
+          const f3 ta{tv[0], tv[1], tv[2]}, tb{tv[3], tv[4], tv[5]}, tc{tv[6], tv[7], tv[8]};
+          const int res = on ? leaf_test<PREC>(p, q, ta, tb, tc, safe) : kMiss;
+          hitbits |= (res == kHit ? 1u : 0u) << t;
+          ambbits |= (res == kAmbig ? 1u : 0u) << t;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) tv[k] = tn[k];
+        }
+        if (ballot(ambbits != 0)) {
+          if (ambbits) grid_tier<PREC>(p, q, ttris, first, 1, hitbits, ambbits, n32, ngrid);
+        }
+        if (ballot(hitbits != 0)) {
+          if (lane == 0) mark_true(pstate);
+          break;
+        }
+        if (ballot(ambbits != 0)) {
+          WaveStats over;
+#pragma unroll 1
+          for (int t = 0; t < cnt && !uni(done); t = uni(t + 1)) {
+            const bool amb = (ambbits >> t) & 1u;
+            if (!ballot(amb)) continue;
+            // the queue is full: the whole pair is decided again later in FP64/exact
+            if (!defer_tests(ra, amb, unit >> 1, unit & 1, gc * kChunk + lane, first + t, over)) done = 1;
+          }
+          acc += over.acc;
+          if (uni(done)) break;
+        }
+        continue;
+      }
+      NodeRegs<W> nd;
+      load_node<W>(nd, nodes + ref);
+      visits = (uint32_t)uni((int32_t)visits + 1);
+      if (stk.top + W > stack_cap<W>()) {  // cannot happen for a valid blob (depth <= kMaxDepth)
+        if (lane == 0) atomicMin(ra.status, (int32_t)PR_E_UNSUPPORTED);
+        break;
+      }
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        if (nd.ch[c] == kEmpty) continue;  // uniform: empty slots cost no vector work
+        uint64_t m = ballot(slab(r, nd.lo[0][c], nd.lo[1][c], nd.lo[2][c], nd.hi[0][c], nd.hi[1][c], nd.hi[2][c])) & nm;
+        if (!safe && !box_meet(cb, nd.lo[0][c], nd.lo[1][c], nd.lo[2][c], nd.hi[0][c], nd.hi[1][c], nd.hi[2][c])) m = 0;
+        if (m) push_node(stk, nd.ch[c], m);
+      }
+    }
+    // ---- statistics ----
+    int32_t inc = 0;
+    if (fresh) {
+      inc = lane_write(live, S_SEG, inc);
+      inc = lane_write(1, S_GTRAV, inc);
+    }
+    inc = lane_write((int32_t)visits, S_VISIT, inc);
+    inc = lane_write((int32_t)leaf_tris, S_TRIF, inc);
+    inc = lane_write((int32_t)tests, S_TESTS, inc);
+    if (PREC == 1) inc = lane_write((int32_t)tests, S_EXACT, inc);
+    acc += (uint32_t)inc;
+    int32_t mx = 0;
+    mx = lane_write((int32_t)visits, S_MAXV, mx);
+    mx = lane_write((int32_t)leaf_tris, S_MAXL, mx);
+    accm = max(accm, (uint32_t)mx);
+    if (helping && lane == 0) {
+      __hip_atomic_fetch_add(&s_share.idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&s_share.busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+  if (PREC != 1 && ballot(n32 != 0)) {
+    const uint32_t a = wave_sum(n32), g = wave_sum(ngrid);
+    if (lane == S_AMB32) acc += a;
+    if (lane == S_EXACT) acc += g;
+  }
+  WaveStats st;
+  st.acc = lane == S_MAXV || lane == S_MAXL ? (uint64_t)accm : acc;
+  flush_stats(st, ra);
+}
+
 // Persistent pass, optional phase 3: the stacks that phase 2 handed over, one task (node,
 // lane mask of its group) at a time, popped like the survivors: task list of
 // the block first, then the other lists of its XCD.
@@ -1856,7 +2288,11 @@ int launch(RefineArgs& ra, const pr_refine_params* prm, hipStream_t s) {
     const int cus = cu_count(dev);
     // the automatic schedule with an all-zero table is the packet traversal
     const int sched = prm->schedule == 0 && ra.seg_table == 0u ? 1 : prm->schedule;
-    const int per = sched == 1   ? blocks_per_cu<k_trace<W, PREC, 1>>(dev)
+    // the packet traversal in batches of nodes; k_trace keeps the wave-per-pair form for
+    // the LDS-first stack and for the continuation pass
+    const bool packet = sched == 1 && !ra.lds_stack && ra.budget == 0;
+    const int per = packet       ? blocks_per_cu<k_packet<W, PREC>>(dev)
+                    : sched == 1 ? blocks_per_cu<k_trace<W, PREC, 1>>(dev)
                     : sched == 2 ? blocks_per_cu<k_trace<W, PREC, 2>>(dev)
                                  : blocks_per_cu<k_trace<W, PREC, 0>>(dev);
     const int per_cull = blocks_per_cu<k_cull<W, PREC>>(dev);
@@ -1872,7 +2308,8 @@ int launch(RefineArgs& ra, const pr_refine_params* prm, hipStream_t s) {
     int r = launch_ra(k_cull<W, PREC>, cus * per_cull, s, ra, eb, nullptr);
     hipEvent_t et = ra.budget > 0 ? nullptr : ee;
     if (r == PR_OK) {
-      if (sched == 1) r = launch_ra(k_trace<W, PREC, 1>, blocks, s, ra, nullptr, et);
+      if (packet) r = launch_ra(k_packet<W, PREC>, blocks, s, ra, nullptr, et);
+      else if (sched == 1) r = launch_ra(k_trace<W, PREC, 1>, blocks, s, ra, nullptr, et);
       else if (sched == 2) r = launch_ra(k_trace<W, PREC, 2>, blocks, s, ra, nullptr, et);
       else r = launch_ra(k_trace<W, PREC, 0>, blocks, s, ra, nullptr, et);
     }
