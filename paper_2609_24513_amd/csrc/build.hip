@@ -1,28 +1,32 @@
 // build_mesh_bvh: per-mesh wide BVHs and unique-edge segments for a dataset.
 //
-// Steps (all on the device, one batched pass over every mesh):
-//  1. validate faces (ids in range, finite coordinates, not exactly collinear),
-//     exact triangle boxes, per-mesh exact boxes and FP32-safe flags;
-//  2. Morton codes of triangle centroids relative to their mesh box, keyed
-//     by mesh id, sorted (one radix sort for all meshes);
-//  3. per mesh, a binary radix tree over the sorted codes (Karras 2012,
+// Steps (all on the device, one batched pass over every mesh; a mesh's faces
+// are handled in chunks, one block each, so that large and small meshes load
+// the chip alike):
+//  1. plan: per mesh, where its chunks, sort cells and node slots begin;
+//  2. validate faces (ids in range, finite coordinates, not exactly
+//     collinear), per-mesh exact boxes and FP32-safe flags;
+//  3. sort the triangles of each mesh by the Morton code of their centroid
+//     (ties by face index), and its half-edges by the Morton code of their
+//     midpoint (ties by vertex ids): a counting pass over cells (the code's
+//     top bits), then units of consecutive cells that fit LDS are sorted
+//     there.  Copies of one edge share midpoint and ids, so they end up side
+//     by side and are merged in the same kernel (Section 3.1: duplicate edges
+//     of one mesh are merged);
+//  4. per mesh, a binary radix tree over the sorted codes (Karras 2012,
 //     "Maximizing parallelism in the construction of BVHs, octrees, and k-d
-//     trees"), ties broken by position;
-//  4. bottom-up refit with exact min/max boxes;
+//     trees"), ties broken by position, with exact min/max boxes bottom up:
+//     the nodes that lie inside a chunk in LDS, the others after them;
 //  5. collapse to width W: each wide node starts from a binary node and
 //     repeatedly opens the child with the largest box surface among those
 //     holding more than L triangles, until it has W children; children of at
 //     most L triangles become leaves (a Karras subtree is a contiguous range
 //     of the sorted order, so a leaf is a range of leaf-order triangles);
-//  6. unique edges (Section 3.1: duplicate edges of one mesh are merged), as
-//     (min, max) global vertex id keys, sorted and deduplicated, then ordered
-//     inside each mesh by the Morton code of their midpoint so that a group of
-//     64 consecutive segments is spatially coherent, and written as FP32
-//     endpoints in groups of 64 with the exact box of each group.
+//  6. the unique edges as FP32 endpoints in groups of 64 consecutive ones,
+//     with the exact box of each group.
 #pragma clang fp contract(off)
 
 #include <hip/hip_runtime.h>
-#include <hipcub/hipcub.hpp>
 
 #include "scan.h"
 
@@ -36,9 +40,12 @@ namespace pr {
 namespace {
 
 constexpr int kBlock = 256;
-// threads of the one-block-per-mesh kernels (refit, collapse): the largest
-// mesh's block is the end of those launches
-constexpr int kMeshBlock = 1024;
+constexpr int kTreeChunk = 512;    // sorted positions (and faces) of one tree block
+constexpr int kUnit = 1024;        // sort unit: the cells that start in this many items
+constexpr int kUnitCap = 2048;     // items a unit may hold to be sorted in LDS
+constexpr int kBins = 2048;        // bins of the LDS sort
+constexpr int kMaxRoots = 128;     // subtrees that tile a chunk: at most two per tree level (62 levels)
+constexpr int kSubtree = kTreeChunk;  // binary subtrees of at most this many triangles are collapsed by one wave
 
 __device__ __forceinline__ uint32_t spread10(uint32_t v) {
   v &= 0x3ffu;
@@ -71,6 +78,42 @@ __device__ __forceinline__ f3 load_v(const float* verts, int64_t g) {
   return f3{verts[3 * g], verts[3 * g + 1], verts[3 * g + 2]};
 }
 
+// Per mesh: its faces (none when its offsets are inconsistent: the build then
+// fails through the status word) and the first of its entries in each table.
+struct MeshPlan {
+  int64_t v0;       // first vertex
+  int32_t nv;       // vertices
+  int32_t f0;       // first face
+  int32_t n;        // faces
+  int32_t tchunk;   // tree chunks of kTreeChunk faces
+  int32_t tunit;    // triangle sort units of kUnit faces
+  int32_t eunit;    // edge sort units of kUnit half-edges
+  int32_t tcell;    // triangle cells
+  int32_t ecell;    // edge cells
+  int32_t node;     // node slots (nodes_bound of them)
+  int32_t rchunk;   // root lists: one per chunk of a mesh of several
+};
+
+// A binary node: the boxes of its two children and the sorted positions
+// [lo, split] and [split + 1, hi] that they cover (relative to the mesh).  The
+// child over one position is a leaf; an inner left child is node `split`, an
+// inner right child node split + 1.
+struct alignas(64) BinNode {
+  float box[2][6];
+  int32_t lo, split, hi, pad;
+};
+
+// A subtree whose parent lies outside its chunk: its box and its node (or
+// ~position for a single triangle).
+struct RootRec {
+  float box[6];
+  int32_t ref, pad;
+};
+
+struct SubItem {
+  int32_t mesh, node, slot, depth;
+};
+
 struct BuildArgs {
   const float* verts;
   const int64_t* vert_off;
@@ -94,124 +137,176 @@ struct BuildArgs {
   int64_t node_cap, chunk_cap;
   // workspace
   int32_t* status;       // min bad face (INT_MAX if none)
-  int32_t* face_mesh;    // [F]
-  float* tbox;           // [F][6]
-  uint8_t* fsafe;        // [F]
-  uint64_t* key0;        // [F]
-  uint64_t* key1;        // [F]
-  int32_t* val0;         // [F]
-  int32_t* val1;         // [F]
-  int32_t* left;         // [F] binary children (bit 31: leaf, payload: global sorted position)
-  int32_t* right;        // [F]
-  int32_t* parent;       // [F] parent of internal node g
-  int32_t* lparent;      // [F] parent of leaf position g
-  float* nbox;           // [F][6]
-  int32_t* nleaf;        // [F] triangles under each binary node
-  int32_t* nfirst;       // [F]
-  uint32_t* visit;       // [F]
-  int64_t* nbound;       // [M+1] scanned node bounds
-  int32_t* stk;          // [F][3] collapse work stacks
-  uint64_t* ekey0;       // [3F]
-  uint64_t* ekey1;       // [3F]
-  int32_t* eval0;        // [3F]
-  int32_t* eval1;        // [3F]
-  int32_t* eflag;        // [3F + 1]
-  int32_t* epos;         // [3F + 1]
-  int32_t* estart;       // [M]
-  int32_t* eend;         // [M]
-  int64_t* cscan;        // [M+1]
-  int32_t* meshctr;      // [4] misc device counters: [0] lowest, [1] highest coordinate bit exponent
-  uint8_t* mesh_ok;      // [M] offsets of the mesh are consistent
-  uint64_t* ekey2;       // [3F] sorted (mesh, Morton) keys of unique edges
-  int64_t* nscan;        // [M+1] scanned node bounds
-  int64_t* chunk_scan;   // [M+1] scanned group counts
-  char* tnodes;          // [node_cap] nodes at bound-sized offsets, before compaction
-  int64_t* ncount;       // [M+1] nodes used per mesh, then scanned
-  int64_t* tsum;         // tile sums of the prefix sums
-  int32_t* morder;       // [M] meshes in decreasing size class (the per-mesh kernels' order)
-  int32_t* mcnt;         // [kSizeClasses][order blocks] meshes of each class in each block
-  int64_t* mpos;         // the same, scanned
+  int32_t* exps;         // [2] lowest, highest coordinate bit exponent
+  int32_t* ctr;          // [0] meshes in `big`, [1] entries of `subs`
+  MeshPlan* plan;        // [M + 1], totals at [M]
+  uint32_t* mm;          // [M][8] ordered box bits (lo xyz, hi xyz), [6] != 0: a coordinate out of the safe range
+  int32_t* used;         // [M] node slots in use
+  int32_t* depth;        // [M] deepest node level
+  int32_t* nedges;       // [M] unique edges
+  int64_t* groups;       // [M + 1] group counts, then scanned
+  int64_t* etotal;       // [1] unique edges of the dataset
+  int32_t* big;          // [M] meshes of more than kSubtree triangles
+  int32_t* tmap;         // [tchunk] mesh of each tree chunk
+  int32_t* tumap;        // [tunit] mesh of each triangle unit
+  int32_t* emap;         // [eunit] mesh of each edge unit
+  uint32_t* hist;        // triangle cells, then edge cells: counts
+  uint32_t* start;       // their exclusive scan
+  int64_t cells_t, cells_all;  // capacity of the triangle cells, of both
+  int64_t* tsum;         // tile sums of the scan
+  uint32_t* key;         // [F] Morton code of each face
+  uint32_t* rank;        // [F] place within its cell
+  uint32_t* pk;          // [F] codes in cell order
+  uint32_t* pv;          // [F] faces in cell order
+  uint32_t* sk;          // [F] sorted codes
+  uint32_t* sv;          // [F] sorted faces
+  uint32_t* ekey;        // [3F] Morton code of each half-edge's midpoint
+  uint32_t* erank;       // [3F]
+  uint32_t* epk;         // [3F] codes, lower and higher vertex ids in cell order
+  uint32_t* epl;
+  uint32_t* eph;
+  uint32_t* ul;          // [3F] unique edges of each unit, at its first item
+  uint32_t* uh;
+  int32_t* ustart;       // [eunit] first item of each unit (from the mesh's first)
+  int32_t* ucount;       // [eunit] unique edges of each unit
+  int32_t* uoff;         // [eunit] unique edges of the mesh before the unit
+  BinNode* bin;          // [F]
+  int32_t* parent;       // [F] parent of an inner node whose parent spans chunks
+  int32_t* lparent;      // [F] the same of a single triangle
+  uint32_t* visit;       // [F] children of a node that spans chunks that are done
+  RootRec* roots;        // [rchunk][kMaxRoots]
+  int32_t* nroots;       // [rchunk]
+  int32_t* items;        // [F][3] work lists of the top collapse (node, slot, depth)
+  SubItem* subs;         // subtrees for the wave-wise collapse
 };
 
-// The per-mesh kernels (refit, collapse, node copy) give each mesh one
-// block, and a launch ends with its largest mesh; blocks therefore take the
-// meshes in decreasing size class (powers of two of the face count), index
-// order within a class: a stable counting sort of kMeshOrdTile meshes per
-// block (class counts, a scan, then each mesh's place).
-constexpr int kSizeClasses = 8;
-constexpr int kMeshOrdTile = 1024;  // meshes per block of the order kernels (4 per thread)
+// ---- ordered float bits (min and max by integer atomics) -----------------------
 
-// ---- mesh order ----------------------------------------------------------------
-
-__device__ __forceinline__ int size_class(const BuildArgs& a, int64_t m) {
-  const int64_t n = a.face_off[m + 1] - a.face_off[m];
-  const int lg = n > 0 ? 63 - __builtin_clzll((uint64_t)n) : 0;
-  return lg >= 16 ? 0 : (lg <= 9 ? kSizeClasses - 1 : 16 - lg);
+__device__ __forceinline__ uint32_t to_ordered(float x) {
+  const uint32_t b = __float_as_uint(x);
+  return b & 0x80000000u ? ~b : b | 0x80000000u;
+}
+__device__ __forceinline__ float from_ordered(uint32_t u) {
+  return __uint_as_float(u & 0x80000000u ? u & 0x7fffffffu : ~u);
 }
 
-// Per thread: the classes of its 4 meshes (kSizeClasses for none) and its
-// count of each class, 16 bits a class (classes 0-3 in w0, 4-7 in w1).
-__device__ __forceinline__ void mesh_items(const BuildArgs& a, int* cls, uint64_t& w0, uint64_t& w1) {
-  const int64_t m0 = blockIdx.x * (int64_t)kMeshOrdTile + 4 * (int64_t)threadIdx.x;
-  w0 = 0;
-  w1 = 0;
+// ---- step 1: plan ----------------------------------------------------------------
+
+// Cells of a sort of n items, as a power of two: one while a unit holds them
+// all, then an eighth to a quarter of n.  A closed surface meets about
+// cells^(2/3) of them, so an occupied cell of 10^5 items holds some 10^2.
+__host__ __device__ __forceinline__ int cell_bits(int64_t n) {
+  if (n <= kUnitCap) return 0;
+  if (n <= kUnitCap) return 0;
+  return 63 - __builtin_clzll((uint64_t)n) - 2;
+}
+
+__device__ __forceinline__ int32_t div_up(int64_t n, int d) { return (int32_t)((n + d - 1) / d); }
+
+// One block: the exclusive sums over the meshes of every table's entries.
+__global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
+  __shared__ int64_t s[16];
+  __shared__ int64_t s_run[7];
+  if (threadIdx.x < 7) s_run[threadIdx.x] = 0;
+  __syncthreads();
+  for (int64_t base = 0; base < a.n_meshes; base += 4096) {
+    MeshPlan p[4];
+    int64_t c[4][7], sum[7] = {0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = m0 + k < a.n_meshes ? size_class(a, m0 + k) : kSizeClasses;
-    cls[k] = c;
-    if (c < 4) w0 += 1ull << (16 * c);
-    else if (c < kSizeClasses) w1 += 1ull << (16 * (c - 4));
-  }
-}
-
-__global__ __launch_bounds__(256) void k_mesh_order_count(BuildArgs a, int64_t nb) {
-  __shared__ uint64_t s[4];
-  int cls[4];
-  uint64_t w0, w1;
-  mesh_items(a, cls, w0, w1);
-  const uint64_t t0 = block_sum<256>(w0, s), t1 = block_sum<256>(w1, s);
-  if (threadIdx.x < kSizeClasses) {
-    const uint64_t t = threadIdx.x < 4 ? t0 >> (16 * threadIdx.x) : t1 >> (16 * (threadIdx.x - 4));
-    a.mcnt[threadIdx.x * nb + blockIdx.x] = (int32_t)(t & 0xffffu);
-  }
-}
-
-__global__ __launch_bounds__(256) void k_mesh_order_place(BuildArgs a, int64_t nb) {
-  __shared__ uint64_t s[4];
-  int cls[4];
-  uint64_t w0, w1;
-  mesh_items(a, cls, w0, w1);
-  uint64_t t0, t1;
-  const uint64_t e0 = block_exclusive_sum<256>(w0, s, t0), e1 = block_exclusive_sum<256>(w1, s, t1);
-  const int64_t m0 = blockIdx.x * (int64_t)kMeshOrdTile + 4 * (int64_t)threadIdx.x;
-  uint32_t seen = 0;  // this thread's earlier meshes, 4 bits a class
+    for (int k = 0; k < 4; ++k) {
+      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
+      p[k] = MeshPlan{};
+      int64_t n = 0;
+      if (m < a.n_meshes) {
+        const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1];
+        const int64_t v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
+        bool ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
+        if (m == 0) ok = ok && f0 == 0 && v0 == 0;
+        if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
+        if (!ok) atomicMin(a.status, 0);
+        n = ok ? f1 - f0 : 0;
+        p[k].v0 = ok ? v0 : 0;
+        p[k].nv = ok ? (int32_t)(v1 - v0) : 0;
+        p[k].f0 = ok ? (int32_t)f0 : 0;
+        p[k].n = (int32_t)n;
+      }
+      c[k][0] = div_up(n, kTreeChunk);
+      c[k][1] = div_up(n, kUnit);
+      c[k][2] = div_up(3 * n, kUnit);
+      c[k][3] = m < a.n_meshes ? (int64_t)1 << cell_bits(n) : 0;
+      c[k][4] = m < a.n_meshes ? (int64_t)1 << cell_bits(3 * n) : 0;
+      c[k][5] = nodes_bound(n, a.width, a.leaf);
+      c[k][6] = n > kTreeChunk ? c[k][0] : 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = cls[k];
-    if (c >= kSizeClasses) continue;
-    const uint64_t before = c < 4 ? (e0 >> (16 * c)) & 0xffffu : (e1 >> (16 * (c - 4))) & 0xffffu;
-    a.morder[a.mpos[c * nb + blockIdx.x] + (int64_t)before + ((seen >> (4 * c)) & 0xfu)] = (int32_t)(m0 + k);
-    seen += 1u << (4 * c);
-  }
-}
-
-// ---- step 1 ---------------------------------------------------------------
-
-__global__ void k_face_mesh(BuildArgs a) {
-  for (int64_t m = blockIdx.x; m < a.n_meshes; m += gridDim.x) {
-    int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1];
-    int64_t v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
-    bool ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
-    if (m == 0) ok = ok && f0 == 0 && v0 == 0;
-    if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
-    if (threadIdx.x == 0) {
-      a.mesh_ok[m] = ok ? 1 : 0;
-      if (!ok) atomicMin(a.status, 0);
+      for (int q = 0; q < 7; ++q) sum[q] += c[k][q];
     }
-    if (!ok) continue;
-    for (int64_t f = f0 + threadIdx.x; f < f1; f += blockDim.x) a.face_mesh[f] = (int32_t)m;
+    int64_t at[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+      int64_t total;
+      const int64_t pre = block_exclusive_sum<1024>(sum[q], s, total);
+      at[q] = s_run[q] + pre;
+      __syncthreads();
+      if (threadIdx.x == 0) s_run[q] += total;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
+      p[k].tchunk = (int32_t)at[0];
+      p[k].tunit = (int32_t)at[1];
+      p[k].eunit = (int32_t)at[2];
+      p[k].tcell = (int32_t)at[3];
+      p[k].ecell = (int32_t)at[4];
+      p[k].node = (int32_t)at[5];
+      p[k].rchunk = (int32_t)at[6];
+      if (m < a.n_meshes) a.plan[m] = p[k];
+#pragma unroll
+      for (int q = 0; q < 7; ++q) at[q] += c[k][q];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    MeshPlan t{};
+    t.tchunk = (int32_t)s_run[0];
+    t.tunit = (int32_t)s_run[1];
+    t.eunit = (int32_t)s_run[2];
+    t.tcell = (int32_t)s_run[3];
+    t.ecell = (int32_t)s_run[4];
+    t.node = (int32_t)s_run[5];
+    a.plan[a.n_meshes] = t;
   }
 }
+
+// Everything that starts at a fixed value.
+__global__ void k_build_init(BuildArgs a) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = i0; i < a.cells_all; i += step) a.hist[i] = 0u;
+  for (int64_t i = i0; i < a.f_total; i += step) a.visit[i] = 0u;
+  for (int64_t i = i0; i < 8 * a.n_meshes; i += step) a.mm[i] = (i & 7) < 3 ? 0xffffffffu : 0u;
+  for (int64_t i = i0; i < a.n_meshes; i += step) a.depth[i] = 0;
+  if (i0 == 0) {
+    *a.status = INT_MAX;
+    a.exps[0] = INT_MAX;
+    a.exps[1] = INT_MIN;
+    a.ctr[0] = 0;
+    a.ctr[1] = 0;
+  }
+}
+
+// The mesh of every chunk and unit, one wave per mesh.
+__global__ __launch_bounds__(kBlock) void k_maps(BuildArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t m = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6; m < a.n_meshes; m += nw) {
+    const MeshPlan p = a.plan[m], q = a.plan[m + 1];
+    for (int32_t i = p.tchunk + lane; i < q.tchunk; i += 64) a.tmap[i] = (int32_t)m;
+    for (int32_t i = p.tunit + lane; i < q.tunit; i += 64) a.tumap[i] = (int32_t)m;
+    for (int32_t i = p.eunit + lane; i < q.eunit; i += 64) a.emap[i] = (int32_t)m;
+  }
+}
+
+// ---- step 2: faces and mesh boxes ------------------------------------------------
 
 // Exponents of the lowest and highest set bit of a finite non-zero FP32 value.
 __device__ __forceinline__ int bit_lo(float x) {
@@ -225,229 +320,720 @@ __device__ __forceinline__ int bit_hi(float x) {
   return e == 0 ? -149 + (31 - __builtin_clz(m)) : (int)e - 127;
 }
 
-__global__ void k_tri_prep(BuildArgs a) {
-  int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kBlock) void k_prep(BuildArgs a) {
+  __shared__ int s_lo[kBlock / 64], s_hi[kBlock / 64];
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
   int elo = INT_MAX, ehi = INT_MIN;  // bit exponents over this thread's coordinates
-  for (; f < a.f_total; f += (int64_t)gridDim.x * blockDim.x) {
-    int32_t m = a.face_mesh[f];
-    bool mok = a.mesh_ok[m];
-    int64_t v0 = mok ? a.vert_off[m] : 0, nv = mok ? a.vert_off[m + 1] - v0 : 0;
-    int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
-    bool bad = !mok;
-    for (int k = 0; k < 3; ++k) bad |= (id[k] < 0 || id[k] >= nv);
-    float* tb = a.tbox + 6 * f;
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  bool unsafe = false;
+  for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
+    const int64_t f = (int64_t)p.f0 + i;
+    const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
+    bool bad = false;
+    for (int k = 0; k < 3; ++k) bad |= id[k] < 0 || id[k] >= p.nv;
     if (bad) {
       atomicMin(a.status, (int32_t)f);
-      for (int k = 0; k < 3; ++k) { tb[k] = 0.f; tb[3 + k] = 0.f; }
-      a.fsafe[f] = 0;
+      unsafe = true;
       continue;
     }
-    f3 p0 = load_v(a.verts, v0 + id[0]), p1 = load_v(a.verts, v0 + id[1]), p2 = load_v(a.verts, v0 + id[2]);
-    float cs[9] = {p0.x, p0.y, p0.z, p1.x, p1.y, p1.z, p2.x, p2.y, p2.z};
-    bool fin = true, safe = true;
-    for (int k = 0; k < 9; ++k) { fin &= isfinite(cs[k]); safe &= safe_coord(cs[k]); }
-    for (int k = 0; k < 9; ++k)
-      if (fin && cs[k] != 0.f) {
-        elo = min(elo, bit_lo(cs[k]));
-        ehi = max(ehi, bit_hi(cs[k]));
-      }
+    const f3 p0 = load_v(a.verts, p.v0 + id[0]), p1 = load_v(a.verts, p.v0 + id[1]), p2 = load_v(a.verts, p.v0 + id[2]);
+    const float cs[9] = {p0.x, p0.y, p0.z, p1.x, p1.y, p1.z, p2.x, p2.y, p2.z};
+    bool fin = true;
+    for (int k = 0; k < 9; ++k) { fin &= isfinite(cs[k]); unsafe |= !safe_coord(cs[k]); }
     if (!fin) {
       atomicMin(a.status, (int32_t)f);
-      safe = false;
+      unsafe = true;
     } else {
+      for (int k = 0; k < 9; ++k)
+        if (cs[k] != 0.f) {
+          elo = min(elo, bit_lo(cs[k]));
+          ehi = max(ehi, bit_hi(cs[k]));
+        }
       // exactly collinear iff all three coordinate-plane orientations vanish
       ExactCounters cnt{0};
-      bool degen = sign_orient2d(p0, p1, p2, 1, 2, cnt) == 0 && sign_orient2d(p0, p1, p2, 2, 0, cnt) == 0 &&
-                   sign_orient2d(p0, p1, p2, 0, 1, cnt) == 0;
+      const bool degen = sign_orient2d(p0, p1, p2, 1, 2, cnt) == 0 && sign_orient2d(p0, p1, p2, 2, 0, cnt) == 0 &&
+                         sign_orient2d(p0, p1, p2, 0, 1, cnt) == 0;
       if (degen) atomicMin(a.status, (int32_t)f);
     }
-    tb[0] = fminf(fminf(p0.x, p1.x), p2.x);
-    tb[1] = fminf(fminf(p0.y, p1.y), p2.y);
-    tb[2] = fminf(fminf(p0.z, p1.z), p2.z);
-    tb[3] = fmaxf(fmaxf(p0.x, p1.x), p2.x);
-    tb[4] = fmaxf(fmaxf(p0.y, p1.y), p2.y);
-    tb[5] = fmaxf(fmaxf(p0.z, p1.z), p2.z);
-    a.fsafe[f] = safe ? 1 : 0;
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = fminf(lo[k], fminf(fminf(cs[k], cs[3 + k]), cs[6 + k]));
+      hi[k] = fmaxf(hi[k], fmaxf(fmaxf(cs[k], cs[3 + k]), cs[6 + k]));
+    }
   }
-  // one atomic pair per wave (the grid is capped so that these stay few)
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int o = 32; o > 0; o >>= 1) {
     elo = min(elo, __shfl_xor(elo, o));
     ehi = max(ehi, __shfl_xor(ehi, o));
-  }
-  if ((threadIdx.x & 63) == 0 && elo != INT_MAX) {
-    atomicMin(a.meshctr + 0, elo);
-    atomicMax(a.meshctr + 1, ehi);
-  }
-}
-
-__device__ __forceinline__ float blk_min(float v, float* sh) {
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-  int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) sh[w] = v;
-  __syncthreads();
-  float r = sh[0];
-  for (int i = 1; i < (int)(blockDim.x >> 6); ++i) r = fminf(r, sh[i]);
-  return r;
-}
-
-__device__ __forceinline__ float blk_max(float v, float* sh) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) sh[w] = v;
-  __syncthreads();
-  float r = sh[0];
-  for (int i = 1; i < (int)(blockDim.x >> 6); ++i) r = fmaxf(r, sh[i]);
-  return r;
-}
-
-__global__ void k_mesh_box(BuildArgs a) {
-  __shared__ float sh[16];
-  for (int64_t m = blockIdx.x; m < a.n_meshes; m += gridDim.x) {
-    int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1];
-    if (!a.mesh_ok[m]) { f0 = 0; f1 = 0; }
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    float safe = 1.f;
-    for (int64_t f = f0 + threadIdx.x; f < f1; f += blockDim.x) {
-      const float* tb = a.tbox + 6 * f;
-      for (int k = 0; k < 3; ++k) { lo[k] = fminf(lo[k], tb[k]); hi[k] = fmaxf(hi[k], tb[3 + k]); }
-      if (!a.fsafe[f]) safe = 0.f;
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = fminf(lo[k], __shfl_xor(lo[k], o));
+      hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], o));
     }
-    float r[6];
-    for (int k = 0; k < 3; ++k) { r[k] = blk_min(lo[k], sh); r[3 + k] = blk_max(hi[k], sh); }
-    float s = blk_min(safe, sh);
-    if (threadIdx.x == 0) {
-      MeshDesc d;
-      for (int k = 0; k < 6; ++k) d.box[k] = r[k];
-      d.node_base = 0; d.n_nodes = 0;
-      d.tri_base = (int32_t)f0;
-      d.n_tris = (int32_t)(f1 - f0);
-      d.chunk_base = 0; d.n_chunks = 0; d.n_edges = 0; d.depth = 0;
-      d.root = kEmpty;
-      d.flags = s > 0.f ? kMeshSafe : 0;
-      a.mesh[m] = d;
-      // representative vertex for the point-in-mesh test: the first corner
-      // of the mesh's first face (the face id is range-checked here; a bad
-      // id fails the build through the status word anyway)
-      float4 rv = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (f1 > f0) {
-        const int64_t v0 = a.vert_off[m], nv = a.vert_off[m + 1] - v0;
-        const int32_t id = a.faces[3 * f0];
-        if (id >= 0 && id < nv) {
-          const float* x = a.verts + 3 * (v0 + id);
-          rv = make_float4(x[0], x[1], x[2], 1.f);
-        }
+  }
+  const bool any_unsafe = __ballot(unsafe) != 0;
+  uint32_t* mm = a.mm + 8 * (int64_t)m;
+  if (lane == 0) {
+    s_lo[w] = elo;
+    s_hi[w] = ehi;
+    if (lo[0] <= hi[0]) {
+      for (int k = 0; k < 3; ++k) {
+        atomicMin(mm + k, to_ordered(lo[k]));
+        atomicMax(mm + 3 + k, to_ordered(hi[k]));
       }
-      reinterpret_cast<float4*>(a.rep)[m] = rv;
+    }
+    if (any_unsafe) atomicOr(mm + 6, 1u);
+  }
+  __syncthreads();
+  // one counter pair serves every block: an atomic only where it changes
+  // (one each per wave took 0.27 of the 0.28 ms of a 5 M-face build's pass)
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kBlock / 64; ++k) {
+      elo = min(elo, s_lo[k]);
+      ehi = max(ehi, s_hi[k]);
+    }
+    if (elo < __hip_atomic_load(a.exps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(a.exps, elo);
+    if (ehi > __hip_atomic_load(a.exps + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(a.exps + 1, ehi);
+  }
+}
+
+// Descriptors of the meshes; the root of a mesh of at most L triangles; the
+// work lists of the collapse.
+template <int W>
+__global__ void k_desc(BuildArgs a) {
+  for (int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; m < a.n_meshes;
+       m += (int64_t)gridDim.x * blockDim.x) {
+    const MeshPlan p = a.plan[m];
+    const uint32_t* mm = a.mm + 8 * m;
+    MeshDesc d;
+    for (int k = 0; k < 3; ++k) {
+      const bool any = mm[k] <= mm[3 + k];
+      d.box[k] = any ? from_ordered(mm[k]) : INFINITY;
+      d.box[3 + k] = any ? from_ordered(mm[3 + k]) : -INFINITY;
+    }
+    d.node_base = p.node;
+    d.n_nodes = p.n > 0 ? 1 : 0;
+    d.tri_base = p.f0;
+    d.n_tris = p.n;
+    d.chunk_base = 0; d.n_chunks = 0; d.n_edges = 0;
+    d.depth = p.n > 0 ? 1 : 0;
+    d.root = p.n > 0 ? p.node : kEmpty;
+    d.flags = mm[6] == 0u ? kMeshSafe : 0;
+    a.mesh[m] = d;
+    // representative vertex for the point-in-mesh test: the first corner of
+    // the mesh's first face (a bad id fails the build through the status word)
+    float4 rv = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p.n > 0) {
+      const int32_t id = a.faces[3 * (int64_t)p.f0];
+      if (id >= 0 && id < p.nv) {
+        const float* x = a.verts + 3 * (p.v0 + id);
+        rv = make_float4(x[0], x[1], x[2], 1.f);
+      }
+    }
+    reinterpret_cast<float4*>(a.rep)[m] = rv;
+    a.used[m] = 1;
+    // a sort in one cell needs no counting pass
+    if (cell_bits(p.n) == 0) a.hist[p.tcell] = (uint32_t)p.n;
+    if (cell_bits(3 * (int64_t)p.n) == 0) a.hist[a.cells_t + p.ecell] = 3u * (uint32_t)p.n;
+    if (p.n > 0 && p.n <= a.leaf) {
+      Node<W> nd;
+      for (int c = 0; c < W; ++c) {
+        for (int k = 0; k < 3; ++k) { nd.lo[k][c] = INFINITY; nd.hi[k][c] = -INFINITY; }
+        nd.child[c] = kEmpty;
+        nd.pad[c] = 0;
+      }
+      for (int k = 0; k < 3; ++k) { nd.lo[k][0] = d.box[k]; nd.hi[k][0] = d.box[3 + k]; }
+      nd.child[0] = leaf_ref(p.f0, p.n);
+      reinterpret_cast<Node<W>*>(a.nodes)[p.node] = nd;
+    } else if (p.n > kSubtree) {
+      a.big[atomicAdd(a.ctr, 1)] = (int32_t)m;
+    } else if (p.n > 0) {
+      a.subs[atomicAdd(a.ctr + 1, 1)] = SubItem{(int32_t)m, 0, 0, 1};
     }
   }
 }
 
-// ---- step 2 ---------------------------------------------------------------
+// ---- step 3: sorts ------------------------------------------------------------------
 
-__global__ void k_morton(BuildArgs a) {
+// Place of each lane's item within its cell: lanes with equal cells side by
+// side (faces come in a coherent order) take one atomic together.
+__device__ __forceinline__ uint32_t cell_rank(uint32_t* hist, uint32_t cell, bool on) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t mine = on ? cell : ~0u;
+  const uint32_t prev = __shfl_up(mine, 1);
+  const uint64_t heads = __ballot(lane == 0 || prev != mine);
+  const int first = 63 - __builtin_clzll(heads & ((2ull << lane) - 1ull));
+  const uint64_t after = heads & ~((2ull << lane) - 1ull);
+  uint32_t base = 0;
+  if (on && lane == first) base = atomicAdd(hist + cell, (uint32_t)((after ? __builtin_ctzll(after) : 64) - lane));
+  base = __shfl(base, first);
+  return base + (uint32_t)(lane - first);
+}
+
+__device__ __forceinline__ void half_edge(const int32_t* id, int k, uint32_t& lo, uint32_t& hi) {
+  const uint32_t u = (uint32_t)id[k], v = (uint32_t)id[k == 2 ? 0 : k + 1];
+  lo = u < v ? u : v;
+  hi = u < v ? v : u;
+}
+
+// Morton codes of the faces and half-edges, and their places in their cells.
+__global__ __launch_bounds__(kBlock) void k_codes(BuildArgs a) {
   if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; f < a.f_total; f += (int64_t)gridDim.x * blockDim.x) {
-    int32_t m = a.face_mesh[f];
-    const float* tb = a.tbox + 6 * f;
-    f3 c{0.5f * (tb[0] + tb[3]), 0.5f * (tb[1] + tb[4]), 0.5f * (tb[2] + tb[5])};
-    uint32_t code = morton3(c, a.mesh[m].box);
-    a.key0[f] = ((uint64_t)(uint32_t)m << kMortonBits) | code;
-    a.val0[f] = (int32_t)f;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk;
+  const int tb = cell_bits(p.n), eb = cell_bits(3 * (int64_t)p.n);
+  float box[6];
+  for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
+  for (int r = 0; r < kTreeChunk / kBlock; ++r) {
+    const int32_t i = c0 + r * kBlock + (int32_t)threadIdx.x;
+    const bool on = i < p.n;
+    const int64_t f = (int64_t)p.f0 + (on ? i : p.n - 1);
+    const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
+    f3 v[3];
+    for (int k = 0; k < 3; ++k) v[k] = load_v(a.verts, p.v0 + id[k]);
+    const f3 c{0.5f * (fminf(fminf(v[0].x, v[1].x), v[2].x) + fmaxf(fmaxf(v[0].x, v[1].x), v[2].x)),
+               0.5f * (fminf(fminf(v[0].y, v[1].y), v[2].y) + fmaxf(fmaxf(v[0].y, v[1].y), v[2].y)),
+               0.5f * (fminf(fminf(v[0].z, v[1].z), v[2].z) + fmaxf(fmaxf(v[0].z, v[1].z), v[2].z))};
+    const uint32_t key = morton3(c, box);
+    if (on) a.key[f] = key;
+    if (tb) {
+      const uint32_t rank = cell_rank(a.hist + p.tcell, key >> (kMortonBits - tb), on);
+      if (on) a.rank[f] = rank;
+    }
+    for (int k = 0; k < 3; ++k) {
+      const f3 x = v[k], y = v[k == 2 ? 0 : k + 1];
+      const f3 mid{0.5f * (x.x + y.x), 0.5f * (x.y + y.y), 0.5f * (x.z + y.z)};
+      const uint32_t ek = morton3(mid, box);
+      if (on) a.ekey[3 * f + k] = ek;
+      if (eb) {
+        const uint32_t rank = cell_rank(a.hist + a.cells_t + p.ecell, ek >> (kMortonBits - eb), on);
+        if (on) a.erank[3 * f + k] = rank;
+      }
+    }
   }
 }
 
-// ---- step 3: Karras radix tree ---------------------------------------------
-
-__device__ __forceinline__ int delta(const uint64_t* keys, int64_t base, int n, int i, int j) {
-  if (j < 0 || j >= n) return -1;
-  uint32_t ki = (uint32_t)(keys[base + i] & ((1u << kMortonBits) - 1));
-  uint32_t kj = (uint32_t)(keys[base + j] & ((1u << kMortonBits) - 1));
-  if (ki != kj) return __clz(ki ^ kj);
-  return 32 + __clz((uint32_t)(i ^ j));
+// First item of edge cell c of a mesh, from the mesh's first (the scan runs
+// on through the triangle cells before).
+__device__ __forceinline__ uint32_t ecell_start(const BuildArgs& a, const MeshPlan& p, uint32_t c) {
+  return a.start[a.cells_t + p.ecell + c] - a.start[a.cells_t + p.ecell];
 }
 
-__global__ void k_karras(BuildArgs a, const uint64_t* keys) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; g < a.f_total; g += (int64_t)gridDim.x * blockDim.x) {
-    int32_t m = a.face_mesh[g];
-    int64_t base = a.face_off[m];
-    int n = (int)(a.face_off[m + 1] - base);
-    int i = (int)(g - base);
-    if (i == 0) a.parent[g] = -1;  // root (or the single leaf's slot)
-    if (n == 1) { a.lparent[g] = -1; continue; }
-    if (i >= n - 1) continue;
-    int d = (delta(keys, base, n, i, i + 1) - delta(keys, base, n, i, i - 1)) >= 0 ? 1 : -1;
-    int dmin = delta(keys, base, n, i, i - d);
+// Meshes of several cells: items to their cells.
+__global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
+  if (*a.status != INT_MAX) return;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int tb = cell_bits(p.n), eb = cell_bits(3 * (int64_t)p.n);
+  if (tb == 0 && eb == 0) return;
+  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  const uint32_t t0 = a.start[p.tcell];
+  for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
+    const int64_t f = (int64_t)p.f0 + i;
+    if (tb) {
+      const uint32_t key = a.key[f];
+      const int64_t at = (int64_t)p.f0 + (a.start[p.tcell + (key >> (kMortonBits - tb))] - t0) + a.rank[f];
+      a.pk[at] = key;
+      a.pv[at] = (uint32_t)f;
+    }
+    if (eb) {
+      const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
+      for (int k = 0; k < 3; ++k) {
+        const uint32_t key = a.ekey[3 * f + k];
+        const int64_t at = 3 * (int64_t)p.f0 + ecell_start(a, p, key >> (kMortonBits - eb)) + a.erank[3 * f + k];
+        uint32_t lo, hi;
+        half_edge(id, k, lo, hi);
+        a.epk[at] = key;
+        a.epl[at] = lo;
+        a.eph[at] = hi;
+      }
+    }
+  }
+}
+
+// Smallest cell start at or above `target` among the `cells` starts s (less
+// s[0]); n when there is none.  One wave, 64 probes a round.
+__device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells, int32_t target, int32_t n) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t s0 = s[0];
+  int64_t lo = 0, hi = cells;  // the answer's cell lies in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t c = lo + lane * step;
+    const uint64_t ge = __ballot(c < hi && (int32_t)(s[c < hi ? c : lo] - s0) >= target);
+    if (ge) {
+      const int f = __builtin_ctzll(ge);
+      hi = lo + f * step;
+      if (f > 0) lo += (f - 1) * step + 1;
+    } else {
+      lo += (hi - lo - 1) / step * step + 1;
+    }
+  }
+  return hi < cells ? (int32_t)(s[hi] - s0) : n;
+}
+
+// An item of a sort: its code, then the words that order equal codes.
+struct Item {
+  uint32_t k, x, y;
+};
+__device__ __forceinline__ bool before(const Item& a, const Item& b) {
+  return a.k != b.k ? a.k < b.k : (a.x != b.x ? a.x < b.x : a.y < b.y);
+}
+__device__ __forceinline__ bool same(const Item& a, const Item& b) { return a.k == b.k && a.x == b.x && a.y == b.y; }
+
+struct SortLds {
+  uint32_t cnt[kBins + 1];       // bin counts, then first places
+  uint32_t k[kUnitCap], x[kUnitCap], y[kUnitCap];
+  uint64_t keep[kUnitCap / 64];  // places that hold the first copy of their item
+  uint32_t before[kUnitCap / 64];
+  uint32_t scan[kBlock / 64];
+  uint32_t kmin, kmax;
+};
+
+// Sorts the n <= kUnitCap items load(0) ... load(n - 1) and hands them to
+// store(place, item), equal items once when UNIQUE; returns the number kept.
+// One pass: the items go to bins linear in the code (any order within a
+// bin), then each finds its place among its bin's items, few for codes as
+// even as a surface's; 2,048 equal codes cost 2,048 comparisons an item.
+// Bound by LDS latency.  Every thread of the block calls it.
+template <bool UNIQUE, typename Load, typename Store>
+__device__ int32_t lds_sort(SortLds& s, int32_t n, Load load, Store store) {
+  constexpr int R = kUnitCap / kBlock;
+  const int t = threadIdx.x;
+  for (int i = t; i <= kBins; i += kBlock) s.cnt[i] = 0u;
+  if (t < kUnitCap / 64) s.keep[t] = 0ull;
+  if (t == 0) { s.kmin = ~0u; s.kmax = 0u; }
+  __syncthreads();
+  Item it[R];
+  uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = t + r * kBlock;
+    if (i < n) {
+      it[r] = load(i);
+      lo = min(lo, it[r].k);
+      hi = max(hi, it[r].k);
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
+  }
+  if ((t & 63) == 0) { atomicMin(&s.kmin, lo); atomicMax(&s.kmax, hi); }
+  __syncthreads();
+  const uint32_t k0 = s.kmin, span = s.kmax - s.kmin;
+  int sh = 0;
+  while ((span >> sh) >= (uint32_t)kBins) ++sh;
+  uint32_t rank[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (t + r * kBlock < n) rank[r] = atomicAdd(&s.cnt[(it[r].k - k0) >> sh], 1u);
+  __syncthreads();
+  {
+    constexpr int C = kBins / kBlock;
+    uint32_t v[C], sum = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) { v[c] = s.cnt[t * C + c]; sum += v[c]; }
+    uint32_t total;
+    uint32_t o = block_exclusive_sum<kBlock>(sum, s.scan, total);
+#pragma unroll
+    for (int c = 0; c < C; ++c) { s.cnt[t * C + c] = o; o += v[c]; }
+    if (t == 0) s.cnt[kBins] = total;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (t + r * kBlock < n) {
+      const uint32_t at = s.cnt[(it[r].k - k0) >> sh] + rank[r];
+      s.k[at] = it[r].k;
+      s.x[at] = it[r].x;
+      s.y[at] = it[r].y;
+    }
+  __syncthreads();
+  auto at = [&](uint32_t j) { return Item{s.k[j], s.x[j], s.y[j]}; };
+  if (UNIQUE) {
+    // the copy at the lowest place stands for its item
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t i = t + r * kBlock;
+      bool first = i < (uint32_t)n;
+      if (first) {
+        const Item me = at(i);
+        for (uint32_t j = s.cnt[(me.k - k0) >> sh]; j < i && first; ++j) first = !same(at(j), me);
+      }
+      const uint64_t b = __ballot(first);
+      if ((t & 63) == 0) s.keep[i >> 6] = b;
+    }
+    __syncthreads();
+    if (t < 64) {
+      const uint32_t c = t < kUnitCap / 64 ? (uint32_t)__popcll(s.keep[t]) : 0u;
+      const uint32_t inc = wave_inclusive_sum(c);
+      if (t < kUnitCap / 64) s.before[t] = inc - c;
+      if (t == 63) s.scan[0] = inc;
+    }
+    __syncthreads();
+  }
+  auto kept_before = [&](uint32_t j) {
+    return s.before[j >> 6] + (uint32_t)__popcll(s.keep[j >> 6] & ((1ull << (j & 63)) - 1ull));
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = t + r * kBlock;
+    if (i >= (uint32_t)n || (UNIQUE && !((s.keep[i >> 6] >> (i & 63)) & 1ull))) continue;
+    const Item me = at(i);
+    const uint32_t b = (me.k - k0) >> sh, j0 = s.cnt[b], j1 = s.cnt[b + 1];
+    uint32_t place = 0;
+    for (uint32_t j = j0; j < j1; ++j)
+      place += before(at(j), me) && (!UNIQUE || ((s.keep[j >> 6] >> (j & 63)) & 1ull)) ? 1u : 0u;
+    store((int32_t)((UNIQUE ? (j0 < (uint32_t)kUnitCap ? kept_before(j0) : 0u) : j0) + place), me);
+  }
+  const int32_t kept = UNIQUE ? (int32_t)s.scan[0] : n;
+  __syncthreads();  // s is reused by the next call
+  return kept;
+}
+
+// A range of more items than LDS holds (one cell of a mesh whose detail is
+// packed into a small part of its box): split by one bit of (k, x, y) at a time, highest
+// first, until the parts fit; the order of the parts is the order of the
+// items.  get / put address the range's items in memory, tmp_get / tmp_put a
+// second buffer of the same size.  Returns the number kept.
+template <bool UNIQUE, typename Get, typename Put, typename TGet, typename TPut, typename Store>
+__device__ int32_t split_sort(SortLds& s, int32_t n, Get get, Put put, TGet tget, TPut tput, Store store) {
+  __shared__ int32_t st_lo[100], st_hi[100], st_bit[100];
+  __shared__ int32_t st_n, s_zero, s_one;
+  const int t = threadIdx.x;
+  if (t == 0) { st_lo[0] = 0; st_hi[0] = n; st_bit[0] = kMortonBits + 63; st_n = 1; }
+  __syncthreads();
+  int32_t kept = 0;
+  while (st_n > 0) {
+    const int32_t lo = st_lo[st_n - 1], hi = st_hi[st_n - 1], bit = st_bit[st_n - 1];
+    __syncthreads();
+    if (t == 0) { --st_n; s_zero = 0; s_one = 0; }
+    __syncthreads();
+    if (hi - lo <= kUnitCap || bit < 0) {
+      // (bit < 0: copies of one item)
+      const int32_t base = kept;
+      kept += lds_sort<UNIQUE>(s, bit < 0 ? 1 : hi - lo, [&](int32_t i) { return get(lo + i); },
+                               [&](int32_t i, const Item& e) { store(base + i, e); });
+      continue;
+    }
+    auto bit_of = [&](const Item& e) {
+      return bit >= 64 ? (e.k >> (bit - 64)) & 1u : (bit >= 32 ? (e.x >> (bit - 32)) & 1u : (e.y >> bit) & 1u);
+    };
+    for (int32_t i = lo + t; i < hi; i += kBlock) {
+      const Item e = get(i);
+      if (bit_of(e)) tput(hi - 1 - atomicAdd(&s_one, 1), e);
+      else tput(lo + atomicAdd(&s_zero, 1), e);
+    }
+    __syncthreads();
+    const int32_t mid = lo + s_zero;
+    for (int32_t i = lo + t; i < hi; i += kBlock) put(i, tget(i));
+    __syncthreads();
+    if (t == 0) {
+      // the lower part comes first: it goes on top
+      if (mid < hi) { st_lo[st_n] = mid; st_hi[st_n] = hi; st_bit[st_n] = bit - 1; ++st_n; }
+      if (lo < mid) { st_lo[st_n] = lo; st_hi[st_n] = mid; st_bit[st_n] = bit - 1; ++st_n; }
+    }
+    __syncthreads();
+  }
+  return kept;
+}
+
+// The item range [s, e) of unit u: the cells that start in [kUnit u, kUnit (u + 1)).
+__device__ __forceinline__ void unit_range(const uint32_t* start, int bits, int32_t n, int32_t u, int32_t* s_range) {
+  if (bits == 0) {
+    if (threadIdx.x == 0) { s_range[0] = u == 0 ? 0 : n; s_range[1] = n; }
+  } else if (threadIdx.x < 128) {
+    const int w = threadIdx.x >> 6;
+    const int32_t x = u == 0 && w == 0 ? 0 : first_start(start, (int64_t)1 << bits, kUnit * (u + w), n);
+    if ((threadIdx.x & 63) == 0) s_range[w] = x;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kBlock) void k_sort_tris(BuildArgs a) {
+  __shared__ SortLds s;
+  __shared__ int32_t s_range[2];
+  if (*a.status != INT_MAX) return;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tunit) return;
+  const int32_t m = a.tumap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int bits = cell_bits(p.n);
+  unit_range(a.start + p.tcell, bits, p.n, (int32_t)blockIdx.x - p.tunit, s_range);
+  const int32_t b = s_range[0], n = s_range[1] - b;
+  if (n <= 0) return;
+  uint32_t *const pk = a.pk + p.f0 + b, *const pv = a.pv + p.f0 + b;
+  uint32_t *const sk = a.sk + p.f0 + b, *const sv = a.sv + p.f0 + b;
+  auto store = [&](int32_t i, const Item& e) {
+    sk[i] = e.k;
+    sv[i] = e.x;
+  };
+  if (bits == 0)
+    lds_sort<false>(s, n, [&](int32_t i) { return Item{a.key[p.f0 + i], (uint32_t)(p.f0 + i), 0u}; }, store);
+  else if (n <= kUnitCap)
+    lds_sort<false>(s, n, [&](int32_t i) { return Item{pk[i], pv[i], 0u}; }, store);
+  else
+    split_sort<false>(
+        s, n, [&](int32_t i) { return Item{pk[i], pv[i], 0u}; },
+        [&](int32_t i, const Item& e) { pk[i] = e.k; pv[i] = e.x; },
+        // the codes' and places' arrays are free by now
+        [&](int32_t i) { return Item{a.key[p.f0 + b + i], a.rank[p.f0 + b + i], 0u}; },
+        [&](int32_t i, const Item& e) { a.key[p.f0 + b + i] = e.k; a.rank[p.f0 + b + i] = e.x; }, store);
+}
+
+__global__ __launch_bounds__(kBlock) void k_sort_edges(BuildArgs a) {
+  __shared__ SortLds s;
+  __shared__ int32_t s_range[2];
+  if (*a.status != INT_MAX) return;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].eunit) return;
+  const int32_t m = a.emap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int32_t n3 = 3 * p.n;
+  const int bits = cell_bits(n3);
+  unit_range(a.start + a.cells_t + p.ecell, bits, n3, (int32_t)blockIdx.x - p.eunit, s_range);
+  const int32_t b = s_range[0], n = s_range[1] - b;
+  const int64_t g0 = 3 * (int64_t)p.f0 + b;
+  int32_t kept = 0;
+  auto store = [&](int32_t i, const Item& e) {
+    a.ul[g0 + i] = e.x;
+    a.uh[g0 + i] = e.y;
+  };
+  auto cell_item = [&](int32_t i) { return Item{a.epk[g0 + i], a.epl[g0 + i], a.eph[g0 + i]}; };
+  if (n > 0) {
+    if (bits == 0)
+      kept = lds_sort<true>(
+          s, n,
+          [&](int32_t i) {
+            const int64_t f = (int64_t)p.f0 + i / 3;
+            const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
+            Item e;
+            e.k = a.ekey[g0 + i];
+            const int k = i % 3;
+            const uint32_t u = (uint32_t)(k == 0 ? id[0] : (k == 1 ? id[1] : id[2]));
+            const uint32_t v = (uint32_t)(k == 0 ? id[1] : (k == 1 ? id[2] : id[0]));
+            e.x = min(u, v);
+            e.y = max(u, v);
+            return e;
+          },
+          store);
+    else if (n <= kUnitCap)
+      kept = lds_sort<true>(s, n, cell_item, store);
+    else
+      kept = split_sort<true>(
+          s, n, cell_item, [&](int32_t i, const Item& e) { a.epk[g0 + i] = e.k; a.epl[g0 + i] = e.x; a.eph[g0 + i] = e.y; },
+          // the codes' and places' arrays, and the output's upper half, written last
+          [&](int32_t i) { return Item{a.ekey[g0 + i], a.erank[g0 + i], a.uh[g0 + i]}; },
+          [&](int32_t i, const Item& e) { a.ekey[g0 + i] = e.k; a.erank[g0 + i] = e.x; a.uh[g0 + i] = e.y; }, store);
+  }
+  if (threadIdx.x == 0) {
+    a.ustart[blockIdx.x] = b;
+    a.ucount[blockIdx.x] = kept;
+  }
+}
+
+// ---- step 4: Karras radix tree and boxes -------------------------------------------
+
+// Length of the common prefix of positions i and j's codes (ties by position).
+__device__ __forceinline__ int prefix(uint32_t ki, uint32_t kj, int i, int j) {
+  return ki != kj ? __clz(ki ^ kj) : 32 + __clz((uint32_t)(i ^ j));
+}
+
+__device__ __forceinline__ void grow_box(float* b, const float* c) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { b[k] = fminf(b[k], c[k]); b[3 + k] = fmaxf(b[3 + k], c[3 + k]); }
+}
+
+// One chunk of kTreeChunk sorted positions: writes the triangles in leaf
+// order, finds the node of each position, and builds the nodes that lie
+// inside the chunk bottom up in LDS (each climb ends at the first child to
+// arrive; the second takes both boxes up).  The subtrees that tile the chunk go to
+// its root list, and the nodes that reach beyond it are left to k_tree_top.
+// Most nodes of a mesh lie inside a chunk, where a level costs LDS latency
+// instead of a round trip to memory: refit of 2 x 35 M triangles in 4,096
+// meshes 11.1 ms with one block a mesh climbing in memory.
+__global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
+  constexpr int R = kTreeChunk / kBlock;
+  constexpr uint16_t kNone = 0xffffu;
+  __shared__ uint32_t s_key[kTreeChunk];
+  __shared__ float s_leaf[6][kTreeChunk], s_node[6][kTreeChunk];
+  __shared__ uint16_t s_lpar[kTreeChunk], s_npar[kTreeChunk], s_lo[kTreeChunk], s_sp[kTreeChunk], s_hi[kTreeChunk];
+  __shared__ uint32_t s_cnt[kTreeChunk];
+  __shared__ int32_t s_roots;
+  if (*a.status != INT_MAX) return;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int32_t n = p.n, c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(n, c0 + kTreeChunk);
+  const int32_t rc = p.rchunk + (int32_t)blockIdx.x - p.tchunk;  // the chunk's root list
+  const uint32_t* keys = a.sk + p.f0;
+  const int t = threadIdx.x;
+  if (t == 0) s_roots = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = t + r * kBlock;
+    s_cnt[i] = 0u;
+    s_lpar[i] = kNone;
+    s_npar[i] = kNone;
+    if (c0 + i < c1) s_key[i] = keys[c0 + i];
+  }
+  float box[R][6];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = t + r * kBlock;
+    if (c0 + i >= c1) continue;
+    const int64_t g = (int64_t)p.f0 + c0 + i;
+    const int64_t f = a.sv[g];
+    float* tr = a.tris + 9 * g;
+    float v[9];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const f3 x = load_v(a.verts, p.v0 + a.faces[3 * f + k]);
+      v[3 * k] = x.x; v[3 * k + 1] = x.y; v[3 * k + 2] = x.z;
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) tr[k] = v[k];
+    a.triid[g] = (int32_t)(f - p.f0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      box[r][k] = fminf(fminf(v[k], v[3 + k]), v[6 + k]);
+      box[r][3 + k] = fmaxf(fmaxf(v[k], v[3 + k]), v[6 + k]);
+    }
+  }
+  __syncthreads();
+  auto key_at = [&](int j) { return j >= c0 && j < c1 ? s_key[j - c0] : keys[j]; };
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const int i = c0 + t + r * kBlock;
+    if (i >= n - 1 || i >= c1) continue;
+    const uint32_t ki = s_key[i - c0];
+    auto delta = [&](int j) { return j < 0 || j >= n ? -1 : prefix(ki, key_at(j), i, j); };
+    const int d = delta(i + 1) >= delta(i - 1) ? 1 : -1;
+    const int dmin = delta(i - d);
     int lmax = 2;
-    while (delta(keys, base, n, i, i + lmax * d) > dmin) lmax <<= 1;
+    while (delta(i + lmax * d) > dmin) lmax <<= 1;
     int l = 0;
-    for (int t = lmax >> 1; t >= 1; t >>= 1)
-      if (delta(keys, base, n, i, i + (l + t) * d) > dmin) l += t;
-    int j = i + l * d;
-    int dnode = delta(keys, base, n, i, j);
-    int s = 0;
-    int t = l;
+    for (int s = lmax >> 1; s >= 1; s >>= 1)
+      if (delta(i + (l + s) * d) > dmin) l += s;
+    const int j = i + l * d;
+    const int dnode = delta(j);
+    int s = 0, u = l;
     do {
-      t = (t + 1) >> 1;
-      if (delta(keys, base, n, i, i + (s + t) * d) > dnode) s += t;
-    } while (t > 1);
-    int split = i + s * d + (d < 0 ? -1 : 0);
-    int lo = i < j ? i : j, hi = i < j ? j : i;
-    int32_t lc, rc;
-    if (lo == split) { lc = (int32_t)(base + split) | INT_MIN; a.lparent[base + split] = (int32_t)g; }
-    else { lc = (int32_t)(base + split); a.parent[base + split] = (int32_t)g; }
-    if (hi == split + 1) { rc = (int32_t)(base + split + 1) | INT_MIN; a.lparent[base + split + 1] = (int32_t)g; }
-    else { rc = (int32_t)(base + split + 1); a.parent[base + split + 1] = (int32_t)g; }
-    a.left[g] = lc;
-    a.right[g] = rc;
+      u = (u + 1) >> 1;
+      if (delta(i + (s + u) * d) > dnode) s += u;
+    } while (u > 1);
+    const int split = i + s * d + (d < 0 ? -1 : 0);
+    const int lo = min(i, j), hi = max(i, j);
+    if (lo >= c0 && hi < c1) {
+      const int q = i - c0;
+      s_lo[q] = (uint16_t)(lo - c0);
+      s_sp[q] = (uint16_t)(split - c0);
+      s_hi[q] = (uint16_t)(hi - c0);
+      (lo == split ? s_lpar : s_npar)[split - c0] = (uint16_t)q;
+      (hi == split + 1 ? s_lpar : s_npar)[split + 1 - c0] = (uint16_t)q;
+    } else {
+      BinNode& b = a.bin[(int64_t)p.f0 + i];
+      b.lo = lo;
+      b.split = split;
+      b.hi = hi;
+      (lo == split ? a.lparent : a.parent)[(int64_t)p.f0 + split] = i;
+      (hi == split + 1 ? a.lparent : a.parent)[(int64_t)p.f0 + split + 1] = i;
+      if (i == 0) a.parent[p.f0] = -1;
+    }
   }
-}
-
-// ---- step 4: refit ------------------------------------------------------------
-
-__device__ __forceinline__ void child_info(const BuildArgs& a, int32_t c, const int32_t* sorted_face, float* box,
-                                           int32_t& count, int32_t& first) {
-  if (c < 0) {
-    int32_t pos = c & INT_MAX;
-    const float* tb = a.tbox + 6 * (int64_t)sorted_face[pos];
-    for (int k = 0; k < 6; ++k) box[k] = tb[k];
-    count = 1;
-    first = pos;
-  } else {
-    for (int k = 0; k < 6; ++k) box[k] = a.nbox[6 * (int64_t)c + k];
-    count = a.nleaf[c];
-    first = a.nfirst[c];
-  }
-}
-
-// One block per mesh: every climb of a mesh stays inside one workgroup, so
-// workgroup-scope acquire/release on the visit counters orders the box
-// writes without device-wide cache maintenance.
-__global__ __launch_bounds__(kMeshBlock) void k_refit(BuildArgs a, const int32_t* sorted_face) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  for (int64_t mi = blockIdx.x; mi < a.n_meshes; mi += gridDim.x) {
-    const int64_t m = a.morder[mi];
-    const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1];
-    for (int64_t g = f0 + threadIdx.x; g < f1; g += blockDim.x) {
-      int32_t p = a.lparent[g];
-      while (p >= 0) {
-        uint32_t old = __hip_atomic_fetch_add(&a.visit[p], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (old == 0) break;  // the sibling subtree is not done yet
-        float bl[6], br[6];
-        int32_t cl, cr, fl, fr;
-        child_info(a, a.left[p], sorted_face, bl, cl, fl);
-        child_info(a, a.right[p], sorted_face, br, cr, fr);
-        for (int k = 0; k < 3; ++k) {
-          a.nbox[6 * (int64_t)p + k] = fminf(bl[k], br[k]);
-          a.nbox[6 * (int64_t)p + 3 + k] = fmaxf(bl[3 + k], br[3 + k]);
+  __syncthreads();
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const int i = t + r * kBlock;
+    if (c0 + i >= c1) continue;
+    float b[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) b[k] = r == 0 ? box[0][k] : box[R - 1][k];
+    int32_t ref = ~(c0 + i);  // the subtree whose box is b: a node, or ~position
+    int at = i;               // its slot in the chunk
+    bool leaf = true;
+    while (true) {
+      const uint32_t q = leaf ? s_lpar[at] : s_npar[at];
+      if (q == kNone) {
+        const int32_t k = n > kTreeChunk ? atomicAdd(&s_roots, 1) : kMaxRoots;
+        if (k < kMaxRoots) {
+          RootRec& o = a.roots[(int64_t)rc * kMaxRoots + k];
+#pragma unroll
+          for (int x = 0; x < 6; ++x) o.box[x] = b[x];
+          o.ref = ref;
         }
-        a.nleaf[p] = cl + cr;
-        a.nfirst[p] = fl < fr ? fl : fr;
-        p = a.parent[p];
+        break;
+      }
+      float(*mine)[kTreeChunk] = leaf ? s_leaf : s_node;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) mine[k][at] = b[k];
+      const uint32_t old = __hip_atomic_fetch_add(&s_cnt[q], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (old == 0) break;  // the sibling subtree is not done yet
+      const int lo = s_lo[q], sp = s_sp[q], hi = s_hi[q];
+      const bool left = at == sp;
+      const int sib = left ? sp + 1 : sp;
+      float(*other)[kTreeChunk] = (left ? hi == sp + 1 : lo == sp) ? s_leaf : s_node;
+      BinNode nd;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const float o = other[k][sib];
+        nd.box[0][k] = left ? b[k] : o;
+        nd.box[1][k] = left ? o : b[k];
+      }
+      nd.lo = c0 + lo;
+      nd.split = c0 + sp;
+      nd.hi = c0 + hi;
+      nd.pad = 0;
+      a.bin[(int64_t)p.f0 + c0 + q] = nd;
+      grow_box(nd.box[0], nd.box[1]);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) b[k] = nd.box[0][k];
+      ref = c0 + (int32_t)q;
+      at = (int)q;
+      leaf = false;
+    }
+  }
+  __syncthreads();
+  if (t == 0 && n > kTreeChunk) a.nroots[rc] = min(s_roots, kMaxRoots);
+}
+
+// The nodes that span chunks, one block per large mesh: the chunks' roots
+// climb in memory (every climb of a mesh stays inside one workgroup, so
+// workgroup-scope acquire and release on the visit counters order the boxes).
+__global__ __launch_bounds__(1024) void k_tree_top(BuildArgs a) {
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int32_t k = blockIdx.x; k < a.ctr[0]; k += gridDim.x) {
+    const int32_t m = a.big[k];
+    const MeshPlan p = a.plan[m];
+    const int32_t c1 = p.rchunk + div_up(p.n, kTreeChunk);
+    for (int32_t c = p.rchunk + w; c < c1; c += 16) {
+      const int32_t nr = a.nroots[c];
+      for (int32_t i = lane; i < nr; i += 64) {
+        const RootRec rr = a.roots[(int64_t)c * kMaxRoots + i];
+        float b[6];
+#pragma unroll
+        for (int x = 0; x < 6; ++x) b[x] = rr.box[x];
+        int32_t pos = rr.ref < 0 ? ~rr.ref : rr.ref;
+        int32_t q = (rr.ref < 0 ? a.lparent : a.parent)[(int64_t)p.f0 + pos];
+        while (q >= 0) {
+          BinNode& nd = a.bin[(int64_t)p.f0 + q];
+          const int side = pos == nd.split ? 0 : 1;
+#pragma unroll
+          for (int x = 0; x < 6; ++x) nd.box[side][x] = b[x];
+          const uint32_t old = __hip_atomic_fetch_add(&a.visit[(int64_t)p.f0 + q], 1u, __ATOMIC_ACQ_REL,
+                                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (old == 0) break;  // the sibling subtree is not done yet
+          float o[6];
+#pragma unroll
+          for (int x = 0; x < 6; ++x) o[x] = nd.box[1 - side][x];
+          grow_box(b, o);
+          pos = q;
+          q = a.parent[(int64_t)p.f0 + q];
+        }
       }
     }
   }
@@ -455,411 +1041,395 @@ __global__ __launch_bounds__(kMeshBlock) void k_refit(BuildArgs a, const int32_t
 
 // ---- step 5: collapse to width W -------------------------------------------
 
-__global__ void k_node_bound(BuildArgs a) {
-  int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; m < a.n_meshes; m += (int64_t)gridDim.x * blockDim.x) {
-    int64_t n = a.mesh[m].n_tris;
-    a.nbound[m] = nodes_bound(n, a.width, a.leaf);
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.nbound[a.n_meshes] = 0;
-}
-
 __device__ __forceinline__ float half_area(const float* b) {
   float dx = b[3] - b[0], dy = b[4] - b[1], dz = b[5] - b[2];
   return dx * dy + dy * dz + dz * dx;
 }
 
-// Collapse of each mesh's binary tree into a width-W tree, one block per
-// mesh, one level of wide nodes per round.  An item is (binary subtree root,
-// wide slot, depth); the block's threads take the items of the current
-// level one each.  A thread starts from the two children of its binary node
-// and keeps opening one of them until it holds W children or none can be
-// opened (only subtrees of more than L triangles are opened): builder 0 opens
-// the child of largest surface area, builder 1 the child of largest surface
-// area x triangle count (its term of the surface-area cost).  It writes the
-// wide node and appends an item, with a fresh slot, for every child that
-// needs a wide node of its own.  Slots are numbered in creation order (root
-// 0), so the top levels of a tree sit together.  Items live in the mesh's
-// part of the work array (at most one per internal binary node).
+// One wide node for each W lanes of the wave (lane c of the group holds child
+// c): from the two children of binary node x, the group keeps opening the
+// child of largest score (builder 0: surface area, builder 1: surface area
+// x triangle count, its term of the surface-area cost) among those of more
+// than L triangles until it has W or none can be opened; an opened child's two halves go to its own lane
+// and to the next free one, each read straight from its binary node.  The
+// node goes to slot `slot`.  On return a lane whose child needs a wide node
+// of its own has its binary node in cx, and its triangles in cn; its
+// reference is still to be written (child_slot).
 template <int W>
-__device__ void collapse_item(const BuildArgs& a, Node<W>* nodes, int64_t nb, int64_t bound, int32_t* items,
-                              int it, int32_t* s_used, int32_t* s_tail, int32_t* s_depth, int32_t* s_over) {
-  const int32_t x = items[3 * it], w = items[3 * it + 1], dep = items[3 * it + 2];
-  atomicMax(s_depth, dep);
+__device__ __forceinline__ void collapse_group(const BuildArgs& a, const MeshPlan& p, bool on, int32_t x, int32_t slot,
+                                               int32_t& cx, int32_t& cn) {
+  const int c = (int)(threadIdx.x & 63) % W, g0 = (int)(threadIdx.x & 63) - c;
   const int L = a.leaf;
-  int32_t S[W];
-  float Sb[W][6];
-  int32_t Sc[W], Sf[W];
-  int ns = 2;
-  S[0] = a.left[x];
-  S[1] = a.right[x];
-  child_info(a, S[0], a.val1, Sb[0], Sc[0], Sf[0]);
-  child_info(a, S[1], a.val1, Sb[1], Sc[1], Sf[1]);
-  while (ns < W) {
-    int best = -1;
-    float bscore = -1.f;
-    for (int k = 0; k < ns; ++k)
-      if (S[k] >= 0 && Sc[k] > L) {
-        const float ar = half_area(Sb[k]);
-        const float score = a.builder == 1 ? ar * (float)Sc[k] : ar;
-        if (score > bscore) { bscore = score; best = k; }
-      }
-    if (best < 0) break;
-    const int32_t y = S[best];
-    S[best] = a.left[y];
-    S[ns] = a.right[y];
-    child_info(a, S[best], a.val1, Sb[best], Sc[best], Sf[best]);
-    child_info(a, S[ns], a.val1, Sb[ns], Sc[ns], Sf[ns]);
-    ++ns;
-  }
-  Node<W> nd;
-  for (int c = 0; c < W; ++c) {
-    nd.pad[c] = 0;
-    if (c < ns) {
-      for (int k = 0; k < 3; ++k) { nd.lo[k][c] = Sb[c][k]; nd.hi[k][c] = Sb[c][3 + k]; }
-      if (Sc[c] <= L) {
-        nd.child[c] = leaf_ref(Sf[c], Sc[c]);
-      } else {
-        const int32_t slot = atomicAdd(s_used, 1);
-        if (slot >= bound) {
-          *s_over = 1;
-          nd.child[c] = kEmpty;
-          continue;
-        }
-        nd.child[c] = (int32_t)(nb + slot);
-        const int32_t pos = atomicAdd(s_tail, 1);
-        items[3 * pos] = S[c];
-        items[3 * pos + 1] = slot;
-        items[3 * pos + 2] = dep + 1;
-      }
-    } else {
-      for (int k = 0; k < 3; ++k) { nd.lo[k][c] = INFINITY; nd.hi[k][c] = -INFINITY; }
-      nd.child[c] = kEmpty;
+  const BinNode* bin = a.bin + p.f0;
+  float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  int32_t first = 0, node = -1;
+  cn = 0;
+  auto take = [&](int32_t y, int side) {
+    const BinNode& nd = bin[y];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) b[k] = nd.box[side][k];
+    first = side == 0 ? nd.lo : nd.split + 1;
+    cn = side == 0 ? nd.split - nd.lo + 1 : nd.hi - nd.split;
+    node = side == 0 ? nd.split : nd.split + 1;
+  };
+  if (on && c < 2) take(x, c);
+#pragma unroll 1
+  for (int ns = 2; ns < W; ++ns) {
+    // the best child: largest score, the lowest lane among equals
+    float score = -1.f;
+    if (cn > L) {
+      const float ar = half_area(b);
+      score = a.builder == 1 ? ar * (float)cn : ar;
+      // NaN or a score that no comparison with -1 passes is never opened
+      if (!(score > -1.f)) score = -1.f;
+    }
+    float top = score;
+    int best = c;
+#pragma unroll
+    for (int o = 1; o < W; o <<= 1) {
+      const float os = __shfl_xor(top, o);
+      const int ob = __shfl_xor(best, o);
+      if (os > top || (os == top && ob < best)) { top = os; best = ob; }
+    }
+    const bool open = on && top > -1.f;
+    if (!__ballot(open)) break;
+    // a group that opens none is done (its later rounds open none either)
+    const int32_t y = __shfl(node, g0 + best);
+    if (open) {
+      if (c == best) take(y, 0);
+      else if (c == ns) take(y, 1);
     }
   }
-  nodes[nb + w] = nd;
+  cx = -1;
+  if (on) {
+    float* nd = reinterpret_cast<float*>(a.nodes + sizeof(Node<W>) * ((int64_t)p.node + slot));
+#pragma unroll
+    for (int k = 0; k < 6; ++k) nd[k * W + c] = b[k];
+    int32_t* ch = reinterpret_cast<int32_t*>(nd) + 6 * W;
+    ch[W + c] = 0;
+    if (cn == 0) ch[c] = kEmpty;
+    else if (cn <= L) ch[c] = leaf_ref(p.f0 + first, cn);
+    else cx = node;
+  }
+}
+
+__device__ __forceinline__ int lanes_before(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 template <int W>
-__global__ __launch_bounds__(kMeshBlock) void k_collapse(BuildArgs a, const int64_t* node_base_scan) {
-  __shared__ int32_t s_used, s_tail, s_depth, s_over;
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  Node<W>* nodes = reinterpret_cast<Node<W>*>(a.tnodes);
-  for (int64_t mi = blockIdx.x; mi < a.n_meshes; mi += gridDim.x) {
-    const int64_t m = a.morder[mi];
-    const int n = a.mesh[m].n_tris;
-    const int64_t fbase = a.face_off[m];
-    const int64_t nb = node_base_scan[m];
-    const int64_t bound = node_base_scan[m + 1] - nb;
-    if (n == 0) {
-      if (threadIdx.x == 0) {
-        a.mesh[m].root = kEmpty;
-        a.mesh[m].n_nodes = 0;
-        a.mesh[m].node_base = (int32_t)nb;
-      }
-      continue;
-    }
-    if (n <= a.leaf) {
-      if (threadIdx.x == 0) {
-        const MeshDesc d = a.mesh[m];
-        Node<W> nd;
-        for (int c = 0; c < W; ++c) {
-          for (int k = 0; k < 3; ++k) { nd.lo[k][c] = INFINITY; nd.hi[k][c] = -INFINITY; }
-          nd.child[c] = kEmpty;
-          nd.pad[c] = 0;
-        }
-        for (int k = 0; k < 3; ++k) { nd.lo[k][0] = d.box[k]; nd.hi[k][0] = d.box[3 + k]; }
-        nd.child[0] = leaf_ref((int32_t)fbase, n);
-        nodes[nb] = nd;
-        a.mesh[m].node_base = (int32_t)nb;
-        a.mesh[m].root = (int32_t)nb;
-        a.mesh[m].n_nodes = 1;
-        a.mesh[m].depth = 1;
-      }
-      continue;
-    }
-    int32_t* items = a.stk + 3 * fbase;
+__device__ __forceinline__ void child_ref(const BuildArgs& a, const MeshPlan& p, int32_t slot, int32_t child) {
+  const int c = (int)(threadIdx.x & 63) % W;
+  reinterpret_cast<int32_t*>(a.nodes + sizeof(Node<W>) * ((int64_t)p.node + slot))[6 * W + c] = p.node + child;
+}
+
+// Top of the trees of meshes of more than kSubtree triangles, one block per
+// mesh, one level of wide nodes a round: children of more than kSubtree
+// triangles go on in the block, smaller ones to the list of subtrees.
+// Slots are numbered in creation order (root 0, its inner children next).
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_collapse_top(BuildArgs a) {
+  constexpr int G = 64 / W, B = (kBlock / 64) * G;  // items of a wave, of a block
+  __shared__ int32_t s_used, s_tail, s_depth;
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int32_t k = blockIdx.x; k < a.ctr[0]; k += gridDim.x) {
+    const int32_t m = a.big[k];
+    const MeshPlan p = a.plan[m];
+    int32_t* items = a.items + 3 * (int64_t)p.f0;
     if (threadIdx.x == 0) {
-      items[0] = (int32_t)fbase;  // binary root: internal node 0 of the mesh
+      items[0] = 0;
       items[1] = 0;
       items[2] = 1;
       s_used = 1;
       s_tail = 1;
       s_depth = 1;
-      s_over = 0;
     }
     __syncthreads();
-    int head = 0;
+    int32_t head = 0;
     for (;;) {
-      const int tail = s_tail;
+      const int32_t tail = s_tail;
       __syncthreads();  // every thread has the level's end before items are appended
       if (head >= tail) break;
-      for (int it = head + (int)threadIdx.x; it < tail; it += (int)blockDim.x)
-        collapse_item<W>(a, nodes, nb, bound, items, it, &s_used, &s_tail, &s_depth, &s_over);
+      for (int32_t i0 = head; i0 < tail; i0 += B) {
+        const int32_t i = i0 + w * G + lane / W;
+        const bool on = i < tail;
+        int32_t x = 0, slot = 0, dep = 0, cx, cn;
+        if (on) { x = items[3 * i]; slot = items[3 * i + 1]; dep = items[3 * i + 2]; }
+        collapse_group<W>(a, p, on, x, slot, cx, cn);
+        const uint64_t inner = __ballot(cx >= 0), here = __ballot(cx >= 0 && cn > kSubtree), down = inner & ~here;
+        int32_t s0 = 0, t0 = 0, l0 = 0;
+        if (lane == 0) {
+          if (inner) s0 = atomicAdd(&s_used, __popcll(inner));
+          if (here) t0 = atomicAdd(&s_tail, __popcll(here));
+          if (down) l0 = atomicAdd(a.ctr + 1, __popcll(down));
+        }
+        s0 = __shfl(s0, 0);
+        t0 = __shfl(t0, 0);
+        l0 = __shfl(l0, 0);
+        if (cx >= 0) {
+          const int32_t cs = s0 + lanes_before(inner);
+          child_ref<W>(a, p, slot, cs);
+          if (cn > kSubtree) {
+            int32_t* o = items + 3 * (t0 + lanes_before(here));
+            o[0] = cx;
+            o[1] = cs;
+            o[2] = dep + 1;
+          } else {
+            a.subs[l0 + lanes_before(down)] = SubItem{m, cx, cs, dep + 1};
+          }
+        }
+        if (on && lane % W == 0) atomicMax(&s_depth, dep);
+      }
       head = tail;
       __syncthreads();  // the next level's items are written
     }
     if (threadIdx.x == 0) {
-      if (s_over || s_depth > kMaxDepth) atomicMin(a.status, (int32_t)fbase);
-      a.mesh[m].node_base = (int32_t)nb;
-      a.mesh[m].root = (int32_t)nb;
-      a.mesh[m].n_nodes = s_used < bound ? s_used : (int32_t)bound;
-      a.mesh[m].depth = s_depth;
+      a.used[m] = s_used;
+      atomicMax(a.depth + m, s_depth);
     }
     __syncthreads();
   }
 }
 
-// Compaction: the collapse reserved nodes_bound() slots per mesh; the used
-// nodes are copied to consecutive positions of the blob (internal child
-// references shifted by the same amount), so a query touches a dense array.
-__global__ void k_node_count(BuildArgs a) {
-  int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; m < a.n_meshes; m += (int64_t)gridDim.x * blockDim.x) a.ncount[m] = a.mesh[m].n_nodes;
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.ncount[a.n_meshes] = 0;
-}
-
+// The subtrees, one wave each: pending items (disjoint subtrees of at least
+// two triangles, so at most kSubtree / 2) wait in LDS, 64 / W are collapsed
+// at a time.
 template <int W>
-__global__ void k_node_copy(BuildArgs a, const int64_t* new_base) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  const Node<W>* src = reinterpret_cast<const Node<W>*>(a.tnodes);
-  Node<W>* dst = reinterpret_cast<Node<W>*>(a.nodes);
-  for (int64_t mi = blockIdx.x; mi < a.n_meshes; mi += gridDim.x) {
-    const int64_t m = a.morder[mi];
-    const int32_t old_base = a.mesh[m].node_base;
-    const int32_t n = a.mesh[m].n_nodes;
-    const int64_t nb = new_base[m];
-    const int32_t shift = (int32_t)(nb - old_base);
-    for (int32_t k = threadIdx.x; k < n; k += blockDim.x) {
-      Node<W> nd = src[old_base + k];
-      for (int c = 0; c < W; ++c)
-        if (nd.child[c] >= 0 && nd.child[c] != kEmpty) nd.child[c] += shift;
-      dst[nb + k] = nd;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      a.mesh[m].node_base = (int32_t)nb;
-      a.mesh[m].root = n > 0 ? (int32_t)nb : kEmpty;
-    }
-  }
-}
-
-// ---- leaf-order triangles ----------------------------------------------------
-
-__global__ void k_write_tris(BuildArgs a) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; g < a.f_total; g += (int64_t)gridDim.x * blockDim.x) {
-    int32_t f = a.val1[g];
-    int32_t m = a.face_mesh[f];
-    bool mok = a.mesh_ok[m];
-    int64_t v0 = mok ? a.vert_off[m] : 0, nv = mok ? a.vert_off[m + 1] - v0 : 0;
-    float* t = a.tris + 9 * g;
-    for (int k = 0; k < 3; ++k) {
-      int32_t id = a.faces[3 * (int64_t)f + k];
-      f3 p{0.f, 0.f, 0.f};
-      if (id >= 0 && id < nv) p = load_v(a.verts, v0 + id);  // invalid input: status already set
-      t[3 * k] = p.x; t[3 * k + 1] = p.y; t[3 * k + 2] = p.z;
-    }
-    a.triid[g] = (int32_t)(f - (mok ? a.face_off[m] : 0));
-  }
-}
-
-// ---- step 6: unique edges --------------------------------------------------------
-
-__global__ void k_edge_keys(BuildArgs a) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; f < a.f_total; f += (int64_t)gridDim.x * blockDim.x) {
-    int32_t m = a.face_mesh[f];
-    bool mok = a.mesh_ok[m];
-    int64_t v0 = mok ? a.vert_off[m] : 0, nv = mok ? a.vert_off[m + 1] - v0 : 0;
-    for (int k = 0; k < 3; ++k) {
-      int32_t i0 = a.faces[3 * f + k], i1 = a.faces[3 * f + (k + 1) % 3];
-      // invalid ids become a self-loop on vertex 0 of the dataset, which is dropped
-      if (i0 < 0 || i0 >= nv || i1 < 0 || i1 >= nv) { a.ekey0[3 * f + k] = 0; continue; }
-      uint64_t u = (uint64_t)(v0 + i0), v = (uint64_t)(v0 + i1);
-      uint64_t lo = u < v ? u : v, hi = u < v ? v : u;
-      a.ekey0[3 * f + k] = (lo << 32) | hi;
-    }
-  }
-}
-
-__global__ void k_edge_flag(BuildArgs a, const uint64_t* keys, int64_t n) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    uint64_t k = keys[i];
-    bool first = (i == 0 || keys[i - 1] != k) && ((k >> 32) != (k & 0xffffffffu));
-    a.eflag[i] = first ? 1 : 0;
-  }
-}
-
-__device__ __forceinline__ int32_t mesh_of_vertex(const int64_t* vert_off, int64_t n_meshes, int64_t v) {
-  int64_t lo = 0, hi = n_meshes;  // vert_off[lo] <= v < vert_off[hi]
-  while (hi - lo > 1) {
-    int64_t mid = (lo + hi) >> 1;
-    if (vert_off[mid] <= v) lo = mid; else hi = mid;
-  }
-  return (int32_t)lo;
-}
-
-// compacts unique keys and builds the (mesh, midpoint Morton) sort keys;
-// keys is the sorted raw key array, output goes to ekey0/eval0
-__global__ void k_edge_compact(BuildArgs a, const uint64_t* keys, int64_t n) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  int32_t total = a.epos[n];
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    if (a.eflag[i]) {
-      int32_t e = a.epos[i];
-      uint64_t k = keys[i];
-      int64_t u = (int64_t)(k >> 32), v = (int64_t)(k & 0xffffffffu);
-      int32_t m = mesh_of_vertex(a.vert_off, a.n_meshes, u);
-      f3 p = load_v(a.verts, u), q = load_v(a.verts, v);
-      f3 mid{0.5f * (p.x + q.x), 0.5f * (p.y + q.y), 0.5f * (p.z + q.z)};
-      a.ekey0[e] = ((uint64_t)(uint32_t)m << kMortonBits) | morton3(mid, a.mesh[m].box);
-      a.eval0[e] = (int32_t)i;
-    }
-    if (i >= total) {
-      a.ekey0[i] = ~0ull;
-      a.eval0[i] = -1;
-    }
-  }
-}
-
-__global__ void k_edge_ranges(BuildArgs a, const uint64_t* skeys, int64_t n) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  int64_t total = a.epos[n];
-  for (; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    int32_t m = (int32_t)(skeys[e] >> kMortonBits);
-    if (e == 0 || (int32_t)(skeys[e - 1] >> kMortonBits) != m) a.estart[m] = (int32_t)e;
-    if (e == total - 1 || (int32_t)(skeys[e + 1] >> kMortonBits) != m) a.eend[m] = (int32_t)(e + 1);
-  }
-}
-
-__global__ void k_chunk_counts(BuildArgs a) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; m < a.n_meshes; m += (int64_t)gridDim.x * blockDim.x) {
-    int32_t ne = a.eend[m] - a.estart[m];
-    a.mesh[m].n_edges = ne;
-    a.cscan[m] = (ne + kChunk - 1) / kChunk;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.cscan[a.n_meshes] = 0;
-}
-
-__global__ void k_write_segs(BuildArgs a, const int64_t* chunk_scan, const uint64_t* ukeys,
-                             const int32_t* order, int64_t n) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  int64_t total = a.epos[n];
-  for (; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    int32_t src = order[e];  // index into the sorted raw key array
-    uint64_t k = ukeys[src];
-    int64_t u = (int64_t)(k >> 32), v = (int64_t)(k & 0xffffffffu);
-    int32_t m = mesh_of_vertex(a.vert_off, a.n_meshes, u);
-    int32_t local = (int32_t)(e - a.estart[m]);
-    int64_t chunk = chunk_scan[m] + local / kChunk;
-    int lane = local % kChunk;
-    if (chunk >= a.chunk_cap) { atomicMin(a.status, 0); continue; }
-    f3 p = load_v(a.verts, u), q = load_v(a.verts, v);
-    float* s = a.seg + chunk * (6 * kChunk);
-    s[0 * kChunk + lane] = p.x; s[1 * kChunk + lane] = p.y; s[2 * kChunk + lane] = p.z;
-    s[3 * kChunk + lane] = q.x; s[4 * kChunk + lane] = q.y; s[5 * kChunk + lane] = q.z;
-    int32_t* ed = a.edge + chunk * (2 * kChunk);
-    int64_t v0 = a.vert_off[m];
-    ed[lane] = (int32_t)(u - v0);
-    ed[kChunk + lane] = (int32_t)(v - v0);
-    if (lane == 0) a.cmesh[chunk] = m;
-  }
-}
-
-__global__ void k_mesh_chunks(BuildArgs a, const int64_t* chunk_scan) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t m = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; m < a.n_meshes; m += (int64_t)gridDim.x * blockDim.x) {
-    a.mesh[m].chunk_base = (int32_t)chunk_scan[m];
-    a.mesh[m].n_chunks = (int32_t)(chunk_scan[m + 1] - chunk_scan[m]);
-  }
-}
-
-// one wavefront per group: exact box of the live segments' endpoints
-__global__ void k_chunk_box(BuildArgs a, const int64_t* chunk_scan) {
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  int64_t total = chunk_scan[a.n_meshes];
-  int lane = threadIdx.x & 63;
-  int64_t c = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  int64_t stride = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (; c < total; c += stride) {
-    int32_t m = a.cmesh[c];
-    int32_t local0 = (int32_t)(c - a.mesh[m].chunk_base) * kChunk;
-    bool live = local0 + lane < a.mesh[m].n_edges;
-    const float* s = a.seg + c * (6 * kChunk);
-    float lo[3], hi[3];
-    for (int k = 0; k < 3; ++k) {
-      float pv = live ? s[k * kChunk + lane] : INFINITY;
-      float qv = live ? s[(3 + k) * kChunk + lane] : INFINITY;
-      lo[k] = fminf(pv, qv);
-      pv = live ? s[k * kChunk + lane] : -INFINITY;
-      qv = live ? s[(3 + k) * kChunk + lane] : -INFINITY;
-      hi[k] = fmaxf(pv, qv);
-      for (int o = 32; o > 0; o >>= 1) {
-        lo[k] = fminf(lo[k], __shfl_xor(lo[k], o));
-        hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], o));
+__global__ __launch_bounds__(kBlock) void k_collapse_sub(BuildArgs a) {
+  constexpr int G = 64 / W;
+  __shared__ int32_t s_item[kBlock / 64][kSubtree / 2][3];
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int32_t(*items)[3] = s_item[w];
+  const int32_t total = a.ctr[1], nw = (int32_t)gridDim.x * (kBlock / 64);
+  for (int32_t e = (int32_t)blockIdx.x * (kBlock / 64) + w; e < total; e += nw) {
+    const SubItem it = a.subs[e];
+    const MeshPlan p = a.plan[it.mesh];
+    int32_t top = 1, deep = 0;
+    if (lane == 0) { items[0][0] = it.node; items[0][1] = it.slot; items[0][2] = it.depth; }
+    while (top > 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int32_t take = min(top, G), i = top - 1 - lane / W;
+      const bool on = lane / W < take;
+      int32_t x = 0, slot = 0, dep = 0, cx, cn;
+      if (on) { x = items[i][0]; slot = items[i][1]; dep = items[i][2]; }
+      __builtin_amdgcn_wave_barrier();  // the items are read before their places are reused
+      top -= take;
+      deep = max(deep, dep);
+      collapse_group<W>(a, p, on, x, slot, cx, cn);
+      const uint64_t inner = __ballot(cx >= 0);
+      int32_t s0 = 0;
+      if (inner && lane == 0) s0 = atomicAdd(a.used + it.mesh, __popcll(inner));
+      s0 = __shfl(s0, 0);
+      if (cx >= 0) {
+        const int32_t k = lanes_before(inner), cs = s0 + k;
+        child_ref<W>(a, p, slot, cs);
+        items[top + k][0] = cx;
+        items[top + k][1] = cs;
+        items[top + k][2] = dep + 1;
       }
+      top += __popcll(inner);
+    }
+    for (int o = 32; o > 0; o >>= 1) deep = max(deep, __shfl_xor(deep, o));
+    if (lane == 0) atomicMax(a.depth + it.mesh, deep);
+  }
+}
+
+// ---- step 6: groups of unique edges --------------------------------------------------
+
+// Unique edges of each mesh, and of the mesh before each of its units; one wave per mesh.
+__global__ __launch_bounds__(kBlock) void k_edge_mesh(BuildArgs a) {
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t m = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6; m < a.n_meshes; m += nw) {
+    const int32_t u0 = a.plan[m].eunit, u1 = a.plan[m + 1].eunit;
+    int32_t run = 0;
+    for (int32_t u = u0; u < u1; u += 64) {
+      const int32_t c = u + lane < u1 ? a.ucount[u + lane] : 0;
+      const int32_t inc = wave_inclusive_sum(c);
+      if (u + lane < u1) a.uoff[u + lane] = run + inc - c;
+      run += __shfl(inc, 63);
     }
     if (lane == 0) {
-      float* b = a.cbox + 8 * c;
-      for (int k = 0; k < 3; ++k) { b[k] = lo[k]; b[3 + k] = hi[k]; }
-      b[6] = 0.f; b[7] = 0.f;
+      a.nedges[m] = run;
+      a.groups[m] = (run + kChunk - 1) / kChunk;
+    }
+  }
+}
+
+// One block: groups before each mesh; the totals at [M].
+__global__ __launch_bounds__(1024) void k_group_plan(BuildArgs a) {
+  __shared__ int64_t s[16];
+  if (*a.status != INT_MAX) return;
+  int64_t run = 0, edges = 0;
+  for (int64_t base = 0; base < a.n_meshes; base += 4096) {
+    int64_t v[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
+      v[k] = m < a.n_meshes ? a.groups[m] : 0;
+      edges += m < a.n_meshes ? a.nedges[m] : 0;
+      sum += v[k];
+    }
+    int64_t total;
+    int64_t o = run + block_exclusive_sum<1024>(sum, s, total);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
+      if (m < a.n_meshes) a.groups[m] = o;
+      o += v[k];
+    }
+    run += total;
+  }
+  edges = block_sum<1024>(edges, s);
+  if (threadIdx.x == 0) {
+    a.groups[a.n_meshes] = run;
+    *a.etotal = edges;
+  }
+}
+
+// The descriptors' counts, and the mesh of every group; one wave per mesh.
+__global__ __launch_bounds__(kBlock) void k_mesh_final(BuildArgs a) {
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t m = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6; m < a.n_meshes; m += nw) {
+    const int64_t g0 = a.groups[m], g1 = a.groups[m + 1];
+    const MeshPlan p = a.plan[m];
+    if (lane == 0) {
+      MeshDesc& d = a.mesh[m];
+      d.chunk_base = (int32_t)g0;
+      d.n_chunks = (int32_t)(g1 - g0);
+      d.n_edges = a.nedges[m];
+      if (p.n > a.leaf) {
+        d.n_nodes = a.used[m];
+        d.depth = a.depth[m];
+        if (a.depth[m] > kMaxDepth || a.used[m] > a.plan[m + 1].node - p.node) atomicMin(a.status, p.f0);
+      }
+      if (g1 > a.chunk_cap) atomicMin(a.status, 0);
+    }
+    for (int64_t g = g0 + lane; g < g1 && g < a.chunk_cap; g += 64) a.cmesh[g] = (int32_t)m;
+  }
+}
+
+// One wave per group of 64 unique edges: endpoints, vertex ids and the exact
+// box of the group.
+__global__ __launch_bounds__(kBlock) void k_groups(BuildArgs a) {
+  if (*a.status != INT_MAX) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t total = a.groups[a.n_meshes];
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t g = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6; g < total; g += nw) {
+    const int32_t m = a.cmesh[g];
+    const MeshPlan p = a.plan[m];
+    const int32_t u1 = a.plan[m + 1].eunit, ne = a.nedges[m];
+    const int32_t e0 = (int32_t)(g - a.groups[m]) * kChunk, e = e0 + lane;
+    const bool live = e < ne;
+    // the last unit that starts at or before e0, then on from there
+    int32_t u = p.eunit;
+    for (int32_t lo = p.eunit, n = u1 - p.eunit; n > 1;) {
+      const int32_t step = (n + 63) / 64, probe = lo + lane * step;
+      const uint64_t le = __ballot(probe < lo + n && a.uoff[min(probe, u1 - 1)] <= e0);
+      lo += (63 - __builtin_clzll(le | 1ull)) * step;
+      n = min(step, u1 - lo);
+      u = lo;
+    }
+    if (live)
+      while (u + 1 < u1 && a.uoff[u + 1] <= e) ++u;
+    float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    uint32_t x = 0, y = 0;
+    if (live) {
+      const int64_t at = 3 * (int64_t)p.f0 + a.ustart[u] + (e - a.uoff[u]);
+      x = a.ul[at];
+      y = a.uh[at];
+      const f3 s = load_v(a.verts, p.v0 + x), q = load_v(a.verts, p.v0 + y);
+      v[0] = s.x; v[1] = s.y; v[2] = s.z; v[3] = q.x; v[4] = q.y; v[5] = q.z;
+      float* o = a.seg + g * (6 * kChunk);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) o[k * kChunk + lane] = v[k];
+      int32_t* ed = a.edge + g * (2 * kChunk);
+      ed[lane] = (int32_t)x;
+      ed[kChunk + lane] = (int32_t)y;
+    }
+    float b[6];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      b[k] = live ? fminf(v[k], v[3 + k]) : INFINITY;
+      b[3 + k] = live ? fmaxf(v[k], v[3 + k]) : -INFINITY;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        b[k] = fminf(b[k], __shfl_xor(b[k], o));
+        b[3 + k] = fmaxf(b[3 + k], __shfl_xor(b[3 + k], o));
+      }
+    }
+    if (lane < 8) {
+      float w = 0.f;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) w = lane == k ? b[k] : w;
+      a.cbox[8 * g + lane] = w;
     }
   }
 }
 
 // Run boxes: the box of each run of 64 consecutive groups of a mesh, stored
-// at the run's first group, so that the cull can skip 64 groups with one test.
-__global__ void k_run_box(BuildArgs a, const int64_t* chunk_scan) {
+// at the run's first group, so that the cull can skip 64 groups with one
+// test; one wave per run, taken by the run's first group.
+__global__ __launch_bounds__(kBlock) void k_run_box(BuildArgs a) {
   if (*a.status != INT_MAX) return;
-  const int64_t total = chunk_scan[a.n_meshes];
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < total; c += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t m = a.cmesh[c];
-    const int64_t c0 = a.mesh[m].chunk_base, c1 = c0 + a.mesh[m].n_chunks;
-    if ((c - c0) % kChunk != 0) continue;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int64_t e = c + kChunk < c1 ? c + kChunk : c1;
-    for (int64_t g = c; g < e; ++g) {
-      const float* b = a.cbox + 8 * g;
-      for (int k = 0; k < 3; ++k) { lo[k] = fminf(lo[k], b[k]); hi[k] = fmaxf(hi[k], b[3 + k]); }
+  const int lane = threadIdx.x & 63;
+  const int64_t total = a.groups[a.n_meshes];
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  // a wave looks at 64 groups at a time for those that start a run
+  for (int64_t c0 = ((blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6) * 64; c0 < total; c0 += nw * 64) {
+    int64_t base = 0, end = 0;
+    const int64_t c = c0 + lane;
+    if (c < total) {
+      const int32_t m = a.cmesh[c];
+      base = a.groups[m];
+      end = a.groups[m + 1];
     }
-    float* r = a.rbox + 8 * c;
-    for (int k = 0; k < 3; ++k) { r[k] = lo[k]; r[3 + k] = hi[k]; }
-    r[6] = 0.f; r[7] = 0.f;
+    for (uint64_t starts = __ballot(c < total && (c - base) % kChunk == 0); starts; starts &= starts - 1) {
+      const int j = __builtin_ctzll(starts);
+      const int64_t first = c0 + j, last = __shfl(end, j);
+      const int64_t g = first + lane;
+      float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      if (g < last) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) b[k] = a.cbox[8 * g + k];
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          b[k] = fminf(b[k], __shfl_xor(b[k], o));
+          b[3 + k] = fmaxf(b[3 + k], __shfl_xor(b[3 + k], o));
+        }
+      }
+      if (lane < 8) {
+        float w = 0.f;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) w = lane == k ? b[k] : w;
+        a.rbox[8 * first + lane] = w;
+      }
+    }
   }
 }
 
-__global__ void k_header(BuildArgs a, BlobHeader h, const int64_t* chunk_scan, int64_t n3) {
-  h.n_chunks = a.f_total > 0 ? chunk_scan[a.n_meshes] : 0;
-  h.n_edges = a.f_total > 0 ? a.epos[n3] : 0;
-  h.exp_lo = a.meshctr[0];
-  h.exp_hi = a.meshctr[1];
+// The header and the status: the smallest bad face, or -1.
+__global__ void k_header(BuildArgs a, BlobHeader h, int32_t* dev_status) {
+  const int32_t st = *a.status;
+  const bool ok = st == INT_MAX;
+  h.n_chunks = ok ? a.groups[a.n_meshes] : 0;
+  h.n_edges = ok ? *a.etotal : 0;
+  h.exp_lo = a.exps[0];
+  h.exp_hi = a.exps[1];
   *reinterpret_cast<BlobHeader*>(a.blob) = h;
-}
-
-__global__ void k_status_out(const int32_t* st, int32_t* out) {
-  int32_t s = *st;
-  *out = (s == INT_MAX) ? -1 : s;
-}
-
-__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
-__global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
+  *dev_status = ok ? -1 : st;
 }
 
 // ---- sizes ------------------------------------------------------------------
@@ -890,73 +1460,54 @@ Layout blob_layout(int64_t M, int64_t F, int W, int L) {
   return y;
 }
 
-int end_bit_for(int64_t M) {
-  int b = 1;
-  while (((int64_t)1 << b) <= M) ++b;  // M <= 2^b - 1, so ids < 2^b - 1
-  return kMortonBits + b;
-}
-
-// Carves the workspace; with base == nullptr only measures.  Sort temp sizes
-// are queried from hipCUB.
-int carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F, int64_t node_cap, int W, void** sort_tmp,
-             size_t* sort_bytes) {
-  int64_t E3 = 3 * F;
+// Carves the workspace; with base == nullptr only measures.
+void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
+  const int64_t E3 = 3 * F;
+  const int64_t tc = F / kTreeChunk + M + 1, tu = F / kUnit + M + 1, eu = E3 / kUnit + M + 1;
+  a.cells_t = F / 4 + M;
+  a.cells_all = a.cells_t + E3 / 4 + M;
   a.status = cv.take<int32_t>(4);
-  a.meshctr = cv.take<int32_t>(4);
-  a.face_mesh = cv.take<int32_t>(F);
-  a.tbox = cv.take<float>(6 * F);
-  a.fsafe = cv.take<uint8_t>(F);
-  a.key0 = cv.take<uint64_t>(F);
-  a.key1 = cv.take<uint64_t>(F);
-  a.val0 = cv.take<int32_t>(F);
-  a.val1 = cv.take<int32_t>(F);
-  a.left = cv.take<int32_t>(F);
-  a.right = cv.take<int32_t>(F);
+  a.exps = cv.take<int32_t>(4);
+  a.ctr = cv.take<int32_t>(4);
+  a.plan = cv.take<MeshPlan>(M + 1);
+  a.mm = cv.take<uint32_t>(8 * M);
+  a.used = cv.take<int32_t>(M);
+  a.depth = cv.take<int32_t>(M);
+  a.nedges = cv.take<int32_t>(M);
+  a.groups = cv.take<int64_t>(M + 1);
+  a.etotal = cv.take<int64_t>(1);
+  a.big = cv.take<int32_t>(M);
+  a.tmap = cv.take<int32_t>(tc);
+  a.tumap = cv.take<int32_t>(tu);
+  a.emap = cv.take<int32_t>(eu);
+  a.hist = cv.take<uint32_t>(a.cells_all + 1);
+  a.start = cv.take<uint32_t>(a.cells_all + 1);
+  a.tsum = cv.take<int64_t>(scan_tiles_of(a.cells_all) + 1);
+  a.key = cv.take<uint32_t>(F);
+  a.rank = cv.take<uint32_t>(F);
+  a.pk = cv.take<uint32_t>(F);
+  a.pv = cv.take<uint32_t>(F);
+  a.sk = cv.take<uint32_t>(F);
+  a.sv = cv.take<uint32_t>(F);
+  a.ekey = cv.take<uint32_t>(E3);
+  a.erank = cv.take<uint32_t>(E3);
+  a.epk = cv.take<uint32_t>(E3);
+  a.epl = cv.take<uint32_t>(E3);
+  a.eph = cv.take<uint32_t>(E3);
+  a.ul = cv.take<uint32_t>(E3);
+  a.uh = cv.take<uint32_t>(E3);
+  a.ustart = cv.take<int32_t>(eu);
+  a.ucount = cv.take<int32_t>(eu);
+  a.uoff = cv.take<int32_t>(eu);
+  a.bin = cv.take<BinNode>(F);
   a.parent = cv.take<int32_t>(F);
   a.lparent = cv.take<int32_t>(F);
-  a.nbox = cv.take<float>(6 * F);
-  a.nleaf = cv.take<int32_t>(F);
-  a.nfirst = cv.take<int32_t>(F);
   a.visit = cv.take<uint32_t>(F);
-  a.nbound = cv.take<int64_t>(M + 1);
-  a.stk = cv.take<int32_t>(3 * F);
-  a.ekey0 = cv.take<uint64_t>(E3);
-  a.ekey1 = cv.take<uint64_t>(E3);
-  a.eval0 = cv.take<int32_t>(E3);
-  a.eval1 = cv.take<int32_t>(E3);
-  a.eflag = cv.take<int32_t>(E3 + 1);
-  a.epos = cv.take<int32_t>(E3 + 1);
-  a.estart = cv.take<int32_t>(M);
-  a.eend = cv.take<int32_t>(M);
-  a.cscan = cv.take<int64_t>(M + 1);
-  a.mesh_ok = cv.take<uint8_t>(M);
-  a.ekey2 = cv.take<uint64_t>(E3);
-  a.nscan = cv.take<int64_t>(M + 1);
-  a.chunk_scan = cv.take<int64_t>(M + 1);
-  a.ncount = cv.take<int64_t>(M + 1);
-  a.tsum = cv.take<int64_t>(scan_tiles_of((E3 > M ? E3 : M) + 1) + 1);
-  a.morder = cv.take<int32_t>(M);
-  a.mcnt = cv.take<int32_t>(kSizeClasses * ((M + kMeshOrdTile - 1) / kMeshOrdTile));
-  a.mpos = cv.take<int64_t>(kSizeClasses * ((M + kMeshOrdTile - 1) / kMeshOrdTile));
-  a.tnodes = cv.take<char>(node_cap * node_bytes(W));
-  // temp storage for the library sorts
-  size_t need = 0, b = 0;
-  int eb = end_bit_for(M);
-  hipError_t e;
-  e = hipcub::DeviceRadixSort::SortPairs(nullptr, b, (uint64_t*)nullptr, (uint64_t*)nullptr, (int32_t*)nullptr,
-                                         (int32_t*)nullptr, (int)(F > 0 ? F : 1), 0, eb);
-  if (e != hipSuccess) return hip_fail(e, "hipcub SortPairs size");
-  need = need > b ? need : b;
-  e = hipcub::DeviceRadixSort::SortKeys(nullptr, b, (uint64_t*)nullptr, (uint64_t*)nullptr, (int)(E3 > 0 ? E3 : 1), 0, 64);
-  if (e != hipSuccess) return hip_fail(e, "hipcub SortKeys size");
-  need = need > b ? need : b;
-  e = hipcub::DeviceRadixSort::SortPairs(nullptr, b, (uint64_t*)nullptr, (uint64_t*)nullptr, (int32_t*)nullptr,
-                                         (int32_t*)nullptr, (int)(E3 > 0 ? E3 : 1), 0, eb);
-  if (e != hipSuccess) return hip_fail(e, "hipcub SortPairs size");
-  need = need > b ? need : b;
-  *sort_bytes = need;
-  *sort_tmp = cv.take<char>((int64_t)need);
-  return PR_OK;
+  const int64_t rc = 2 * F / kTreeChunk + 1;  // a mesh of several chunks has less than two per kTreeChunk faces
+  a.roots = cv.take<RootRec>(rc * kMaxRoots);
+  a.nroots = cv.take<int32_t>(rc);
+  a.items = cv.take<int32_t>(3 * F);
+  a.subs = cv.take<SubItem>(F / 2 + M + 1);
 }
 
 int check_params(int64_t M, int64_t F, int64_t V, const pr_bvh_params* p) {
@@ -987,15 +1538,10 @@ extern "C" int build_mesh_bvh_sizes(int64_t n_meshes, int64_t f_total, int64_t v
   int r = check_params(n_meshes, f_total, v_total, params);
   if (r) return r;
   if (!blob_bytes || !ws_bytes) { set_error("output pointer is NULL"); return PR_E_ARG; }
-  Layout y = blob_layout(n_meshes, f_total, params->width, params->leaf_size);
-  *blob_bytes = (size_t)y.total;
+  *blob_bytes = (size_t)blob_layout(n_meshes, f_total, params->width, params->leaf_size).total;
   Carve cv{nullptr, 0};
   BuildArgs a{};
-  void* tmp;
-  size_t tb;
-  Layout y0 = blob_layout(n_meshes, f_total, params->width, params->leaf_size);
-  r = carve_ws(cv, a, n_meshes, f_total, y0.node_cap, params->width, &tmp, &tb);
-  if (r) return r;
+  carve_ws(cv, a, n_meshes, f_total);
   *ws_bytes = cv.used + 256;
   return PR_OK;
 }
@@ -1022,11 +1568,8 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   hipStream_t s = (hipStream_t)stream;
   BuildArgs a{};
   Carve cv{(char*)ws, ws_bytes};
-  void* tmp = nullptr;
-  size_t tmp_bytes = 0;
-  r = carve_ws(cv, a, n_meshes, f_total, y.node_cap, W, &tmp, &tmp_bytes);
-  if (r) return r;
-  if (cv.used > ws_bytes || !tmp) { set_error("ws_bytes %zu < required %zu", ws_bytes, cv.used); return PR_E_CAPACITY; }
+  carve_ws(cv, a, n_meshes, f_total);
+  if (cv.used > ws_bytes) { set_error("ws_bytes %zu < required %zu", ws_bytes, cv.used); return PR_E_CAPACITY; }
   a.verts = verts; a.vert_off = vert_off; a.faces = faces; a.face_off = face_off;
   a.n_meshes = n_meshes; a.v_total = v_total; a.f_total = f_total; a.width = W; a.leaf = L;
   a.builder = params->builder;
@@ -1044,76 +1587,51 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   a.node_cap = y.node_cap;
   a.chunk_cap = y.chunk_cap;
 
-  const int64_t F = f_total, M = n_meshes, E3 = 3 * F;
-  const int gF = grid_for(F, kBlock), gM = grid_for(M, kBlock), gE = grid_for(E3, kBlock);
-  int eb = end_bit_for(M);
-
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, a.status, 1, INT_MAX);
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, a.meshctr + 0, 1, INT_MAX);
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, a.meshctr + 1, 1, INT_MIN);
-  if (M > 0) {
-    hipLaunchKernelGGL(k_fill_i32, dim3(gM), dim3(kBlock), 0, s, a.estart, M, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(gM), dim3(kBlock), 0, s, a.eend, M, 0);
-    if (F > 0) hipLaunchKernelGGL(k_fill_i32, dim3(gF), dim3(kBlock), 0, s, a.face_mesh, F, 0);
-    hipLaunchKernelGGL(k_face_mesh, dim3((int)(M < 65536 ? M : 65536)), dim3(kBlock), 0, s, a);
-  }
+  const int64_t F = f_total, M = n_meshes;
+  const int64_t tc = F / kTreeChunk + M, tu = F / kUnit + M, eu = 3 * F / kUnit + M;  // bounds of the tables
+  const int gM = grid_for(M, kBlock), gMw = grid_for(M, kBlock / 64);
+  const int64_t fill = a.cells_all > 8 * M ? a.cells_all : 8 * M;
+  const int gI = grid_for(fill, kBlock) < 8192 ? grid_for(fill, kBlock) : 8192;
+  // waves of the loops over groups, subtrees and large meshes
+  const int kWide = 4096, kTops = 1024;
+#define PR_W(kernel, grid)                                                                       \
+  do {                                                                                           \
+    if (W == 2) hipLaunchKernelGGL(kernel<2>, dim3(grid), dim3(kBlock), 0, s, a);                \
+    else if (W == 4) hipLaunchKernelGGL(kernel<4>, dim3(grid), dim3(kBlock), 0, s, a);           \
+    else hipLaunchKernelGGL(kernel<8>, dim3(grid), dim3(kBlock), 0, s, a);                       \
+  } while (0)
+  hipLaunchKernelGGL(k_build_init, dim3(gI), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, a);
   if (F > 0) {
-    hipLaunchKernelGGL(k_fill_u32, dim3(gF), dim3(kBlock), 0, s, a.visit, F, 0u);
-    hipLaunchKernelGGL(k_tri_prep, dim3(gF < 4096 ? gF : 4096), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_maps, dim3(gMw), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_prep, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
   }
-  if (M > 0) hipLaunchKernelGGL(k_mesh_box, dim3((int)(M < 65536 ? M : 65536)), dim3(kBlock), 0, s, a);
-  if (M > 0) {
-    // the per-mesh kernels below take the meshes largest first
-    const int64_t nbm = (M + kMeshOrdTile - 1) / kMeshOrdTile;
-    hipLaunchKernelGGL(k_mesh_order_count, dim3((unsigned)nbm), dim3(256), 0, s, a, nbm);
-    PR_HIP(device_exclusive_scan((const int32_t*)a.mcnt, a.mpos, kSizeClasses * nbm, a.tsum, (int64_t*)nullptr, s));
-    hipLaunchKernelGGL(k_mesh_order_place, dim3((unsigned)nbm), dim3(256), 0, s, a, nbm);
-  }
+  if (M > 0) PR_W(k_desc, gM);
   if (F > 0) {
-    hipLaunchKernelGGL(k_morton, dim3(gF), dim3(kBlock), 0, s, a);
-    PR_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, a.key0, a.key1, a.val0, a.val1, (int)F, 0, eb, s));
-    hipLaunchKernelGGL(k_karras, dim3(gF), dim3(kBlock), 0, s, a, (const uint64_t*)a.key1);
-    hipLaunchKernelGGL(k_refit, dim3((int)(M < 65536 ? M : 65536)), dim3(kMeshBlock), 0, s, a, (const int32_t*)a.val1);
-  }
-  if (M > 0) {
-    hipLaunchKernelGGL(k_node_bound, dim3(gM), dim3(kBlock), 0, s, a);
-    PR_HIP(device_exclusive_scan((const int64_t*)a.nbound, a.nscan, M + 1, a.tsum, (int64_t*)nullptr, s));
-    const int gC = (int)(M < 65536 ? M : 65536);  // one block per mesh
-    if (W == 2) hipLaunchKernelGGL(k_collapse<2>, dim3(gC), dim3(kMeshBlock), 0, s, a, (const int64_t*)a.nscan);
-    else if (W == 4) hipLaunchKernelGGL(k_collapse<4>, dim3(gC), dim3(kMeshBlock), 0, s, a, (const int64_t*)a.nscan);
-    else hipLaunchKernelGGL(k_collapse<8>, dim3(gC), dim3(kMeshBlock), 0, s, a, (const int64_t*)a.nscan);
-    hipLaunchKernelGGL(k_node_count, dim3(gM), dim3(kBlock), 0, s, a);
-    PR_HIP(device_exclusive_scan((const int64_t*)a.ncount, a.nbound, M + 1, a.tsum, (int64_t*)nullptr, s));
-    const int gMB = (int)(M < 65536 ? M : 65536);
-    if (W == 2) hipLaunchKernelGGL(k_node_copy<2>, dim3(gMB), dim3(kBlock), 0, s, a, (const int64_t*)a.nbound);
-    else if (W == 4) hipLaunchKernelGGL(k_node_copy<4>, dim3(gMB), dim3(kBlock), 0, s, a, (const int64_t*)a.nbound);
-    else hipLaunchKernelGGL(k_node_copy<8>, dim3(gMB), dim3(kBlock), 0, s, a, (const int64_t*)a.nbound);
-  }
-  if (F > 0) {
-    hipLaunchKernelGGL(k_write_tris, dim3(gF), dim3(kBlock), 0, s, a);
-    // unique edges: raw keys -> sorted (ekey1) -> flags/positions -> (mesh, Morton) keys (ekey0)
-    hipLaunchKernelGGL(k_edge_keys, dim3(gF), dim3(kBlock), 0, s, a);
-    PR_HIP(hipcub::DeviceRadixSort::SortKeys(tmp, tmp_bytes, a.ekey0, a.ekey1, (int)E3, 0, 64, s));
-    hipLaunchKernelGGL(k_edge_flag, dim3(gE), dim3(kBlock), 0, s, a, (const uint64_t*)a.ekey1, E3);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, a.eflag + E3, 1, 0);
-    PR_HIP(device_exclusive_scan((const int32_t*)a.eflag, a.epos, E3 + 1, a.tsum, (int64_t*)nullptr, s));
-    hipLaunchKernelGGL(k_edge_compact, dim3(gE), dim3(kBlock), 0, s, a, (const uint64_t*)a.ekey1, E3);
-    PR_HIP(hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, a.ekey0, a.ekey2, a.eval0, a.eval1, (int)E3, 0, eb, s));
-    hipLaunchKernelGGL(k_edge_ranges, dim3(gE), dim3(kBlock), 0, s, a, (const uint64_t*)a.ekey2, E3);
+    hipLaunchKernelGGL(k_codes, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    PR_HIP(device_exclusive_scan((const uint32_t*)a.hist, a.start, a.cells_all, a.tsum, (int64_t*)nullptr, s));
+    hipLaunchKernelGGL(k_to_cells, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_tris, dim3((unsigned)tu), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_edges, dim3((unsigned)eu), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_tree, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    const int tops = (int)(M < kTops ? M : kTops);
+    hipLaunchKernelGGL(k_tree_top, dim3(tops), dim3(1024), 0, s, a);
+    PR_W(k_collapse_top, tops);
+    const int64_t sub = (F / 2 + M) / 4 + 1;
+    PR_W(k_collapse_sub, (int)(sub < kWide ? sub : kWide));
   }
   if (M > 0) {
-    hipLaunchKernelGGL(k_chunk_counts, dim3(gM), dim3(kBlock), 0, s, a);
-    PR_HIP(device_exclusive_scan((const int64_t*)a.cscan, a.chunk_scan, M + 1, a.tsum, (int64_t*)nullptr, s));
-    hipLaunchKernelGGL(k_mesh_chunks, dim3(gM), dim3(kBlock), 0, s, a, (const int64_t*)a.chunk_scan);
+    hipLaunchKernelGGL(k_edge_mesh, dim3(gMw), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_group_plan, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(k_mesh_final, dim3(gMw), dim3(kBlock), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_group_plan, dim3(1), dim3(1024), 0, s, a);
   }
   if (F > 0) {
-    hipLaunchKernelGGL(k_write_segs, dim3(gE), dim3(kBlock), 0, s, a, (const int64_t*)a.chunk_scan,
-                       (const uint64_t*)a.ekey1, (const int32_t*)a.eval1, E3);
-    hipLaunchKernelGGL(k_chunk_box, dim3(grid_for(a.chunk_cap * 64, kBlock)), dim3(kBlock), 0, s, a,
-                       (const int64_t*)a.chunk_scan);
-    hipLaunchKernelGGL(k_run_box, dim3(grid_for(a.chunk_cap, kBlock)), dim3(kBlock), 0, s, a,
-                       (const int64_t*)a.chunk_scan);
+    hipLaunchKernelGGL(k_groups, dim3(grid_for(a.chunk_cap, kBlock / 64)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_run_box, dim3(grid_for(a.chunk_cap, kBlock)), dim3(kBlock), 0, s, a);
   }
+#undef PR_W
   BlobHeader h{};
   h.magic = kMagic;
   h.version = PR_ABI_VERSION;
@@ -1135,8 +1653,7 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   h.off_rep = y.off_rep;
   h.off_rbox = y.off_rbox;
   h.total_bytes = y.total;
-  hipLaunchKernelGGL(k_header, dim3(1), dim3(1), 0, s, a, h, (const int64_t*)a.chunk_scan, E3);
-  hipLaunchKernelGGL(k_status_out, dim3(1), dim3(1), 0, s, (const int32_t*)a.status, dev_status);
+  hipLaunchKernelGGL(k_header, dim3(1), dim3(1), 0, s, a, h, dev_status);
   PR_HIP(hipGetLastError());
   return PR_OK;
 }

@@ -1,0 +1,193 @@
+"""The build's blob, decoded and checked section by section against the input:
+leaf-order triangles, unique edges and their groups, exact boxes at every
+level, and a tree that covers each triangle once.  Sizes sit at the edges of
+the build's chunks, sort units and cells, and at what overfills them: detail
+packed into one cell, equal Morton codes, an edge shared by thousands of faces."""
+import struct
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+EMPTY = 0x7fffffff
+FIELDS = ("magic version width leaf_size n_meshes f_total v_total node_cap chunk_cap off_mesh off_node off_tri off_triid "
+          "off_seg off_edge off_cbox off_cmesh total_bytes n_chunks n_edges exp_lo exp_hi off_rep off_rbox").split()
+
+
+def _soup(rng, n, scale=1.0):
+    """n triangles over about n / 2 shared random vertices: no two equal vertices in a face."""
+    nv = max(3, n // 2 + 3)
+    v = (scale * rng.uniform(-1, 1, size=(nv, 3))).astype(np.float32)
+    f = np.stack([rng.integers(0, nv, n), np.zeros(n, np.int64), np.zeros(n, np.int64)], 1)
+    f[:, 1] = (f[:, 0] + rng.integers(1, nv - 1, n)) % nv
+    f[:, 2] = (f[:, 1] + rng.integers(1, nv - 1, n)) % nv
+    bad = f[:, 2] == f[:, 0]
+    f[bad, 2] = (f[bad, 2] + 1) % nv
+    bad = f[:, 2] == f[:, 1]
+    f[bad, 2] = (f[bad, 2] + 1) % nv
+    return v, f.astype(np.int32)
+
+
+def _surface(n):
+    """A height field of about n triangles (coherent faces, every inner edge shared by two)."""
+    k = max(1, int(np.sqrt(n / 2)))
+    x, y = np.meshgrid(np.arange(k + 1), np.arange(k + 1), indexing="ij")
+    z = 0.3 * np.sin(0.7 * x) * np.cos(0.9 * y)
+    v = np.stack([x, y, z], -1).reshape(-1, 3).astype(np.float32)
+    i = (np.arange(k)[:, None] * (k + 1) + np.arange(k)[None]).reshape(-1)
+    f = np.concatenate([np.stack([i, i + 1, i + k + 1], 1), np.stack([i + 1, i + k + 2, i + k + 1], 1)])
+    return v, f.astype(np.int32)
+
+
+def _packed(rng, n):
+    """n triangles in one Morton cell of a box that one far triangle spans."""
+    v, f = _soup(rng, n, 1e-5)
+    far = np.array([[0, 0, 0], [900, 1000, 800], [1000, 900, 1000]], np.float32)
+    return np.concatenate([v, far]), np.concatenate([f, [[v.shape[0], v.shape[0] + 1, v.shape[0] + 2]]]).astype(np.int32)
+
+
+def _book(n):
+    """n faces that share the edge (0, 1)."""
+    a = 2 * np.pi * np.arange(n) / n
+    v = np.concatenate([[[0, 0, -1], [0, 0, 1]], np.stack([np.cos(a), np.sin(a), 0 * a], 1)]).astype(np.float32)
+    return v, np.stack([np.zeros(n, int), np.ones(n, int), 2 + np.arange(n)], 1).astype(np.int32)
+
+
+def _case(name):
+    rng = np.random.default_rng(sum(map(ord, name)))
+    if name == "sizes":       # chunk and unit edges, as faces and as half-edges; an empty mesh
+        sizes = [1, 2, 3, 4, 5, 8, 9, 511, 512, 513, 682, 683, 1023, 1024, 1025, 2047, 2048, 2049, 4097]
+        m = [_soup(rng, n) for n in sizes]
+        m.insert(4, (np.zeros((0, 3), np.float32), np.zeros((0, 3), np.int32)))
+        return m
+    if name == "surfaces":    # several cells, units of partly filled cells
+        return [_surface(n) for n in (700, 3000, 20_000, 90_000)] + [_soup(rng, 30_000)]
+    if name == "packed":      # cells that overfill a unit, one bit at a time
+        return [_packed(rng, n) for n in (2500, 9000)] + [_soup(rng, 100)]
+    if name == "book":        # thousands of copies of one edge
+        return [_book(3000), _book(700), _soup(rng, 50)]
+    return [_soup(rng, int(n)) for n in rng.integers(1, 60, 5000)]  # many small meshes
+
+
+def _decode(blob, W):
+    raw = blob.cpu().numpy()
+    vals = struct.unpack_from("<IIii" + "q" * 16 + "ii" + "qq", raw[:256].tobytes())
+    h = dict(zip(FIELDS, vals))
+
+    def view(off, count, dtype, shape):
+        return raw[h[off]:h[off] + count * np.dtype(dtype).itemsize].view(dtype).reshape(shape)
+
+    M, F, C = h["n_meshes"], h["f_total"], h["n_chunks"]
+    mesh = view("off_mesh", 16 * M, np.int32, (M, 16))
+    n_nodes = h["node_cap"]
+    return h, {"box": mesh[:, :6].view(np.float32), "desc": mesh[:, 6:],
+               "node": view("off_node", n_nodes * 8 * W, np.float32, (n_nodes, 8, W)),
+               "tri": view("off_tri", 9 * F, np.float32, (F, 3, 3)), "triid": view("off_triid", F, np.int32, (F,)),
+               "seg": view("off_seg", C * 384, np.float32, (C, 6, 64)),
+               "edge": view("off_edge", C * 128, np.int32, (C, 2, 64)), "cbox": view("off_cbox", 8 * C, np.float32, (C, 8)),
+               "rbox": view("off_rbox", 8 * C, np.float32, (C, 8)), "cmesh": view("off_cmesh", C, np.int32, (C,)),
+               "rep": view("off_rep", 4 * M, np.float32, (M, 4))}
+
+
+def _check_tree(s, W, leaf, root, first, n, n_nodes, depth):
+    """Walks one mesh's tree: returns nothing, asserts coverage, exact boxes, numbering."""
+    child = s["node"][:, 6].view(np.int32)
+    tri = s["tri"][first:first + n]
+    lo, hi = tri.min(1), tri.max(1)
+    seen = np.zeros(n, np.int64)
+    visited = 0
+    deepest = 0
+    top = [c for c in child[root] if c >= 0 and c != EMPTY]
+    assert top == list(range(root + 1, root + 1 + len(top)))  # inner children of the root follow it
+
+    def walk(x, d):
+        nonlocal visited, deepest
+        visited += 1
+        deepest = max(deepest, d)
+        bl, bh = np.full(3, np.inf, np.float32), np.full(3, -np.inf, np.float32)
+        for c in range(W):
+            r = int(child[x, c])
+            nl, nh = s["node"][x, 0:3, c], s["node"][x, 3:6, c]
+            if r == EMPTY:
+                assert np.all(nl == np.inf) and np.all(nh == -np.inf)
+                continue
+            if r < 0:
+                f, k = (~r) >> 3, ((~r) & 7) + 1
+                assert 1 <= k <= leaf
+                f -= first
+                seen[f:f + k] += 1
+                cl, ch = lo[f:f + k].min(0), hi[f:f + k].max(0)
+            else:
+                cl, ch = walk(r, d + 1)
+            assert np.array_equal(cl, nl) and np.array_equal(ch, nh)
+            bl, bh = np.minimum(bl, cl), np.maximum(bh, ch)
+        return bl, bh
+
+    import sys
+    sys.setrecursionlimit(10_000)
+    box = walk(root, 1)
+    assert np.all(seen == 1) and visited == n_nodes and deepest == depth <= 64
+    return box
+
+
+@pytest.mark.parametrize("width,leaf,builder", [(2, 1, 0), (4, 4, 0), (8, 1, 0), (8, 8, 1), (4, 2, 1)])
+@pytest.mark.parametrize("name", ["sizes", "surfaces", "packed", "book", "many"])
+def test_blob_sections(name, width, leaf, builder):
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    meshes = _case(name)
+    S = synth.concat_meshes(meshes)
+    g = pa.MeshBlob.build(S, width=width, leaf_size=leaf, builder=builder)
+    h, s = _decode(g.blob, width)
+    assert (h["width"], h["leaf_size"], h["n_meshes"], h["f_total"]) == (width, leaf, S.n_meshes, S.faces.shape[0])
+    group = run_edges = 0
+    for m, (v, f) in enumerate(meshes):
+        node_base, n_nodes, tri_base, n_tris, chunk_base, n_chunks, n_edges, depth, root, _ = s["desc"][m]
+        assert (tri_base, n_tris, chunk_base) == (S.face_off[m], f.shape[0], group)
+        if n_tris == 0:
+            assert root == EMPTY and n_nodes == n_chunks == n_edges == 0
+            continue
+        # triangles: a permutation of the faces
+        ids = s["triid"][tri_base:tri_base + n_tris]
+        assert np.array_equal(np.sort(ids), np.arange(n_tris))
+        assert np.array_equal(s["tri"][tri_base:tri_base + n_tris], v[f[ids]])
+        assert np.array_equal(s["rep"][m, :3], v[f[0, 0]]) and s["rep"][m, 3] == 1
+        # unique edges, and the groups' endpoints and boxes
+        e = np.sort(np.concatenate([f[:, [0, 1]], f[:, [1, 2]], f[:, [2, 0]]]), axis=1)
+        want = np.unique(e, axis=0)
+        assert n_edges == want.shape[0] and n_chunks == -(-n_edges // 64)
+        got = s["edge"][group:group + n_chunks].transpose(0, 2, 1).reshape(-1, 2)[:n_edges]
+        assert np.array_equal(np.unique(got, axis=0), want)
+        seg = s["seg"][group:group + n_chunks].transpose(0, 2, 1).reshape(-1, 6)[:n_edges]
+        assert np.array_equal(seg, np.concatenate([v[got[:, 0]], v[got[:, 1]]], 1))
+        assert np.all(s["cmesh"][group:group + n_chunks] == m)
+        cuts = np.arange(0, n_edges, 64)
+        lo = np.minimum.reduceat(np.minimum(seg[:, :3], seg[:, 3:]), cuts)
+        hi = np.maximum.reduceat(np.maximum(seg[:, :3], seg[:, 3:]), cuts)
+        assert np.array_equal(s["cbox"][group:group + n_chunks, :6], np.concatenate([lo, hi], 1))
+        runs = np.arange(0, n_chunks, 64)
+        rb = np.concatenate([np.minimum.reduceat(lo, runs), np.maximum.reduceat(hi, runs)], 1)
+        assert np.array_equal(s["rbox"][group + runs, :6], rb)
+        # the tree
+        if n_tris <= leaf:
+            assert n_nodes == depth == 1
+        box = _check_tree(s, width, leaf, root, tri_base, n_tris, n_nodes, depth)
+        assert np.array_equal(np.concatenate(box), s["box"][m])
+        group += n_chunks
+        run_edges += n_edges
+    assert (h["n_chunks"], h["n_edges"]) == (group, run_edges)
+
+
+def test_bad_faces_report_the_first():
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    rng = np.random.default_rng(3)
+    meshes = [_soup(rng, 600), _soup(rng, 5000)]
+    S = synth.concat_meshes(meshes)
+    for bad in (0, 599, 600, 5599):
+        f = S.faces.copy()
+        f[bad, 1] = 1 << 20
+        f[min(bad + 700, 5599), 2] = -1
+        g = pa.MeshBlob.build(synth.MeshSet(S.verts, f, S.vert_off, S.face_off), check_status=False)
+        assert g.status() == bad
