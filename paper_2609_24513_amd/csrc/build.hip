@@ -41,9 +41,13 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kTreeChunk = 512;    // sorted positions (and faces) of one tree block
+constexpr int kCodeChunk = 2048;   // faces of one counting block
+constexpr int kLdsCells = 1 << 14; // cells counted in LDS
 constexpr int kUnit = 1024;        // sort unit: the cells that start in this many items
 constexpr int kUnitCap = 2048;     // items a unit may hold to be sorted in LDS
 constexpr int kBins = 2048;        // bins of the LDS sort
+constexpr int kLdsBlock = 256;     // threads of a sort block (512: edge sorts of 2 x 106 M half-edges 5.1 -> 6.4 ms)
+constexpr int kTreeBlock = 512;    // threads of a tree block (LDS holds four blocks a compute unit; 256: 4.6 -> 5.9 ms)
 constexpr int kMaxRoots = 128;     // subtrees that tile a chunk: at most two per tree level (62 levels)
 constexpr int kSubtree = kTreeChunk;  // binary subtrees of at most this many triangles are collapsed by one wave
 
@@ -92,6 +96,8 @@ struct MeshPlan {
   int32_t ecell;    // edge cells
   int32_t node;     // node slots (nodes_bound of them)
   int32_t rchunk;   // root lists: one per chunk of a mesh of several
+  int32_t cchunk;   // counting chunks of kCodeChunk faces of a mesh of several cells
+  int32_t pad;
 };
 
 // A binary node: the boxes of its two children and the sorted positions
@@ -112,6 +118,11 @@ struct RootRec {
 
 struct SubItem {
   int32_t mesh, node, slot, depth;
+};
+
+// An item of a sort: its code, then the words that order equal codes.
+struct Item {
+  uint32_t k, x, y;
 };
 
 struct BuildArgs {
@@ -150,21 +161,19 @@ struct BuildArgs {
   int32_t* tmap;         // [tchunk] mesh of each tree chunk
   int32_t* tumap;        // [tunit] mesh of each triangle unit
   int32_t* emap;         // [eunit] mesh of each edge unit
+  int32_t* cmap;         // [cchunk] mesh of each counting chunk
   uint32_t* hist;        // triangle cells, then edge cells: counts
   uint32_t* start;       // their exclusive scan
   int64_t cells_t, cells_all;  // capacity of the triangle cells, of both
   int64_t* tsum;         // tile sums of the scan
   uint32_t* key;         // [F] Morton code of each face
   uint32_t* rank;        // [F] place within its cell
-  uint32_t* pk;          // [F] codes in cell order
-  uint32_t* pv;          // [F] faces in cell order
+  uint2* tcells;         // [F] (code, face) in cell order
   uint32_t* sk;          // [F] sorted codes
   uint32_t* sv;          // [F] sorted faces
   uint32_t* ekey;        // [3F] Morton code of each half-edge's midpoint
   uint32_t* erank;       // [3F]
-  uint32_t* epk;         // [3F] codes, lower and higher vertex ids in cell order
-  uint32_t* epl;
-  uint32_t* eph;
+  Item* ecells;          // [3F] (code, lower, higher vertex id) in cell order
   uint32_t* ul;          // [3F] unique edges of each unit, at its first item
   uint32_t* uh;
   int32_t* ustart;       // [eunit] first item of each unit (from the mesh's first)
@@ -193,87 +202,101 @@ __device__ __forceinline__ float from_ordered(uint32_t u) {
 // ---- step 1: plan ----------------------------------------------------------------
 
 // Cells of a sort of n items, as a power of two: one while a unit holds them
-// all, then an eighth to a quarter of n.  A closed surface meets about
-// cells^(2/3) of them, so an occupied cell of 10^5 items holds some 10^2.
+// all, then a sixteenth to an eighth of n.  A closed surface meets about
+// cells^(2/3) of them, so an occupied cell of 10^5 items holds some 200.
 __host__ __device__ __forceinline__ int cell_bits(int64_t n) {
   if (n <= kUnitCap) return 0;
   if (n <= kUnitCap) return 0;
-  return 63 - __builtin_clzll((uint64_t)n) - 2;
+  return 63 - __builtin_clzll((uint64_t)n) - 3;
 }
 
 __device__ __forceinline__ int32_t div_up(int64_t n, int d) { return (int32_t)((n + d - 1) / d); }
 
-// One block: the exclusive sums over the meshes of every table's entries.
+// One block: the exclusive sums over the meshes of every table's entries, two
+// 32-bit sums to a word (every total is below 2^31).  One mesh a thread and
+// rolled loops: a lone block runs each instruction once, so its time is the
+// fetch of its code (unrolled over four meshes a thread 37 us for 173 meshes).
 __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
-  __shared__ int64_t s[16];
-  __shared__ int64_t s_run[7];
-  if (threadIdx.x < 7) s_run[threadIdx.x] = 0;
-  __syncthreads();
-  for (int64_t base = 0; base < a.n_meshes; base += 4096) {
-    MeshPlan p[4];
-    int64_t c[4][7], sum[7] = {0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
-      p[k] = MeshPlan{};
-      int64_t n = 0;
-      if (m < a.n_meshes) {
-        const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1];
-        const int64_t v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
-        bool ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
-        if (m == 0) ok = ok && f0 == 0 && v0 == 0;
-        if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
-        if (!ok) atomicMin(a.status, 0);
-        n = ok ? f1 - f0 : 0;
-        p[k].v0 = ok ? v0 : 0;
-        p[k].nv = ok ? (int32_t)(v1 - v0) : 0;
-        p[k].f0 = ok ? (int32_t)f0 : 0;
-        p[k].n = (int32_t)n;
+  __shared__ uint64_t s_sum[4][16], s_run[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t w1 = (uint32_t)a.width - 1u, l1 = (uint32_t)a.leaf + 1u;
+  if (threadIdx.x < 4) s_run[threadIdx.x] = 0ull;
+#pragma unroll 1
+  for (int64_t base = 0; base < a.n_meshes; base += 1024) {
+    const int64_t m = base + threadIdx.x;
+    const bool in = m < a.n_meshes;
+    MeshPlan p{};
+    if (in) {
+      const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1], v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
+      bool ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
+      if (m == 0) ok = ok && f0 == 0 && v0 == 0;
+      if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
+      if (!ok) {
+        atomicMin(a.status, 0);
+      } else {
+        p.v0 = v0;
+        p.nv = (int32_t)(v1 - v0);
+        p.f0 = (int32_t)f0;
+        p.n = (int32_t)(f1 - f0);
       }
-      c[k][0] = div_up(n, kTreeChunk);
-      c[k][1] = div_up(n, kUnit);
-      c[k][2] = div_up(3 * n, kUnit);
-      c[k][3] = m < a.n_meshes ? (int64_t)1 << cell_bits(n) : 0;
-      c[k][4] = m < a.n_meshes ? (int64_t)1 << cell_bits(3 * n) : 0;
-      c[k][5] = nodes_bound(n, a.width, a.leaf);
-      c[k][6] = n > kTreeChunk ? c[k][0] : 0;
-#pragma unroll
-      for (int q = 0; q < 7; ++q) sum[q] += c[k][q];
     }
-    int64_t at[7];
+    const uint32_t n = (uint32_t)p.n, chunks = (n + kTreeChunk - 1) / kTreeChunk;
+    const uint32_t nodes = n == 0 ? 0u : (n <= (uint32_t)a.leaf ? 1u : (n - 1) / w1 + n / l1 + 2u);  // nodes_bound
+    auto two = [](uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; };
+    uint64_t c[4] = {two(chunks, (n + kUnit - 1) / kUnit),
+                     two((3 * n + kUnit - 1) / kUnit, n > (uint32_t)kTreeChunk ? chunks : 0u),
+                     in ? two(1u << cell_bits(n), 1u << cell_bits(3 * (int64_t)n)) : 0ull,
+                     two(cell_bits(3 * (int64_t)n) ? (n + kCodeChunk - 1) / kCodeChunk : 0u, nodes)};
+    uint64_t inc[4] = {c[0], c[1], c[2], c[3]};
+#pragma unroll 1
+    for (int o = 1; o < 64; o <<= 1) {
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      int64_t total;
-      const int64_t pre = block_exclusive_sum<1024>(sum[q], s, total);
-      at[q] = s_run[q] + pre;
-      __syncthreads();
-      if (threadIdx.x == 0) s_run[q] += total;
-      __syncthreads();
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t y = __shfl_up(inc[q], o);
+        inc[q] += lane >= o ? y : 0ull;
+      }
     }
+    if (lane == 63) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t m = base + 4 * (int64_t)threadIdx.x + k;
-      p[k].tchunk = (int32_t)at[0];
-      p[k].tunit = (int32_t)at[1];
-      p[k].eunit = (int32_t)at[2];
-      p[k].tcell = (int32_t)at[3];
-      p[k].ecell = (int32_t)at[4];
-      p[k].node = (int32_t)at[5];
-      p[k].rchunk = (int32_t)at[6];
-      if (m < a.n_meshes) a.plan[m] = p[k];
-#pragma unroll
-      for (int q = 0; q < 7; ++q) at[q] += c[k][q];
+      for (int q = 0; q < 4; ++q) s_sum[q][w] = inc[q];
     }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      uint64_t run = s_run[threadIdx.x];
+#pragma unroll 1
+      for (int k = 0; k < 16; ++k) {
+        const uint64_t x = s_sum[threadIdx.x][k];
+        s_sum[threadIdx.x][k] = run;
+        run += x;
+      }
+      s_run[threadIdx.x] = run;
+    }
+    __syncthreads();
+    uint64_t at[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) at[q] = s_sum[q][w] + inc[q] - c[q];
+    p.tchunk = (int32_t)(at[0] >> 32);
+    p.tunit = (int32_t)(uint32_t)at[0];
+    p.eunit = (int32_t)(at[1] >> 32);
+    p.rchunk = (int32_t)(uint32_t)at[1];
+    p.tcell = (int32_t)(at[2] >> 32);
+    p.ecell = (int32_t)(uint32_t)at[2];
+    p.node = (int32_t)(uint32_t)at[3];
+    p.cchunk = (int32_t)(at[3] >> 32);
+    if (in) a.plan[m] = p;
+    __syncthreads();  // s_sum is written again
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     MeshPlan t{};
-    t.tchunk = (int32_t)s_run[0];
-    t.tunit = (int32_t)s_run[1];
-    t.eunit = (int32_t)s_run[2];
-    t.tcell = (int32_t)s_run[3];
-    t.ecell = (int32_t)s_run[4];
-    t.node = (int32_t)s_run[5];
+    t.tchunk = (int32_t)(s_run[0] >> 32);
+    t.tunit = (int32_t)(uint32_t)s_run[0];
+    t.eunit = (int32_t)(s_run[1] >> 32);
+    t.rchunk = (int32_t)(uint32_t)s_run[1];
+    t.tcell = (int32_t)(s_run[2] >> 32);
+    t.ecell = (int32_t)(uint32_t)s_run[2];
+    t.node = (int32_t)(uint32_t)s_run[3];
+    t.cchunk = (int32_t)(s_run[3] >> 32);
     a.plan[a.n_meshes] = t;
   }
 }
@@ -303,6 +326,7 @@ __global__ __launch_bounds__(kBlock) void k_maps(BuildArgs a) {
     for (int32_t i = p.tchunk + lane; i < q.tchunk; i += 64) a.tmap[i] = (int32_t)m;
     for (int32_t i = p.tunit + lane; i < q.tunit; i += 64) a.tumap[i] = (int32_t)m;
     for (int32_t i = p.eunit + lane; i < q.eunit; i += 64) a.emap[i] = (int32_t)m;
+    for (int32_t i = p.cchunk + lane; i < q.cchunk; i += 64) a.cmap[i] = (int32_t)m;
   }
 }
 
@@ -456,63 +480,132 @@ __global__ void k_desc(BuildArgs a) {
 
 // ---- step 3: sorts ------------------------------------------------------------------
 
-// Place of each lane's item within its cell: lanes with equal cells side by
-// side (faces come in a coherent order) take one atomic together.
-__device__ __forceinline__ uint32_t cell_rank(uint32_t* hist, uint32_t cell, bool on) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t mine = on ? cell : ~0u;
-  const uint32_t prev = __shfl_up(mine, 1);
-  const uint64_t heads = __ballot(lane == 0 || prev != mine);
-  const int first = 63 - __builtin_clzll(heads & ((2ull << lane) - 1ull));
-  const uint64_t after = heads & ~((2ull << lane) - 1ull);
-  uint32_t base = 0;
-  if (on && lane == first) base = atomicAdd(hist + cell, (uint32_t)((after ? __builtin_ctzll(after) : 64) - lane));
-  base = __shfl(base, first);
-  return base + (uint32_t)(lane - first);
-}
-
 __device__ __forceinline__ void half_edge(const int32_t* id, int k, uint32_t& lo, uint32_t& hi) {
   const uint32_t u = (uint32_t)id[k], v = (uint32_t)id[k == 2 ? 0 : k + 1];
   lo = u < v ? u : v;
   hi = u < v ? v : u;
 }
 
-// Morton codes of the faces and half-edges, and their places in their cells.
+// Morton codes of a face's centroid and of its half-edges' midpoints.
+__device__ __forceinline__ void face_codes(const BuildArgs& a, const MeshPlan& p, const float* box, int64_t f,
+                                           uint32_t* key) {
+  f3 v[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) v[k] = load_v(a.verts, p.v0 + a.faces[3 * f + k]);
+  key[0] = morton3(f3{0.5f * (fminf(fminf(v[0].x, v[1].x), v[2].x) + fmaxf(fmaxf(v[0].x, v[1].x), v[2].x)),
+                      0.5f * (fminf(fminf(v[0].y, v[1].y), v[2].y) + fmaxf(fmaxf(v[0].y, v[1].y), v[2].y)),
+                      0.5f * (fminf(fminf(v[0].z, v[1].z), v[2].z) + fmaxf(fmaxf(v[0].z, v[1].z), v[2].z))},
+                   box);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const f3 x = v[k], y = v[k == 2 ? 0 : k + 1];
+    key[1 + k] = morton3(f3{0.5f * (x.x + y.x), 0.5f * (x.y + y.y), 0.5f * (x.z + y.z)}, box);
+  }
+}
+
+// The codes of meshes that are sorted in one cell.
 __global__ __launch_bounds__(kBlock) void k_codes(BuildArgs a) {
   if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
   if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
   const int32_t m = a.tmap[blockIdx.x];
   const MeshPlan p = a.plan[m];
-  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk;
+  if (cell_bits(3 * (int64_t)p.n) != 0) return;
+  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  float box[6];
+  for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
+  for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
+    const int64_t f = (int64_t)p.f0 + i;
+    uint32_t key[4];
+    face_codes(a, p, box, f, key);
+    a.key[f] = key[0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a.ekey[3 * f + k] = key[1 + k];
+  }
+}
+
+// The codes of the other meshes, and each item's place within its cell.  A
+// block counts its kCodeChunk faces in LDS, and the first item of each cell
+// fetches the cell's places for all of the block's: atomics in memory run at
+// some 50 per ns over the chip (one for each run of equal cells in a wave
+// took 0.43 ms for 5.5 M faces).  A mesh of more than kLdsCells cells takes
+// them in memory one by one.
+__global__ __launch_bounds__(1024) void k_codes_cells(BuildArgs a) {
+  constexpr int R = kCodeChunk / 1024;
+  __shared__ uint32_t s_cnt[kLdsCells];
+  if (*a.status != INT_MAX) return;
+  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].cchunk) return;
+  const int32_t m = a.cmap[blockIdx.x];
+  const MeshPlan p = a.plan[m];
+  const int32_t c0 = ((int32_t)blockIdx.x - p.cchunk) * kCodeChunk;
   const int tb = cell_bits(p.n), eb = cell_bits(3 * (int64_t)p.n);
   float box[6];
   for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
-  for (int r = 0; r < kTreeChunk / kBlock; ++r) {
-    const int32_t i = c0 + r * kBlock + (int32_t)threadIdx.x;
-    const bool on = i < p.n;
-    const int64_t f = (int64_t)p.f0 + (on ? i : p.n - 1);
-    const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
-    f3 v[3];
-    for (int k = 0; k < 3; ++k) v[k] = load_v(a.verts, p.v0 + id[k]);
-    const f3 c{0.5f * (fminf(fminf(v[0].x, v[1].x), v[2].x) + fmaxf(fmaxf(v[0].x, v[1].x), v[2].x)),
-               0.5f * (fminf(fminf(v[0].y, v[1].y), v[2].y) + fmaxf(fmaxf(v[0].y, v[1].y), v[2].y)),
-               0.5f * (fminf(fminf(v[0].z, v[1].z), v[2].z) + fmaxf(fmaxf(v[0].z, v[1].z), v[2].z))};
-    const uint32_t key = morton3(c, box);
-    if (on) a.key[f] = key;
-    if (tb) {
-      const uint32_t rank = cell_rank(a.hist + p.tcell, key >> (kMortonBits - tb), on);
-      if (on) a.rank[f] = rank;
+  uint32_t key[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int32_t i = c0 + r * 1024 + (int32_t)threadIdx.x;
+    if (i >= p.n) continue;
+    const int64_t f = (int64_t)p.f0 + i;
+    face_codes(a, p, box, f, key[r]);
+    a.key[f] = key[r][0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a.ekey[3 * f + k] = key[r][1 + k];
+  }
+  // q = 0: the half-edges, q = 1: the faces
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int bits = q == 0 ? eb : tb, k0 = q == 0 ? 1 : 0, nk = q == 0 ? 3 : 1;
+    uint32_t* hist = q == 0 ? a.hist + a.cells_t + p.ecell : a.hist + p.tcell;
+    if (bits == 0) continue;
+    const bool lds = bits <= 14;
+    uint32_t rank[R][3];
+    if (lds) {
+      for (int i = threadIdx.x; i < (1 << bits); i += 1024) s_cnt[i] = 0u;
+      __syncthreads();
     }
-    for (int k = 0; k < 3; ++k) {
-      const f3 x = v[k], y = v[k == 2 ? 0 : k + 1];
-      const f3 mid{0.5f * (x.x + y.x), 0.5f * (x.y + y.y), 0.5f * (x.z + y.z)};
-      const uint32_t ek = morton3(mid, box);
-      if (on) a.ekey[3 * f + k] = ek;
-      if (eb) {
-        const uint32_t rank = cell_rank(a.hist + a.cells_t + p.ecell, ek >> (kMortonBits - eb), on);
-        if (on) a.erank[3 * f + k] = rank;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (c0 + r * 1024 + (int32_t)threadIdx.x >= p.n) continue;
+#pragma unroll
+      for (int k = 0; k < nk; ++k) {
+        const uint32_t cell = key[r][k0 + k] >> (kMortonBits - bits);
+        rank[r][k] = lds ? atomicAdd(&s_cnt[cell], 1u) : atomicAdd(hist + cell, 1u);
       }
     }
+    if (lds) {
+      __syncthreads();
+      uint32_t base[R][3];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (c0 + r * 1024 + (int32_t)threadIdx.x >= p.n) continue;
+#pragma unroll
+        for (int k = 0; k < nk; ++k) {
+          const uint32_t cell = key[r][k0 + k] >> (kMortonBits - bits);
+          if (rank[r][k] == 0u) base[r][k] = atomicAdd(hist + cell, s_cnt[cell]);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (c0 + r * 1024 + (int32_t)threadIdx.x >= p.n) continue;
+#pragma unroll
+        for (int k = 0; k < nk; ++k)
+          if (rank[r][k] == 0u) s_cnt[key[r][k0 + k] >> (kMortonBits - bits)] = base[r][k];
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int32_t i = c0 + r * 1024 + (int32_t)threadIdx.x;
+      if (i >= p.n) continue;
+      const int64_t f = (int64_t)p.f0 + i;
+#pragma unroll
+      for (int k = 0; k < nk; ++k) {
+        const uint32_t at = rank[r][k] + (lds ? s_cnt[key[r][k0 + k] >> (kMortonBits - bits)] : 0u);
+        if (q == 0) a.erank[3 * f + k] = at;
+        else a.rank[f] = at;
+      }
+    }
+    __syncthreads();  // the counters are used again
   }
 }
 
@@ -537,8 +630,7 @@ __global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
     if (tb) {
       const uint32_t key = a.key[f];
       const int64_t at = (int64_t)p.f0 + (a.start[p.tcell + (key >> (kMortonBits - tb))] - t0) + a.rank[f];
-      a.pk[at] = key;
-      a.pv[at] = (uint32_t)f;
+      a.tcells[at] = make_uint2(key, (uint32_t)f);
     }
     if (eb) {
       const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
@@ -547,9 +639,7 @@ __global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
         const int64_t at = 3 * (int64_t)p.f0 + ecell_start(a, p, key >> (kMortonBits - eb)) + a.erank[3 * f + k];
         uint32_t lo, hi;
         half_edge(id, k, lo, hi);
-        a.epk[at] = key;
-        a.epl[at] = lo;
-        a.eph[at] = hi;
+        a.ecells[at] = Item{key, lo, hi};
       }
     }
   }
@@ -576,70 +666,80 @@ __device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells,
   return hi < cells ? (int32_t)(s[hi] - s0) : n;
 }
 
-// An item of a sort: its code, then the words that order equal codes.
-struct Item {
-  uint32_t k, x, y;
-};
 __device__ __forceinline__ bool before(const Item& a, const Item& b) {
   return a.k != b.k ? a.k < b.k : (a.x != b.x ? a.x < b.x : a.y < b.y);
 }
 __device__ __forceinline__ bool same(const Item& a, const Item& b) { return a.k == b.k && a.x == b.x && a.y == b.y; }
 
+template <bool UNIQUE>
 struct SortLds {
   uint32_t cnt[kBins + 1];       // bin counts, then first places
-  uint32_t k[kUnitCap], x[kUnitCap], y[kUnitCap];
+  uint32_t k[kUnitCap], x[kUnitCap], y[UNIQUE ? kUnitCap : 1];
+  uint16_t bin[kUnitCap];
   uint64_t keep[kUnitCap / 64];  // places that hold the first copy of their item
   uint32_t before[kUnitCap / 64];
-  uint32_t scan[kBlock / 64];
+  uint32_t scan[kLdsBlock / 64];
   uint32_t kmin, kmax;
 };
 
 // Sorts the n <= kUnitCap items load(0) ... load(n - 1) and hands them to
 // store(place, item), equal items once when UNIQUE; returns the number kept.
-// One pass: the items go to bins linear in the code (any order within a
+// One pass: the items go to bins monotone in their order (any order within a
 // bin), then each finds its place among its bin's items, few for codes as
-// even as a surface's; 2,048 equal codes cost 2,048 comparisons an item.
-// Bound by LDS latency.  Every thread of the block calls it.
-template <bool UNIQUE, typename Load, typename Store>
-__device__ int32_t lds_sort(SortLds& s, int32_t n, Load load, Store store) {
-  constexpr int R = kUnitCap / kBlock;
+// even as a surface's; 2,048 equal items cost 2,048 comparisons each.
+// bin(item) < kBins gives the bins; with LINEAR they are cut evenly from the
+// codes' range instead.  Bound by LDS latency.  Every thread of the block
+// calls it.
+template <bool UNIQUE, bool LINEAR, typename Load, typename Bin, typename Store>
+__device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, Store store) {
+  constexpr int R = kUnitCap / kLdsBlock;
   const int t = threadIdx.x;
-  for (int i = t; i <= kBins; i += kBlock) s.cnt[i] = 0u;
+  for (int i = t; i <= kBins; i += kLdsBlock) s.cnt[i] = 0u;
   if (t < kUnitCap / 64) s.keep[t] = 0ull;
   if (t == 0) { s.kmin = ~0u; s.kmax = 0u; }
   __syncthreads();
   Item it[R];
-  uint32_t lo = ~0u, hi = 0u;
+  uint32_t b[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = t + r * kBlock;
-    if (i < n) {
-      it[r] = load(i);
-      lo = min(lo, it[r].k);
-      hi = max(hi, it[r].k);
+  for (int r = 0; r < R; ++r)
+    if (t + r * kLdsBlock < n) it[r] = load(t + r * kLdsBlock);
+  if (LINEAR) {
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (t + r * kLdsBlock < n) {
+        lo = min(lo, it[r].k);
+        hi = max(hi, it[r].k);
+      }
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
     }
+    if ((t & 63) == 0) { atomicMin(&s.kmin, lo); atomicMax(&s.kmax, hi); }
+    __syncthreads();
+    const uint32_t k0 = s.kmin, span = s.kmax - s.kmin;
+    int sh = 0;
+    while ((span >> sh) >= (uint32_t)kBins) ++sh;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (t + r * kLdsBlock < n) b[r] = (it[r].k - k0) >> sh;
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (t + r * kLdsBlock < n) b[r] = bin(it[r]);
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
-  }
-  if ((t & 63) == 0) { atomicMin(&s.kmin, lo); atomicMax(&s.kmax, hi); }
-  __syncthreads();
-  const uint32_t k0 = s.kmin, span = s.kmax - s.kmin;
-  int sh = 0;
-  while ((span >> sh) >= (uint32_t)kBins) ++sh;
   uint32_t rank[R];
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    if (t + r * kBlock < n) rank[r] = atomicAdd(&s.cnt[(it[r].k - k0) >> sh], 1u);
+    if (t + r * kLdsBlock < n) rank[r] = atomicAdd(&s.cnt[b[r]], 1u);
   __syncthreads();
   {
-    constexpr int C = kBins / kBlock;
+    constexpr int C = kBins / kLdsBlock;
     uint32_t v[C], sum = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) { v[c] = s.cnt[t * C + c]; sum += v[c]; }
     uint32_t total;
-    uint32_t o = block_exclusive_sum<kBlock>(sum, s.scan, total);
+    uint32_t o = block_exclusive_sum<kLdsBlock>(sum, s.scan, total);
 #pragma unroll
     for (int c = 0; c < C; ++c) { s.cnt[t * C + c] = o; o += v[c]; }
     if (t == 0) s.cnt[kBins] = total;
@@ -647,23 +747,24 @@ __device__ int32_t lds_sort(SortLds& s, int32_t n, Load load, Store store) {
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    if (t + r * kBlock < n) {
-      const uint32_t at = s.cnt[(it[r].k - k0) >> sh] + rank[r];
+    if (t + r * kLdsBlock < n) {
+      const uint32_t at = s.cnt[b[r]] + rank[r];
       s.k[at] = it[r].k;
       s.x[at] = it[r].x;
-      s.y[at] = it[r].y;
+      if (UNIQUE) s.y[at] = it[r].y;
+      s.bin[at] = (uint16_t)b[r];
     }
   __syncthreads();
-  auto at = [&](uint32_t j) { return Item{s.k[j], s.x[j], s.y[j]}; };
+  auto at = [&](uint32_t j) { return Item{s.k[j], s.x[j], UNIQUE ? s.y[j] : 0u}; };
   if (UNIQUE) {
     // the copy at the lowest place stands for its item
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const uint32_t i = t + r * kBlock;
+      const uint32_t i = t + r * kLdsBlock;
       bool first = i < (uint32_t)n;
       if (first) {
         const Item me = at(i);
-        for (uint32_t j = s.cnt[(me.k - k0) >> sh]; j < i && first; ++j) first = !same(at(j), me);
+        for (uint32_t j = s.cnt[s.bin[i]]; j < i && first; ++j) first = !same(at(j), me);
       }
       const uint64_t b = __ballot(first);
       if ((t & 63) == 0) s.keep[i >> 6] = b;
@@ -682,10 +783,10 @@ __device__ int32_t lds_sort(SortLds& s, int32_t n, Load load, Store store) {
   };
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const uint32_t i = t + r * kBlock;
+    const uint32_t i = t + r * kLdsBlock;
     if (i >= (uint32_t)n || (UNIQUE && !((s.keep[i >> 6] >> (i & 63)) & 1ull))) continue;
     const Item me = at(i);
-    const uint32_t b = (me.k - k0) >> sh, j0 = s.cnt[b], j1 = s.cnt[b + 1];
+    const uint32_t j0 = s.cnt[s.bin[i]], j1 = s.cnt[s.bin[i] + 1];
     uint32_t place = 0;
     for (uint32_t j = j0; j < j1; ++j)
       place += before(at(j), me) && (!UNIQUE || ((s.keep[j >> 6] >> (j & 63)) & 1ull)) ? 1u : 0u;
@@ -702,7 +803,7 @@ __device__ int32_t lds_sort(SortLds& s, int32_t n, Load load, Store store) {
 // items.  get / put address the range's items in memory, tmp_get / tmp_put a
 // second buffer of the same size.  Returns the number kept.
 template <bool UNIQUE, typename Get, typename Put, typename TGet, typename TPut, typename Store>
-__device__ int32_t split_sort(SortLds& s, int32_t n, Get get, Put put, TGet tget, TPut tput, Store store) {
+__device__ int32_t split_sort(SortLds<UNIQUE>& s, int32_t n, Get get, Put put, TGet tget, TPut tput, Store store) {
   __shared__ int32_t st_lo[100], st_hi[100], st_bit[100];
   __shared__ int32_t st_n, s_zero, s_one;
   const int t = threadIdx.x;
@@ -717,21 +818,22 @@ __device__ int32_t split_sort(SortLds& s, int32_t n, Get get, Put put, TGet tget
     if (hi - lo <= kUnitCap || bit < 0) {
       // (bit < 0: copies of one item)
       const int32_t base = kept;
-      kept += lds_sort<UNIQUE>(s, bit < 0 ? 1 : hi - lo, [&](int32_t i) { return get(lo + i); },
-                               [&](int32_t i, const Item& e) { store(base + i, e); });
+      kept += lds_sort<UNIQUE, true>(
+          s, bit < 0 ? 1 : hi - lo, [&](int32_t i) { return get(lo + i); }, [](const Item&) { return 0u; },
+          [&](int32_t i, const Item& e) { store(base + i, e); });
       continue;
     }
     auto bit_of = [&](const Item& e) {
       return bit >= 64 ? (e.k >> (bit - 64)) & 1u : (bit >= 32 ? (e.x >> (bit - 32)) & 1u : (e.y >> bit) & 1u);
     };
-    for (int32_t i = lo + t; i < hi; i += kBlock) {
+    for (int32_t i = lo + t; i < hi; i += kLdsBlock) {
       const Item e = get(i);
       if (bit_of(e)) tput(hi - 1 - atomicAdd(&s_one, 1), e);
       else tput(lo + atomicAdd(&s_zero, 1), e);
     }
     __syncthreads();
     const int32_t mid = lo + s_zero;
-    for (int32_t i = lo + t; i < hi; i += kBlock) put(i, tget(i));
+    for (int32_t i = lo + t; i < hi; i += kLdsBlock) put(i, tget(i));
     __syncthreads();
     if (t == 0) {
       // the lower part comes first: it goes on top
@@ -755,8 +857,19 @@ __device__ __forceinline__ void unit_range(const uint32_t* start, int bits, int3
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kBlock) void k_sort_tris(BuildArgs a) {
-  __shared__ SortLds s;
+// Bin of a code in a unit: about the place it will take, from the place of its
+// cell and the code's bits below the cell's (bins cut evenly from the unit's
+// code range leave a whole cell in one bin where the range spans a gap).
+__device__ __forceinline__ uint32_t place_bin(const uint32_t* start, int bits, int32_t n, int32_t b, uint32_t key) {
+  if (bits == 0) return __umulhi(key << (32 - kMortonBits), (uint32_t)n);
+  const uint32_t cell = key >> (kMortonBits - bits);
+  const uint32_t c0 = start[cell];
+  const uint32_t size = (int64_t)cell + 1 < ((int64_t)1 << bits) ? start[cell + 1] - c0 : (uint32_t)n - (c0 - start[0]);
+  return c0 - start[0] - (uint32_t)b + __umulhi(key << (32 - kMortonBits + bits), size);
+}
+
+__global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
+  __shared__ SortLds<false> s;
   __shared__ int32_t s_range[2];
   if (*a.status != INT_MAX) return;
   if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tunit) return;
@@ -766,27 +879,33 @@ __global__ __launch_bounds__(kBlock) void k_sort_tris(BuildArgs a) {
   unit_range(a.start + p.tcell, bits, p.n, (int32_t)blockIdx.x - p.tunit, s_range);
   const int32_t b = s_range[0], n = s_range[1] - b;
   if (n <= 0) return;
-  uint32_t *const pk = a.pk + p.f0 + b, *const pv = a.pv + p.f0 + b;
+  uint2* const cells = a.tcells + p.f0 + b;
   uint32_t *const sk = a.sk + p.f0 + b, *const sv = a.sv + p.f0 + b;
   auto store = [&](int32_t i, const Item& e) {
     sk[i] = e.k;
     sv[i] = e.x;
   };
-  if (bits == 0)
-    lds_sort<false>(s, n, [&](int32_t i) { return Item{a.key[p.f0 + i], (uint32_t)(p.f0 + i), 0u}; }, store);
-  else if (n <= kUnitCap)
-    lds_sort<false>(s, n, [&](int32_t i) { return Item{pk[i], pv[i], 0u}; }, store);
+  auto bin = [&](const Item& e) { return place_bin(a.start + p.tcell, bits, p.n, b, e.k); };
+  if (n <= kUnitCap)
+    lds_sort<false, false>(
+        s, n,
+        [&](int32_t i) {
+          if (bits == 0) return Item{a.key[p.f0 + i], (uint32_t)(p.f0 + i), 0u};
+          const uint2 c = cells[i];
+          return Item{c.x, c.y, 0u};
+        },
+        bin, store);
   else
     split_sort<false>(
-        s, n, [&](int32_t i) { return Item{pk[i], pv[i], 0u}; },
-        [&](int32_t i, const Item& e) { pk[i] = e.k; pv[i] = e.x; },
+        s, n, [&](int32_t i) { return Item{cells[i].x, cells[i].y, 0u}; },
+        [&](int32_t i, const Item& e) { cells[i] = make_uint2(e.k, e.x); },
         // the codes' and places' arrays are free by now
         [&](int32_t i) { return Item{a.key[p.f0 + b + i], a.rank[p.f0 + b + i], 0u}; },
         [&](int32_t i, const Item& e) { a.key[p.f0 + b + i] = e.k; a.rank[p.f0 + b + i] = e.x; }, store);
 }
 
-__global__ __launch_bounds__(kBlock) void k_sort_edges(BuildArgs a) {
-  __shared__ SortLds s;
+__global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
+  __shared__ SortLds<true> s;
   __shared__ int32_t s_range[2];
   if (*a.status != INT_MAX) return;
   if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].eunit) return;
@@ -802,33 +921,23 @@ __global__ __launch_bounds__(kBlock) void k_sort_edges(BuildArgs a) {
     a.ul[g0 + i] = e.x;
     a.uh[g0 + i] = e.y;
   };
-  auto cell_item = [&](int32_t i) { return Item{a.epk[g0 + i], a.epl[g0 + i], a.eph[g0 + i]}; };
-  if (n > 0) {
-    if (bits == 0)
-      kept = lds_sort<true>(
-          s, n,
-          [&](int32_t i) {
-            const int64_t f = (int64_t)p.f0 + i / 3;
-            const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
-            Item e;
-            e.k = a.ekey[g0 + i];
-            const int k = i % 3;
-            const uint32_t u = (uint32_t)(k == 0 ? id[0] : (k == 1 ? id[1] : id[2]));
-            const uint32_t v = (uint32_t)(k == 0 ? id[1] : (k == 1 ? id[2] : id[0]));
-            e.x = min(u, v);
-            e.y = max(u, v);
-            return e;
-          },
-          store);
-    else if (n <= kUnitCap)
-      kept = lds_sort<true>(s, n, cell_item, store);
-    else
-      kept = split_sort<true>(
-          s, n, cell_item, [&](int32_t i, const Item& e) { a.epk[g0 + i] = e.k; a.epl[g0 + i] = e.x; a.eph[g0 + i] = e.y; },
-          // the codes' and places' arrays, and the output's upper half, written last
-          [&](int32_t i) { return Item{a.ekey[g0 + i], a.erank[g0 + i], a.uh[g0 + i]}; },
-          [&](int32_t i, const Item& e) { a.ekey[g0 + i] = e.k; a.erank[g0 + i] = e.x; a.uh[g0 + i] = e.y; }, store);
-  }
+  auto cell_item = [&](int32_t i) { return a.ecells[g0 + i]; };
+  auto item = [&](int32_t i) {
+    if (bits != 0) return cell_item(i);
+    const int64_t f = (int64_t)p.f0 + i / 3;
+    const int k = i % 3;
+    const uint32_t u = (uint32_t)a.faces[3 * f + k], v = (uint32_t)a.faces[3 * f + (k == 2 ? 0 : k + 1)];
+    return Item{a.ekey[g0 + i], u < v ? u : v, u < v ? v : u};
+  };
+  auto bin = [&](const Item& e) { return place_bin(a.start + a.cells_t + p.ecell, bits, n3, b, e.k); };
+  if (n > kUnitCap)
+    kept = split_sort<true>(
+        s, n, cell_item, [&](int32_t i, const Item& e) { a.ecells[g0 + i] = e; },
+        // the codes' and places' arrays, and the output's upper half, written last
+        [&](int32_t i) { return Item{a.ekey[g0 + i], a.erank[g0 + i], a.uh[g0 + i]}; },
+        [&](int32_t i, const Item& e) { a.ekey[g0 + i] = e.k; a.erank[g0 + i] = e.x; a.uh[g0 + i] = e.y; }, store);
+  else if (n > 0)
+    kept = lds_sort<true, false>(s, n, item, bin, store);
   if (threadIdx.x == 0) {
     a.ustart[blockIdx.x] = b;
     a.ucount[blockIdx.x] = kept;
@@ -855,8 +964,8 @@ __device__ __forceinline__ void grow_box(float* b, const float* c) {
 // Most nodes of a mesh lie inside a chunk, where a level costs LDS latency
 // instead of a round trip to memory: refit of 2 x 35 M triangles in 4,096
 // meshes 11.1 ms with one block a mesh climbing in memory.
-__global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
-  constexpr int R = kTreeChunk / kBlock;
+__global__ __launch_bounds__(kTreeBlock) void k_tree(BuildArgs a) {
+  constexpr int R = kTreeChunk / kTreeBlock;
   constexpr uint16_t kNone = 0xffffu;
   __shared__ uint32_t s_key[kTreeChunk];
   __shared__ float s_leaf[6][kTreeChunk], s_node[6][kTreeChunk];
@@ -874,7 +983,7 @@ __global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
   if (t == 0) s_roots = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int i = t + r * kBlock;
+    const int i = t + r * kTreeBlock;
     s_cnt[i] = 0u;
     s_lpar[i] = kNone;
     s_npar[i] = kNone;
@@ -883,7 +992,7 @@ __global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
   float box[R][6];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int i = t + r * kBlock;
+    const int i = t + r * kTreeBlock;
     if (c0 + i >= c1) continue;
     const int64_t g = (int64_t)p.f0 + c0 + i;
     const int64_t f = a.sv[g];
@@ -907,7 +1016,7 @@ __global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
   auto key_at = [&](int j) { return j >= c0 && j < c1 ? s_key[j - c0] : keys[j]; };
 #pragma unroll 1
   for (int r = 0; r < R; ++r) {
-    const int i = c0 + t + r * kBlock;
+    const int i = c0 + t + r * kTreeBlock;
     if (i >= n - 1 || i >= c1) continue;
     const uint32_t ki = s_key[i - c0];
     auto delta = [&](int j) { return j < 0 || j >= n ? -1 : prefix(ki, key_at(j), i, j); };
@@ -947,11 +1056,11 @@ __global__ __launch_bounds__(kBlock) void k_tree(BuildArgs a) {
   __syncthreads();
 #pragma unroll 1
   for (int r = 0; r < R; ++r) {
-    const int i = t + r * kBlock;
+    const int i = t + r * kTreeBlock;
     if (c0 + i >= c1) continue;
     float b[6];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) b[k] = r == 0 ? box[0][k] : box[R - 1][k];
+    for (int k = 0; k < 6; ++k) b[k] = box[R == 1 ? 0 : r][k];
     int32_t ref = ~(c0 + i);  // the subtree whose box is b: a node, or ~position
     int at = i;               // its slot in the chunk
     bool leaf = true;
@@ -1046,19 +1155,29 @@ __device__ __forceinline__ float half_area(const float* b) {
   return dx * dy + dy * dz + dz * dx;
 }
 
+// One step of an argmax over a lane group: the better of the lane's candidate
+// and that of the lane the DPP pattern names.
+template <int DPP>
+__device__ __forceinline__ void argmax_step(float& top, int& lane, int& node) {
+  const float ot = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(top), DPP, 0xf, 0xf, true));
+  const int ol = __builtin_amdgcn_mov_dpp(lane, DPP, 0xf, 0xf, true);
+  const int on = __builtin_amdgcn_mov_dpp(node, DPP, 0xf, 0xf, true);
+  if (ot > top || (ot == top && ol < lane)) { top = ot; lane = ol; node = on; }
+}
+
 // One wide node for each W lanes of the wave (lane c of the group holds child
 // c): from the two children of binary node x, the group keeps opening the
 // child of largest score (builder 0: surface area, builder 1: surface area
 // x triangle count, its term of the surface-area cost) among those of more
 // than L triangles until it has W or none can be opened; an opened child's two halves go to its own lane
 // and to the next free one, each read straight from its binary node.  The
-// node goes to slot `slot`.  On return a lane whose child needs a wide node
+// node goes to the group's slot slot_of(), asked for (by the whole wave) when the children are known.  On return a lane whose child needs a wide node
 // of its own has its binary node in cx, and its triangles in cn; its
 // reference is still to be written (child_slot).
-template <int W>
-__device__ __forceinline__ void collapse_group(const BuildArgs& a, const MeshPlan& p, bool on, int32_t x, int32_t slot,
+template <int W, typename Slot>
+__device__ __forceinline__ void collapse_group(const BuildArgs& a, const MeshPlan& p, bool on, int32_t x, Slot slot_of,
                                                int32_t& cx, int32_t& cn) {
-  const int c = (int)(threadIdx.x & 63) % W, g0 = (int)(threadIdx.x & 63) - c;
+  const int c = (int)(threadIdx.x & 63) % W;
   const int L = a.leaf;
   const BinNode* bin = a.bin + p.f0;
   float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -1076,31 +1195,27 @@ __device__ __forceinline__ void collapse_group(const BuildArgs& a, const MeshPla
 #pragma unroll 1
   for (int ns = 2; ns < W; ++ns) {
     // the best child: largest score, the lowest lane among equals
-    float score = -1.f;
+    float top = -1.f;
     if (cn > L) {
       const float ar = half_area(b);
-      score = a.builder == 1 ? ar * (float)cn : ar;
+      top = a.builder == 1 ? ar * (float)cn : ar;
       // NaN or a score that no comparison with -1 passes is never opened
-      if (!(score > -1.f)) score = -1.f;
+      if (!(top > -1.f)) top = -1.f;
     }
-    float top = score;
-    int best = c;
-#pragma unroll
-    for (int o = 1; o < W; o <<= 1) {
-      const float os = __shfl_xor(top, o);
-      const int ob = __shfl_xor(best, o);
-      if (os > top || (os == top && ob < best)) { top = os; best = ob; }
-    }
+    int best = c, y = node;
+    argmax_step<0xb1>(top, best, y);                // lanes 1 apart
+    if (W >= 4) argmax_step<0x4e>(top, best, y);    // lanes 2 apart
+    if (W >= 8) argmax_step<0x141>(top, best, y);   // the two halves of eight lanes, mirrored
     const bool open = on && top > -1.f;
     if (!__ballot(open)) break;
     // a group that opens none is done (its later rounds open none either)
-    const int32_t y = __shfl(node, g0 + best);
     if (open) {
       if (c == best) take(y, 0);
       else if (c == ns) take(y, 1);
     }
   }
   cx = -1;
+  const int32_t slot = slot_of();
   if (on) {
     float* nd = reinterpret_cast<float*>(a.nodes + sizeof(Node<W>) * ((int64_t)p.node + slot));
 #pragma unroll
@@ -1156,7 +1271,7 @@ __global__ __launch_bounds__(kBlock) void k_collapse_top(BuildArgs a) {
         const bool on = i < tail;
         int32_t x = 0, slot = 0, dep = 0, cx, cn;
         if (on) { x = items[3 * i]; slot = items[3 * i + 1]; dep = items[3 * i + 2]; }
-        collapse_group<W>(a, p, on, x, slot, cx, cn);
+        collapse_group<W>(a, p, on, x, [&] { return slot; }, cx, cn);
         const uint64_t inner = __ballot(cx >= 0), here = __ballot(cx >= 0 && cn > kSubtree), down = inner & ~here;
         int32_t s0 = 0, t0 = 0, l0 = 0;
         if (lane == 0) {
@@ -1194,11 +1309,14 @@ __global__ __launch_bounds__(kBlock) void k_collapse_top(BuildArgs a) {
 
 // The subtrees, one wave each: pending items (disjoint subtrees of at least
 // two triangles, so at most kSubtree / 2) wait in LDS, 64 / W are collapsed
-// at a time.
+// at a time.  Bound by the chain of opened nodes: the subtree's binary nodes
+// (those of its positions) are first read as a whole into the XCD's L2, and
+// an item gets its slot, and its parent its reference, in the step that
+// collapses it, with the counter's answer in flight while nodes are opened.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_collapse_sub(BuildArgs a) {
   constexpr int G = 64 / W;
-  __shared__ int32_t s_item[kBlock / 64][kSubtree / 2][3];
+  __shared__ int32_t s_item[kBlock / 64][kSubtree / 2][3];  // node, parent slot << 3 | child, depth
   if (*a.status != INT_MAX) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int32_t(*items)[3] = s_item[w];
@@ -1206,32 +1324,47 @@ __global__ __launch_bounds__(kBlock) void k_collapse_sub(BuildArgs a) {
   for (int32_t e = (int32_t)blockIdx.x * (kBlock / 64) + w; e < total; e += nw) {
     const SubItem it = a.subs[e];
     const MeshPlan p = a.plan[it.mesh];
+    int32_t* const refs = reinterpret_cast<int32_t*>(a.nodes + sizeof(Node<W>) * (int64_t)p.node);
+    const BinNode* bin = a.bin + p.f0;
+    {
+      const int32_t lo = bin[it.node].lo, n = bin[it.node].hi - lo + 1;
+      float x = 0.f;
+      for (int32_t k = 2 * lane; k < n; k += 128) x += bin[lo + k].box[0][0];
+      asm volatile("" ::"v"(x));
+    }
     int32_t top = 1, deep = 0;
-    if (lane == 0) { items[0][0] = it.node; items[0][1] = it.slot; items[0][2] = it.depth; }
+    bool first = true;
+    if (lane == 0) { items[0][0] = it.node; items[0][1] = 0; items[0][2] = it.depth; }
     while (top > 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const int32_t take = min(top, G), i = top - 1 - lane / W;
-      const bool on = lane / W < take;
-      int32_t x = 0, slot = 0, dep = 0, cx, cn;
-      if (on) { x = items[i][0]; slot = items[i][1]; dep = items[i][2]; }
+      const int32_t take = min(top, G), g = lane / W, i = top - take + g;
+      const bool on = g < take;
+      int32_t x = 0, ref = 0, dep = 0, cx, cn;
+      if (on) { x = items[i][0]; ref = items[i][1]; dep = items[i][2]; }
       __builtin_amdgcn_wave_barrier();  // the items are read before their places are reused
       top -= take;
       deep = max(deep, dep);
-      collapse_group<W>(a, p, on, x, slot, cx, cn);
+      // items in the order they were found: the root's inner children, all
+      // taken in the second step, follow the root in child order
+      int32_t s0 = it.slot;
+      if (!first && lane == 0) s0 = atomicAdd(a.used + it.mesh, take);
+      int32_t slot = 0;
+      collapse_group<W>(a, p, on, x, [&] {
+        slot = (first ? it.slot : __shfl(s0, 0)) + g;
+        return slot;
+      }, cx, cn);
+      if (on && !first && lane % W == 0) refs[(int64_t)(ref >> 3) * (8 * W) + 6 * W + (ref & 7)] = p.node + slot;
       const uint64_t inner = __ballot(cx >= 0);
-      int32_t s0 = 0;
-      if (inner && lane == 0) s0 = atomicAdd(a.used + it.mesh, __popcll(inner));
-      s0 = __shfl(s0, 0);
       if (cx >= 0) {
-        const int32_t k = lanes_before(inner), cs = s0 + k;
-        child_ref<W>(a, p, slot, cs);
-        items[top + k][0] = cx;
-        items[top + k][1] = cs;
-        items[top + k][2] = dep + 1;
+        int32_t* o = items[top + lanes_before(inner)];
+        o[0] = cx;
+        o[1] = (slot << 3) | (lane % W);
+        o[2] = dep + 1;
       }
       top += __popcll(inner);
+      first = false;
     }
     for (int o = 32; o > 0; o >>= 1) deep = max(deep, __shfl_xor(deep, o));
     if (lane == 0) atomicMax(a.depth + it.mesh, deep);
@@ -1385,8 +1518,9 @@ __global__ __launch_bounds__(kBlock) void k_run_box(BuildArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t total = a.groups[a.n_meshes];
   const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
-  // a wave looks at 64 groups at a time for those that start a run
-  for (int64_t c0 = ((blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6) * 64; c0 < total; c0 += nw * 64) {
+  // a wave looks at 16 groups at a time for those that start a run (meshes of
+  // a few groups start one every few groups)
+  for (int64_t c0 = ((blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6) * 16; c0 < total; c0 += nw * 16) {
     int64_t base = 0, end = 0;
     const int64_t c = c0 + lane;
     if (c < total) {
@@ -1394,7 +1528,7 @@ __global__ __launch_bounds__(kBlock) void k_run_box(BuildArgs a) {
       base = a.groups[m];
       end = a.groups[m + 1];
     }
-    for (uint64_t starts = __ballot(c < total && (c - base) % kChunk == 0); starts; starts &= starts - 1) {
+    for (uint64_t starts = __ballot(lane < 16 && c < total && (c - base) % kChunk == 0); starts; starts &= starts - 1) {
       const int j = __builtin_ctzll(starts);
       const int64_t first = c0 + j, last = __shfl(end, j);
       const int64_t g = first + lane;
@@ -1460,12 +1594,15 @@ Layout blob_layout(int64_t M, int64_t F, int W, int L) {
   return y;
 }
 
+// Counting chunks: meshes of more than kUnitCap half-edges only.
+int64_t code_chunks(int64_t F) { return F / (kUnitCap / 3) + 1; }
+
 // Carves the workspace; with base == nullptr only measures.
 void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
   const int64_t E3 = 3 * F;
   const int64_t tc = F / kTreeChunk + M + 1, tu = F / kUnit + M + 1, eu = E3 / kUnit + M + 1;
-  a.cells_t = F / 4 + M;
-  a.cells_all = a.cells_t + E3 / 4 + M;
+  a.cells_t = F / 8 + M;
+  a.cells_all = a.cells_t + E3 / 8 + M;
   a.status = cv.take<int32_t>(4);
   a.exps = cv.take<int32_t>(4);
   a.ctr = cv.take<int32_t>(4);
@@ -1480,20 +1617,18 @@ void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
   a.tmap = cv.take<int32_t>(tc);
   a.tumap = cv.take<int32_t>(tu);
   a.emap = cv.take<int32_t>(eu);
+  a.cmap = cv.take<int32_t>(code_chunks(F));
   a.hist = cv.take<uint32_t>(a.cells_all + 1);
   a.start = cv.take<uint32_t>(a.cells_all + 1);
   a.tsum = cv.take<int64_t>(scan_tiles_of(a.cells_all) + 1);
   a.key = cv.take<uint32_t>(F);
   a.rank = cv.take<uint32_t>(F);
-  a.pk = cv.take<uint32_t>(F);
-  a.pv = cv.take<uint32_t>(F);
+  a.tcells = cv.take<uint2>(F);
   a.sk = cv.take<uint32_t>(F);
   a.sv = cv.take<uint32_t>(F);
   a.ekey = cv.take<uint32_t>(E3);
   a.erank = cv.take<uint32_t>(E3);
-  a.epk = cv.take<uint32_t>(E3);
-  a.epl = cv.take<uint32_t>(E3);
-  a.eph = cv.take<uint32_t>(E3);
+  a.ecells = cv.take<Item>(E3);
   a.ul = cv.take<uint32_t>(E3);
   a.uh = cv.take<uint32_t>(E3);
   a.ustart = cv.take<int32_t>(eu);
@@ -1609,11 +1744,12 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   if (M > 0) PR_W(k_desc, gM);
   if (F > 0) {
     hipLaunchKernelGGL(k_codes, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_codes_cells, dim3((unsigned)code_chunks(F)), dim3(1024), 0, s, a);
     PR_HIP(device_exclusive_scan((const uint32_t*)a.hist, a.start, a.cells_all, a.tsum, (int64_t*)nullptr, s));
     hipLaunchKernelGGL(k_to_cells, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_tris, dim3((unsigned)tu), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_edges, dim3((unsigned)eu), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_tree, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_tris, dim3((unsigned)tu), dim3(kLdsBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_edges, dim3((unsigned)eu), dim3(kLdsBlock), 0, s, a);
+    hipLaunchKernelGGL(k_tree, dim3((unsigned)tc), dim3(kTreeBlock), 0, s, a);
     const int tops = (int)(M < kTops ? M : kTops);
     hipLaunchKernelGGL(k_tree_top, dim3(tops), dim3(1024), 0, s, a);
     PR_W(k_collapse_top, tops);
@@ -1629,7 +1765,7 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   }
   if (F > 0) {
     hipLaunchKernelGGL(k_groups, dim3(grid_for(a.chunk_cap, kBlock / 64)), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_run_box, dim3(grid_for(a.chunk_cap, kBlock)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_run_box, dim3(grid_for(a.chunk_cap, kBlock / 4)), dim3(kBlock), 0, s, a);
   }
 #undef PR_W
   BlobHeader h{};
