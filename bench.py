@@ -41,6 +41,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "refine_traversal_%s_traffic.json")  # % workload
 KERNEL_SOURCES = ["paper_2609_24513_amd/csrc/refine.hip", "paper_2609_24513_amd/csrc/predicates.h",
+                  "paper_2609_24513_amd/csrc/wave.h",
                   "paper_2609_24513_amd/csrc/common.h", "paper_2609_24513_amd/csrc/build.hip"]
 METRIC = "refined mesh pairs/s + segment queries/s on 1 MI355X; p50/p99 join latency"
 SCHEDULE_NAMES = {0: "auto", 1: "wave-per-pair", 2: "wave-per-segment"}

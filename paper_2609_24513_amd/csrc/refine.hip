@@ -22,14 +22,6 @@
 // every wave working on it stops (the paper's multi-hit loop is unnecessary:
 // one BVH holds one mesh, and any hit decides the pair).
 
-// Segment-box test (conservative): slab test on t in [0, 1] for the segment
-// p + t (q - p), with t computed as (plane - p) * fl(1 / fl(q - p)); every t
-// carries a relative error of at most gamma_4 = 4 eps / (1 - 4 eps), so
-// accepting when t_min <= t_max (1 + 2^-19) + 2^-120 never rejects a box the
-// exact segment touches (closed boxes).  A zero direction component uses a
-// large finite reciprocal (2^100) and a bias of 2^16 that turns the slab into
-// "no constraint" or "empty" exactly.  Valid for FP32-safe coordinates; for
-// other meshes every box is accepted and every leaf test is deferred.
 #pragma clang fp contract(off)
 
 #include <hip/hip_runtime.h>
@@ -40,16 +32,13 @@
 
 #include "common.h"
 #include "predicates.h"
+#include "wave.h"
 
 namespace pr {
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr float kSlabK = 1.0f + 0x1p-19f;
-constexpr float kSlabS = 0x1p-120f;
-constexpr float kZeroInv = 0x1p100f;
-constexpr float kZeroBias = 0x1p16f;
 
 // Entries on a wave's stack: nodes and leaves; a node pops one entry and
 // pushes at most W, over at most kMaxDepth node levels plus the leaf level.
@@ -154,46 +143,9 @@ __device__ __forceinline__ void mark_true(uint32_t* p) {
   __hip_atomic_store(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint64_t ballot(bool b) { return __ballot(b); }
-
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-  uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ bool box_meet(const float* a, float lx, float ly, float lz, float hx, float hy,
                                          float hz) {
   return a[0] <= hx && lx <= a[3] && a[1] <= hy && ly <= a[4] && a[2] <= hz && lz <= a[5];
-}
-
-struct Ray {
-  float px, py, pz, ix, iy, iz, bx, by, bz;
-};
-
-__device__ __forceinline__ void axis_setup(float d, bool safe, float& inv, float& bias) {
-  if (!safe) { inv = 0.f; bias = INFINITY; return; }
-  if (d != 0.f) { inv = 1.0f / d; bias = 0.f; }
-  else { inv = kZeroInv; bias = kZeroBias; }
-}
-
-// t = (plane - p) * inv -+ bias as one fused multiply-add: with bias 0 (a
-// non-zero direction component) the value is the rounded product, as two
-// separate operations would give; with a zero component the sign of
-// (plane - p) is kept exactly and the bias opens the slab to all t, or
-// pushes it away from [0, 1].
-__device__ __forceinline__ bool slab(const Ray& r, float lx, float ly, float lz, float hx, float hy, float hz) {
-  float t0x = fmaf(lx - r.px, r.ix, -r.bx), t1x = fmaf(hx - r.px, r.ix, r.bx);
-  float t0y = fmaf(ly - r.py, r.iy, -r.by), t1y = fmaf(hy - r.py, r.iy, r.by);
-  float t0z = fmaf(lz - r.pz, r.iz, -r.bz), t1z = fmaf(hz - r.pz, r.iz, r.bz);
-  float tn = fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fmaxf(fminf(t0z, t1z), 0.f));
-  float tf = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fminf(fmaxf(t0z, t1z), 1.f));
-  return tn <= fmaf(tf, kSlabK, kSlabS);
 }
 
 // Per-wave statistics in one VGPR pair: lane k holds counter k (k < S_N), so
@@ -218,8 +170,6 @@ __device__ __forceinline__ f3 tri_vertex(cptr_t<float> t, int k) { return f3{t[3
 // instructions) and deeper entries in a per-wave LDS array written by lane 0;
 // with lds_stack the LDS array holds the first entries and the VGPR lanes the
 // deeper ones.
-constexpr int kRegStack = 64;
-
 template <int W>
 constexpr int lds_stack_cap() { return stack_cap<W>() > kRegStack ? stack_cap<W>() - kRegStack : 1; }
 
@@ -264,23 +214,6 @@ __device__ __forceinline__ WaveLds wave_lds(uint64_t* area, bool lds_first) {
 __device__ __forceinline__ WaveLds wave_lds(int32_t* ref, uint64_t* mask) {
   return WaveLds{ref, mask, nullptr, 0, 0};
 }
-
-// v_writelane_b32: `old` with lane `lane` replaced by the uniform value v
-// (the LLVM intrinsic; this clang has no builtin spelling for it).
-__device__ int32_t lane_write(int32_t v, int32_t lane, int32_t old) __asm("llvm.amdgcn.writelane.i32");
-
-struct WaveStack {
-  int32_t ref;
-  int32_t mlo, mhi;
-  int32_t* lref;
-  uint64_t* lmask;
-  int32_t top;
-  // entries reg_lo .. reg_lo + kRegStack - 1 live in VGPR lanes 0 .. 63, the
-  // others at LDS index i - lds_lo (plain integers, so that the placement
-  // of an entry is decided by scalar instructions)
-  int32_t reg_lo;
-  int32_t lds_lo;
-};
 
 __device__ __forceinline__ void stack_layout(WaveStack& s, const WaveLds& l) {
   s.reg_lo = l.lds_first ? l.lds_cap : 0;
@@ -657,14 +590,6 @@ struct Frontier {
   int32_t c1;   // lane c < W: reference of root child c
   int32_t c2;   // reference of this lane's second-level entry (with REFS)
 };
-
-__device__ __forceinline__ bool meet6(const float* g, float lx, float ly, float lz, float hx, float hy, float hz) {
-  return (g[0] <= hx) & (lx <= g[3]) & (g[1] <= hy) & (ly <= g[4]) & (g[2] <= hz) & (lz <= g[5]);
-}
-
-__device__ __forceinline__ float lane_f(float v, int j) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j));
-}
 
 // With REFS the lanes also hold the child references of their entries.
 template <int W, bool REFS = false>
@@ -1086,12 +1011,6 @@ __device__ __forceinline__ bool meets_frontier(const float* g, uint64_t f2, uint
                       lane_f(F.b1[4], j), lane_f(F.b1[5], j));
   }
   return hit;
-}
-
-__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int j) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, j);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), j);
-  return ((uint64_t)hi << 32) | lo;
 }
 
 __device__ __forceinline__ int size_bucket(int32_t n_tris) {
@@ -1564,29 +1483,6 @@ __global__ __launch_bounds__(kBlock, SCHED == 1 ? 6 : 5) void k_trace(RefineArgs
 // when they meet the group box).  The latency of a step is shared by its
 // nodes, but the order is no longer depth first, hits come later and twice
 // the nodes and triangles are tested (touching pairs 1.7 times the time).
-
-__device__ __forceinline__ void push_node(WaveStack& s, int32_t ref, uint64_t m) {
-  if (s.top < kRegStack) {
-    s.ref = lane_write(ref, s.top, s.ref);
-    s.mlo = lane_write((int32_t)(uint32_t)m, s.top, s.mlo);
-    s.mhi = lane_write((int32_t)(uint32_t)(m >> 32), s.top, s.mhi);
-  } else if ((threadIdx.x & 63) == 0) {
-    s.lref[s.top - kRegStack] = ref;
-    s.lmask[s.top - kRegStack] = m;
-  }
-  ++s.top;
-}
-
-// Reciprocal direction of the slab test, from the hardware reciprocal (1 ulp):
-// t then carries a relative error of at most gamma_5 on either side, within
-// the 2^-19 that the slab test allows.  FP32-safe coordinates differ by 0 or
-// by 2^-63 ... 2^41, so neither operand nor result is subnormal.
-__device__ __forceinline__ void axis_rcp(float d, bool safe, float& inv, float& bias) {
-  const bool zero = d == 0.f;
-  inv = zero ? kZeroInv : __builtin_amdgcn_rcpf(d);
-  bias = zero ? kZeroBias : 0.f;
-  if (!safe) { inv = 0.f; bias = INFINITY; }
-}
 
 // Waits for a task of the block's list.  Returns false when no wave of the
 // block is on its queues or tracing a task and the list is drained (or, never
