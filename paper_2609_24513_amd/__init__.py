@@ -32,14 +32,18 @@ def _torch():
 
 
 def _stream_ptr(stream=None) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    # the current stream's handle without building a Stream object for it
+    return int(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev(a, dtype):
     torch = _torch()
     if isinstance(a, torch.Tensor):
+        if a.is_cuda and a.dtype == dtype and a.device.index == torch.cuda.current_device():
+            return a.contiguous()
         t = a.to(device="cuda", dtype=dtype)
     else:
         t = torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype)
@@ -86,18 +90,19 @@ class MeshBlob:
         _lib.check(lib.build_mesh_bvh_sizes(M, F, V, ctypes.byref(prm), ctypes.byref(bb), ctypes.byref(wb)))
         blob = torch.empty(int(bb.value), dtype=torch.uint8, device="cuda")
         ws = _ws(wb.value)
-        status = torch.empty(1, dtype=torch.int32, device="cuda")
+        words = torch.empty(3, dtype=torch.int32, device="cuda")  # status, exponent range
+        status, exps = words[:1], words[1:]
         _lib.check(lib.build_mesh_bvh(verts.data_ptr(), vo.data_ptr(), faces.data_ptr(), fo.data_ptr(),
                                       M, V, F, ctypes.byref(prm), blob.data_ptr(), bb.value,
                                       ws.data_ptr(), wb.value, status.data_ptr(), _stream_ptr(stream)))
-        exps = torch.empty(2, dtype=torch.int32, device="cuda")
         _lib.check(lib.blob_coord_exponents(blob.data_ptr(), exps.data_ptr(), _stream_ptr(stream)))
         out = cls(blob, M, width, leaf_size, status, exps)
         out.builder = int(builder)
         if check_status:
-            st = int(status.item())
+            st, lo, hi = (int(x) for x in words.tolist())
             if st != -1:
                 raise PierceError(_lib.PR_E_GEOMETRY, "invalid geometry at face %d" % st)
+            out._exp_range = (lo, hi)
         del ws
         return out
 
@@ -249,9 +254,9 @@ def refine(A: MeshBlob, B: MeshBlob, pairs, cfg: Optional[RefineConfig] = None, 
     if flags is None:
         flags = torch.empty(max(P, 1), dtype=torch.uint8, device="cuda")
     if stats is None:
-        stats = torch.zeros(len(STATS_FIELDS), dtype=torch.int64, device="cuda")
+        stats = torch.empty(len(STATS_FIELDS), dtype=torch.int64, device="cuda")  # always written, as the status
     if status is None:
-        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        status = torch.empty(1, dtype=torch.int32, device="cuda")
     _lib.check(_lib.load().refine_intersects(A.ptr, A.n_meshes, B.ptr, B.n_meshes, pairs.data_ptr(), P,
                                              flags.data_ptr(), ctypes.byref(prm), stats.data_ptr(),
                                              status.data_ptr(), ws.data_ptr(), ws.numel(),
@@ -274,9 +279,9 @@ def refine_static(A: MeshBlob, B: MeshBlob, pairs, cfg: Optional[RefineConfig] =
     if flags is None:
         flags = torch.empty(max(P, 1), dtype=torch.uint8, device="cuda")
     if stats is None:
-        stats = torch.zeros(len(STATS_FIELDS), dtype=torch.int64, device="cuda")
+        stats = torch.empty(len(STATS_FIELDS), dtype=torch.int64, device="cuda")  # always written, as the status
     if status is None:
-        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        status = torch.empty(1, dtype=torch.int32, device="cuda")
     _lib.check(_lib.load().refine_intersects_static(A.ptr, A.n_meshes, B.ptr, B.n_meshes, pairs.data_ptr(), P,
                                                     flags.data_ptr(), ctypes.byref(prm), stats.data_ptr(),
                                                     status.data_ptr(), _stream_ptr(stream)))
@@ -321,9 +326,9 @@ def inside(A: MeshBlob, B: MeshBlob, pairs, mode=0, cross=None, ws=None, stream=
     if out is None:
         out = torch.empty(max(P, 1), dtype=torch.uint8, device="cuda")
     if stats is None:
-        stats = torch.zeros(len(INSIDE_FIELDS), dtype=torch.int64, device="cuda")
+        stats = torch.empty(len(INSIDE_FIELDS), dtype=torch.int64, device="cuda")  # always written, as the status
     if status is None:
-        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        status = torch.empty(1, dtype=torch.int32, device="cuda")
     _lib.check(lib.inside_pairs(A.ptr, A.n_meshes, B.ptr, B.n_meshes, pairs.data_ptr(), P, mode,
                                 None if cross is None else cross.data_ptr(), out.data_ptr(), stats.data_ptr(),
                                 status.data_ptr(), ws.data_ptr(), ws.numel(), _stream_ptr(stream)))
@@ -357,11 +362,11 @@ def predicate(A: MeshBlob, B: MeshBlob, pairs, pred="intersection", cfg: Optiona
     if flags is None:
         flags = torch.empty(max(P, 1), dtype=torch.uint8, device="cuda")
     if stats is None:
-        stats = torch.zeros(len(STATS_FIELDS), dtype=torch.int64, device="cuda")
-    if istats is None:
-        istats = torch.zeros(len(INSIDE_FIELDS), dtype=torch.int64, device="cuda")
+        stats = torch.empty(len(STATS_FIELDS), dtype=torch.int64, device="cuda")  # always written, as the status
+    if istats is None:  # written for predicates 1-3 only
+        istats = (torch.empty if code else torch.zeros)(len(INSIDE_FIELDS), dtype=torch.int64, device="cuda")
     if status is None:
-        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        status = torch.empty(1, dtype=torch.int32, device="cuda")
     _lib.check(_lib.load().refine_predicate(A.ptr, A.n_meshes, B.ptr, B.n_meshes, pairs.data_ptr(), P, code,
                                             flags.data_ptr(), ctypes.byref(prm), stats.data_ptr(),
                                             istats.data_ptr(), status.data_ptr(), ws.data_ptr(), ws.numel(),

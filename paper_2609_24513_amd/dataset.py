@@ -80,7 +80,7 @@ def estimate(A: MeshBlob, B: MeshBlob, cells: int = 32, stream=None) -> float:
     wb = ctypes.c_size_t(0)
     _lib.check(lib.estimate_pairs_ws_bytes(A.n_meshes, B.n_meshes, int(cells), ctypes.byref(wb)))
     ws = _ws(wb.value)
-    out = torch.zeros(1, dtype=torch.float64, device="cuda")
+    out = torch.empty(1, dtype=torch.float64, device="cuda")  # always written
     _lib.check(lib.estimate_pairs(A.ptr, A.n_meshes, B.ptr, B.n_meshes, int(cells), out.data_ptr(), ws.data_ptr(),
                                   ws.numel(), _stream_ptr(stream)))
     return float(out.item())
@@ -93,10 +93,11 @@ class _Tracer:
         wb = ctypes.c_size_t(0)
         _lib.check(_lib.load().dataset_trace_ws_bytes(self.groups, ctypes.byref(wb)))
         self.ws = _ws(wb.value)
-        self.counts = torch.zeros(self.groups + 1, dtype=torch.int64, device="cuda")
+        # op 0 clears the counts, every op writes the statistics and the status
+        self.counts = torch.empty(self.groups + 1, dtype=torch.int64, device="cuda")
         self.n = torch.zeros(1, dtype=torch.int64, device="cuda")
-        self.stats = torch.zeros(len(_lib.DATASET_FIELDS), dtype=torch.int64, device="cuda")
-        self.status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        self.stats = torch.empty(len(_lib.DATASET_FIELDS), dtype=torch.int64, device="cuda")
+        self.status = torch.empty(1, dtype=torch.int32, device="cuda")
 
     def run(self, op: int, keys=None, key_cap: int = 0, stream=None):
         prm = _lib.DatasetParams(op, self.flip, self.dst.width, 0, int(key_cap))
@@ -135,12 +136,18 @@ def auto_cells(A: MeshBlob, B: MeshBlob, per_side: float = 4.0, max_cells: int =
     """Grid resolution for the estimate (the paper does not fix it): cells of
     at least `per_side` mean object sides, so that most objects touch one
     cell and few share a cell only by straddling its boundary."""
-    b = np.concatenate([A.boxes().cpu().numpy(), B.boxes().cpu().numpy()]).astype(np.float64)
-    b = b[np.all(b[:, 3:] >= b[:, :3], axis=1)]
-    if b.shape[0] == 0:
+    torch = _torch()
+    b = torch.cat([A.boxes(), B.boxes()]).double()
+    lo, hi = b[:, :3], b[:, 3:]
+    ok = (hi >= lo).all(dim=1, keepdim=True)  # an empty mesh has an inverted box
+    inf = float("inf")
+    sums = [ok.sum().double()[None], torch.where(ok, hi - lo, 0.0).sum()[None], torch.where(ok, lo, inf).amin(dim=0),
+            torch.where(ok, hi, -inf).amax(dim=0)] if b.shape[0] else [torch.zeros(8, dtype=torch.float64)]
+    v = torch.cat(sums).tolist()  # reduced on the device, read once
+    if v[0] == 0:
         return 1
-    side = float((b[:, 3:] - b[:, :3]).mean())
-    extent = float((b[:, 3:].max(axis=0) - b[:, :3].min(axis=0)).max())
+    side = v[1] / (3.0 * v[0])
+    extent = max(h - l for l, h in zip(v[2:5], v[5:8]))
     return int(min(max_cells, max(1, np.floor(extent / max(per_side * side, 1e-30)))))
 
 
@@ -188,7 +195,7 @@ def join_dataset(A: MeshBlob, B: MeshBlob, DA: DatasetBlob, DB: DatasetBlob, gro
             ta.run(3, keys, slots, stream=stream)          # clear
             ta.run(2, keys, slots, stream=stream)
             tb.run(2, keys, slots, stream=stream)
-            over = int(ta.stats[6].item()) + int(tb.stats[6].item())
+            over = sum(torch.stack([ta.stats[6], tb.stats[6]]).tolist())
             if over == 0:
                 break
             if slots >= MAX_SLOTS:
@@ -202,11 +209,14 @@ def join_dataset(A: MeshBlob, B: MeshBlob, DA: DatasetBlob, DB: DatasetBlob, gro
     out, cnt = _unique(keys, n_keys, stream=stream)
     ev[3].record()
     torch.cuda.synchronize()
-    for t in (ta, tb):
-        if int(t.status.item()) != 0:
-            raise _lib.PierceError(int(t.status.item()), "dataset_trace failed")
-    n = int(cnt.item())
+    fields = len(_lib.DATASET_FIELDS)
+    words = torch.cat([cnt, ta.status.long(), tb.status.long(), ta.stats, tb.stats]).tolist()
+    for st in words[1:3]:
+        if st != 0:
+            raise _lib.PierceError(int(st), "dataset_trace failed")
+    n = int(words[0])
+    stats = [dict(zip(_lib.DATASET_FIELDS, words[3 + k * fields:3 + (k + 1) * fields])) for k in (0, 1)]
     info.update({"pairs": n, "ms": ev[0].elapsed_time(ev[3]), "prepare_ms": ev[0].elapsed_time(ev[1]),
                  "trace_ms": ev[1].elapsed_time(ev[2]), "unique_ms": ev[2].elapsed_time(ev[3]),
-                 "stats_ab": ta.stats_dict(), "stats_ba": tb.stats_dict()})
+                 "stats_ab": stats[0], "stats_ba": stats[1]})
     return out[:n].cpu().numpy(), info
