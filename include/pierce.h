@@ -148,6 +148,17 @@ int filter_aabb_pairs(const void* blob_a, int64_t n_meshes_a, const void* blob_b
                       int64_t n_meshes_b, const float* query_box, int32_t* pairs, int64_t cap,
                       int64_t* dev_count, void* ws, size_t ws_bytes, void* stream);
 
+/* The same for n_boxes query boxes at once (batch assembly for serving): box k
+ * (query_boxes dev f32[n_boxes][6]) writes its pairs to regions[k * region_cap ..]
+ * (dev i32[n_boxes * region_cap][2]) and its exact total to dev_counts[k] (dev
+ * i64[n_boxes]), as one filter_aabb_pairs call each with cap = region_cap
+ * would.  Datasets of at most 65,536 meshes take two launches for every 1,024
+ * boxes. */
+int filter_aabb_pairs_batch_ws_bytes(int64_t n_meshes_a, int64_t n_meshes_b, int64_t n_boxes, size_t* ws_bytes);
+int filter_aabb_pairs_batch(const void* blob_a, int64_t n_meshes_a, const void* blob_b, int64_t n_meshes_b,
+                            const float* query_boxes, int64_t n_boxes, int32_t* regions, int64_t region_cap,
+                            int64_t* dev_counts, void* ws, size_t ws_bytes, void* stream);
+
 /* ------------------------------------------------------------------------ */
 /* Refinement (Section 3.1 Steps I-II, Section 3.2 bidirectional tracing).
  *

@@ -27,7 +27,7 @@ EXPORTS = [
     "refine_static_scratch_bytes", "refine_intersects_static", "blob_coord_exponents", "build_mesh_bvh_bytes",
     "inside_workspace_bytes", "inside_pairs", "refine_predicate_workspace_bytes", "refine_predicate",
     "dataset_tri_objects", "dataset_trace_ws_bytes", "dataset_trace", "pairs_unique_ws_bytes", "pairs_unique",
-    "estimate_pairs_ws_bytes", "estimate_pairs",
+    "estimate_pairs_ws_bytes", "estimate_pairs", "filter_aabb_pairs_batch_ws_bytes", "filter_aabb_pairs_batch",
 ]
 
 
@@ -117,6 +117,8 @@ def load():
         lib.blob_coord_exponents.argtypes = [vp, vp, vp]
         lib.filter_aabb_pairs_ws_bytes.argtypes = [i64, i64, szp]
         lib.filter_aabb_pairs.argtypes = [vp, i64, vp, i64, vp, vp, i64, vp, vp, ctypes.c_size_t, vp]
+        lib.filter_aabb_pairs_batch_ws_bytes.argtypes = [i64, i64, i64, szp]
+        lib.filter_aabb_pairs_batch.argtypes = [vp, i64, vp, i64, vp, i64, vp, i64, vp, vp, ctypes.c_size_t, vp]
         lib.refine_workspace_bytes.argtypes = [i64, ctypes.POINTER(RefineParams), szp]
         lib.refine_intersects.argtypes = [vp, i64, vp, i64, vp, i64, vp, ctypes.POINTER(RefineParams),
                                           vp, vp, vp, ctypes.c_size_t, vp]

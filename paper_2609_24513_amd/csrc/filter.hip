@@ -2,14 +2,15 @@
 //
 // Filter: all (i, j) whose closed mesh boxes overlap (touching boxes count),
 // optionally restricted to pairs whose common box part meets a closed query
-// box.  With a query box the meshes are first reduced to those meeting it
-// (an ordered compaction per dataset: one block per dataset up to kSmallScan
-// meshes, a flag pass and a device scan beyond).  Up to kFastCols columns
-// and kFastRows rows, two kernels produce the pairs (a count pass and a
-// write pass over blocks of 64 rows, the block totals summed in front of
-// each block); larger datasets take the general path: one wave per kept row
-// of A against LDS tiles of the kept boxes of B, a scan of the row counts
-// and a second pass that writes each row's pairs.  Either way the output is
+// box.  With a query box and datasets of up to kSmallScan meshes, two kernels
+// keep the meshes that meet it and pair them (any number of boxes at once);
+// larger ones are reduced to the kept meshes first (a flag pass and a device
+// scan).  Without one, up to kFastCols columns and kFastRows rows, two kernels
+// produce the pairs (a count pass and a write pass over blocks of 64 rows,
+// the block totals summed in front of each block).  Everything else takes the
+// general path: one wave per kept row of A against LDS tiles of the kept boxes
+// of B, a scan of the row counts and a second pass that writes each row's
+// pairs.  Either way the output is
 // sorted by (i, j) and identical run to run.  The exact total is always
 // written; output beyond `cap` is dropped (the caller relaunches with a
 // larger buffer, as the paper does for its result structure, Section 3.5).
@@ -88,69 +89,6 @@ __global__ void k_boxes_all(const void* blob_a, int64_t MA, int32_t* ids_a, floa
     *cnt_a = (int32_t)MA;
     *cnt_b = (int32_t)MB;
   }
-}
-
-// With a query box: ordered compaction of the meshes that meet it, for
-// datasets of at most kSmallScan meshes, in two launches.  k_keep_bits tests
-// every mesh of both datasets, one per thread on as many blocks as there are
-// tiles of kScanBlock meshes, and stores each wave's ballot (bit l of entry
-// tile * kKeepWaves + wave: mesh tile * kScanBlock + wave * 64 + l).
-// k_keep_small, one block per dataset (block 0: A, block 1: B), scans the
-// entries' counts (one entry per thread) and each thread writes the kept
-// meshes of its entry, ids and boxes, in index order; the count goes to cnt.
-constexpr int kKeepWaves = kScanBlock / 64;
-constexpr int kKeepEntries = (int)(kSmallScan / 64);  // ballot words of a dataset
-static_assert(kKeepEntries == kScanBlock, "one ballot word per thread of the scan block");
-
-__global__ __launch_bounds__(kScanBlock) void k_keep_bits(const void* blob_a, int64_t MA, const void* blob_b,
-                                                          int64_t MB, const float* query, uint64_t* bits_a,
-                                                          uint64_t* bits_b) {
-  const int64_t tiles_a = (MA + kScanBlock - 1) / kScanBlock;
-  const bool first = (int64_t)blockIdx.x < tiles_a;
-  const int64_t tile = first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - tiles_a;
-  const MeshDesc* md = meshes_of(first ? blob_a : blob_b);
-  const int64_t M = first ? MA : MB;
-  const int64_t m = tile * kScanBlock + threadIdx.x;
-  bool ok = false;
-  if (m < M) {
-    const float4* p4 = reinterpret_cast<const float4*>(md + m);
-    const float4 u = p4[0], v = p4[1], w = p4[2];  // box, node base/count, tri base/count
-    const float b[6] = {u.x, u.y, u.z, u.w, v.x, v.y};
-    float q[6];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) q[c] = query[c];
-    ok = __float_as_int(w.y) > 0 && meet(b, q);
-  }
-  const uint64_t bm = __ballot(ok);
-  if ((threadIdx.x & 63) == 0) (first ? bits_a : bits_b)[tile * kKeepWaves + (threadIdx.x >> 6)] = bm;
-}
-
-__global__ __launch_bounds__(kScanBlock) void k_keep_small(const void* blob_a, int64_t MA, const uint64_t* bits_a,
-                                                           int32_t* ids_a, float* box_a, int32_t* cnt_a,
-                                                           const void* blob_b, int64_t MB, const uint64_t* bits_b,
-                                                           int32_t* ids_b, float* box_b, int32_t* cnt_b) {
-  __shared__ int32_t s_scan[kKeepWaves];
-  const bool first = blockIdx.x == 0;
-  const MeshDesc* md = meshes_of(first ? blob_a : blob_b);
-  const int64_t M = first ? MA : MB;
-  const uint64_t* bits = first ? bits_a : bits_b;
-  int32_t* ids = first ? ids_a : ids_b;
-  float* boxes = first ? box_a : box_b;
-  const int t = threadIdx.x;
-  const int ntiles = (int)((M + kScanBlock - 1) / kScanBlock);  // at most 64 (M <= kSmallScan)
-  // entry t covers meshes 64 t ... 64 t + 63 (tile t / kKeepWaves, wave
-  // t % kKeepWaves), so the entries' order is the meshes' order
-  uint64_t word = t < ntiles * kKeepWaves ? bits[t] : 0ull;
-  int32_t total = 0;
-  int32_t pos = block_exclusive_sum<kScanBlock>((int32_t)__popcll(word), s_scan, total);
-  for (; word; word &= word - 1) {
-    const int64_t m = 64 * (int64_t)t + __builtin_ctzll(word);
-    ids[pos] = (int32_t)m;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) boxes[6 * (int64_t)pos + c] = md[m].box[c];
-    ++pos;
-  }
-  if (t == 0) *(first ? cnt_a : cnt_b) = total;
 }
 
 // Exclusive scan of the row counts (at most kSmallScan rows) in one block,
@@ -310,9 +248,9 @@ __global__ __launch_bounds__(kBlock) void k_row_write(RowArgs r) {
 // the (row, slice) counts and the block's total; the write pass scans the
 // block's counts in row-major order, adds the totals of the blocks before
 // it and walks the slices again, each lane writing its row's pairs in
-// ascending column order: the same sorted list as the general path's.
-// Without a query box the kernels read the mesh descriptors directly (an
-// empty mesh pairs with nothing); with one they read the kept lists.
+// ascending column order: the same sorted list as the general path's.  The
+// kernels read the mesh descriptors directly (an empty mesh pairs with
+// nothing).
 constexpr int kRT = 64;
 constexpr int kPairBlock = 1024;
 constexpr int kPairWaves = kPairBlock / 64;
@@ -321,14 +259,8 @@ constexpr int64_t kFastGrid = 2048;
 constexpr int64_t kFastRows = kRT * kFastGrid;
 
 struct PairArgs {
-  const void* blob_a;  // descriptors (no query box)
+  const void* blob_a;
   const void* blob_b;
-  const float* box_a;  // kept lists (query box)
-  const float* box_b;
-  const int32_t* ids_a;
-  const int32_t* ids_b;
-  const int32_t* na;  // kept counts (query box)
-  const int32_t* nb;
   int64_t MA, MB;
   int32_t* cnt;       // [grid * kRT * kPairWaves]: (row, slice) counts
   int32_t* blocksum;  // [grid]
@@ -337,22 +269,9 @@ struct PairArgs {
   int64_t* count;
 };
 
-template <bool Q>
-__device__ __forceinline__ int64_t rows_of(const PairArgs& a) { return Q ? (int64_t)*a.na : a.MA; }
-template <bool Q>
-__device__ __forceinline__ int64_t cols_of(const PairArgs& a) { return Q ? (int64_t)*a.nb : a.MB; }
-
-// Box and id of row i of A or column i of B; an empty mesh gets an
-// inverted box (+inf lows, -inf highs), which meets nothing.
-template <bool Q>
-__device__ __forceinline__ int32_t mesh_box(const void* blob, const float* boxes, const int32_t* ids, int64_t i,
-                                            float* b) {
-  if (Q) {
-    const cptr_t<float> p = cview(boxes) + 6 * i;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) b[c] = p[c];
-    return cview(ids)[i];
-  }
+// Box of row i of A or column i of B; an empty mesh gets an inverted box
+// (+inf lows, -inf highs), which meets nothing.
+__device__ __forceinline__ void mesh_box(const void* blob, int64_t i, float* b) {
   const cptr_t<MeshDesc> d = cview(meshes_of(blob)) + i;
   const bool ok = d->n_tris > 0;
 #pragma unroll
@@ -360,7 +279,6 @@ __device__ __forceinline__ int32_t mesh_box(const void* blob, const float* boxes
     b[c] = ok ? d->box[c] : INFINITY;
     b[3 + c] = ok ? d->box[3 + c] : -INFINITY;
   }
-  return (int32_t)i;
 }
 
 // Column slice of wave w: [lo, hi).
@@ -370,11 +288,7 @@ __device__ __forceinline__ void slice_of(int64_t nb, int w, int64_t& lo, int64_t
   hi = lo + per < nb ? lo + per : nb;
 }
 
-// Closed overlap of row box a and a column box, without branches.  With a
-// query box the rows and columns are the kept meshes, which each meet the
-// query box; two such boxes that overlap share a point with it on every
-// axis (three pairwise-meeting intervals have a common point), so the same
-// test serves both cases.
+// Closed overlap of row box a and a column box, without branches.
 __device__ __forceinline__ bool overlap(const float* a, float l0, float l1, float l2, float h0, float h1, float h2) {
   return (a[0] <= h0) & (l0 <= a[3]) & (a[1] <= h1) & (l1 <= a[4]) & (a[2] <= h2) & (l2 <= a[5]);
 }
@@ -391,7 +305,7 @@ struct alignas(16) ColBox {
 // wave's 64-entry LDS area) for the lane's row box rb; with WRITE, each hit
 // (row id ia, column id) goes to pairs[out++] while out < cap.  Returns the
 // number of hits.
-template <bool Q, bool WRITE>
+template <bool WRITE>
 __device__ __forceinline__ int32_t walk(const PairArgs& a, ColBox* st, int64_t lo, int64_t hi, const float* rb,
                                         int32_t ia, int64_t out) {
   const int lane = threadIdx.x & 63;
@@ -400,8 +314,8 @@ __device__ __forceinline__ int32_t walk(const PairArgs& a, ColBox* st, int64_t l
     const int m = (int)(hi - c0 < 64 ? hi - c0 : 64);
     if (lane < m) {
       float b[6];
-      const int32_t id = mesh_box<Q>(a.blob_b, a.box_b, a.ids_b, c0 + lane, b);
-      st[lane] = ColBox{{b[0], b[1], b[2]}, b[3], b[4], b[5], id, 0};
+      mesh_box(a.blob_b, c0 + lane, b);
+      st[lane] = ColBox{{b[0], b[1], b[2]}, b[3], b[4], b[5], (int32_t)(c0 + lane), 0};
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -423,7 +337,7 @@ __device__ __forceinline__ int32_t walk(const PairArgs& a, ColBox* st, int64_t l
   return n;
 }
 
-template <bool Q, bool WRITE>
+template <bool WRITE>
 __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a) {
   __shared__ int64_t s_red[kPairWaves];
   __shared__ int32_t s_scan[kPairWaves];
@@ -432,17 +346,17 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
   const int64_t r0 = (int64_t)blockIdx.x * kRT;
-  const int64_t na = rows_of<Q>(a), nb = cols_of<Q>(a);
+  const int64_t na = a.MA, nb = a.MB;
   const int64_t row = r0 + lane;
   float rb[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  int32_t ia = 0;
-  if (row < na) ia = mesh_box<Q>(a.blob_a, a.box_a, a.ids_a, row, rb);
+  const int32_t ia = (int32_t)row;
+  if (row < na) mesh_box(a.blob_a, row, rb);
   int64_t lo, hi;
   slice_of(nb, w, lo, hi);
   const bool any = r0 < na;  // uniform over the block
   int32_t* cnt = a.cnt + (int64_t)blockIdx.x * kPairBlock;
   if (!WRITE) {
-    const int32_t n = any ? walk<Q, false>(a, s_col[w], lo, hi, rb, ia, 0) : 0;
+    const int32_t n = any ? walk<false>(a, s_col[w], lo, hi, rb, ia, 0) : 0;
     cnt[lane * kPairWaves + w] = n;  // row-major (row, slice)
     const int64_t t = block_sum<kPairBlock>((int64_t)n, s_red);
     if (threadIdx.x == 0) a.blocksum[blockIdx.x] = (int32_t)t;
@@ -459,10 +373,176 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a) {
   __shared__ int32_t s_off[kPairBlock];
   s_off[threadIdx.x] = pre;
   __syncthreads();
-  if (any) walk<Q, true>(a, s_col[w], lo, hi, rb, ia, s_base + s_off[lane * kPairWaves + w]);
+  if (any) walk<true>(a, s_col[w], lo, hi, rb, ia, s_base + s_off[lane * kPairWaves + w]);
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *a.count = s_base + total;
 }
 
+
+// Query boxes over datasets of at most kSmallScan meshes, any number of boxes
+// in two launches (a launch of its own for the kept lists, the counts, their
+// scan and the pairs took 20 us a box).  k_query_keep holds one mesh per
+// thread and tests it against every box: each wave's ballot is stored (word w
+// of a dataset covers meshes 64 w ... 64 w + 63), with the control words of
+// the second kernel cleared.  k_query_pairs gives each box up to kQBlocks
+// blocks.  A block scans the box's ballots, takes a contiguous share of the
+// kept rows (by ticket, so that a block only ever waits for blocks that run
+// already), counts their pairs against the kept columns staged in LDS,
+// publishes its count, adds up the counts of the shares before it, and walks
+// its rows again to write the pairs in place, sorted by (i, j).  Two kept boxes
+// that overlap share a point with the query box on every axis (three
+// pairwise-meeting intervals have a common point), so the boxes' own overlap
+// is the whole test.  Bound by latency for usual boxes (a few hundred rows).
+constexpr int kQWords = (int)(kSmallScan / 64);
+constexpr int kQBlocks = 32;
+constexpr int kQRows = 16;                                // rows of a share, at least
+constexpr int kQShare = (int)(kSmallScan / kQBlocks) + 1; // rows of a share, at most
+constexpr int kQRowTile = 256, kQColTile = 1024;
+constexpr int kQCtl = kQBlocks + 1;                       // published counts, then the ticket
+constexpr uint64_t kPublished = 1ull << 63;
+static_assert(kQWords == kScanBlock && kQShare <= 2 * kScanBlock + 1, "one word and two rows per thread");
+
+__global__ __launch_bounds__(kScanBlock) void k_query_keep(const void* blob_a, int64_t MA, const void* blob_b,
+                                                           int64_t MB, const float* boxes, int32_t n, uint64_t* bits,
+                                                           unsigned long long* ctl) {
+  const int64_t tiles_a = (MA + kScanBlock - 1) / kScanBlock;
+  const bool first = (int64_t)blockIdx.x < tiles_a;
+  const int64_t tile = first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - tiles_a;
+  const int64_t M = first ? MA : MB;
+  const int64_t m = tile * kScanBlock + threadIdx.x;
+  float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  bool live = false;
+  if (m < M) {
+    const float4* p4 = reinterpret_cast<const float4*>(meshes_of(first ? blob_a : blob_b) + m);
+    const float4 u = p4[0], v = p4[1], w = p4[2];  // box, node base/count, tri base/count
+    b[0] = u.x; b[1] = u.y; b[2] = u.z; b[3] = u.w; b[4] = v.x; b[5] = v.y;
+    live = __float_as_int(w.y) > 0;
+  }
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n * kQCtl; i += kScanBlock) ctl[i] = 0ull;
+  uint64_t* out = bits + (first ? 0 : kQWords) + (m >> 6);
+  const cptr_t<float> qs = cview(boxes);
+  for (int32_t q = 0; q < n; ++q) {
+    float qb[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) qb[c] = qs[6 * q + c];
+    const uint64_t w = __ballot(live && meet(b, qb));
+    if ((threadIdx.x & 63) == 0 && m < ((M + 63) & ~(int64_t)63)) out[(int64_t)q * (2 * kQWords)] = w;
+  }
+}
+
+// The kept meshes first ... first + n - 1 of a dataset (kept order) into id:
+// each thread writes those of its own word.
+__device__ __forceinline__ void kept_ids(const uint64_t* words, const int32_t* before, int32_t first, int32_t n,
+                                         int32_t* id) {
+  uint64_t w = words[threadIdx.x];
+  for (int32_t k = before[threadIdx.x] - first; w && k < n; w &= w - 1, ++k)
+    if (k >= 0) id[k] = 64 * (int32_t)threadIdx.x + __builtin_ctzll(w);
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_query_pairs(const void* blob_a, int64_t MA, const void* blob_b,
+                                                            int64_t MB, const uint64_t* bits, unsigned long long* ctl,
+                                                            int32_t* pairs, int64_t cap, int64_t* counts) {
+  __shared__ uint64_t s_wa[kQWords], s_wb[kQWords];
+  __shared__ int32_t s_pa[kQWords], s_pb[kQWords];
+  __shared__ float s_col[6][kQColTile], s_rbox[6][kQRowTile];
+  __shared__ int32_t s_cid[kQColTile], s_rid[kQRowTile];
+  __shared__ int32_t s_row[2 * kScanBlock + 2];  // pairs of each row of the share, then their places
+  __shared__ int32_t s_i32[kScanBlock / 64];
+  __shared__ int64_t s_i64[kScanBlock / 64];
+  __shared__ int32_t s_ticket;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t q = blockIdx.y;
+  ctl += q * kQCtl;
+  pairs += 2 * q * cap;
+  const uint64_t* wa = bits + q * (2 * kQWords);
+  if (t == 0) s_ticket = (int32_t)atomicAdd(ctl + kQBlocks, 1ull);
+  const uint64_t a = t < (MA + 63) / 64 ? wa[t] : 0ull, b = t < (MB + 63) / 64 ? wa[kQWords + t] : 0ull;
+  s_wa[t] = a;
+  s_wb[t] = b;
+  int32_t na, nb;
+  s_pa[t] = block_exclusive_sum<kScanBlock>((int32_t)__popcll(a), s_i32, na);
+  s_pb[t] = block_exclusive_sum<kScanBlock>((int32_t)__popcll(b), s_i32, nb);
+  s_row[2 * t] = 0;
+  s_row[2 * t + 1] = 0;
+  if (t == 0) s_row[2 * kScanBlock] = 0;
+  __syncthreads();
+  const int32_t share = s_ticket, shares = max(1, min(kQBlocks, (na + kQRows - 1) / kQRows));
+  if (share >= shares) return;
+  const int32_t r0 = (int32_t)((int64_t)na * share / shares), r1 = (int32_t)((int64_t)na * (share + 1) / shares);
+  const MeshDesc *ma = meshes_of(blob_a), *mb = meshes_of(blob_b);
+  int32_t staged = -1;  // first column of the tile in LDS
+  int64_t base = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int32_t rt = r0; rt < r1; rt += kQRowTile) {
+      const int32_t nr = min(kQRowTile, r1 - rt);
+      __syncthreads();
+      kept_ids(s_wa, s_pa, rt, nr, s_rid);
+      __syncthreads();
+      if (t < nr) {
+        const MeshDesc& d = ma[s_rid[t]];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) s_rbox[c][t] = d.box[c];
+      }
+      for (int32_t ct = 0; ct < nb; ct += kQColTile) {
+        const int32_t nc = min(kQColTile, nb - ct);
+        if (staged != ct) {
+          __syncthreads();
+          kept_ids(s_wb, s_pb, ct, nc, s_cid);
+          __syncthreads();
+          if (t < nc) {
+            const MeshDesc& d = mb[s_cid[t]];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) s_col[c][t] = d.box[c];
+          }
+          staged = ct;
+        }
+        __syncthreads();
+        for (int32_t r = w; r < nr; r += kScanBlock / 64) {
+          float x[6];
+#pragma unroll
+          for (int c = 0; c < 6; ++c) x[c] = s_rbox[c][r];
+          const int32_t ia = s_rid[r], row = rt - r0 + r;
+          int32_t at = s_row[row];
+          for (int32_t i0 = 0; i0 < nc; i0 += 64) {
+            const int32_t i = i0 + lane;
+            const bool ok = i < nc && overlap(x, s_col[0][i], s_col[1][i], s_col[2][i], s_col[3][i], s_col[4][i],
+                                              s_col[5][i]);
+            const uint64_t m = __ballot(ok);
+            if (pass == 1 && ok) {
+              const int64_t pos = base + at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+              if (pos < cap) {
+                pairs[2 * pos] = ia;
+                pairs[2 * pos + 1] = s_cid[i];
+              }
+            }
+            at += __popcll(m);
+          }
+          if (lane == 0) s_row[row] = at;
+        }
+      }
+    }
+    if (pass == 1) break;
+    __syncthreads();
+    const int32_t v0 = s_row[2 * t], v1 = s_row[2 * t + 1];
+    int64_t total;
+    const int64_t pre = block_exclusive_sum<kScanBlock>((int64_t)v0 + v1, s_i64, total);
+    if (t == 0) __hip_atomic_store(ctl + share, kPublished | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int64_t earlier = 0;
+    if (t < share) {
+      uint64_t v;
+      do v = __hip_atomic_load(ctl + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      while (!(v & kPublished));
+      earlier = (int64_t)(v & ~kPublished);
+    }
+    base = block_sum<kScanBlock>(earlier, s_i64);
+    s_row[2 * t] = (int32_t)pre;
+    s_row[2 * t + 1] = (int32_t)(pre + v0);
+    if (t == 0 && share == shares - 1) counts[q] = base + total;
+    if (total == 0) return;
+    __syncthreads();
+  }
+}
 
 __global__ void k_set_i64(int64_t* out, int64_t v) { *out = v; }
 
@@ -564,16 +644,20 @@ __global__ __launch_bounds__(kBlock) void k_gather(const int32_t* regions, int64
   if (k == n - 1 && threadIdx.x == 0) *total = off + c;
 }
 
+// Boxes that one pair of launches takes.
+int64_t boxes_at_once(int64_t n) { return n < 1 ? 1 : (n < 1024 ? n : 1024); }
+
 struct FilterWs {
   int32_t *flag_a, *flag_b, *pos_a, *pos_b, *ids_a, *ids_b;
   float *box_a, *box_b;
   int64_t *rowcnt, *rowoff;
   int32_t *blocksum, *paircnt;
   int64_t* tsum;  // tile sums of the device-wide scans
-  uint64_t *keep_a, *keep_b;  // query-box ballots of the single-block keep path
+  uint64_t* qbits;            // query-box ballots, [n][2][kQWords]
+  unsigned long long* qctl;   // [n][kQCtl]
 };
 
-int carve_filter(Carve& cv, FilterWs& w, int64_t MA, int64_t MB) {
+int carve_filter(Carve& cv, FilterWs& w, int64_t MA, int64_t MB, int64_t n_boxes) {
   w.flag_a = cv.take<int32_t>(MA + 1);
   w.flag_b = cv.take<int32_t>(MB + 1);
   w.pos_a = cv.take<int32_t>(MA + 1);
@@ -589,21 +673,24 @@ int carve_filter(Carve& cv, FilterWs& w, int64_t MA, int64_t MB) {
   w.paircnt = cv.take<int32_t>((fast_rows + kRT - 1) / kRT * kPairBlock);
   const int64_t mx = MA > MB ? MA : MB;
   w.tsum = cv.take<int64_t>(scan_tiles_of(mx + 1));
-  w.keep_a = cv.take<uint64_t>(kKeepEntries);
-  w.keep_b = cv.take<uint64_t>(kKeepEntries);
+  w.qbits = cv.take<uint64_t>(n_boxes * 2 * kQWords);
+  w.qctl = cv.take<unsigned long long>(n_boxes * kQCtl);
   return PR_OK;
 }
 
-// The meshes of both datasets (each of at most kSmallScan) that meet the
-// query box: ids, boxes and counts in the filter workspace.
-void launch_keep_small(hipStream_t s, const void* blob_a, int64_t MA, const void* blob_b, int64_t MB,
-                       const float* query, const FilterWs& w) {
+// Query boxes over datasets of at most kSmallScan meshes; box q's pairs start
+// at pairs[q * cap].
+bool small_query(int64_t MA, int64_t MB) { return MA <= kSmallScan && MB <= kSmallScan; }
+
+void launch_query(hipStream_t s, const void* blob_a, int64_t MA, const void* blob_b, int64_t MB, const float* boxes,
+                  int32_t n, int32_t* pairs, int64_t cap, int64_t* counts, const FilterWs& w) {
   const int64_t tiles = (MA + kScanBlock - 1) / kScanBlock + (MB + kScanBlock - 1) / kScanBlock;
-  if (tiles > 0)
-    hipLaunchKernelGGL(k_keep_bits, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, blob_a, MA, blob_b, MB, query,
-                       w.keep_a, w.keep_b);
-  hipLaunchKernelGGL(k_keep_small, dim3(2), dim3(kScanBlock), 0, s, blob_a, MA, (const uint64_t*)w.keep_a, w.ids_a,
-                     w.box_a, w.pos_a + MA, blob_b, MB, (const uint64_t*)w.keep_b, w.ids_b, w.box_b, w.pos_b + MB);
+  hipLaunchKernelGGL(k_query_keep, dim3((unsigned)(tiles > 0 ? tiles : 1)), dim3(kScanBlock), 0, s, blob_a, MA, blob_b,
+                     MB, boxes, n, w.qbits, w.qctl);
+  // shares of kQRows rows at least: a small dataset needs fewer blocks
+  const int64_t blocks = MA / kQRows + 1 < kQBlocks ? MA / kQRows + 1 : kQBlocks;
+  hipLaunchKernelGGL(k_query_pairs, dim3((unsigned)blocks, (unsigned)n), dim3(kScanBlock), 0, s, blob_a, MA, blob_b, MB,
+                     (const uint64_t*)w.qbits, w.qctl, pairs, cap, counts);
 }
 
 struct CompactWs {
@@ -625,7 +712,7 @@ extern "C" int filter_aabb_pairs_ws_bytes(int64_t n_meshes_a, int64_t n_meshes_b
   if (n_meshes_a >= ((int64_t)1 << 30) || n_meshes_b >= ((int64_t)1 << 30)) { set_error("too many meshes"); return PR_E_UNSUPPORTED; }
   Carve cv{nullptr, 0};
   FilterWs w{};
-  int r = carve_filter(cv, w, n_meshes_a, n_meshes_b);
+  int r = carve_filter(cv, w, n_meshes_a, n_meshes_b, 1);
   if (r) return r;
   *ws_bytes = cv.used + 256;
   return PR_OK;
@@ -642,11 +729,16 @@ extern "C" int filter_aabb_pairs(const void* blob_a, int64_t n_meshes_a, const v
   hipStream_t s = (hipStream_t)stream;
   Carve cv{(char*)ws, ws_bytes};
   FilterWs w{};
-  int r = carve_filter(cv, w, n_meshes_a, n_meshes_b);
+  int r = carve_filter(cv, w, n_meshes_a, n_meshes_b, 1);
   if (r) return r;
   if (cv.used > ws_bytes) { set_error("ws_bytes %zu < required %zu", ws_bytes, cv.used); return PR_E_CAPACITY; }
   const int64_t MA = n_meshes_a, MB = n_meshes_b;
-  if (MA > 0 && MB > 0 && MA <= kFastRows && MB <= kFastCols && (!query_box || MA <= kSmallScan)) {
+  if (query_box && small_query(MA, MB)) {
+    launch_query(s, blob_a, MA, blob_b, MB, query_box, 1, pairs, cap, dev_count, w);
+    PR_HIP(hipGetLastError());
+    return PR_OK;
+  }
+  if (!query_box && MA > 0 && MB > 0 && MA <= kFastRows && MB <= kFastCols) {
     PairArgs pa{};
     pa.MA = MA;
     pa.MB = MB;
@@ -655,31 +747,17 @@ extern "C" int filter_aabb_pairs(const void* blob_a, int64_t n_meshes_a, const v
     pa.pairs = pairs;
     pa.cap = cap;
     pa.count = dev_count;
+    pa.blob_a = blob_a;
+    pa.blob_b = blob_b;
     const int grid = (int)((MA + kRT - 1) / kRT);
-    if (!query_box) {
-      pa.blob_a = blob_a;
-      pa.blob_b = blob_b;
-      hipLaunchKernelGGL((k_pairs<false, false>), dim3(grid), dim3(kPairBlock), 0, s, pa);
-      hipLaunchKernelGGL((k_pairs<false, true>), dim3(grid), dim3(kPairBlock), 0, s, pa);
-    } else {
-      launch_keep_small(s, blob_a, MA, blob_b, MB, query_box, w);
-      pa.box_a = w.box_a;
-      pa.box_b = w.box_b;
-      pa.ids_a = w.ids_a;
-      pa.ids_b = w.ids_b;
-      pa.na = w.pos_a + MA;
-      pa.nb = w.pos_b + MB;
-      hipLaunchKernelGGL((k_pairs<true, false>), dim3(grid), dim3(kPairBlock), 0, s, pa);
-      hipLaunchKernelGGL((k_pairs<true, true>), dim3(grid), dim3(kPairBlock), 0, s, pa);
-    }
+    hipLaunchKernelGGL(k_pairs<false>, dim3(grid), dim3(kPairBlock), 0, s, pa);
+    hipLaunchKernelGGL(k_pairs<true>, dim3(grid), dim3(kPairBlock), 0, s, pa);
     PR_HIP(hipGetLastError());
     return PR_OK;
   }
   if (!query_box) {
     hipLaunchKernelGGL(k_boxes_all, dim3(grid_for(MA + MB, kBlock)), dim3(kBlock), 0, s, blob_a, MA, w.ids_a,
                        w.box_a, w.pos_a + MA, blob_b, MB, w.ids_b, w.box_b, w.pos_b + MB);
-  } else if (MA <= kSmallScan && MB <= kSmallScan) {
-    launch_keep_small(s, blob_a, MA, blob_b, MB, query_box, w);
   } else {
     hipLaunchKernelGGL(k_keep, dim3(grid_for(MA + 1, kBlock)), dim3(kBlock), 0, s, blob_a, MA, query_box, w.flag_a);
     hipLaunchKernelGGL(k_keep, dim3(grid_for(MB + 1, kBlock)), dim3(kBlock), 0, s, blob_b, MB, query_box, w.flag_b);
@@ -715,6 +793,52 @@ extern "C" int filter_aabb_pairs(const void* blob_a, int64_t n_meshes_a, const v
     PR_HIP(device_exclusive_scan((const int64_t*)w.rowcnt, w.rowoff, MA + 1, w.tsum, dev_count, s));
     hipLaunchKernelGGL(k_row_write, dim3(rows_grid), dim3(kBlock), 0, s, ra);
   }
+  PR_HIP(hipGetLastError());
+  return PR_OK;
+}
+
+extern "C" int filter_aabb_pairs_batch_ws_bytes(int64_t n_meshes_a, int64_t n_meshes_b, int64_t n_boxes,
+                                                size_t* ws_bytes) {
+  if (n_meshes_a < 0 || n_meshes_b < 0 || n_boxes < 0 || !ws_bytes) { set_error("bad argument"); return PR_E_ARG; }
+  if (n_meshes_a >= ((int64_t)1 << 30) || n_meshes_b >= ((int64_t)1 << 30)) { set_error("too many meshes"); return PR_E_UNSUPPORTED; }
+  Carve cv{nullptr, 0};
+  FilterWs w{};
+  int r = carve_filter(cv, w, n_meshes_a, n_meshes_b, boxes_at_once(n_boxes));
+  if (r) return r;
+  *ws_bytes = cv.used + 256;
+  return PR_OK;
+}
+
+extern "C" int filter_aabb_pairs_batch(const void* blob_a, int64_t n_meshes_a, const void* blob_b, int64_t n_meshes_b,
+                                       const float* query_boxes, int64_t n_boxes, int32_t* regions, int64_t region_cap,
+                                       int64_t* dev_counts, void* ws, size_t ws_bytes, void* stream) {
+  size_t need = 0;
+  int r = filter_aabb_pairs_batch_ws_bytes(n_meshes_a, n_meshes_b, n_boxes, &need);
+  if (r) return r;
+  if (!blob_a || !blob_b || !ws || region_cap < 0 || (n_boxes > 0 && (!query_boxes || !dev_counts)) ||
+      (n_boxes > 0 && region_cap > 0 && !regions)) {
+    set_error("bad argument");
+    return PR_E_ARG;
+  }
+  if (n_boxes == 0) return PR_OK;
+  if (!small_query(n_meshes_a, n_meshes_b)) {
+    for (int64_t k = 0; k < n_boxes; ++k) {
+      r = filter_aabb_pairs(blob_a, n_meshes_a, blob_b, n_meshes_b, query_boxes + 6 * k, regions + 2 * k * region_cap,
+                            region_cap, dev_counts + k, ws, ws_bytes, stream);
+      if (r) return r;
+    }
+    return PR_OK;
+  }
+  Carve cv{(char*)ws, ws_bytes};
+  FilterWs w{};
+  const int64_t chunk = boxes_at_once(n_boxes);
+  r = carve_filter(cv, w, n_meshes_a, n_meshes_b, chunk);
+  if (r) return r;
+  if (cv.used > ws_bytes) { set_error("ws_bytes %zu < required %zu", ws_bytes, cv.used); return PR_E_CAPACITY; }
+  for (int64_t k = 0; k < n_boxes; k += chunk)
+    launch_query((hipStream_t)stream, blob_a, n_meshes_a, blob_b, n_meshes_b, query_boxes + 6 * k,
+                 (int32_t)(n_boxes - k < chunk ? n_boxes - k : chunk), regions + 2 * k * region_cap, region_cap,
+                 dev_counts + k, w);
   PR_HIP(hipGetLastError());
   return PR_OK;
 }

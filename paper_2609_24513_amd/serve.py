@@ -16,7 +16,8 @@ runs without blocking the host:
     max_req_per_batch waiting requests in arrival order (nothing waits while
     a slot is free, nothing is dropped);
   * the batch's query boxes go to the device in one asynchronous copy; each
-    admitted request's candidate filter writes its own region of the slot,
+    admitted request's candidates are filtered into its own region of the slot
+    (one batched filter call),
     the regions are concatenated on the device with the counts left there
     (gather_pair_regions), and the concatenation is refined in ONE persistent
     launch that reads the count on the device: the whole batch is enqueued at
@@ -109,7 +110,7 @@ class _Slot:
         self.boxes = torch.empty((max_req, 6), dtype=torch.float32, device="cuda")
         lib = _lib.load()
         wb = ctypes.c_size_t(0)
-        _lib.check(lib.filter_aabb_pairs_ws_bytes(R.n_meshes, S.n_meshes, ctypes.byref(wb)))
+        _lib.check(lib.filter_aabb_pairs_batch_ws_bytes(R.n_meshes, S.n_meshes, max_req, ctypes.byref(wb)))
         self.fws = torch.empty(max(256, wb.value), dtype=torch.uint8, device="cuda")
         self.rws = pa.refine_workspace(cap, R.width, cfg)
         self.reqs: List[Request] = []
@@ -157,7 +158,7 @@ class JoinServer:
     def _enqueue(self, slot: _Slot, n: int):
         """The device work of a batch of n requests whose query boxes are in
         slot.boxes_h[:n], on the slot's stream with no host round trip: the
-        boxes copied in, one filter per query into its region, the regions
+        boxes copied in, one batched filter into the queries' regions, the regions
         concatenated on the device (gather_pair_regions), one refinement of
         the concatenation with the device count, then the counts, status,
         pairs and flags copied back to pinned host buffers.  Every buffer
@@ -168,11 +169,10 @@ class JoinServer:
         with torch.cuda.stream(slot.stream):
             sp = int(slot.stream.cuda_stream)
             slot.boxes[:n].copy_(slot.boxes_h[:n], non_blocking=True)
-            for k in range(n):
-                _lib.check(lib.filter_aabb_pairs(
-                    self.R.ptr, self.R.n_meshes, self.S.ptr, self.S.n_meshes, slot.boxes.data_ptr() + 24 * k,
-                    slot.region.data_ptr() + k * self.max_pairs * 8, self.max_pairs,
-                    slot.counts.data_ptr() + 8 * k, slot.fws.data_ptr(), slot.fws.numel(), sp))
+            _lib.check(lib.filter_aabb_pairs_batch(
+                self.R.ptr, self.R.n_meshes, self.S.ptr, self.S.n_meshes, slot.boxes.data_ptr(), n,
+                slot.region.data_ptr(), self.max_pairs, slot.counts.data_ptr(), slot.fws.data_ptr(),
+                slot.fws.numel(), sp))
             _lib.check(lib.gather_pair_regions(slot.region.data_ptr(), self.max_pairs, slot.counts.data_ptr(),
                                                n, slot.batch.data_ptr(), cap, slot.total.data_ptr(), sp))
             cfg = copy.copy(self.cfg)
