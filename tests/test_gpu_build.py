@@ -67,6 +67,13 @@ def _case(name):
         return [_packed(rng, n) for n in (2500, 9000)] + [_soup(rng, 100)]
     if name == "book":        # thousands of copies of one edge
         return [_book(3000), _book(700), _soup(rng, 50)]
+    if name == "huge":        # extents that overflow, in a plane: half areas of inf x 0
+        out = []
+        for n in (40, 600, 3000):
+            v, f = _soup(rng, n, 3.0e38)
+            v[:, 2] = 1.0
+            out.append((v, f))
+        return out
     return [_soup(rng, int(n)) for n in rng.integers(1, 60, 5000)]  # many small meshes
 
 
@@ -132,7 +139,7 @@ def _check_tree(s, W, leaf, root, first, n, n_nodes, depth):
 
 
 @pytest.mark.parametrize("width,leaf,builder", [(2, 1, 0), (4, 4, 0), (8, 1, 0), (8, 8, 1), (4, 2, 1)])
-@pytest.mark.parametrize("name", ["sizes", "surfaces", "packed", "book", "many"])
+@pytest.mark.parametrize("name", ["sizes", "surfaces", "packed", "book", "huge", "many"])
 def test_blob_sections(name, width, leaf, builder):
     import paper_2609_24513_amd as pa
     from paper_2609_24513_amd import synth
