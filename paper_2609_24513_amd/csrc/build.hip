@@ -33,6 +33,8 @@
 #include <climits>
 #include <cstdio>
 
+#include <type_traits>
+
 #include "common.h"
 #include "predicates.h"
 
@@ -43,10 +45,10 @@ constexpr int kBlock = 256;
 constexpr int kTreeChunk = 512;    // sorted positions (and faces) of one tree block
 constexpr int kCodeChunk = 2048;   // faces of one counting block
 constexpr int kLdsCells = 1 << 14; // cells counted in LDS
-constexpr int kUnit = 1024;        // sort unit: the cells that start in this many items
+constexpr int kUnit = 1280;        // sort unit: the cells that start in this many items (2 x 106 M half-edges: 1,024 3.2, this 3.0 ms)
 constexpr int kUnitCap = 2048;     // items a unit may hold to be sorted in LDS
 constexpr int kBins = 2048;        // bins of the LDS sort
-constexpr int kLdsBlock = 256;     // threads of a sort block (512: edge sorts of 2 x 106 M half-edges 5.1 -> 6.4 ms)
+constexpr int kLdsBlock = 512;     // threads of a sort block (the same: 256 3.0, this 2.74, 1,024 5.5 ms)
 constexpr int kTreeBlock = 512;    // threads of a tree block, one position each
 constexpr int kMaxRoots = 128;     // subtrees that tile a chunk: at most two per tree level (62 levels)
 constexpr int kTopUnits = 512;     // subtrees of chunks that one pass of a top block joins
@@ -670,18 +672,14 @@ __device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells,
   return hi < cells ? (int32_t)(s[hi] - s0) : n;
 }
 
-__device__ __forceinline__ bool before(const Item& a, const Item& b) {
-  return a.k != b.k ? a.k < b.k : (a.x != b.x ? a.x < b.x : a.y < b.y);
-}
-__device__ __forceinline__ bool same(const Item& a, const Item& b) { return a.k == b.k && a.x == b.x && a.y == b.y; }
-
 template <bool UNIQUE>
 struct SortLds {
+  using Low = std::conditional_t<UNIQUE, uint64_t, uint32_t>;
   uint32_t cnt[kBins + 1];       // bin counts, then first places
-  uint32_t k[kUnitCap], x[kUnitCap], y[UNIQUE ? kUnitCap : 1];
-  uint16_t bin[kUnitCap];
-  uint64_t keep[kUnitCap / 64];  // places that hold the first copy of their item
-  uint32_t before[kUnitCap / 64];
+  uint32_t k[kUnitCap];
+  Low low[kUnitCap];             // x, and y below it
+  uint32_t keep[kUnitCap / 32];  // places of the sorted items that hold the first copy of one
+  uint32_t before[kUnitCap / 32];
   uint32_t scan[kLdsBlock / 64];
   uint32_t kmin, kmax;
 };
@@ -689,17 +687,22 @@ struct SortLds {
 // Sorts the n <= kUnitCap items load(0) ... load(n - 1) and hands them to
 // store(place, item), equal items once when UNIQUE; returns the number kept.
 // One pass: the items go to bins monotone in their order (any order within a
-// bin), then each finds its place among its bin's items, few for codes as
-// even as a surface's; 2,048 equal items cost 2,048 comparisons each.
-// bin(item) < kBins gives the bins; with LINEAR they are cut evenly from the
-// codes' range instead.  Bound by LDS latency.  Every thread of the block
-// calls it.
+// bin), then each counts the items of its bin that come before it, few for
+// codes as even as a surface's, and looks for a copy at a lower place; 2,048
+// equal items cost 2,048 comparisons each.  bin(item) < kBins gives the bins;
+// with LINEAR they are cut evenly from the codes' range instead.  Bound by the
+// instructions of the comparing loop: the edges of 2 x 35 M triangles take
+// 2.74 ms with one loop without branches and took 5.07 ms with one for copies
+// and one for places, each with early outs.  Every thread of the block calls it.
 template <bool UNIQUE, bool LINEAR, typename Load, typename Bin, typename Store>
 __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, Store store) {
   constexpr int R = kUnitCap / kLdsBlock;
+  using Low = typename SortLds<UNIQUE>::Low;
+  static_assert(kUnitCap / 32 == 64, "one word of `keep` a lane");
+  auto low_of = [](const Item& e) { return UNIQUE ? (Low)((uint64_t)e.x << 32 | e.y) : (Low)e.x; };
   const int t = threadIdx.x;
   for (int i = t; i <= kBins; i += kLdsBlock) s.cnt[i] = 0u;
-  if (t < kUnitCap / 64) s.keep[t] = 0ull;
+  if (UNIQUE && t < kUnitCap / 32) s.keep[t] = 0u;
   if (t == 0) { s.kmin = ~0u; s.kmax = 0u; }
   __syncthreads();
   Item it[R];
@@ -754,48 +757,45 @@ __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, S
     if (t + r * kLdsBlock < n) {
       const uint32_t at = s.cnt[b[r]] + rank[r];
       s.k[at] = it[r].k;
-      s.x[at] = it[r].x;
-      if (UNIQUE) s.y[at] = it[r].y;
-      s.bin[at] = (uint16_t)b[r];
+      s.low[at] = low_of(it[r]);
     }
   __syncthreads();
-  auto at = [&](uint32_t j) { return Item{s.k[j], s.x[j], UNIQUE ? s.y[j] : 0u}; };
-  if (UNIQUE) {
-    // the copy at the lowest place stands for its item
+  uint32_t place[R];  // ~0: a copy
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t i = t + r * kLdsBlock;
-      bool first = i < (uint32_t)n;
-      if (first) {
-        const Item me = at(i);
-        for (uint32_t j = s.cnt[s.bin[i]]; j < i && first; ++j) first = !same(at(j), me);
-      }
-      const uint64_t b = __ballot(first);
-      if ((t & 63) == 0) s.keep[i >> 6] = b;
+  for (int r = 0; r < R; ++r) {
+    place[r] = ~0u;
+    if (t + r * kLdsBlock >= n) continue;
+    const uint32_t j0 = s.cnt[b[r]], j1 = s.cnt[b[r] + 1], me = j0 + rank[r];
+    const uint32_t k = it[r].k;
+    const Low low = low_of(it[r]);
+    uint32_t less = 0;
+    bool copy = false;
+    for (uint32_t j = j0; j < j1; ++j) {
+      const uint32_t kj = s.k[j];
+      const Low lj = s.low[j];
+      less += (kj < k) | ((kj == k) & (lj < low)) ? 1u : 0u;
+      if (UNIQUE) copy |= (j < me) & (kj == k) & (lj == low);
     }
+    if (copy) continue;
+    place[r] = j0 + less;
+    if (UNIQUE) atomicOr(&s.keep[place[r] >> 5], 1u << (place[r] & 31u));
+  }
+  if (UNIQUE) {
     __syncthreads();
     if (t < 64) {
-      const uint32_t c = t < kUnitCap / 64 ? (uint32_t)__popcll(s.keep[t]) : 0u;
+      const uint32_t c = (uint32_t)__popc(s.keep[t]);
       const uint32_t inc = wave_inclusive_sum(c);
-      if (t < kUnitCap / 64) s.before[t] = inc - c;
+      s.before[t] = inc - c;
       if (t == 63) s.scan[0] = inc;
     }
     __syncthreads();
   }
-  auto kept_before = [&](uint32_t j) {
-    return s.before[j >> 6] + (uint32_t)__popcll(s.keep[j >> 6] & ((1ull << (j & 63)) - 1ull));
-  };
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t i = t + r * kLdsBlock;
-    if (i >= (uint32_t)n || (UNIQUE && !((s.keep[i >> 6] >> (i & 63)) & 1ull))) continue;
-    const Item me = at(i);
-    const uint32_t j0 = s.cnt[s.bin[i]], j1 = s.cnt[s.bin[i] + 1];
-    uint32_t place = 0;
-    for (uint32_t j = j0; j < j1; ++j)
-      place += before(at(j), me) && (!UNIQUE || ((s.keep[j >> 6] >> (j & 63)) & 1ull)) ? 1u : 0u;
-    store((int32_t)((UNIQUE ? (j0 < (uint32_t)kUnitCap ? kept_before(j0) : 0u) : j0) + place), me);
-  }
+  for (int r = 0; r < R; ++r)
+    if (place[r] != ~0u)
+      store((int32_t)(UNIQUE ? s.before[place[r] >> 5] + (uint32_t)__popc(s.keep[place[r] >> 5] & ((1u << (place[r] & 31u)) - 1u))
+                             : place[r]),
+            it[r]);
   const int32_t kept = UNIQUE ? (int32_t)s.scan[0] : n;
   __syncthreads();  // s is reused by the next call
   return kept;
