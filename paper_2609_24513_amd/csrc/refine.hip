@@ -894,6 +894,14 @@ __device__ __forceinline__ bool blobs_ok(const BlobView& A, const BlobView& B, c
          B.n_meshes == ra.n_meshes_b;
 }
 
+// Counters of the blocks that are done, in the unused part of the survivor
+// counters' lines: line l of kDoneLines, then the lines that are complete.
+constexpr int kDoneLines = 16;
+static_assert(kDoneLines < kQueues && kCtrStride > 1, "a line each");
+__device__ __forceinline__ unsigned long long* done_ctr(const RefineArgs& ra, uint32_t l) {
+  return ra.surv_cnt + kCtrStride * l + 1;
+}
+
 // ---- setup --------------------------------------------------------------------
 
 // Pair states are cleared for the pairs processed only (every kernel bounds
@@ -902,6 +910,7 @@ __global__ void k_init(RefineArgs ra) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t np = npairs(ra);
   for (int64_t p = i; p < np; p += (int64_t)gridDim.x * blockDim.x) ra.state[p] = 0u;
+  if (i <= kDoneLines) *done_ctr(ra, (uint32_t)i) = 0ull;
   if (i < kStatCopies * S_N) ra.stats[kCtrStride * (i / S_N) + i % S_N] = 0ull;
   if (i < kSlices) {
     ra.ctr[kCtrStride * i] = 0ull;
@@ -1949,50 +1958,6 @@ __global__ __launch_bounds__(kBlock) void k_refine_pair(RefineArgs ra, int64_t p
   flush_stats(st, ra);
 }
 
-__device__ void redecide(const RefineArgs& ra);
-
-// After the traversal: (1) the deferred tests of undecided pairs (state 0) are
-// decided in FP64/exact, one thread per test; (2) pairs whose deferred tests
-// or survivors overflowed a queue (state 2) are traced again with every leaf
-// test decided in place in FP64/exact, one block per pair.  The two parts
-// touch disjoint pairs.
-template <int W>
-__global__ __launch_bounds__(kBlock) void k_fix(RefineArgs ra) {
-  constexpr int CAP = lds_stack_cap<W>();
-  __shared__ int32_t s_node[kWaves][CAP];
-  __shared__ uint64_t s_mask[kWaves][CAP];
-  __shared__ uint32_t s_hit;
-  redecide(ra);
-  const int wv = threadIdx.x >> 6;
-  const BlobView A = view_of(ra.blob_a), B = view_of(ra.blob_b);
-  if (!blobs_ok(A, B, ra, W)) return;
-  WaveStats st;
-  if (ra.stats[S_QOVER] == 0) return;  // nothing overflowed: nothing to rerun
-  const int64_t np = npairs(ra);
-  for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
-    if (load_state(ra.state + p) != 2u) continue;
-    if (threadIdx.x == 0) s_hit = 0;
-    __syncthreads();
-    int32_t i, j;
-    pair_ok(ra, p, i, j);
-    const MeshDesc a = A.mesh[i], b = B.mesh[j];
-    for (int dir = 0; dir < 2; ++dir) {
-      const MeshDesc& sm = dir == 0 ? a : b;
-      const MeshDesc& tm = dir == 0 ? b : a;
-      for (int32_t c = wv; c < sm.n_chunks; c += kWaves) {
-        if (s_hit) break;
-        if (trace_chunk<W, 1>(dir == 0 ? A : B, dir == 0 ? B : A, sm, tm, c, (int32_t)p, dir,
-                              (sm.flags & tm.flags & kMeshSafe) != 0, ra, s_node[wv], s_mask[wv], st, true))
-          s_hit = 1;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) ra.state[p] = s_hit ? 1u : 0u;
-    __syncthreads();
-  }
-  flush_stats(st, ra);
-}
-
 // ---- deferred FP64 / exact decisions ----------------------------------------------
 
 __device__ void redecide(const RefineArgs& ra) {
@@ -2063,24 +2028,118 @@ __device__ void report(const RefineArgs& ra, pr_refine_stats* out, int32_t* dev_
     *dev_status = __hip_atomic_load(ra.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Flags from the pair states and the intersecting-pair count; the report
-// follows as a kernel of its own (the launch boundary orders the counts
-// without device-wide fences in every block).
-__global__ __launch_bounds__(kBlock) void k_finalize(RefineArgs ra) {
-  int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// True in the last block of the grid to come here, in all of its threads.  What
+// the threads stored or added at agent scope before is at its place in memory
+// by then (each waits for its own), so the last block finds all of it by
+// agent-scope loads; no fence that would write back or drop an L2.  The blocks
+// count in kDoneLines lines and then in one (one address takes some 11 ns a block).
+__device__ __forceinline__ bool last_block(const RefineArgs& ra) {
+  __shared__ bool s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t lines = min(gridDim.x, (uint32_t)kDoneLines), l = blockIdx.x % lines;
+    const uint32_t mine = (gridDim.x - l + lines - 1) / lines;
+    s_last = atomicAdd(done_ctr(ra, l), 1ull) + 1 == mine && atomicAdd(done_ctr(ra, kDoneLines), 1ull) + 1 == lines;
+  }
+  __syncthreads();
+  return s_last;
+}
+
+// Flags of the pairs first, first + step, ... from the pair states, and the
+// count of intersecting ones.  The states of a thread's kFlagBatch next pairs
+// load together.
+constexpr int kFlagBatch = 8;
+__device__ __forceinline__ void write_flags(const RefineArgs& ra, int64_t first, int64_t step) {
   unsigned long long cnt = 0;
   const int64_t np = npairs(ra);
-  for (; p < np; p += (int64_t)gridDim.x * blockDim.x) {
-    const uint8_t f = ra.state[p] == 1u ? 1 : 0;
-    ra.flags[p] = f;
-    cnt += f;
+  for (int64_t p = first; p < np; p += kFlagBatch * step) {
+    uint32_t v[kFlagBatch];
+#pragma unroll
+    for (int k = 0; k < kFlagBatch; ++k) v[k] = p + k * step < np ? load_state(ra.state + p + k * step) : 0u;
+#pragma unroll
+    for (int k = 0; k < kFlagBatch; ++k)
+      if (p + k * step < np) {
+        ra.flags[p + k * step] = v[k] == 1u ? 1 : 0;
+        cnt += v[k] == 1u ? 1 : 0;
+      }
   }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
   if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(stat_copy(ra.stats) + S_TRUE, cnt);
 }
 
+// Flags of many pairs; the last block reports.
+__global__ __launch_bounds__(kBlock) void k_finalize(RefineArgs ra, pr_refine_stats* out, int32_t* dev_status) {
+  write_flags(ra, blockIdx.x * (int64_t)kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+  if (last_block(ra) && threadIdx.x < 64) report(ra, out, dev_status);
+}
+
+// After the traversal: (1) the deferred tests of undecided pairs (state 0) are
+// decided in FP64/exact, one thread per test; (2) pairs whose deferred tests
+// or survivors overflowed a queue (state 2) are traced again with every leaf
+// test decided in place in FP64/exact, one block per pair.  The two parts
+// touch disjoint pairs.  With `all` the flags and the report follow here
+// instead of in k_finalize: every block's share of the flags at once if
+// nothing was deferred (the states are final then, and every block sees that),
+// else all of them in the last block.
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_fix(RefineArgs ra, bool all, pr_refine_stats* out, int32_t* dev_status) {
+  constexpr int CAP = lds_stack_cap<W>();
+  __shared__ int32_t s_node[kWaves][CAP];
+  __shared__ uint64_t s_mask[kWaves][CAP];
+  __shared__ uint32_t s_hit;
+  const bool over = ra.stats[S_QOVER] != 0;
+  bool pending = over;
+  for (int qx = 0; qx < kSlices; ++qx) pending = pending || ra.qcount[kQCtrStride * qx] != 0u;
+  if (pending) redecide(ra);
+  const int wv = threadIdx.x >> 6;
+  const BlobView A = view_of(ra.blob_a), B = view_of(ra.blob_b);
+  if (over && blobs_ok(A, B, ra, W)) {
+    WaveStats st;
+    const int64_t np = npairs(ra);
+    for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
+      if (load_state(ra.state + p) != 2u) continue;
+      if (threadIdx.x == 0) s_hit = 0;
+      __syncthreads();
+      int32_t i, j;
+      pair_ok(ra, p, i, j);
+      const MeshDesc a = A.mesh[i], b = B.mesh[j];
+      for (int dir = 0; dir < 2; ++dir) {
+        const MeshDesc& sm = dir == 0 ? a : b;
+        const MeshDesc& tm = dir == 0 ? b : a;
+        for (int32_t c = wv; c < sm.n_chunks; c += kWaves) {
+          if (s_hit) break;
+          if (trace_chunk<W, 1>(dir == 0 ? A : B, dir == 0 ? B : A, sm, tm, c, (int32_t)p, dir,
+                                (sm.flags & tm.flags & kMeshSafe) != 0, ra, s_node[wv], s_mask[wv], st, true))
+            s_hit = 1;
+        }
+      }
+      __syncthreads();
+      if (threadIdx.x == 0)
+        __hip_atomic_store(ra.state + p, s_hit ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+    }
+    flush_stats(st, ra);
+  }
+  if (!all) return;
+  if (!pending) write_flags(ra, blockIdx.x * (int64_t)kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+  if (!last_block(ra)) return;
+  if (pending) {
+    write_flags(ra, threadIdx.x, kBlock);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  if (threadIdx.x < 64) report(ra, out, dev_status);
+}
+
 // The report alone (no pairs).
 __global__ void k_report(RefineArgs ra, pr_refine_stats* out, int32_t* dev_status) { report(ra, out, dev_status); }
+
+// Pairs up to which k_fix writes the flags and reports: 9 us for 2,000 pairs
+// where k_fix, k_finalize and a report kernel took 14 and two gaps.  With
+// deferred tests one block writes all flags, about 7 us at this number and 13
+// at twice it, against 5.5 us and a gap for k_finalize.
+constexpr int64_t kFinishPairs = 1 << 13;
 
 // ---- host side ---------------------------------------------------------------------
 
@@ -2280,11 +2339,11 @@ int refine_run(const void* blob_a, int64_t n_meshes_a, const void* blob_b, int64
 #undef PR_LAUNCH
     if (r) return r;
     const int fb = 256;  // enough threads for the deferred tests, blocks for the reruns
-    if (W == 2) hipLaunchKernelGGL(k_fix<2>, dim3(fb), dim3(kBlock), 0, s, ra);
-    else if (W == 4) hipLaunchKernelGGL(k_fix<4>, dim3(fb), dim3(kBlock), 0, s, ra);
-    else hipLaunchKernelGGL(k_fix<8>, dim3(fb), dim3(kBlock), 0, s, ra);
-    hipLaunchKernelGGL(k_finalize, dim3(grid_for(n_pairs, kBlock)), dim3(kBlock), 0, s, ra);
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, ra, dev_stats, dev_status);
+    const bool all = n_pairs <= kFinishPairs;
+    if (W == 2) hipLaunchKernelGGL(k_fix<2>, dim3(fb), dim3(kBlock), 0, s, ra, all, dev_stats, dev_status);
+    else if (W == 4) hipLaunchKernelGGL(k_fix<4>, dim3(fb), dim3(kBlock), 0, s, ra, all, dev_stats, dev_status);
+    else hipLaunchKernelGGL(k_fix<8>, dim3(fb), dim3(kBlock), 0, s, ra, all, dev_stats, dev_status);
+    if (!all) hipLaunchKernelGGL(k_finalize, dim3(grid_for(n_pairs, kBlock)), dim3(kBlock), 0, s, ra, dev_stats, dev_status);
   } else {
     hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, ra, dev_stats, dev_status);
   }

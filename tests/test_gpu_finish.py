@@ -1,0 +1,64 @@
+"""After the traversal: flags and report in one kernel or two, with and without
+deferred tests, overflowed queues and a device count; the compaction at the
+edges of its tiles and of its one-launch range, at any alignment of the flags."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def scene(oracle_mod):
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    rng = np.random.default_rng(11)
+    v, f = synth.icosphere(1)
+
+    def side():
+        return synth.concat_meshes([((rng.uniform(0, 2.5, 3) + 0.6 * v).astype(np.float32), f) for _ in range(24)])
+
+    A, B = side(), side()
+    every = np.array([(i, j) for i in range(24) for j in range(24)], np.int32)
+    want = oracle_mod.join(A, B, every, mode=1)
+    assert 0 < want.sum() < want.size
+    return pa.MeshBlob.build(A, width=4, leaf_size=4), pa.MeshBlob.build(B, width=4, leaf_size=4), every, want
+
+
+@pytest.mark.parametrize("count", [1, 255, 8192, 8193])
+@pytest.mark.parametrize("kw", [{}, {"precision": 2}, {"precision": 2, "queue_cap": 64}, {"precision": 1}])
+def test_flags_and_report(scene, count, kw):
+    import torch
+    import paper_2609_24513_amd as pa
+    ga, gb, every, want = scene
+    sel = np.random.default_rng(count).integers(0, every.shape[0], count)
+    for n in (None, 0, count // 2, count + 5):
+        n_dev = None if n is None else torch.tensor([n], dtype=torch.int64, device="cuda")
+        flags, stats, status = pa.refine(ga, gb, every[sel], pa.RefineConfig(n_dev=n_dev, **kw))
+        torch.cuda.synchronize()
+        m = count if n is None else min(n, count)
+        assert int(status.item()) == 0
+        assert np.array_equal(flags.cpu().numpy()[:m], want[sel][:m])
+        st = pa.stats_dict(stats)
+        assert st["pairs_true"] == int(want[sel][:m].sum())
+        if kw.get("queue_cap") and m > 1000:
+            assert st["queue_overflow"] > 0
+
+
+@pytest.mark.parametrize("n", [1, 15, 4095, 4096, 4097, 16 * 4096, 16 * 4096 + 1])
+def test_compaction_at_tile_edges(n):
+    import torch
+    import paper_2609_24513_amd as pa
+    rng = np.random.default_rng(n)
+    pairs = rng.integers(0, 1 << 30, (n, 2)).astype(np.int32)
+    dp = torch.from_numpy(pairs).cuda()
+    raw = np.zeros(n + 16, np.uint8)
+    for shift in (0, 1, 8):
+        for fill in (0.0, 0.3, 1.0):
+            f = (rng.random(n) < fill) * rng.integers(1, 256, n)
+            raw[shift:shift + n] = f
+            df = torch.from_numpy(raw).cuda()[shift:shift + n]
+            for m in (None, 0, n - 1, n // 2 + 7, n + 3):
+                n_dev = None if m is None else torch.tensor([m], dtype=torch.int64, device="cuda")
+                k = n if m is None else min(m, n)
+                got = pa.compact(dp, df, n_dev=n_dev).cpu().numpy()
+                assert np.array_equal(got, pairs[:k][f[:k] != 0])
