@@ -1034,6 +1034,7 @@ constexpr uint64_t kSpread = 2654435761ull;
 // k_cull: up to kCullStatic units per wave are dealt in a fixed stride;
 // beyond, waves take kCullGrab units at a time from their XCD's share.
 constexpr int kCullStatic = 8;
+constexpr int kCullSplit = 4;
 constexpr int kCullGrab = 4;
 
 // Appends a wave's buffered survivors to its slice queue with one atomic.
@@ -1089,8 +1090,9 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
   WaveStats st;
   const int64_t U = 2 * npairs(ra);
   const cptr_t<int32_t> pairs = cview(ra.pairs);
-  // Culls unit u (pair ids ia, jb).
-  auto cull_unit = [&](int64_t u, int32_t ia, int32_t jb) {
+  // Culls unit u (pair ids ia, jb): of its runs those that are part modulo
+  // 1 << split.
+  auto cull_unit = [&](int64_t u, int32_t ia, int32_t jb, int split, int part) {
     const int32_t pair = (int32_t)(u >> 1), dir = (int32_t)(u & 1);
     if (ia < 0 || ia >= ra.n_meshes_a || jb < 0 || jb >= ra.n_meshes_b) {
       if (lane == 0) atomicMin(ra.status, (int32_t)PR_E_ARG);
@@ -1108,7 +1110,8 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     const int32_t n_chunks = smd->n_chunks, n_edges = smd->n_edges, chunk_base = smd->chunk_base;
     const bool safe = (smd->flags & tmd->flags & kMeshSafe) != 0;
     const int32_t tword = (safe ? 256 : 0) | (size_bucket(tmd->n_tris) << 9) | (min(tmd->n_nodes, (1 << 21) - 1) << 11);
-    if (troot == kEmpty || n_chunks <= 0 || !box_meet(sb, tb[0], tb[1], tb[2], tb[3], tb[4], tb[5])) return;
+    const int32_t n_all = (n_chunks + kChunk - 1) / kChunk;
+    if (troot == kEmpty || part >= n_all || !box_meet(sb, tb[0], tb[1], tb[2], tb[3], tb[4], tb[5])) return;
     // Groups come in runs of 64 (one per lane), each with a run box.  With
     // at least kRunsMin runs, the run boxes are tested first, 64 at a time,
     // and only the groups of the runs that pass are read; fewer runs are
@@ -1117,13 +1120,12 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     // frontier.
     const float* cbox = S.cbox + 8 * (int64_t)chunk_base;
     const float* rbox = S.rbox + 8 * (int64_t)chunk_base;
-    const int32_t n_all = (n_chunks + kChunk - 1) / kChunk;
     const bool hier = n_all >= kRunsMin;
     const int32_t n_runs = hier ? n_all : 1;
     float g[6], gn[6];
     {
       const float* cp = hier ? rbox + 8 * (int64_t)kChunk * min(lane, n_runs - 1)
-                                   : cbox + 8 * (int64_t)min(lane, n_chunks - 1);
+                                   : cbox + 8 * (int64_t)min(part * kChunk + lane, n_chunks - 1);
 #pragma unroll
       for (int k = 0; k < 6; ++k) g[k] = cp[k];
     }
@@ -1145,9 +1147,12 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     uint64_t f2 = f2m;            // entries the groups in g can meet
     uint32_t f1 = f1m;
     int32_t r0 = 0;               // first run of the current batch
+    // the part's runs of a batch (a batch's first run is a multiple of 64)
+    const uint64_t own = (split == 0 ? ~0ull : split == 1 ? 0x5555555555555555ull : split == 2 ? 0x1111111111111111ull
+                          : split == 3 ? 0x0101010101010101ull : 0x0001000100010001ull) << part;
     // passing runs of the batch not yet loaded (without the run level:
     // every run after the first, whose groups are in g)
-    uint64_t rmask = hier ? 0ull : ((1ull << n_all) - 1ull) & ~1ull;
+    uint64_t rmask = hier ? 0ull : ((1ull << n_all) - 1ull) & own & (own - 1);
     auto load_runs = [&](int32_t rb, float* dst) {
       const float* cp = rbox + 8 * (int64_t)kChunk * min(rb + lane, n_runs - 1);
 #pragma unroll
@@ -1165,13 +1170,13 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     };
     float g2[6];                  // boxes of the run after next
     bool batch = hier;            // g holds a batch of run boxes
-    int32_t cur = 0;              // run of the groups in g
+    int32_t cur = part;           // run of the groups in g
     while (true) {
       if (batch) {
         frontier_masks<W>(g, f2m, f1m, F, rm2, rm1);
         const bool pass = r0 + lane < n_runs && box_meet(g, tb[0], tb[1], tb[2], tb[3], tb[4], tb[5]) &&
                           (rm2 | rm1) != 0;
-        rmask = ballot(pass);
+        rmask = ballot(pass) & own;
         if (!rmask) {
           if (r0 + kChunk >= n_runs) break;
           r0 += kChunk;
@@ -1224,7 +1229,15 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     }
   };
   const int64_t nw = (int64_t)gridDim.x * kWaves;
-  if (U <= kCullStatic * nw) {
+  if (2 * U <= nw) {
+    // fewer units than waves: up to 1 << kCullSplit waves share a unit, each
+    // taking every so many of its runs, so that large meshes are not one
+    // wave's serial chain (466 units of 15 runs: 82 -> 29 us)
+    int split = 0;
+    while (split < kCullSplit && (U << (split + 1)) <= nw) ++split;
+    const int64_t x = (int64_t)blockIdx.x * kWaves + wv, u = x >> split;
+    if (u < U) cull_unit(u, pairs[2 * (u >> 1)], pairs[2 * (u >> 1) + 1], split, (int)(x & ((1 << split) - 1)));
+  } else if (U <= kCullStatic * nw) {
     // few units per wave: dealt in a fixed stride, the pair of the wave's
     // next unit read while the current one is culled
     const int64_t u0 = (int64_t)blockIdx.x * kWaves + wv;
@@ -1239,7 +1252,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
         next_a = pairs[2 * ((u + nw) >> 1)];
         next_b = pairs[2 * ((u + nw) >> 1) + 1];
       }
-      cull_unit(u, ia, jb);
+      cull_unit(u, ia, jb, 0, 0);
     }
   } else {
     // many units per wave, of uneven cost: one share per XCD, from which the
@@ -1271,7 +1284,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
           ia = pairs[2 * pl];
           jb = pairs[2 * pl + 1];
         }
-        cull_unit(u, ia, jb);
+        cull_unit(u, ia, jb, 0, 0);
       }
       ub = slo + (int64_t)uni64(gnext);
     }

@@ -62,3 +62,35 @@ def test_compaction_at_tile_edges(n):
                 k = n if m is None else min(m, n)
                 got = pa.compact(dp, df, n_dev=n_dev).cpu().numpy()
                 assert np.array_equal(got, pairs[:k][f[:k] != 0])
+
+
+@pytest.mark.parametrize("width,leaf", [(2, 4), (4, 4), (8, 1)])
+def test_few_units_are_shared_by_several_waves(oracle_mod, width, leaf):
+    """Meshes of one run of 64 groups, of two and three (no run boxes) and of eight:
+    the same groups are culled whether one wave takes a unit or several."""
+    import torch
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    rng = np.random.default_rng(width)
+
+    def side():
+        out = []
+        for k in (1, 4, 5, 3, 4, 5):
+            v, f = synth.icosphere(k)
+            out.append(((rng.uniform(0, 1.2, 3) + rng.uniform(0.5, 1.0) * v).astype(np.float32), f[:len(f) - 7 * k]))
+        return synth.concat_meshes(out)
+
+    A, B = side(), side()
+    every = np.array([(i, j) for i in range(6) for j in range(6)], np.int32)
+    want = oracle_mod.join(A, B, every, mode=1)
+    ga, gb = pa.MeshBlob.build(A, width=width, leaf_size=leaf), pa.MeshBlob.build(B, width=width, leaf_size=leaf)
+    many = 120  # 4,320 pairs: more units than half the waves
+    totals = {}
+    for reps in (1, 3, many):
+        flags, stats, status = pa.refine(ga, gb, np.tile(every, (reps, 1)), pa.RefineConfig())
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        assert np.array_equal(flags.cpu().numpy(), np.tile(want, reps))
+        st = pa.stats_dict(stats)
+        totals[reps] = (st["groups"] * many // reps, st["groups_box_pass"] * many // reps)
+    assert totals[1] == totals[3] == totals[many]
