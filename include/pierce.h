@@ -474,6 +474,17 @@ int compact_pairs(const int32_t* pairs, const uint8_t* flags, int64_t n_pairs,
 int gather_pair_regions(const int32_t* regions, int64_t region_cap, const int64_t* dev_counts,
                         int64_t n_regions, int32_t* out, int64_t cap, int64_t* dev_total, void* stream);
 
+/* A batch's results back to the host in one launch, sized by the device count:
+ * the leading min(max(*dev_total, 0), cap) rows of pairs dev i32[][2] and of
+ * flags dev u8[], the n_counts values of dev_counts dev i64[], and dev_status
+ * dev i32[1], into host buffers of the same types that hold cap, cap, n_counts
+ * and 1 of them.  The host buffers are pinned (hipHostMalloc; other memory is
+ * refused with PR_E_ARG) and complete when the stream reaches an event or is
+ * synchronised. */
+int results_to_host(const int32_t* pairs, const uint8_t* flags, const int64_t* dev_total, int64_t cap,
+                    const int64_t* dev_counts, int64_t n_counts, const int32_t* dev_status, int32_t* host_pairs,
+                    uint8_t* host_flags, int64_t* host_counts, int32_t* host_status, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

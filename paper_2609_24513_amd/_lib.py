@@ -28,6 +28,7 @@ EXPORTS = [
     "inside_workspace_bytes", "inside_pairs", "refine_predicate_workspace_bytes", "refine_predicate",
     "dataset_tri_objects", "dataset_trace_ws_bytes", "dataset_trace", "pairs_unique_ws_bytes", "pairs_unique",
     "estimate_pairs_ws_bytes", "estimate_pairs", "filter_aabb_pairs_batch_ws_bytes", "filter_aabb_pairs_batch",
+    "results_to_host",
 ]
 
 
@@ -125,6 +126,7 @@ def load():
         lib.compact_pairs_ws_bytes.argtypes = [i64, szp]
         lib.compact_pairs.argtypes = [vp, vp, i64, vp, vp, i64, vp, vp, ctypes.c_size_t, vp]
         lib.gather_pair_regions.argtypes = [vp, i64, vp, i64, vp, i64, vp, vp]
+        lib.results_to_host.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp]
         lib.refine_intersects_static.argtypes = [vp, i64, vp, i64, vp, i64, vp, ctypes.POINTER(RefineParams),
                                                  vp, vp, vp]
         lib.refine_static_scratch_bytes.argtypes = []

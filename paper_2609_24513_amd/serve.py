@@ -24,10 +24,9 @@ runs without blocking the host:
     once, with no host round trip; this work is captured once per slot and
     batch size as a HIP graph when the server starts, so a batch is one
     graph launch;
-  * the counts, the status and the batch's pairs and flags (up to
-    max_pairs per admitted request, an upper bound of the batch size) go
-    back to pinned host buffers by asynchronous copies enqueued behind the
-    refinement; when the slot's stream has finished, the results are read
+  * the counts, the status and the batch's pairs and flags (as many as the
+    device count says) go to pinned host buffers in one launch behind the
+    refinement (results_to_host); when the slot's stream has finished, the results are read
     from those buffers with no further device transfer; a request completes
     then, and its latency is completion time minus arrival time.
 
@@ -161,7 +160,7 @@ class JoinServer:
         boxes copied in, one batched filter into the queries' regions, the regions
         concatenated on the device (gather_pair_regions), one refinement of
         the concatenation with the device count, then the counts, status,
-        pairs and flags copied back to pinned host buffers.  Every buffer
+        pairs and flags into pinned host buffers.  Every buffer
         is the slot's own, so the same work can be captured once per batch
         size and replayed."""
         torch, pa, lib = self.torch, self.pa, _lib.load()
@@ -181,12 +180,11 @@ class JoinServer:
             # launch is sized for that many (small batches skip the cull order)
             pa.refine(self.R, self.S, slot.batch[:n * self.max_pairs], cfg, ws=slot.rws, flags=slot.flags,
                       stats=slot.stats, status=slot.status, stream=slot.stream)
-            slot.counts_h[:n].copy_(slot.counts[:n], non_blocking=True)
-            slot.status_h.copy_(slot.status, non_blocking=True)
             # every request holds at most max_pairs candidates in the batch
-            m = n * self.max_pairs
-            slot.batch_h[:m].copy_(slot.batch[:m], non_blocking=True)
-            slot.flags_h[:m].copy_(slot.flags[:m], non_blocking=True)
+            _lib.check(lib.results_to_host(
+                slot.batch.data_ptr(), slot.flags.data_ptr(), slot.total.data_ptr(), n * self.max_pairs,
+                slot.counts.data_ptr(), n, slot.status.data_ptr(), slot.batch_h.data_ptr(), slot.flags_h.data_ptr(),
+                slot.counts_h.data_ptr(), slot.status_h.data_ptr(), sp))
 
     def _capture(self) -> bool:
         """Captures each slot's batch work for every batch size (HIP graphs:

@@ -94,3 +94,35 @@ def test_few_units_are_shared_by_several_waves(oracle_mod, width, leaf):
         st = pa.stats_dict(stats)
         totals[reps] = (st["groups"] * many // reps, st["groups_box_pass"] * many // reps)
     assert totals[1] == totals[3] == totals[many]
+
+
+@pytest.mark.parametrize("total", [-1, 0, 1, 15, 16, 33, 5000, 5001])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_results_to_host(total, shift):
+    """As many rows as the device count says, nothing beyond them, at any alignment."""
+    import torch
+    from paper_2609_24513_amd import _lib
+    lib = _lib.load()
+    cap, nc = 5000, 7
+    rng = np.random.default_rng(total + 2)
+    pairs = torch.from_numpy(rng.integers(0, 1 << 30, (cap + 2, 2)).astype(np.int32)).cuda()[shift:]
+    flags = torch.from_numpy(rng.integers(0, 2, cap + 2).astype(np.uint8)).cuda()[shift:]
+    counts = torch.arange(nc, dtype=torch.int64, device="cuda")
+    t = torch.tensor([total], dtype=torch.int64, device="cuda")
+    status = torch.tensor([-5], dtype=torch.int32, device="cuda")
+    hp = torch.full((cap + 2, 2), -7, dtype=torch.int32, pin_memory=True)
+    hf = torch.full((cap + 2,), 9, dtype=torch.uint8, pin_memory=True)
+    hc = torch.full((nc + 1,), -7, dtype=torch.int64, pin_memory=True)
+    hs = torch.zeros(1, dtype=torch.int32, pin_memory=True)
+    s = torch.cuda.current_stream().cuda_stream
+    _lib.check(lib.results_to_host(pairs.data_ptr(), flags.data_ptr(), t.data_ptr(), cap, counts.data_ptr(), nc,
+                                   status.data_ptr(), hp.data_ptr() + 8 * shift, hf.data_ptr() + shift, hc.data_ptr(),
+                                   hs.data_ptr(), s))
+    torch.cuda.synchronize()
+    m = min(max(total, 0), cap)
+    gp, gf = hp.numpy(), hf.numpy()
+    assert np.array_equal(gp[shift:shift + m], pairs.cpu().numpy()[:m])
+    assert np.array_equal(gf[shift:shift + m], flags.cpu().numpy()[:m])
+    assert np.all(gp[:shift] == -7) and np.all(gp[shift + m:] == -7)
+    assert np.all(gf[:shift] == 9) and np.all(gf[shift + m:] == 9)
+    assert np.array_equal(hc.numpy()[:nc], np.arange(nc)) and hc[nc] == -7 and hs[0] == -5
