@@ -213,7 +213,6 @@ __device__ __forceinline__ float from_ordered(uint32_t u) {
 // cells^(2/3) of them, so an occupied cell of 10^5 items holds some 200.
 __host__ __device__ __forceinline__ int cell_bits(int64_t n) {
   if (n <= kUnitCap) return 0;
-  if (n <= kUnitCap) return 0;
   return 63 - __builtin_clzll((uint64_t)n) - 3;
 }
 

@@ -1582,15 +1582,16 @@ __device__ __forceinline__ int pop_shift(uint32_t n, uint32_t waves) {
 // columns 657 us, 64 columns 682 us).
 constexpr uint32_t kPopCols = 16;
 
-// Waves a SIMD.  FP32 tests with deferral hide latency best with seven, at
-// the price of a few spills (50,000 mixed pairs, cull + trace: five 647, six
-// 622, seven 614, eight 655 us; 5,000 sphere pairs six 262, seven 255 us); the
-// exact grid tier needs registers more (2,000 touching pairs: six 212, five
-// 204, four 200 us).
-constexpr int packet_waves(int prec) { return prec == 0 ? 7 : (prec == 3 ? 4 : 6); }
+// Waves a SIMD.  FP32 tests with deferral hide latency best with seven at
+// W <= 4, at the price of a few spills (5,000 sphere pairs, cull + trace: six
+// 262, seven 255, eight 272 us); at W = 8 seven gain 1 % where the queues are
+// long (50,000 mixed pairs: five 647, six 622, seven 614, eight 655 us) and
+// lose 3 % where they are short (233 pairs of 950-group meshes); the exact grid
+// tier needs registers more (2,000 touching pairs: six 212, five 204, four 200 us).
+constexpr int packet_waves(int w, int prec) { return prec == 0 ? (w < 8 ? 7 : 6) : (prec == 3 ? 4 : 6); }
 
 template <int W, int PREC>
-__global__ __launch_bounds__(kBlock, packet_waves(PREC)) void k_packet(RefineArgs ra) {
+__global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(RefineArgs ra) {
   __shared__ int32_t s_ref[kWaves][lds_stack_cap<W>()];
   __shared__ uint64_t s_mask[kWaves][lds_stack_cap<W>()];
   __shared__ BlockShare s_share;

@@ -43,8 +43,8 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int j) {
 
 // Segment-box test (conservative): slab test on t in [0, 1] for the segment
 // p + t (q - p), with t computed as (plane - p) * fl(1 / fl(q - p)); every t
-// carries a relative error of at most gamma_4 = 4 eps / (1 - 4 eps), so
-// accepting when t_min <= t_max (1 + 2^-19) + 2^-120 never rejects a box the
+// carries a relative error of at most gamma_4 = 4 eps / (1 - 4 eps) (gamma_5
+// with axis_rcp), so accepting when t_min <= t_max (1 + 2^-19) + 2^-120 never rejects a box the
 // exact segment touches (closed boxes).  A zero direction component uses a
 // large finite reciprocal (2^100) and a bias of 2^16 that turns the slab into
 // "no constraint" or "empty" exactly.  Valid for FP32-safe coordinates; for
