@@ -212,7 +212,7 @@ def roofline_of(st: dict, W: int, kern_ms: float, workload: str, L: int = 0, sch
     # valu_use: share of SIMD cycles issuing vector instructions, per kernel,
     # from the profiled run's counters (4 x SQ_INSTS_VALU / SIMD cycles)
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": "k_cull + k_trace",
+            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": "k_cull + k_packet",
             "kernel_ms": kern_ms, "algorithmic_bytes": int(alg), "loaded_bytes_model": int(loaded),
             "loaded_gbs": loaded / (kern_ms * 1e-3) / 1e9, "valu_use": valu}
 

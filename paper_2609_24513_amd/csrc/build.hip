@@ -15,8 +15,10 @@
 //     of one mesh are merged);
 //  4. per mesh, a binary radix tree over the sorted codes (Karras 2012,
 //     "Maximizing parallelism in the construction of BVHs, octrees, and k-d
-//     trees"), ties broken by position, with exact min/max boxes bottom up:
-//     the nodes that lie inside a chunk in LDS, the others after them;
+//     trees"; numbering of nodes from there), ties broken by position, with
+//     exact min/max boxes, bottom up from neighbours' common prefixes (Apetrei
+//     2014, "Fast and simple agglomerative LBVH construction"): the nodes that
+//     lie inside a chunk in LDS, the others after them;
 //  5. collapse to width W: each wide node starts from a binary node and
 //     repeatedly opens the child with the largest box surface among those
 //     holding more than L triangles, until it has W children; children of at
@@ -947,7 +949,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
   }
 }
 
-// ---- step 4: Karras radix tree and boxes -------------------------------------------
+// ---- step 4: radix tree and boxes --------------------------------------------------
 
 // Length of the common prefix of the codes of positions i and i + 1 (equal
 // codes are told apart by position).
