@@ -90,8 +90,10 @@ __device__ __forceinline__ f3 load_v(const float* verts, int64_t g) {
   return f3{verts[3 * g], verts[3 * g + 1], verts[3 * g + 2]};
 }
 
-// Per mesh: its faces (none when its offsets are inconsistent: the build then
-// fails through the status word) and the first of its entries in each table.
+// Per mesh: its faces and the first of its entries in each table.  When a
+// mesh's offsets are inconsistent no mesh has faces or entries: the build
+// fails through the status word, and ranges that overlap, which each look
+// sound, cannot add up to more than the tables hold.
 struct MeshPlan {
   int64_t v0;       // first vertex
   int32_t nv;       // vertices
@@ -226,9 +228,12 @@ __device__ __forceinline__ int32_t div_up(int64_t n, int d) { return (int32_t)((
 // fetch of its code (unrolled over four meshes a thread 37 us for 173 meshes).
 __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
   __shared__ uint64_t s_sum[4][16], s_run[4];
+  __shared__ int s_bad;  // a mesh's offsets are inconsistent
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint32_t w1 = (uint32_t)a.width - 1u, l1 = (uint32_t)a.leaf + 1u;
   if (threadIdx.x < 4) s_run[threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
 #pragma unroll 1
   for (int64_t base = 0; base < a.n_meshes; base += 1024) {
     const int64_t m = base + threadIdx.x;
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
       if (m == 0) ok = ok && f0 == 0 && v0 == 0;
       if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
       if (!ok) {
-        atomicMin(a.status, 0);
+        s_bad = 1;
       } else {
         p.v0 = v0;
         p.nv = (int32_t)(v1 - v0);
@@ -307,6 +312,11 @@ __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
     t.cchunk = (int32_t)(s_run[3] >> 32);
     a.plan[a.n_meshes] = t;
   }
+  if (!s_bad) return;
+  if (threadIdx.x == 0) *a.status = 0;
+  __syncthreads();  // the totals are written
+#pragma unroll 1
+  for (int64_t m = threadIdx.x; m <= a.n_meshes; m += 1024) a.plan[m] = MeshPlan{};
 }
 
 // Everything that starts at a fixed value.

@@ -1,0 +1,56 @@
+"""What the build does with inputs that it refuses: nothing is written outside
+the blob and the workspace, and the status names the first bad face."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 1 << 16
+
+
+def _build(verts, faces, vert_off, face_off, width=4, leaf=4):
+    """build_mesh_bvh with guard bytes on both sides of the blob and of the
+    workspace: (status, guards untouched)."""
+    import torch
+    from paper_2609_24513_amd import _lib
+    lib = _lib.load()
+    prm = _lib.BvhParams(width, leaf, 0, 0)
+    M, F, V = len(face_off) - 1, faces.shape[0], verts.shape[0]
+    bb, wb = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    _lib.check(lib.build_mesh_bvh_sizes(M, F, V, ctypes.byref(prm), ctypes.byref(bb), ctypes.byref(wb)))
+    bufs = [torch.full((2 * GUARD + n.value,), 0xA5, dtype=torch.uint8, device="cuda") for n in (bb, wb)]
+    dev = [torch.as_tensor(x).cuda() for x in (verts, vert_off, faces, face_off)]
+    status = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    _lib.check(lib.build_mesh_bvh(dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), dev[3].data_ptr(), M, V, F,
+                                  ctypes.byref(prm), bufs[0].data_ptr() + GUARD, bb.value, bufs[1].data_ptr() + GUARD,
+                                  wb.value, status.data_ptr(), None))
+    torch.cuda.synchronize()
+    clean = all(bool((b[:GUARD] == 0xA5).all()) and bool((b[-GUARD:] == 0xA5).all()) for b in bufs)
+    return int(status.item()), clean
+
+
+def _faces(n):
+    f = np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2], 1).astype(np.int32)
+    v = np.random.default_rng(n).uniform(-1, 1, size=(n + 2, 3)).astype(np.float32)
+    return v, f
+
+
+@pytest.mark.parametrize("name", ["alternating", "one_after", "past_the_end", "negative", "not_from_zero", "vertices"])
+def test_offsets_that_overlap_or_leave_the_arrays(name):
+    v, f = _faces(1000)
+    F, V = f.shape[0], v.shape[0]
+    fo = {"alternating": [0, F] * 20 + [F], "one_after": [0, F] * 20 + [0, 1, F], "past_the_end": [0, F + 5, F],
+          "negative": [0, -4, F], "not_from_zero": [3, 500, F], "vertices": [0, 500, F]}[name]
+    vo = np.array([0] + [V] * (len(fo) - 1), np.int64)
+    if name == "vertices":
+        vo = np.array([0, V + 1, V], np.int64)
+    fo = np.array(fo, np.int64)
+    status, clean = _build(v, f, vo, fo)
+    assert clean and status == 0
+
+
+def test_sound_offsets_with_the_same_helper():
+    v, f = _faces(1000)
+    assert _build(v, f, np.array([0, 1002], np.int64), np.array([0, 1000], np.int64)) == (-1, True)
