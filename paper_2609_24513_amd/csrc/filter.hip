@@ -390,8 +390,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a) {
 // publishes its count, adds up the counts of the shares before it, and walks
 // its rows again to write the pairs in place, sorted by (i, j).  Two kept boxes
 // that overlap share a point with the query box on every axis (three
-// pairwise-meeting intervals have a common point), so the boxes' own overlap
-// is the whole test.  Bound by latency for usual boxes (a few hundred rows).
+// pairwise-meeting intervals, none empty, have a common point; an empty query
+// box keeps nothing), so the boxes' own overlap is the whole test.  Bound by latency for usual boxes (a few hundred rows).
 constexpr int kQWords = (int)(kSmallScan / 64);
 constexpr int kQBlocks = 32;
 constexpr int kQRows = 16;                                // rows of a share, at least
@@ -425,7 +425,9 @@ __global__ __launch_bounds__(kScanBlock) void k_query_keep(const void* blob_a, i
     float qb[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) qb[c] = qs[6 * q + c];
-    const uint64_t w = __ballot(live && meet(b, qb));
+    // an inverted box is empty, though a mesh box that spans both of its planes passes the closed compares
+    const bool some = qb[0] <= qb[3] && qb[1] <= qb[4] && qb[2] <= qb[5];
+    const uint64_t w = __ballot(live && some && meet(b, qb));
     if ((threadIdx.x & 63) == 0 && m < ((M + 63) & ~(int64_t)63)) out[(int64_t)q * (2 * kQWords)] = w;
   }
 }

@@ -1,0 +1,61 @@
+"""Query boxes at the limits of the small-dataset path: empty boxes (one or
+more axes inverted)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+INF = 1e30
+
+
+def _cubes(rng, n, side, lo=0.5, hi=1.5):
+    from paper_2609_24513_amd import synth
+    v = rng.uniform(0, side, size=(n, 1, 3)) + rng.uniform(lo, hi, size=(n, 1, 1)) * synth._CUBE_V[None]
+    k = synth._CUBE_V.shape[0]
+    f = np.broadcast_to(synth._CUBE_F[None], (n,) + synth._CUBE_F.shape).reshape(-1, 3)
+    return synth.MeshSet(v.reshape(-1, 3).astype(np.float32), np.ascontiguousarray(f, np.int32),
+                         k * np.arange(n + 1, dtype=np.int64), synth._CUBE_F.shape[0] * np.arange(n + 1, dtype=np.int64))
+
+
+def _batch(ga, gb, boxes, cap):
+    """filter_aabb_pairs_batch: (pairs i32[n, cap, 2], counts)."""
+    import torch
+    from paper_2609_24513_amd import _lib
+    lib = _lib.load()
+    n = len(boxes)
+    wb = ctypes.c_size_t(0)
+    _lib.check(lib.filter_aabb_pairs_batch_ws_bytes(ga.n_meshes, gb.n_meshes, n, ctypes.byref(wb)))
+    ws = torch.empty(wb.value, dtype=torch.uint8, device="cuda")
+    dq = torch.as_tensor(np.asarray(boxes, np.float32)).cuda()
+    out = torch.full((n * cap, 2), -7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((n,), -7, dtype=torch.int64, device="cuda")
+    _lib.check(lib.filter_aabb_pairs_batch(ga.ptr, ga.n_meshes, gb.ptr, gb.n_meshes, dq.data_ptr(), n, out.data_ptr(),
+                                           cap, cnt.data_ptr(), ws.data_ptr(), ws.numel(), None))
+    torch.cuda.synchronize()
+    return out.cpu().numpy().reshape(n, cap, 2), cnt.tolist()
+
+
+@pytest.mark.parametrize("ma,mb", [(3, 4), (300, 200), (40, 9000)])
+def test_an_inverted_box_selects_nothing(ma, mb):
+    import oracle
+    import paper_2609_24513_amd as pa
+    rng = np.random.default_rng(ma + mb)
+    A, B = _cubes(rng, ma, 1.0, 4.0, 6.0), _cubes(rng, mb, 1.0, 4.0, 6.0)  # every box spans [1, 4]
+    ga, gb = pa.MeshBlob.build(A), pa.MeshBlob.build(B)
+    ba, bb = oracle.mesh_boxes(A), oracle.mesh_boxes(B)
+    q = np.array([2, 2, 2, 3, 3, 3], np.float32)
+    assert oracle.candidate_pairs(ba, bb, q).shape[0] == ma * mb
+    boxes = [q]
+    for axes in ((0,), (1,), (2,), (0, 1, 2)):
+        e = q.copy()
+        for k in axes:
+            e[k], e[3 + k] = q[3 + k], q[k]
+        boxes.append(e)
+    want = [oracle.candidate_pairs(ba, bb, e).astype(np.int32) for e in boxes]
+    assert [w.shape[0] for w in want] == [ma * mb, 0, 0, 0, 0]
+    for e, w in zip(boxes, want):
+        assert np.array_equal(pa.filter_pairs(ga, gb, query_box=e, cap=ma * mb).cpu().numpy(), w)
+    got, cnt = _batch(ga, gb, boxes, 5)
+    assert cnt == [ma * mb, 0, 0, 0, 0] and np.all(got[1:] == -7)
