@@ -1230,7 +1230,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
   };
   const int64_t nw = (int64_t)gridDim.x * kWaves;
   const int64_t upad = (U + 8 * kWaves - 1) / (8 * kWaves) * (8 * kWaves);
-  if (2 * upad <= nw) {
+  if (U > 0 && 2 * upad <= nw) {  // (a device count may be 0)
     // fewer units than waves: up to 1 << kCullSplit waves share a unit, each
     // taking every so many of its runs, so that large meshes are not one
     // wave's serial chain (466 units of 15 runs: 82 -> 29 us).  Part 0 goes to
@@ -1239,8 +1239,9 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
     // (190 pairs of 48-triangle meshes, cull + trace: 39 us, so 30 us)
     int split = 0;
     while (split < kCullSplit && (upad << (split + 1)) <= nw) ++split;
-    const int64_t x = (int64_t)blockIdx.x * kWaves + wv, part = x / upad, u = x - part * upad;
-    if (u < U && part < (1 << split)) cull_unit(u, pairs[2 * (u >> 1)], pairs[2 * (u >> 1) + 1], split, (int)part);
+    const uint32_t x = blockIdx.x * kWaves + wv, part = x / (uint32_t)upad;
+    const int64_t u = x - part * (uint32_t)upad;
+    if (u < U && part < (1u << split)) cull_unit(u, pairs[2 * (u >> 1)], pairs[2 * (u >> 1) + 1], split, (int)part);
   } else if (U <= kCullStatic * nw) {
     // few units per wave: dealt in a fixed stride, the pair of the wave's
     // next unit read while the current one is culled
