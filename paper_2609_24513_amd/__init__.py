@@ -66,6 +66,7 @@ class MeshBlob:
         self._status = status
         self._exps = exps          # device i32[2]: coordinate bit-exponent range
         self._exp_range = None
+        self._ready = None         # event behind the build, when it ran on a stream of the caller's choice
 
     @property
     def ptr(self) -> int:
@@ -98,7 +99,14 @@ class MeshBlob:
         _lib.check(lib.blob_coord_exponents(blob.data_ptr(), exps.data_ptr(), _stream_ptr(stream)))
         out = cls(blob, M, width, leaf_size, status, exps)
         out.builder = int(builder)
+        if stream is not None:
+            for t in (verts, vo, faces, fo, ws, words):
+                t.record_stream(stream)
+            if not torch.cuda.is_current_stream_capturing():
+                out._ready = torch.cuda.Event()
+                out._ready.record(stream)
         if check_status:
+            out._wait()
             st, lo, hi = (int(x) for x in words.tolist())
             if st != -1:
                 raise PierceError(_lib.PR_E_GEOMETRY, "invalid geometry at face %d" % st)
@@ -106,13 +114,21 @@ class MeshBlob:
         del ws
         return out
 
+    def _wait(self):
+        """The current stream, on which the build's words are read, after the
+        build's own."""
+        if self._ready is not None:
+            _torch().cuda.current_stream().wait_event(self._ready)
+
     def status(self) -> int:
+        self._wait()
         return int(self._status.item())
 
     def exp_range(self):
         """(lowest, highest) exponent of a set bit over the blob's coordinates
         (read once from the device)."""
         if self._exp_range is None:
+            self._wait()
             lo, hi = (int(x) for x in self._exps.cpu().tolist())
             self._exp_range = (lo, hi)
         return self._exp_range

@@ -54,3 +54,39 @@ def test_offsets_that_overlap_or_leave_the_arrays(name):
 def test_sound_offsets_with_the_same_helper():
     v, f = _faces(1000)
     assert _build(v, f, np.array([0, 1002], np.int64), np.array([0, 1000], np.int64)) == (-1, True)
+
+
+@pytest.mark.parametrize("check", [True, False])
+def test_build_on_another_stream_is_waited_for(check):
+    """The status and the exponent range are read behind the build, though its
+    stream is busy when it is enqueued."""
+    import torch
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    rng = np.random.default_rng(5)
+    v = np.array([[0, 0, 0], [1, 0, 0], [0, 2, 0], [0, 0, 8]], np.float32)
+    f = np.array([[0, 2, 1], [0, 1, 3], [0, 3, 2], [1, 2, 3]], np.int32)
+    good = synth.concat_meshes([(v, f)] * 40)
+    bad = synth.MeshSet(good.verts, good.faces.copy(), good.vert_off, good.face_off)
+    bad.faces[77, 1] = 99
+    pa.MeshBlob.build(good)  # the kernels are loaded
+    s = torch.cuda.Stream()
+    for k in range(3):
+        torch.cuda.synchronize()
+        # the words' memory holds what an earlier build left: neither -1 nor a face, nor a range
+        junk = torch.full((1 << 16,), -1000 - k, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        del junk
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(int(rng.integers(20_000_000, 60_000_000)))
+        if check:
+            assert pa.MeshBlob.build(good, stream=s).exp_range() == (0, 3)
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(20_000_000)
+            with pytest.raises(pa.PierceError):
+                pa.MeshBlob.build(bad, stream=s)
+        else:
+            g = pa.MeshBlob.build(good, stream=s, check_status=False)
+            assert g.exp_range() == (0, 3) and g.status() == -1
+            b = pa.MeshBlob.build(bad, stream=s, check_status=False)
+            assert b.status() == 77
