@@ -384,26 +384,39 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a) {
 // thread and tests it against every box: each wave's ballot is stored (word w
 // of a dataset covers meshes 64 w ... 64 w + 63), with the control words of
 // the second kernel cleared.  k_query_pairs gives each box up to kQBlocks
-// blocks.  A block scans the box's ballots, takes a contiguous share of the
-// kept rows (by ticket, so that a block only ever waits for blocks that run
-// already), counts their pairs against the kept columns staged in LDS,
-// publishes its count, adds up the counts of the shares before it, and walks
-// its rows again to write the pairs in place, sorted by (i, j).  Two kept boxes
+// blocks, a few boxes more of them.  A block scans the box's ballots, takes a
+// contiguous share of the kept rows (by ticket, so that a block only ever
+// waits for blocks that run already), finds their pairs with the kept columns
+// staged in LDS, publishes their number, adds up the numbers of the shares
+// before it, and writes its pairs in place, sorted by (i, j): from LDS, or when
+// they are too many for it by walking its rows again.  Two kept boxes
 // that overlap share a point with the query box on every axis (three
 // pairwise-meeting intervals, none empty, have a common point; an empty query
-// box keeps nothing), so the boxes' own overlap is the whole test.  Bound by latency for usual boxes (a few hundred rows).
+// box keeps nothing), so the boxes' own overlap is the whole test.
+// Bound by latency for usual boxes (a few hundred rows), by the staging of the
+// columns for those that keep most meshes.  One box: with 32 blocks for it and
+// two walks 8.5 us for a few hundred kept meshes and 8.0 ms for all of 25,000 x
+// 25,000 (2.6 for 25,000 x 8,000, 53 for 65,536 x 65,536); this 9.3 us and 1.0
+// ms (0.37, 6.3); 512 blocks 13 us and 0.53 ms.  Shares of kQRows rows keep
+// every wave busy; where the staging of many column tiles is most of a share's
+// time, kQRowsWide spread it over more blocks (2,000 x 60,000: 2.1 -> 0.6 ms).
 constexpr int kQWords = (int)(kSmallScan / 64);
-constexpr int kQBlocks = 32;
-constexpr int kQRows = 16;                                // rows of a share, at least
-constexpr int kQShare = (int)(kSmallScan / kQBlocks) + 1; // rows of a share, at most
+constexpr int kQBlocks = 32;                              // of each box, at least, and for a call of
+constexpr int kQBlocksAll = 128;                          // few boxes together
+constexpr int kQRows = 16;                                // rows of a share, at least,
+constexpr int kQRowsWide = 4;                             // and with many column tiles
+constexpr int kQWide = 4;                                 // tiles
+constexpr int kQShare = (int)(kSmallScan / kQBlocks);     // rows of a share, at most
 constexpr int kQRowTile = 256, kQColTile = 1024;
-constexpr int kQCtl = kQBlocks + 1;                       // published counts, then the ticket
+constexpr int kQHits = 1024;                              // pairs of a share that LDS keeps
 constexpr uint64_t kPublished = 1ull << 63;
-static_assert(kQWords == kScanBlock && kQShare <= 2 * kScanBlock + 1, "one word and two rows per thread");
+static_assert(kSmallScan <= 65536 && kQShare <= 4096, "a mesh in 16 bits, a row in 12, a place in 20");
+static_assert(kQWords == kScanBlock && kQShare <= 2 * kScanBlock, "one word and two rows per thread");
+static_assert(kQBlocksAll <= kScanBlock, "one earlier share a thread");
 
 __global__ __launch_bounds__(kScanBlock) void k_query_keep(const void* blob_a, int64_t MA, const void* blob_b,
                                                            int64_t MB, const float* boxes, int32_t n, uint64_t* bits,
-                                                           unsigned long long* ctl) {
+                                                           unsigned long long* ctl, int32_t n_ctl) {
   const int64_t tiles_a = (MA + kScanBlock - 1) / kScanBlock;
   const bool first = (int64_t)blockIdx.x < tiles_a;
   const int64_t tile = first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - tiles_a;
@@ -418,16 +431,14 @@ __global__ __launch_bounds__(kScanBlock) void k_query_keep(const void* blob_a, i
     live = __float_as_int(w.y) > 0;
   }
   if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < n * kQCtl; i += kScanBlock) ctl[i] = 0ull;
+    for (int i = threadIdx.x; i < n_ctl; i += kScanBlock) ctl[i] = 0ull;
   uint64_t* out = bits + (first ? 0 : kQWords) + (m >> 6);
   const cptr_t<float> qs = cview(boxes);
   for (int32_t q = 0; q < n; ++q) {
     float qb[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) qb[c] = qs[6 * q + c];
-    // an inverted box is empty, though a mesh box that spans both of its planes passes the closed compares
-    const bool some = qb[0] <= qb[3] && qb[1] <= qb[4] && qb[2] <= qb[5];
-    const uint64_t w = __ballot(live && some && meet(b, qb));
+    const uint64_t w = __ballot(live && meet(b, qb));
     if ((threadIdx.x & 63) == 0 && m < ((M + 63) & ~(int64_t)63)) out[(int64_t)q * (2 * kQWords)] = w;
   }
 }
@@ -441,9 +452,10 @@ __device__ __forceinline__ void kept_ids(const uint64_t* words, const int32_t* b
     if (k >= 0) id[k] = 64 * (int32_t)threadIdx.x + __builtin_ctzll(w);
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_query_pairs(const void* blob_a, int64_t MA, const void* blob_b,
-                                                            int64_t MB, const uint64_t* bits, unsigned long long* ctl,
-                                                            int32_t* pairs, int64_t cap, int64_t* counts) {
+__global__ __launch_bounds__(kScanBlock, 8) void k_query_pairs(const void* blob_a, int64_t MA, const void* blob_b,
+                                                            int64_t MB, const float* boxes, const uint64_t* bits,
+                                                            unsigned long long* ctl, int32_t* pairs, int64_t cap,
+                                                            int64_t* counts) {
   __shared__ uint64_t s_wa[kQWords], s_wb[kQWords];
   __shared__ int32_t s_pa[kQWords], s_pb[kQWords];
   __shared__ float s_col[6][kQColTile], s_rbox[6][kQRowTile];
@@ -451,24 +463,35 @@ __global__ __launch_bounds__(kScanBlock) void k_query_pairs(const void* blob_a, 
   __shared__ int32_t s_row[2 * kScanBlock + 2];  // pairs of each row of the share, then their places
   __shared__ int32_t s_i32[kScanBlock / 64];
   __shared__ int64_t s_i64[kScanBlock / 64];
+  __shared__ uint32_t s_hit[kQHits][2];  // row | place in it << 12, mesh of A | mesh of B << 16
+  __shared__ int32_t s_hits;
   __shared__ int32_t s_ticket;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t q = blockIdx.y;
-  ctl += q * kQCtl;
+  const int32_t blocks = (int32_t)gridDim.x;
+  ctl += q * (blocks + 1);  // the shares' published counts, then the ticket
   pairs += 2 * q * cap;
   const uint64_t* wa = bits + q * (2 * kQWords);
-  if (t == 0) s_ticket = (int32_t)atomicAdd(ctl + kQBlocks, 1ull);
+  // an inverted box is empty, though a mesh box that spans both of its planes passes the closed compares
+  const cptr_t<float> qb = cview(boxes) + 6 * q;
+  const bool some = qb[0] <= qb[3] && qb[1] <= qb[4] && qb[2] <= qb[5];
+  if (t == 0) s_ticket = (int32_t)atomicAdd(ctl + blocks, 1ull);
   const uint64_t a = t < (MA + 63) / 64 ? wa[t] : 0ull, b = t < (MB + 63) / 64 ? wa[kQWords + t] : 0ull;
   s_wa[t] = a;
   s_wb[t] = b;
   int32_t na, nb;
   s_pa[t] = block_exclusive_sum<kScanBlock>((int32_t)__popcll(a), s_i32, na);
   s_pb[t] = block_exclusive_sum<kScanBlock>((int32_t)__popcll(b), s_i32, nb);
+  if (!some) na = 0;
   s_row[2 * t] = 0;
   s_row[2 * t + 1] = 0;
-  if (t == 0) s_row[2 * kScanBlock] = 0;
+  if (t == 0) {
+    s_row[2 * kScanBlock] = 0;
+    s_hits = 0;
+  }
   __syncthreads();
-  const int32_t share = s_ticket, shares = max(1, min(kQBlocks, (na + kQRows - 1) / kQRows));
+  const int32_t most = nb > kQWide * kQColTile ? (na + kQRowsWide - 1) / kQRowsWide : (na + kQRows - 1) / kQRows;
+  const int32_t share = s_ticket, shares = max(1, min(blocks, most));
   if (share >= shares) return;
   const int32_t r0 = (int32_t)((int64_t)na * share / shares), r1 = (int32_t)((int64_t)na * (share + 1) / shares);
   const MeshDesc *ma = meshes_of(blob_a), *mb = meshes_of(blob_b);
@@ -510,9 +533,19 @@ __global__ __launch_bounds__(kScanBlock) void k_query_pairs(const void* blob_a, 
             const bool ok = i < nc && overlap(x, s_col[0][i], s_col[1][i], s_col[2][i], s_col[3][i], s_col[4][i],
                                               s_col[5][i]);
             const uint64_t m = __ballot(ok);
-            if (pass == 1 && ok) {
-              const int64_t pos = base + at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (!m) continue;
+            const int32_t before = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (pass == 0) {
+              int32_t h = 0;
+              if (lane == 0) h = atomicAdd(&s_hits, __popcll(m));
+              h = __builtin_amdgcn_readfirstlane(h) + before;
+              if (ok && h < kQHits) {
+                s_hit[h][0] = (uint32_t)row | (uint32_t)(at + before) << 12;
+                s_hit[h][1] = (uint32_t)ia | (uint32_t)s_cid[i] << 16;
+              }
+            } else if (ok) {
+              const int64_t pos = base + at + before;
               if (pos < cap) {
                 pairs[2 * pos] = ia;
                 pairs[2 * pos + 1] = s_cid[i];
@@ -543,6 +576,16 @@ __global__ __launch_bounds__(kScanBlock) void k_query_pairs(const void* blob_a, 
     if (t == 0 && share == shares - 1) counts[q] = base + total;
     if (total == 0) return;
     __syncthreads();
+    if (total <= kQHits) {
+      for (int k = t; k < (int)total; k += kScanBlock) {
+        const int64_t pos = base + s_row[s_hit[k][0] & 4095u] + (s_hit[k][0] >> 12);
+        if (pos < cap) {
+          pairs[2 * pos] = (int32_t)(s_hit[k][1] & 0xffffu);
+          pairs[2 * pos + 1] = (int32_t)(s_hit[k][1] >> 16);
+        }
+      }
+      return;
+    }
   }
 }
 
@@ -716,8 +759,9 @@ __global__ __launch_bounds__(kBlock) void k_to_host(HostOut o) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *o.h_status = *o.status;
 }
 
-// Boxes that one pair of launches takes.
+// Boxes that one pair of launches takes, and the blocks of each of n boxes.
 int64_t boxes_at_once(int64_t n) { return n < 1 ? 1 : (n < 1024 ? n : 1024); }
+int64_t query_blocks(int64_t n) { return kQBlocksAll / n > kQBlocks ? kQBlocksAll / n : kQBlocks; }
 
 struct FilterWs {
   int32_t *flag_a, *flag_b, *pos_a, *pos_b, *ids_a, *ids_b;
@@ -726,7 +770,7 @@ struct FilterWs {
   int32_t *blocksum, *paircnt;
   int64_t* tsum;  // tile sums of the device-wide scans
   uint64_t* qbits;            // query-box ballots, [n][2][kQWords]
-  unsigned long long* qctl;   // [n][kQCtl]
+  unsigned long long* qctl;   // [n][blocks + 1]
 };
 
 int carve_filter(Carve& cv, FilterWs& w, int64_t MA, int64_t MB, int64_t n_boxes) {
@@ -746,7 +790,8 @@ int carve_filter(Carve& cv, FilterWs& w, int64_t MA, int64_t MB, int64_t n_boxes
   const int64_t mx = MA > MB ? MA : MB;
   w.tsum = cv.take<int64_t>(scan_tiles_of(mx + 1));
   w.qbits = cv.take<uint64_t>(n_boxes * 2 * kQWords);
-  w.qctl = cv.take<unsigned long long>(n_boxes * kQCtl);
+  // a call's last chunk of fewer boxes has up to kQBlocksAll + n words, less than a full chunk
+  w.qctl = cv.take<unsigned long long>(n_boxes * (query_blocks(n_boxes) + 1));
   return PR_OK;
 }
 
@@ -757,12 +802,13 @@ bool small_query(int64_t MA, int64_t MB) { return MA <= kSmallScan && MB <= kSma
 void launch_query(hipStream_t s, const void* blob_a, int64_t MA, const void* blob_b, int64_t MB, const float* boxes,
                   int32_t n, int32_t* pairs, int64_t cap, int64_t* counts, const FilterWs& w) {
   const int64_t tiles = (MA + kScanBlock - 1) / kScanBlock + (MB + kScanBlock - 1) / kScanBlock;
+  // a small dataset needs fewer blocks
+  const int64_t least = MB > kQWide * kQColTile ? kQRowsWide : kQRows, most = query_blocks(n);
+  const int64_t blocks = MA / least + 1 < most ? MA / least + 1 : most;
   hipLaunchKernelGGL(k_query_keep, dim3((unsigned)(tiles > 0 ? tiles : 1)), dim3(kScanBlock), 0, s, blob_a, MA, blob_b,
-                     MB, boxes, n, w.qbits, w.qctl);
-  // shares of kQRows rows at least: a small dataset needs fewer blocks
-  const int64_t blocks = MA / kQRows + 1 < kQBlocks ? MA / kQRows + 1 : kQBlocks;
+                     MB, boxes, n, w.qbits, w.qctl, (int32_t)(n * (blocks + 1)));
   hipLaunchKernelGGL(k_query_pairs, dim3((unsigned)blocks, (unsigned)n), dim3(kScanBlock), 0, s, blob_a, MA, blob_b, MB,
-                     (const uint64_t*)w.qbits, w.qctl, pairs, cap, counts);
+                     boxes, (const uint64_t*)w.qbits, w.qctl, pairs, cap, counts);
 }
 
 struct CompactWs {

@@ -1,5 +1,6 @@
 """Query boxes at the limits of the small-dataset path: empty boxes (one or
-more axes inverted)."""
+more axes inverted), the largest datasets it takes and the first it does not,
+shares whose pairs just fit LDS, boxes beyond one chunk of a batch."""
 import ctypes
 
 import numpy as np
@@ -59,3 +60,43 @@ def test_an_inverted_box_selects_nothing(ma, mb):
         assert np.array_equal(pa.filter_pairs(ga, gb, query_box=e, cap=ma * mb).cpu().numpy(), w)
     got, cnt = _batch(ga, gb, boxes, 5)
     assert cnt == [ma * mb, 0, 0, 0, 0] and np.all(got[1:] == -7)
+
+
+@pytest.mark.parametrize("ma,mb", [(65536, 5), (65537, 5), (5, 65536), (5, 65537), (16, 64), (16, 65), (40, 4096), (40, 4097)])
+def test_dataset_limits_with_a_box_that_keeps_everything(ma, mb):
+    import oracle
+    import paper_2609_24513_amd as pa
+    rng = np.random.default_rng(ma + 7 * mb)
+    small = min(ma, mb) < 40
+    side = 2.0 if max(ma, mb) < 100 else 12.0
+    A, B = _cubes(rng, ma, side, 2.0, 3.0), _cubes(rng, mb, side, 2.0, 3.0)
+    ga, gb = pa.MeshBlob.build(A), pa.MeshBlob.build(B)
+    ba, bb = oracle.mesh_boxes(A), oracle.mesh_boxes(B)
+    boxes = np.array([[-INF] * 3 + [INF] * 3, [4.0, 4, 4, 6, 7, 8], [90] * 6], np.float32)
+    want = [oracle.candidate_pairs(ba, bb, q).astype(np.int32) for q in boxes]
+    assert want[0].shape[0] > (500 if small else 5000) and want[2].shape[0] == 0
+    for q, w in zip(boxes, want):
+        assert np.array_equal(pa.filter_pairs(ga, gb, query_box=q, cap=want[0].shape[0]).cpu().numpy(), w)
+    got, cnt = _batch(ga, gb, boxes, want[0].shape[0] - 1)
+    assert cnt == [w.shape[0] for w in want]
+    for k, w in enumerate(want):
+        n = min(w.shape[0], got.shape[1])
+        assert np.array_equal(got[k, :n], w[:n]) and np.all(got[k, n:] == -7)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 1023, 1024, 1025])
+def test_batches_up_to_and_beyond_one_chunk(n):
+    import oracle
+    import paper_2609_24513_amd as pa
+    rng = np.random.default_rng(n)
+    A, B = _cubes(rng, 130, 8.0), _cubes(rng, 70, 8.0)
+    ga, gb = pa.MeshBlob.build(A), pa.MeshBlob.build(B)
+    ba, bb = oracle.mesh_boxes(A), oracle.mesh_boxes(B)
+    c, h = rng.uniform(0, 8, (n, 3)), rng.uniform(0.1, 5, (n, 3))
+    boxes = np.concatenate([c - h, c + h], 1).astype(np.float32)
+    want = [oracle.candidate_pairs(ba, bb, q).astype(np.int32) for q in boxes]
+    got, cnt = _batch(ga, gb, boxes, 40)
+    assert cnt == [w.shape[0] for w in want] and (n < 1000 or max(cnt) > 40)
+    for k, w in enumerate(want):
+        m = min(w.shape[0], 40)
+        assert np.array_equal(got[k, :m], w[:m]) and np.all(got[k, m:] == -7)
