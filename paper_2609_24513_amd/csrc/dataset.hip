@@ -502,13 +502,20 @@ __global__ void k_est_init(EstArgs e, int64_t grid_words) {
 // Volume of a mesh by the divergence theorem over its triangles (FP64), mean
 // box side and volume ratio; the union box.  One wave per mesh where the mean
 // mesh has at most kEstWave triangles (a block's other waves and its barriers
-// were most of 0.18 ms for 50,000 meshes of 12), else one block.  The union
+// were most of 0.18 ms for 50,000 meshes of 12), else one block.  Among small
+// meshes the waves leave those of more than kEstBig triangles to their whole
+// block, up to kEstList of them (beside 50,000 cubes one mesh of 2 M triangles
+// takes a wave 19.4 ms, a block 5.1).  The union
 // box is kept in registers and joined once a block.  (The host checks nothing
 // on the device blobs: a count above the blob's is cut to it.)
 constexpr int kEstWave = 512;
+constexpr int kEstBig = 4096;
+constexpr int kEstList = 16;
 
 __global__ __launch_bounds__(kDB) void k_est_objects(EstArgs e, int d) {
   __shared__ double s_red[kDWaves], s_ext[6][kDWaves];
+  __shared__ int64_t s_big[kEstList];
+  __shared__ int s_nbig;
   const BlobHeader* h = reinterpret_cast<const BlobHeader*>(e.blob[d]);
   if (h->magic != kMagic) return;
   const int64_t nm = e.n[d] < h->n_meshes ? e.n[d] : h->n_meshes;
@@ -516,12 +523,12 @@ __global__ __launch_bounds__(kDB) void k_est_objects(EstArgs e, int d) {
   const float* tris = reinterpret_cast<const float*>(e.blob[d] + h->off_tri);
   const bool by_wave = h->f_total <= kEstWave * h->n_meshes;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int t0 = by_wave ? lane : (int)threadIdx.x, step = by_wave ? 64 : kDB;
+  if (threadIdx.x == 0) s_nbig = 0;
+  __syncthreads();
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  const int64_t first = by_wave ? (int64_t)blockIdx.x * kDWaves + w : (int64_t)blockIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * (by_wave ? kDWaves : 1);
-  for (int64_t m = first; m < nm; m += stride) {
-    const MeshDesc D = md[m];
+  // one mesh by a wave, or (every thread of the block calls it) by the block
+  auto object = [&](int64_t m, const MeshDesc& D, bool wave) {
+    const int t0 = wave ? lane : (int)threadIdx.x, step = wave ? 64 : kDB;
     double acc = 0.0;
     for (int32_t t = t0; t < D.n_tris; t += step) {
       const float* p = tris + 9 * ((int64_t)D.tri_base + t);
@@ -530,7 +537,7 @@ __global__ __launch_bounds__(kDB) void k_est_objects(EstArgs e, int d) {
       acc += ax * (by * cz - bz * cy) + ay * (bz * cx - bx * cz) + az * (bx * cy - by * cx);
     }
     acc = wave_sum(acc);
-    if (!by_wave) {
+    if (!wave) {
       if (lane == 0) s_red[w] = acc;
       __syncthreads();
       acc = 0.0;
@@ -556,6 +563,25 @@ __global__ __launch_bounds__(kDB) void k_est_objects(EstArgs e, int d) {
         hi[k] = fmax(hi[k], (double)D.box[3 + k]);
       }
     }
+  };
+  if (by_wave) {
+    for (int64_t m = (int64_t)blockIdx.x * kDWaves + w; m < nm; m += (int64_t)gridDim.x * kDWaves) {
+      const MeshDesc D = md[m];
+      int at = kEstList;
+      if (D.n_tris > kEstBig) {
+        if (lane == 0) at = atomicAdd(&s_nbig, 1);
+        at = __shfl(at, 0);
+      }
+      if (at < kEstList) {
+        if (lane == 0) s_big[at] = m;
+      } else {
+        object(m, D, true);
+      }
+    }
+    __syncthreads();
+    for (int k = 0; k < min(s_nbig, kEstList); ++k) object(s_big[k], md[s_big[k]], false);
+  } else {
+    for (int64_t m = blockIdx.x; m < nm; m += gridDim.x) object(m, md[m], false);
   }
   if (lane == 0)
     for (int k = 0; k < 3; ++k) { s_ext[k][w] = lo[k]; s_ext[3 + k][w] = hi[k]; }
