@@ -148,7 +148,12 @@ def auto_cells(A: MeshBlob, B: MeshBlob, per_side: float = 4.0, max_cells: int =
         return 1
     side = v[1] / (3.0 * v[0])
     extent = max(h - l for l, h in zip(v[2:5], v[5:8]))
-    return int(min(max_cells, max(1, np.floor(extent / max(per_side * side, 1e-30)))))
+    x = extent / max(per_side * side, 1e-30)
+    if x < max_cells + 1 and abs(x - round(x)) <= 1e-8 * x:
+        # next to a whole number the order of the sum decides: the host's, so that the cells do not depend on the device's
+        h = b[ok[:, 0]].cpu().numpy()
+        x = extent / max(per_side * float((h[:, 3:] - h[:, :3]).mean()), 1e-30)
+    return int(min(max_cells, max(1, np.floor(x))))
 
 
 def join_dataset(A: MeshBlob, B: MeshBlob, DA: DatasetBlob, DB: DatasetBlob, groups_a: int, groups_b: int,
