@@ -222,6 +222,15 @@ __host__ __device__ __forceinline__ int cell_bits(int64_t n) {
 
 __device__ __forceinline__ int32_t div_up(int64_t n, int d) { return (int32_t)((n + d - 1) / d); }
 
+// Grids of one block a table entry: a launch takes less than 2^32 threads a
+// dimension, which 8.4 M meshes of a chunk each exceed, so the blocks are
+// numbered over two.
+constexpr int64_t kGridX = 1 << 22;
+__device__ __forceinline__ int32_t block_id() { return (int32_t)(blockIdx.y * gridDim.x + blockIdx.x); }
+inline dim3 grid_of(int64_t n) {
+  return n <= kGridX ? dim3((unsigned)n) : dim3((unsigned)kGridX, (unsigned)((n + kGridX - 1) / kGridX));
+}
+
 // One block: the exclusive sums over the meshes of every table's entries, two
 // 32-bit sums to a word (every total is below 2^31).  One mesh a thread and
 // rolled loops: a lone block runs each instruction once, so its time is the
@@ -362,11 +371,12 @@ __device__ __forceinline__ int bit_hi(float x) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_prep(BuildArgs a) {
+  const int32_t block = block_id();
   __shared__ int s_lo[kBlock / 64], s_hi[kBlock / 64];
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
-  const int32_t m = a.tmap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[block];
   const MeshPlan p = a.plan[m];
-  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  const int32_t c0 = (block - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
   int elo = INT_MAX, ehi = INT_MIN;  // bit exponents over this thread's coordinates
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   bool unsafe = false;
@@ -522,12 +532,13 @@ __device__ __forceinline__ void face_codes(const BuildArgs& a, const MeshPlan& p
 
 // The codes of meshes that are sorted in one cell.
 __global__ __launch_bounds__(kBlock) void k_codes(BuildArgs a) {
+  const int32_t block = block_id();
   if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
-  const int32_t m = a.tmap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[block];
   const MeshPlan p = a.plan[m];
   if (cell_bits(3 * (int64_t)p.n) != 0) return;
-  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  const int32_t c0 = (block - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
   float box[6];
   for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
   for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
@@ -634,13 +645,14 @@ __device__ __forceinline__ uint32_t ecell_start(const BuildArgs& a, const MeshPl
 
 // Meshes of several cells: items to their cells.
 __global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
+  const int32_t block = block_id();
   if (*a.status != INT_MAX) return;
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
-  const int32_t m = a.tmap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[block];
   const MeshPlan p = a.plan[m];
   const int tb = cell_bits(p.n), eb = cell_bits(3 * (int64_t)p.n);
   if (tb == 0 && eb == 0) return;
-  const int32_t c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  const int32_t c0 = (block - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
   const uint32_t t0 = a.start[p.tcell];
   for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
     const int64_t f = (int64_t)p.f0 + i;
@@ -884,14 +896,15 @@ __device__ __forceinline__ uint32_t place_bin(const uint32_t* start, int bits, i
 }
 
 __global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
+  const int32_t block = block_id();
   __shared__ SortLds<false> s;
   __shared__ int32_t s_range[2];
   if (*a.status != INT_MAX) return;
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tunit) return;
-  const int32_t m = a.tumap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].tunit) return;
+  const int32_t m = a.tumap[block];
   const MeshPlan p = a.plan[m];
   const int bits = cell_bits(p.n);
-  unit_range(a.start + p.tcell, bits, p.n, (int32_t)blockIdx.x - p.tunit, s_range);
+  unit_range(a.start + p.tcell, bits, p.n, block - p.tunit, s_range);
   const int32_t b = s_range[0], n = s_range[1] - b;
   if (n <= 0) return;
   uint2* const cells = a.tcells + p.f0 + b;
@@ -920,15 +933,16 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
 }
 
 __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
+  const int32_t block = block_id();
   __shared__ SortLds<true> s;
   __shared__ int32_t s_range[2];
   if (*a.status != INT_MAX) return;
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].eunit) return;
-  const int32_t m = a.emap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].eunit) return;
+  const int32_t m = a.emap[block];
   const MeshPlan p = a.plan[m];
   const int32_t n3 = 3 * p.n;
   const int bits = cell_bits(n3);
-  unit_range(a.start + a.cells_t + p.ecell, bits, n3, (int32_t)blockIdx.x - p.eunit, s_range);
+  unit_range(a.start + a.cells_t + p.ecell, bits, n3, block - p.eunit, s_range);
   const int32_t b = s_range[0], n = s_range[1] - b;
   const int64_t g0 = 3 * (int64_t)p.f0 + b;
   int32_t kept = 0;
@@ -954,8 +968,8 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
   else if (n > 0)
     kept = lds_sort<true, false>(s, n, item, bin, store);
   if (threadIdx.x == 0) {
-    a.ustart[blockIdx.x] = b;
-    a.ucount[blockIdx.x] = kept;
+    a.ustart[block] = b;
+    a.ucount[block] = kept;
   }
 }
 
@@ -1070,13 +1084,14 @@ __device__ __forceinline__ void put_node(const BuildArgs& a, const MeshPlan& p, 
 // block a mesh climbing in memory 11.1 ms, chunks with a search for each
 // node's range and triangles written by their own lanes 4.6 ms, this 3.4 ms.
 __global__ __launch_bounds__(kTreeBlock) void k_tree(BuildArgs a) {
+  const int32_t block = block_id();
   static_assert(kTreeBlock == kTreeChunk, "one position a thread");
   __shared__ ClimbLds<kTreeChunk> s;
   if (*a.status != INT_MAX) return;
-  if ((int32_t)blockIdx.x >= a.plan[a.n_meshes].tchunk) return;
-  const int32_t m = a.tmap[blockIdx.x];
+  if (block >= a.plan[a.n_meshes].tchunk) return;
+  const int32_t m = a.tmap[block];
   const MeshPlan p = a.plan[m];
-  const int32_t n = p.n, c0 = ((int32_t)blockIdx.x - p.tchunk) * kTreeChunk, nu = min(n - c0, kTreeChunk);
+  const int32_t n = p.n, c0 = (block - p.tchunk) * kTreeChunk, nu = min(n - c0, kTreeChunk);
   const uint32_t* keys = a.sk + p.f0;
   const int t = threadIdx.x;
   float b[6];
@@ -1114,7 +1129,7 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree(BuildArgs a) {
       put_node(a, p, c0 + lo, c0 + split, c0 + hi, left, lb, rb);
     });
   if (n <= kTreeChunk) return;
-  const int32_t rc = p.rchunk + (int32_t)blockIdx.x - p.tchunk;  // the chunk's root list
+  const int32_t rc = p.rchunk + block - p.tchunk;  // the chunk's root list
   RootRec* out = a.roots + (int64_t)rc * kMaxRoots;
   const int32_t nr = leftover<kTreeChunk, kTreeBlock>(s, nu, [&](int32_t k, int, int hi, const float* x) {
     RootRec r;
@@ -1932,17 +1947,17 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, a);
   if (F > 0) {
     hipLaunchKernelGGL(k_maps, dim3(gMw), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_prep, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_prep, grid_of(tc), dim3(kBlock), 0, s, a);
   }
   if (M > 0) PR_W(k_desc, gM, kBlock);
   if (F > 0) {
-    hipLaunchKernelGGL(k_codes, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_codes, grid_of(tc), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_codes_cells, dim3((unsigned)code_chunks(F)), dim3(1024), 0, s, a);
     PR_HIP(device_exclusive_scan((const uint32_t*)a.hist, a.start, a.cells_all, a.tsum, (int64_t*)nullptr, s));
-    hipLaunchKernelGGL(k_to_cells, dim3((unsigned)tc), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_tris, dim3((unsigned)tu), dim3(kLdsBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_edges, dim3((unsigned)eu), dim3(kLdsBlock), 0, s, a);
-    hipLaunchKernelGGL(k_tree, dim3((unsigned)tc), dim3(kTreeBlock), 0, s, a);
+    hipLaunchKernelGGL(k_to_cells, grid_of(tc), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_tris, grid_of(tu), dim3(kLdsBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_edges, grid_of(eu), dim3(kLdsBlock), 0, s, a);
+    hipLaunchKernelGGL(k_tree, grid_of(tc), dim3(kTreeBlock), 0, s, a);
     const int tops = (int)(M < kTops ? M : kTops);
     hipLaunchKernelGGL(k_tree_top, dim3(tops), dim3(kTopUnits), 0, s, a);
     PR_W(k_collapse_top, tops, kBlock);

@@ -90,3 +90,25 @@ def test_build_on_another_stream_is_waited_for(check):
             assert g.exp_range() == (0, 3) and g.status() == -1
             b = pa.MeshBlob.build(bad, stream=s, check_status=False)
             assert b.status() == 77
+
+
+def test_more_meshes_than_one_grid_dimension_takes():
+    """2^23 + 5 meshes of one triangle: a block each of 512 threads is beyond 2^32 threads."""
+    import torch
+    import paper_2609_24513_amd as pa
+    from paper_2609_24513_amd import synth
+    M = (1 << 23) + 5
+    g = torch.Generator(device="cuda").manual_seed(1)
+    v = torch.rand(M, 3, 3, generator=g, device="cuda")
+    f = torch.arange(3, dtype=torch.int32, device="cuda").expand(M, 3).contiguous()
+    off = torch.arange(M + 1, device="cuda")
+    blob = pa.MeshBlob.build(synth.MeshSet(v.reshape(-1, 3), f, 3 * off, off), width=8, leaf_size=1)
+    want = torch.cat([v.amin(dim=1), v.amax(dim=1)], dim=1)
+    assert torch.equal(blob.boxes(), want)
+    assert bool((blob.edge_counts() == 3).all())
+    # the last meshes meet themselves and their neighbours as the first do
+    k = 600
+    pairs = torch.cat([torch.arange(k), torch.arange(M - k, M)]).int()[:, None].expand(-1, 2).cuda()
+    flags, _, status = pa.refine(blob, blob, pairs)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and bool(flags.bool().all())
