@@ -164,6 +164,7 @@ struct BuildArgs {
   int32_t* status;       // min bad face (INT_MAX if none)
   int32_t* exps;         // [2] lowest, highest coordinate bit exponent
   int32_t* ctr;          // [0] meshes in `big`, [1] entries of `subs`
+  uint64_t* psum;        // [kPlanBlocks][4] entries of each plan block's meshes
   MeshPlan* plan;        // [M + 1], totals at [M]
   uint32_t* mm;          // [M][8] ordered box bits (lo xyz, hi xyz), [6] != 0: a coordinate out of the safe range
   int32_t* used;         // [M] node slots in use
@@ -231,44 +232,85 @@ inline dim3 grid_of(int64_t n) {
   return n <= kGridX ? dim3((unsigned)n) : dim3((unsigned)kGridX, (unsigned)((n + kGridX - 1) / kGridX));
 }
 
-// One block: the exclusive sums over the meshes of every table's entries, two
-// 32-bit sums to a word (every total is below 2^31).  One mesh a thread and
-// rolled loops: a lone block runs each instruction once, so its time is the
-// fetch of its code (unrolled over four meshes a thread 37 us for 173 meshes).
-__global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
+// Entries of mesh m (in: there is one) in every table, two 32-bit numbers to a
+// word (every total is below 2^31); false when its offsets are inconsistent.
+__device__ __forceinline__ bool plan_entries(const BuildArgs& a, int64_t m, bool in, MeshPlan& p, uint64_t* c) {
+  p = MeshPlan{};
+  bool ok = true;
+  if (in) {
+    const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1], v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
+    ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
+    if (m == 0) ok = ok && f0 == 0 && v0 == 0;
+    if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
+    if (ok) {
+      p.v0 = v0;
+      p.nv = (int32_t)(v1 - v0);
+      p.f0 = (int32_t)f0;
+      p.n = (int32_t)(f1 - f0);
+    }
+  }
+  const uint32_t w1 = (uint32_t)a.width - 1u, l1 = (uint32_t)a.leaf + 1u;
+  const uint32_t n = (uint32_t)p.n, chunks = (n + kTreeChunk - 1) / kTreeChunk;
+  const uint32_t nodes = n == 0 ? 0u : (n <= (uint32_t)a.leaf ? 1u : (n - 1) / w1 + n / l1 + 2u);  // nodes_bound
+  auto two = [](uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; };
+  c[0] = two(chunks, (n + kUnit - 1) / kUnit);
+  c[1] = two((3 * n + kUnit - 1) / kUnit, n > (uint32_t)kTreeChunk ? chunks : 0u);
+  c[2] = in ? two(1u << cell_bits(n), 1u << cell_bits(3 * (int64_t)n)) : 0ull;
+  c[3] = two(cell_bits(3 * (int64_t)n) ? (n + kCodeChunk - 1) / kCodeChunk : 0u, nodes);
+  return ok;
+}
+
+// The plan of many meshes is made by several blocks, `span` meshes each (a
+// multiple of 1,024), after k_plan_sums has summed every block's entries (one
+// block for 1 M meshes 5.1 ms).
+constexpr int64_t kPlanOne = 2048;  // meshes that one block plans alone, at most
+constexpr int64_t kPlanBlocks = 512;
+
+__global__ __launch_bounds__(1024) void k_plan_sums(BuildArgs a, int64_t span) {
+  __shared__ int64_t s[16];
+  int64_t sum[4] = {0, 0, 0, 0};
+  bool bad = false;
+  const int64_t m0 = blockIdx.x * span, m1 = m0 + span < a.n_meshes ? m0 + span : a.n_meshes;
+#pragma unroll 1
+  for (int64_t m = m0 + threadIdx.x; m < m1; m += 1024) {
+    MeshPlan p;
+    uint64_t c[4];
+    bad |= !plan_entries(a, m, true, p, c);
+    for (int q = 0; q < 4; ++q) sum[q] += (int64_t)c[q];
+  }
+  for (int q = 0; q < 4; ++q) {
+    const int64_t t = block_sum<1024>(sum[q], s);
+    if (threadIdx.x == 0) a.psum[4 * blockIdx.x + q] = (uint64_t)t;
+  }
+  if (bad) *a.status = 0;
+}
+
+// The exclusive sums over the meshes of every table's entries.  One mesh a
+// thread and rolled loops: a lone block runs each instruction once, so its time
+// is the fetch of its code (unrolled over four meshes a thread 37 us for 173
+// meshes).
+__global__ __launch_bounds__(1024) void k_plan(BuildArgs a, int64_t span) {
   __shared__ uint64_t s_sum[4][16], s_run[4];
   __shared__ int s_bad;  // a mesh's offsets are inconsistent
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t w1 = (uint32_t)a.width - 1u, l1 = (uint32_t)a.leaf + 1u;
+  const bool last = blockIdx.x == gridDim.x - 1;
+  const int64_t m0 = blockIdx.x * span, m1 = last ? a.n_meshes : m0 + span;
   if (threadIdx.x < 4) s_run[threadIdx.x] = 0ull;
-  if (threadIdx.x == 0) s_bad = 0;
+  if (threadIdx.x == 0) s_bad = gridDim.x > 1 && *a.status != INT_MAX;
   __syncthreads();
+  if (blockIdx.x > 0 && threadIdx.x < 4) {
+    uint64_t run = 0;
+#pragma unroll 8
+    for (uint32_t b = 0; b < blockIdx.x; ++b) run += a.psum[4 * b + threadIdx.x];
+    s_run[threadIdx.x] = run;
+  }
 #pragma unroll 1
-  for (int64_t base = 0; base < a.n_meshes; base += 1024) {
+  for (int64_t base = m0; base < m1; base += 1024) {
     const int64_t m = base + threadIdx.x;
-    const bool in = m < a.n_meshes;
-    MeshPlan p{};
-    if (in) {
-      const int64_t f0 = a.face_off[m], f1 = a.face_off[m + 1], v0 = a.vert_off[m], v1 = a.vert_off[m + 1];
-      bool ok = f0 >= 0 && f1 >= f0 && f1 <= a.f_total && v0 >= 0 && v1 >= v0 && v1 <= a.v_total;
-      if (m == 0) ok = ok && f0 == 0 && v0 == 0;
-      if (m == a.n_meshes - 1) ok = ok && f1 == a.f_total && v1 == a.v_total;
-      if (!ok) {
-        s_bad = 1;
-      } else {
-        p.v0 = v0;
-        p.nv = (int32_t)(v1 - v0);
-        p.f0 = (int32_t)f0;
-        p.n = (int32_t)(f1 - f0);
-      }
-    }
-    const uint32_t n = (uint32_t)p.n, chunks = (n + kTreeChunk - 1) / kTreeChunk;
-    const uint32_t nodes = n == 0 ? 0u : (n <= (uint32_t)a.leaf ? 1u : (n - 1) / w1 + n / l1 + 2u);  // nodes_bound
-    auto two = [](uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; };
-    uint64_t c[4] = {two(chunks, (n + kUnit - 1) / kUnit),
-                     two((3 * n + kUnit - 1) / kUnit, n > (uint32_t)kTreeChunk ? chunks : 0u),
-                     in ? two(1u << cell_bits(n), 1u << cell_bits(3 * (int64_t)n)) : 0ull,
-                     two(cell_bits(3 * (int64_t)n) ? (n + kCodeChunk - 1) / kCodeChunk : 0u, nodes)};
+    const bool in = m < m1;
+    MeshPlan p;
+    uint64_t c[4];
+    if (!plan_entries(a, m, in, p, c)) s_bad = 1;
     uint64_t inc[4] = {c[0], c[1], c[2], c[3]};
 #pragma unroll 1
     for (int o = 1; o < 64; o <<= 1) {
@@ -309,7 +351,7 @@ __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
     __syncthreads();  // s_sum is written again
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (last && threadIdx.x == 0) {
     MeshPlan t{};
     t.tchunk = (int32_t)(s_run[0] >> 32);
     t.tunit = (int32_t)(uint32_t)s_run[0];
@@ -325,7 +367,7 @@ __global__ __launch_bounds__(1024) void k_plan(BuildArgs a) {
   if (threadIdx.x == 0) *a.status = 0;
   __syncthreads();  // the totals are written
 #pragma unroll 1
-  for (int64_t m = threadIdx.x; m <= a.n_meshes; m += 1024) a.plan[m] = MeshPlan{};
+  for (int64_t m = m0 + threadIdx.x; m < (last ? m1 + 1 : m1); m += 1024) a.plan[m] = MeshPlan{};
 }
 
 // Everything that starts at a fixed value.
@@ -824,6 +866,36 @@ __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, S
   return kept;
 }
 
+// The same for n <= 64 items, by one wave: each lane compares its item with all
+// of them (a block's bins and barriers were 3.8 and 4.5 of 21 ms for a million
+// meshes of one triangle; the other waves leave at once: 1.4 and 1.8 ms).
+template <bool UNIQUE, typename Load, typename Store>
+__device__ __forceinline__ int32_t wave_sort(int32_t n, Load load, Store store) {
+  const int lane = threadIdx.x & 63;
+  Item e{0, 0, 0};
+  if (lane < n) e = load(lane);
+  int32_t less = 0;  // items before this lane's, copies among them
+  bool copy = false;
+#pragma unroll 1
+  for (int j = 0; j < n; ++j) {
+    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)e.k, j), x = (uint32_t)__builtin_amdgcn_readlane((int)e.x, j);
+    const uint32_t y = UNIQUE ? (uint32_t)__builtin_amdgcn_readlane((int)e.y, j) : 0u;
+    const bool same = k == e.k && x == e.x;
+    less += k < e.k || (k == e.k && x < e.x) || (UNIQUE && same && y < e.y) ? 1 : 0;
+    if (UNIQUE) copy |= same && y == e.y && j < lane;
+  }
+  if (!UNIQUE) {
+    if (lane < n) store(less, e);
+    return n;
+  }
+  // the places of the items that are kept, as a mask
+  const bool keep = lane < n && !copy;
+  uint64_t places = keep ? 1ull << less : 0ull;
+  for (int o = 32; o > 0; o >>= 1) places |= __shfl_xor(places, o);
+  if (keep) store(__popcll(places & ((1ull << less) - 1ull)), e);
+  return __popcll(places);
+}
+
 // A range of more items than LDS holds (one cell of a mesh whose detail is
 // packed into a small part of its box): split by one bit of (k, x, y) at a time, highest
 // first, until the parts fit; the order of the parts is the order of the
@@ -904,6 +976,13 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
   const int32_t m = a.tumap[block];
   const MeshPlan p = a.plan[m];
   const int bits = cell_bits(p.n);
+  if (p.n <= 64) {
+    if (threadIdx.x < 64)
+      wave_sort<false>(
+          p.n, [&](int32_t i) { return Item{a.key[p.f0 + i], (uint32_t)(p.f0 + i), 0u}; },
+          [&](int32_t i, const Item& e) { a.sk[p.f0 + i] = e.k; a.sv[p.f0 + i] = e.x; });
+    return;
+  }
   unit_range(a.start + p.tcell, bits, p.n, block - p.tunit, s_range);
   const int32_t b = s_range[0], n = s_range[1] - b;
   if (n <= 0) return;
@@ -942,6 +1021,25 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
   const MeshPlan p = a.plan[m];
   const int32_t n3 = 3 * p.n;
   const int bits = cell_bits(n3);
+  // half-edge i of the mesh, in the faces' order
+  auto face_item = [&](int32_t i) {
+    const int64_t f = (int64_t)p.f0 + i / 3;
+    const int k = i % 3;
+    const uint32_t u = (uint32_t)a.faces[3 * f + k], v = (uint32_t)a.faces[3 * f + (k == 2 ? 0 : k + 1)];
+    return Item{a.ekey[3 * (int64_t)p.f0 + i], u < v ? u : v, u < v ? v : u};
+  };
+  if (n3 <= 64) {
+    if (threadIdx.x >= 64) return;
+    const int32_t kept = wave_sort<true>(n3, face_item, [&](int32_t i, const Item& e) {
+      a.ul[3 * (int64_t)p.f0 + i] = e.x;
+      a.uh[3 * (int64_t)p.f0 + i] = e.y;
+    });
+    if (threadIdx.x == 0) {
+      a.ustart[block] = 0;
+      a.ucount[block] = kept;
+    }
+    return;
+  }
   unit_range(a.start + a.cells_t + p.ecell, bits, n3, block - p.eunit, s_range);
   const int32_t b = s_range[0], n = s_range[1] - b;
   const int64_t g0 = 3 * (int64_t)p.f0 + b;
@@ -951,13 +1049,7 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
     a.uh[g0 + i] = e.y;
   };
   auto cell_item = [&](int32_t i) { return a.ecells[g0 + i]; };
-  auto item = [&](int32_t i) {
-    if (bits != 0) return cell_item(i);
-    const int64_t f = (int64_t)p.f0 + i / 3;
-    const int k = i % 3;
-    const uint32_t u = (uint32_t)a.faces[3 * f + k], v = (uint32_t)a.faces[3 * f + (k == 2 ? 0 : k + 1)];
-    return Item{a.ekey[g0 + i], u < v ? u : v, u < v ? v : u};
-  };
+  auto item = [&](int32_t i) { return bits != 0 ? cell_item(i) : face_item(i); };
   auto bin = [&](const Item& e) { return place_bin(a.start + a.cells_t + p.ecell, bits, n3, b, e.k); };
   if (n > kUnitCap)
     kept = split_sort<true>(
@@ -1817,6 +1909,7 @@ void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
   a.status = cv.take<int32_t>(4);
   a.exps = cv.take<int32_t>(4);
   a.ctr = cv.take<int32_t>(4);
+  a.psum = cv.take<uint64_t>(M > kPlanOne ? 4 * kPlanBlocks : 0);
   a.plan = cv.take<MeshPlan>(M + 1);
   a.mm = cv.take<uint32_t>(8 * M);
   a.used = cv.take<int32_t>(M);
@@ -1944,7 +2037,13 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
     else hipLaunchKernelGGL(kernel<8>, dim3(grid), dim3(block), 0, s, a);                        \
   } while (0)
   hipLaunchKernelGGL(k_build_init, dim3(gI), dim3(kBlock), 0, s, a);
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, a);
+  int64_t span = M, plans = 1;
+  if (M > kPlanOne) {
+    span = ((M + kPlanBlocks - 1) / kPlanBlocks + 1023) / 1024 * 1024;
+    plans = (M + span - 1) / span;
+    hipLaunchKernelGGL(k_plan_sums, dim3((unsigned)plans), dim3(1024), 0, s, a, span);
+  }
+  hipLaunchKernelGGL(k_plan, dim3((unsigned)plans), dim3(1024), 0, s, a, span);
   if (F > 0) {
     hipLaunchKernelGGL(k_maps, dim3(gMw), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_prep, grid_of(tc), dim3(kBlock), 0, s, a);

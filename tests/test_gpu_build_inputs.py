@@ -112,3 +112,16 @@ def test_more_meshes_than_one_grid_dimension_takes():
     flags, _, status = pa.refine(blob, blob, pairs)
     torch.cuda.synchronize()
     assert int(status.item()) == 0 and bool(flags.bool().all())
+
+
+@pytest.mark.parametrize("at", [0, 1500, 2600, 4999])
+def test_bad_offsets_among_many_meshes(at):
+    v, f = _faces(10_000)
+    fo, vo = 2 * np.arange(5001, dtype=np.int64), np.full(5001, v.shape[0], np.int64)
+    vo[0] = 0
+    f = f % 3  # every mesh after the first has no vertices of its own, so its faces are bad too
+    ok_status, clean = _build(v, f, vo, fo)
+    assert clean and ok_status == 2
+    fo[at + 1 if at < 4999 else at] = 3 if at else 9_000
+    status, clean = _build(v, f, vo, fo)
+    assert clean and status == 0
