@@ -50,7 +50,15 @@ constexpr int kLdsCells = 1 << 14; // cells counted in LDS
 constexpr int kUnit = 1280;        // sort unit: the cells that start in this many items (2 x 106 M half-edges: 1,024 3.2, this 3.0 ms)
 constexpr int kUnitCap = 2048;     // items a unit may hold to be sorted in LDS
 constexpr int kBins = 2048;        // bins of the LDS sort
-constexpr int kLdsBlock = 512;     // threads of a sort block (the same: 256 3.0, this 2.74, 1,024 5.5 ms)
+constexpr int kBinMax = 128;       // items of a bin that are placed by comparing them with each other
+constexpr int kSplitBits = 14;     // bins of one split of an overfull cell, at most (as a power of two)
+constexpr int kSplitBlock = 1024;
+// Sort units that one launch takes, triangles' and half-edges': fewer than the
+// chip holds twice over are bound by launches (2 x 173 meshes of 320 faces: a
+// launch less is 2 % of build and join); a build of 2 x 35 M triangles takes 3.0
+// ms in two launches and 3.5 in one.
+constexpr int64_t kSortOne = 2048;
+constexpr int kLdsBlock = 512;     // threads of a sort block (the same sort, at 79 registers: 256 3.0, this 2.74, 1,024 5.5 ms)
 constexpr int kTreeBlock = 512;    // threads of a tree block, one position each
 constexpr int kMaxRoots = 128;     // subtrees that tile a chunk: at most two per tree level (62 levels)
 constexpr int kTopUnits = 512;     // subtrees of chunks that one pass of a top block joins
@@ -79,6 +87,10 @@ __device__ __forceinline__ uint32_t quant10(float c, float lo, float hi) {
 __device__ __forceinline__ uint32_t morton3(f3 c, const float* box) {
   return (spread10(quant10(c.x, box[0], box[3])) << 2) | (spread10(quant10(c.y, box[1], box[4])) << 1) |
          spread10(quant10(c.z, box[2], box[5]));
+}
+
+__device__ __forceinline__ int lanes_before(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 __device__ __forceinline__ bool safe_coord(float c) {
@@ -163,7 +175,7 @@ struct BuildArgs {
   // workspace
   int32_t* status;       // min bad face (INT_MAX if none)
   int32_t* exps;         // [2] lowest, highest coordinate bit exponent
-  int32_t* ctr;          // [0] meshes in `big`, [1] entries of `subs`
+  int32_t* ctr;          // [0] meshes in `big`, [1] entries of `subs`, [2] of `over`, [3] of `packed`
   uint64_t* psum;        // [kPlanBlocks][4] entries of each plan block's meshes
   MeshPlan* plan;        // [M + 1], totals at [M]
   uint32_t* mm;          // [M][8] ordered box bits (lo xyz, hi xyz), [6] != 0: a coordinate out of the safe range
@@ -191,6 +203,12 @@ struct BuildArgs {
   Item* ecells;          // [3F] (code, lower, higher vertex id) in cell order
   uint32_t* ul;          // [3F] unique edges of each unit, at its first item
   uint32_t* uh;
+  int2* over;            // cells of more than kUnitCap items: mesh, cell (half-edges: the sign bit set)
+  int32_t* packed;       // sort units for k_sort_packed (half-edges: the sign bit set)
+  int32_t* tfirst;       // [tunit] of an overfull cell's parts that start in a unit the first start, the last
+  int32_t* tlast;
+  int32_t* efirst;       // [eunit]
+  int32_t* elast;
   int32_t* ustart;       // [eunit] first item of each unit (from the mesh's first)
   int32_t* ucount;       // [eunit] unique edges of each unit
   int32_t* uoff;         // [eunit] unique edges of the mesh before the unit
@@ -382,6 +400,8 @@ __global__ void k_build_init(BuildArgs a) {
     a.exps[1] = INT_MIN;
     a.ctr[0] = 0;
     a.ctr[1] = 0;
+    a.ctr[2] = 0;
+    a.ctr[3] = 0;
   }
 }
 
@@ -392,8 +412,16 @@ __global__ __launch_bounds__(kBlock) void k_maps(BuildArgs a) {
   for (int64_t m = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6; m < a.n_meshes; m += nw) {
     const MeshPlan p = a.plan[m], q = a.plan[m + 1];
     for (int32_t i = p.tchunk + lane; i < q.tchunk; i += 64) a.tmap[i] = (int32_t)m;
-    for (int32_t i = p.tunit + lane; i < q.tunit; i += 64) a.tumap[i] = (int32_t)m;
-    for (int32_t i = p.eunit + lane; i < q.eunit; i += 64) a.emap[i] = (int32_t)m;
+    for (int32_t i = p.tunit + lane; i < q.tunit; i += 64) {
+      a.tumap[i] = (int32_t)m;
+      a.tfirst[i] = INT_MAX;
+      a.tlast[i] = -1;
+    }
+    for (int32_t i = p.eunit + lane; i < q.eunit; i += 64) {
+      a.emap[i] = (int32_t)m;
+      a.efirst[i] = INT_MAX;
+      a.elast[i] = -1;
+    }
     for (int32_t i = p.cchunk + lane; i < q.cchunk; i += 64) a.cmap[i] = (int32_t)m;
   }
 }
@@ -572,33 +600,14 @@ __device__ __forceinline__ void face_codes(const BuildArgs& a, const MeshPlan& p
   }
 }
 
-// The codes of meshes that are sorted in one cell.
-__global__ __launch_bounds__(kBlock) void k_codes(BuildArgs a) {
-  const int32_t block = block_id();
-  if (*a.status != INT_MAX) return;  // invalid input: the blob is not built
-  if (block >= a.plan[a.n_meshes].tchunk) return;
-  const int32_t m = a.tmap[block];
-  const MeshPlan p = a.plan[m];
-  if (cell_bits(3 * (int64_t)p.n) != 0) return;
-  const int32_t c0 = (block - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
-  float box[6];
-  for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
-  for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
-    const int64_t f = (int64_t)p.f0 + i;
-    uint32_t key[4];
-    face_codes(a, p, box, f, key);
-    a.key[f] = key[0];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) a.ekey[3 * f + k] = key[1 + k];
-  }
-}
-
-// The codes of the other meshes, and each item's place within its cell.  A
+// The codes of meshes of several cells, and each item's place within its cell.  A
 // block counts its kCodeChunk faces in LDS, and the first item of each cell
 // fetches the cell's places for all of the block's: atomics in memory run at
 // some 50 per ns over the chip (one for each run of equal cells in a wave
 // took 0.43 ms for 5.5 M faces).  A mesh of more than kLdsCells cells takes
-// them in memory one by one.
+// them in memory one by one, or a wave's at once if they are of one cell
+// (atomics on one address take some 9 ns each: the 4 M of a mesh of 1 M faces
+// that lie in one cell 35 ms, so 0.7).
 __global__ __launch_bounds__(1024) void k_codes_cells(BuildArgs a) {
   constexpr int R = kCodeChunk / 1024;
   __shared__ uint32_t s_cnt[kLdsCells];
@@ -639,7 +648,17 @@ __global__ __launch_bounds__(1024) void k_codes_cells(BuildArgs a) {
 #pragma unroll
       for (int k = 0; k < nk; ++k) {
         const uint32_t cell = key[r][k0 + k] >> (kMortonBits - bits);
-        rank[r][k] = lds ? atomicAdd(&s_cnt[cell], 1u) : atomicAdd(hist + cell, 1u);
+        if (lds) {
+          rank[r][k] = atomicAdd(&s_cnt[cell], 1u);
+        } else if (__ballot(cell != (uint32_t)__builtin_amdgcn_readfirstlane((int)cell)) == 0ull) {
+          const uint64_t all = __ballot(true);
+          const int before = lanes_before(all);
+          uint32_t base = 0;
+          if (before == 0) base = atomicAdd(hist + cell, (uint32_t)__popcll(all));
+          rank[r][k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + (uint32_t)before;
+        } else {
+          rank[r][k] = atomicAdd(hist + cell, 1u);
+        }
       }
     }
     if (lds) {
@@ -685,7 +704,9 @@ __device__ __forceinline__ uint32_t ecell_start(const BuildArgs& a, const MeshPl
   return a.start[a.cells_t + p.ecell + c] - a.start[a.cells_t + p.ecell];
 }
 
-// Meshes of several cells: items to their cells.
+// Meshes of several cells: items to their cells.  A cell of more than kUnitCap
+// items is listed by the one that takes place kUnitCap in it.  Meshes that are
+// sorted in one cell: the codes.
 __global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
   const int32_t block = block_id();
   if (*a.status != INT_MAX) return;
@@ -693,32 +714,48 @@ __global__ __launch_bounds__(kBlock) void k_to_cells(BuildArgs a) {
   const int32_t m = a.tmap[block];
   const MeshPlan p = a.plan[m];
   const int tb = cell_bits(p.n), eb = cell_bits(3 * (int64_t)p.n);
-  if (tb == 0 && eb == 0) return;
   const int32_t c0 = (block - p.tchunk) * kTreeChunk, c1 = min(p.n, c0 + kTreeChunk);
+  if (eb == 0) {
+    float box[6];
+    for (int k = 0; k < 6; ++k) box[k] = a.mesh[m].box[k];
+    for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
+      const int64_t f = (int64_t)p.f0 + i;
+      uint32_t key[4];
+      face_codes(a, p, box, f, key);
+      a.key[f] = key[0];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) a.ekey[3 * f + k] = key[1 + k];
+    }
+    return;
+  }
   const uint32_t t0 = a.start[p.tcell];
   for (int32_t i = c0 + (int32_t)threadIdx.x; i < c1; i += kBlock) {
     const int64_t f = (int64_t)p.f0 + i;
     if (tb) {
       const uint32_t key = a.key[f];
-      const int64_t at = (int64_t)p.f0 + (a.start[p.tcell + (key >> (kMortonBits - tb))] - t0) + a.rank[f];
+      const uint32_t cell = key >> (kMortonBits - tb), rank = a.rank[f];
+      const int64_t at = (int64_t)p.f0 + (a.start[p.tcell + cell] - t0) + rank;
       a.tcells[at] = make_uint2(key, (uint32_t)f);
+      if (rank == (uint32_t)kUnitCap) a.over[atomicAdd(a.ctr + 2, 1)] = make_int2(m, (int)cell);
     }
     if (eb) {
       const int32_t id[3] = {a.faces[3 * f], a.faces[3 * f + 1], a.faces[3 * f + 2]};
       for (int k = 0; k < 3; ++k) {
-        const uint32_t key = a.ekey[3 * f + k];
-        const int64_t at = 3 * (int64_t)p.f0 + ecell_start(a, p, key >> (kMortonBits - eb)) + a.erank[3 * f + k];
+        const uint32_t key = a.ekey[3 * f + k], cell = key >> (kMortonBits - eb), rank = a.erank[3 * f + k];
+        const int64_t at = 3 * (int64_t)p.f0 + ecell_start(a, p, cell) + rank;
         uint32_t lo, hi;
         half_edge(id, k, lo, hi);
         a.ecells[at] = Item{key, lo, hi};
+        if (rank == (uint32_t)kUnitCap) a.over[atomicAdd(a.ctr + 2, 1)] = make_int2(m, (int)(cell | 0x80000000u));
       }
     }
   }
 }
 
 // Smallest cell start at or above `target` among the `cells` starts s (less
-// s[0]); n when there is none.  One wave, 64 probes a round.
-__device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells, int32_t target, int32_t n) {
+// s[0]); n when there is none.  Its cell goes to `at`.  One wave, 64 probes a
+// round.
+__device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells, int32_t target, int32_t n, int32_t& at) {
   const int lane = threadIdx.x & 63;
   const uint32_t s0 = s[0];
   int64_t lo = 0, hi = cells;  // the answer's cell lies in [lo, hi]
@@ -734,6 +771,7 @@ __device__ __forceinline__ int32_t first_start(const uint32_t* s, int64_t cells,
       lo += (hi - lo - 1) / step * step + 1;
     }
   }
+  at = (int32_t)hi;
   return hi < cells ? (int32_t)(s[hi] - s0) : n;
 }
 
@@ -746,21 +784,42 @@ struct SortLds {
   uint32_t keep[kUnitCap / 32];  // places of the sorted items that hold the first copy of one
   uint32_t before[kUnitCap / 32];
   uint32_t scan[kLdsBlock / 64];
-  uint32_t kmin, kmax;
+  int full;                      // a bin holds more than kBinMax items
 };
+
+// (UNIQUE) fills in the kept items before each word of `keep`; returns their number.
+__device__ __forceinline__ int32_t count_kept(SortLds<true>& s) {
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const uint32_t c = (uint32_t)__popc(s.keep[threadIdx.x]);
+    const uint32_t inc = wave_inclusive_sum(c);
+    s.before[threadIdx.x] = inc - c;
+    if (threadIdx.x == 63) s.scan[0] = inc;
+  }
+  __syncthreads();
+  return (int32_t)s.scan[0];
+}
+__device__ __forceinline__ int32_t count_kept(SortLds<false>&) { return 0; }
+
+template <bool UNIQUE>
+__device__ __forceinline__ int32_t kept_place(const SortLds<UNIQUE>& s, uint32_t place) {
+  return (int32_t)(UNIQUE ? s.before[place >> 5] + (uint32_t)__popc(s.keep[place >> 5] & ((1u << (place & 31u)) - 1u)) : place);
+}
 
 // Sorts the n <= kUnitCap items load(0) ... load(n - 1) and hands them to
 // store(place, item), equal items once when UNIQUE; returns the number kept.
-// One pass: the items go to bins monotone in their order (any order within a
-// bin), then each counts the items of its bin that come before it, few for
-// codes as even as a surface's, and looks for a copy at a lower place; 2,048
-// equal items cost 2,048 comparisons each.  bin(item) < kBins gives the bins;
-// with LINEAR they are cut evenly from the codes' range instead.  Bound by the
-// instructions of the comparing loop: the edges of 2 x 35 M triangles take
-// 2.74 ms with one loop without branches and took 5.07 ms with one for copies
-// and one for places, each with early outs.  Every thread of the block calls it.
-template <bool UNIQUE, bool LINEAR, typename Load, typename Bin, typename Store>
-__device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, Store store) {
+// One pass: the items go to bins bin(item) < kBins monotone in their order (any
+// order within a bin), then each counts the items of its bin that come before
+// it, few for codes as even as a surface's, and looks for a copy at a lower
+// place.  Returns -1 with nothing stored when a bin has more than kBinMax
+// items (k_sort_packed).  Bound by the instructions of the comparing loop: the
+// edges of 2 x 35 M triangles take 2.34 ms with one loop without branches and
+// took 5.07 ms with one for copies and one for places, each with early outs
+// (2.74 ms with the splitting of overfull units in the same kernel: 79
+// registers in place of 50).
+// Every thread of the block calls it.
+template <bool UNIQUE, typename Load, typename Bin, typename Store>
+__device__ __forceinline__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, Store store) {
   constexpr int R = kUnitCap / kLdsBlock;
   using Low = typename SortLds<UNIQUE>::Low;
   static_assert(kUnitCap / 32 == 64, "one word of `keep` a lane");
@@ -768,38 +827,16 @@ __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, S
   const int t = threadIdx.x;
   for (int i = t; i <= kBins; i += kLdsBlock) s.cnt[i] = 0u;
   if (UNIQUE && t < kUnitCap / 32) s.keep[t] = 0u;
-  if (t == 0) { s.kmin = ~0u; s.kmax = 0u; }
+  if (t == 0) s.full = 0;
   __syncthreads();
   Item it[R];
   uint32_t b[R];
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (t + r * kLdsBlock < n) it[r] = load(t + r * kLdsBlock);
-  if (LINEAR) {
-    uint32_t lo = ~0u, hi = 0u;
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (t + r * kLdsBlock < n) {
-        lo = min(lo, it[r].k);
-        hi = max(hi, it[r].k);
-      }
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
-    }
-    if ((t & 63) == 0) { atomicMin(&s.kmin, lo); atomicMax(&s.kmax, hi); }
-    __syncthreads();
-    const uint32_t k0 = s.kmin, span = s.kmax - s.kmin;
-    int sh = 0;
-    while ((span >> sh) >= (uint32_t)kBins) ++sh;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (t + r * kLdsBlock < n) b[r] = (it[r].k - k0) >> sh;
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (t + r * kLdsBlock < n) b[r] = bin(it[r]);
-  }
+  for (int r = 0; r < R; ++r)
+    if (t + r * kLdsBlock < n) b[r] = bin(it[r]);
   uint32_t rank[R];
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -813,10 +850,15 @@ __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, S
     uint32_t total;
     uint32_t o = block_exclusive_sum<kLdsBlock>(sum, s.scan, total);
 #pragma unroll
-    for (int c = 0; c < C; ++c) { s.cnt[t * C + c] = o; o += v[c]; }
+    for (int c = 0; c < C; ++c) {
+      if (v[c] > (uint32_t)kBinMax) s.full = 1;
+      s.cnt[t * C + c] = o;
+      o += v[c];
+    }
     if (t == 0) s.cnt[kBins] = total;
   }
   __syncthreads();
+  if (s.full) return -1;
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (t + r * kLdsBlock < n) {
@@ -845,23 +887,52 @@ __device__ int32_t lds_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Bin bin, S
     place[r] = j0 + less;
     if (UNIQUE) atomicOr(&s.keep[place[r] >> 5], 1u << (place[r] & 31u));
   }
-  if (UNIQUE) {
-    __syncthreads();
-    if (t < 64) {
-      const uint32_t c = (uint32_t)__popc(s.keep[t]);
-      const uint32_t inc = wave_inclusive_sum(c);
-      s.before[t] = inc - c;
-      if (t == 63) s.scan[0] = inc;
-    }
-    __syncthreads();
-  }
+  const int32_t kept = UNIQUE ? count_kept(s) : n;
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    if (place[r] != ~0u)
-      store((int32_t)(UNIQUE ? s.before[place[r] >> 5] + (uint32_t)__popc(s.keep[place[r] >> 5] & ((1u << (place[r] & 31u)) - 1u))
-                             : place[r]),
-            it[r]);
-  const int32_t kept = UNIQUE ? (int32_t)s.scan[0] : n;
+    if (place[r] != ~0u) store(kept_place(s, place[r]), it[r]);
+  return kept;
+}
+
+// The same for items whose codes are packed together, by a bitonic network.
+template <bool UNIQUE, typename Load, typename Store>
+__device__ __forceinline__ int32_t network_sort(SortLds<UNIQUE>& s, int32_t n, Load load, Store store) {
+  using Low = typename SortLds<UNIQUE>::Low;
+  const int t = threadIdx.x;
+  if (UNIQUE && t < kUnitCap / 32) s.keep[t] = 0u;
+  int size = 64;
+  while (size < n) size <<= 1;
+  for (int i = t; i < size; i += kLdsBlock) {
+    const Item e = i < n ? load(i) : Item{~0u, ~0u, ~0u};
+    s.k[i] = e.k;
+    s.low[i] = UNIQUE ? (Low)((uint64_t)e.x << 32 | e.y) : (Low)e.x;
+  }
+  for (int g = 2; g <= size; g <<= 1)
+    for (int d = g >> 1; d > 0; d >>= 1) {
+      __syncthreads();
+      for (int h = t; h < size / 2; h += kLdsBlock) {
+        const int i = 2 * h - (h & (d - 1)), j = i + d;  // h's bits above d's, one place up
+        const uint32_t ki = s.k[i], kj = s.k[j];
+        const Low li = s.low[i], lj = s.low[j];
+        const bool after = ki > kj || (ki == kj && li > lj);
+        if (after == ((i & g) == 0)) {
+          s.k[i] = kj; s.k[j] = ki;
+          s.low[i] = lj; s.low[j] = li;
+        }
+      }
+    }
+  __syncthreads();
+  auto copy = [&](int i) { return UNIQUE && i > 0 && s.k[i - 1] == s.k[i] && s.low[i - 1] == s.low[i]; };
+  if (UNIQUE) {
+    for (int i = t; i < n; i += kLdsBlock)
+      if (!copy(i)) atomicOr(&s.keep[i >> 5], 1u << (i & 31));
+  }
+  const int32_t kept = UNIQUE ? count_kept(s) : n;
+  for (int i = t; i < n; i += kLdsBlock)
+    if (!copy(i)) {
+      const uint64_t low = s.low[i];
+      store(kept_place(s, (uint32_t)i), UNIQUE ? Item{s.k[i], (uint32_t)(low >> 32), (uint32_t)low} : Item{s.k[i], (uint32_t)low, 0u});
+    }
   __syncthreads();  // s is reused by the next call
   return kept;
 }
@@ -896,64 +967,173 @@ __device__ __forceinline__ int32_t wave_sort(int32_t n, Load load, Store store) 
   return __popcll(places);
 }
 
-// A range of more items than LDS holds (one cell of a mesh whose detail is
-// packed into a small part of its box): split by one bit of (k, x, y) at a time, highest
-// first, until the parts fit; the order of the parts is the order of the
-// items.  get / put address the range's items in memory, tmp_get / tmp_put a
-// second buffer of the same size.  Returns the number kept.
-template <bool UNIQUE, typename Get, typename Put, typename TGet, typename TPut, typename Store>
-__device__ int32_t split_sort(SortLds<UNIQUE>& s, int32_t n, Get get, Put put, TGet tget, TPut tput, Store store) {
-  __shared__ int32_t st_lo[100], st_hi[100], st_bit[100];
-  __shared__ int32_t st_n, s_zero, s_one;
+// Overfull cells: a mesh whose detail is packed into a small part of its box
+// (by one far vertex) has cells of far more items than LDS sorts.  One block
+// takes such a cell and moves its items, in place, to bins of their order (up
+// to 2^kSplitBits) below the highest bit of (k, x, y) in which any two of
+// them differ, the bins of more than kUnitCap items again in turn, until every
+// part holds at most kUnitCap items or copies of one.  The units then find the
+// parts' starts as they find the cells'.  Bound by the passes of one block over
+// its cell (differing bits, counts, scatter, copy back).  Build of a surface of
+// 1 M triangles beside a triangle 3,000 times its size: 6.6 ms, of which 4.9
+// here; splitting by one bit at a time in the sorts 1,376 ms.
+template <bool EDGE>
+__device__ __forceinline__ void split_cell(const BuildArgs& a, const MeshPlan& p, uint32_t cell, uint32_t* cnt, uint32_t* s_scan,
+                           uint32_t* s_diff, int32_t* s_next) {
   const int t = threadIdx.x;
-  if (t == 0) { st_lo[0] = 0; st_hi[0] = n; st_bit[0] = kMortonBits + 63; st_n = 1; }
-  __syncthreads();
-  int32_t kept = 0;
-  while (st_n > 0) {
-    const int32_t lo = st_lo[st_n - 1], hi = st_hi[st_n - 1], bit = st_bit[st_n - 1];
+  const int32_t n = EDGE ? 3 * p.n : p.n;
+  const int64_t base = EDGE ? 3 * (int64_t)p.f0 : (int64_t)p.f0;
+  const uint32_t* start = a.start + (EDGE ? a.cells_t + p.ecell : (int64_t)p.tcell);
+  const int64_t cells = (int64_t)1 << cell_bits(n);
+  // the second buffer: arrays that are free after the scatter to cells and before the sorts
+  uint32_t* const tk = EDGE ? a.ekey + base : a.key + base;
+  uint32_t* const tx = EDGE ? a.erank + base : a.rank + base;
+  uint32_t* const ty = EDGE ? a.uh + base : nullptr;
+  int32_t* const first = EDGE ? a.efirst + p.eunit : a.tfirst + p.tunit;
+  int32_t* const last = EDGE ? a.elast + p.eunit : a.tlast + p.tunit;
+  auto get = [&](int32_t i) {
+    if (EDGE) return a.ecells[base + i];
+    const uint2 c = a.tcells[base + i];
+    return Item{c.x, c.y, 0u};
+  };
+  auto part = [&](int32_t at) {  // one starts here
+    atomicMin(first + at / kUnit, at);
+    atomicMax(last + at / kUnit, at);
+  };
+  int32_t lo = (int32_t)(start[cell] - start[0]);
+  int32_t hi = (int64_t)cell + 1 < cells ? (int32_t)(start[cell + 1] - start[0]) : n;
+  if (t == 0) *s_next = -1;
+  for (;;) {
+    if (t < 3) s_diff[t] = 0u;
     __syncthreads();
-    if (t == 0) { --st_n; s_zero = 0; s_one = 0; }
-    __syncthreads();
-    if (hi - lo <= kUnitCap || bit < 0) {
-      // (bit < 0: copies of one item)
-      const int32_t base = kept;
-      kept += lds_sort<UNIQUE, true>(
-          s, bit < 0 ? 1 : hi - lo, [&](int32_t i) { return get(lo + i); }, [](const Item&) { return 0u; },
-          [&](int32_t i, const Item& e) { store(base + i, e); });
-      continue;
+    {
+      const Item e0 = get(lo);
+      uint32_t dk = 0, dx = 0, dy = 0;
+#pragma unroll 4
+      for (int32_t i = lo + t; i < hi; i += kSplitBlock) {
+        const Item e = get(i);
+        dk |= e.k ^ e0.k;
+        dx |= e.x ^ e0.x;
+        dy |= e.y ^ e0.y;
+      }
+      if (dk) atomicOr(s_diff, dk);
+      if (dx) atomicOr(s_diff + 1, dx);
+      if (dy) atomicOr(s_diff + 2, dy);
     }
-    auto bit_of = [&](const Item& e) {
-      return bit >= 64 ? (e.k >> (bit - 64)) & 1u : (bit >= 32 ? (e.x >> (bit - 32)) & 1u : (e.y >> bit) & 1u);
-    };
-    for (int32_t i = lo + t; i < hi; i += kLdsBlock) {
-      const Item e = get(i);
-      if (bit_of(e)) tput(hi - 1 - atomicAdd(&s_one, 1), e);
-      else tput(lo + atomicAdd(&s_zero, 1), e);
+    __syncthreads();
+    const uint32_t dk = s_diff[0], dx = s_diff[1], dy = s_diff[2];
+    if ((dk | dx | dy) == 0u) {  // copies of one item
+      if (t == 0) part(lo);
+    } else {
+      const int top = dk ? 95 - __clz(dk) : (dx ? 63 - __clz(dx) : 31 - __clz(dy));
+      const int want = 31 - __clz((uint32_t)(hi - lo)) - 4;  // 16 items a bin if they are spread evenly
+      const int bits = min(top + 1, min(want, kSplitBits)), sh = top + 1 - bits;
+      auto bin = [&](const Item& e) {
+        const uint64_t kx = (uint64_t)e.k << 32 | e.x;
+        const uint64_t v = sh >= 32 ? kx >> (sh - 32) : kx << (32 - sh) | e.y >> sh;
+        return (uint32_t)v & ((1u << bits) - 1u);
+      };
+      const int per = (1 << bits) > kSplitBlock ? (1 << bits) / kSplitBlock : 1;
+      for (int i = t; i < (1 << bits); i += kSplitBlock) cnt[i] = 0u;
+      __syncthreads();
+#pragma unroll 4
+      for (int32_t i = lo + t; i < hi; i += kSplitBlock) atomicAdd(cnt + bin(get(i)), 1u);
+      __syncthreads();
+      uint32_t sum = 0, total;
+      const bool mine = t * per < (1 << bits);
+      if (mine)
+        for (int c = 0; c < per; ++c) sum += cnt[t * per + c];
+      uint32_t at = block_exclusive_sum<kSplitBlock>(sum, s_scan, total);
+      if (mine)
+        for (int c = 0; c < per; ++c) {
+          const uint32_t v = cnt[t * per + c];
+          cnt[t * per + c] = at;
+          if (v > 0u && v <= (uint32_t)kUnitCap) part(lo + (int32_t)at);
+          at += v;
+        }
+      __syncthreads();
+#pragma unroll 4
+      for (int32_t i = lo + t; i < hi; i += kSplitBlock) {
+        const Item e = get(i);
+        const int32_t to = lo + (int32_t)atomicAdd(cnt + bin(e), 1u);
+        tk[to] = e.k;
+        tx[to] = e.x;
+        if (EDGE) ty[to] = e.y;
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int32_t i = lo + t; i < hi; i += kSplitBlock) {
+        if (EDGE) a.ecells[base + i] = Item{tk[i], tx[i], ty[i]};
+        else a.tcells[base + i] = make_uint2(tk[i], tx[i]);
+      }
+      __syncthreads();
+      // the bins that are still too large, as a list through the second
+      // buffer: at a bin's first item its end and the next bin's first item
+      // (a bin's count is its end by now)
+      for (int i = t; i < (1 << bits); i += kSplitBlock) {
+        const uint32_t e = cnt[i], b = i > 0 ? cnt[i - 1] : 0u;
+        if (e - b <= (uint32_t)kUnitCap) continue;
+        tk[lo + (int32_t)b] = (uint32_t)(lo + (int32_t)e);
+        tx[lo + (int32_t)b] = (uint32_t)atomicExch(s_next, lo + (int32_t)b);
+      }
     }
     __syncthreads();
-    const int32_t mid = lo + s_zero;
-    for (int32_t i = lo + t; i < hi; i += kLdsBlock) put(i, tget(i));
-    __syncthreads();
-    if (t == 0) {
-      // the lower part comes first: it goes on top
-      if (mid < hi) { st_lo[st_n] = mid; st_hi[st_n] = hi; st_bit[st_n] = bit - 1; ++st_n; }
-      if (lo < mid) { st_lo[st_n] = lo; st_hi[st_n] = mid; st_bit[st_n] = bit - 1; ++st_n; }
-    }
-    __syncthreads();
+    lo = *s_next;
+    if (lo < 0) return;
+    hi = (int32_t)tk[lo];
+    const int32_t next = (int32_t)tx[lo];
+    __syncthreads();  // everyone has the bin
+    if (t == 0) *s_next = next;
   }
-  return kept;
 }
 
-// The item range [s, e) of unit u: the cells that start in [kUnit u, kUnit (u + 1)).
-__device__ __forceinline__ void unit_range(const uint32_t* start, int bits, int32_t n, int32_t u, int32_t* s_range) {
-  if (bits == 0) {
-    if (threadIdx.x == 0) { s_range[0] = u == 0 ? 0 : n; s_range[1] = n; }
-  } else if (threadIdx.x < 128) {
-    const int w = threadIdx.x >> 6;
-    const int32_t x = u == 0 && w == 0 ? 0 : first_start(start, (int64_t)1 << bits, kUnit * (u + w), n);
-    if ((threadIdx.x & 63) == 0) s_range[w] = x;
+__global__ __launch_bounds__(kSplitBlock) void k_split(BuildArgs a) {
+  __shared__ uint32_t s_cnt[1 << kSplitBits], s_scan[kSplitBlock / 64], s_diff[3];
+  __shared__ int32_t s_next;
+  if (*a.status != INT_MAX) return;
+  for (int32_t i = blockIdx.x; i < a.ctr[2]; i += gridDim.x) {
+    const int2 o = a.over[i];
+    if (o.y < 0) split_cell<true>(a, a.plan[o.x], (uint32_t)o.y & 0x7fffffffu, s_cnt, s_scan, s_diff, &s_next);
+    else split_cell<false>(a, a.plan[o.x], (uint32_t)o.y, s_cnt, s_scan, s_diff, &s_next);
+    __syncthreads();
+  }
+}
+
+// The items of unit u of a mesh with n: the cells, and parts of overfull cells,
+// that start in [kUnit u, kUnit (u + 1)).  All but the last of them hold less
+// than kUnit items, the last kUnitCap at most or copies of one item.
+struct UnitRange {
+  int32_t b, e;  // first item, behind the last
+  int32_t cut;   // where more than kUnitCap items are divided: the last cell or part
+  bool parts;    // of overfull cells are among them
+};
+
+__device__ __forceinline__ UnitRange unit_range(const uint32_t* start, int bits, int32_t n, int32_t u, bool over,
+                                                const int32_t* first, const int32_t* last, int32_t (*s)[3]) {
+  if (bits == 0) return UnitRange{u == 0 ? 0 : n, n, n, false};
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (w < 2) {
+    int32_t x = 0, cell = 0, part = 0;
+    if (u + w > 0) x = first_start(start, (int64_t)1 << bits, kUnit * (u + w), n, cell);
+    // the cell before that one holds the item before the target
+    if (over && cell > 0 && x - (int32_t)(start[cell - 1] - start[0]) > kUnitCap) {
+      part = 1;
+      for (int32_t v = u + w; kUnit * v < x; v += 64) {
+        const int32_t f = kUnit * (v + lane) < x ? first[v + lane] : INT_MAX;
+        const uint64_t in = __ballot(f < x);  // a later cell's part may be the first of its unit
+        if (in) {
+          x = __builtin_amdgcn_readlane(f, __builtin_ctzll(in));
+          break;
+        }
+      }
+    }
+    if (lane == 0) { s[w][0] = x; s[w][1] = cell; s[w][2] = part; }
   }
   __syncthreads();
+  UnitRange r{s[0][0], s[1][0], 0, (s[0][2] | s[1][2]) != 0};
+  r.cut = r.e;
+  if (r.e - r.b > kUnitCap) r.cut = s[1][2] ? last[u] : (int32_t)(start[s[1][1] - 1] - start[0]);
+  return r;
 }
 
 // Bin of a code in a unit: about the place it will take, from the place of its
@@ -967,12 +1147,15 @@ __device__ __forceinline__ uint32_t place_bin(const uint32_t* start, int bits, i
   return c0 - start[0] - (uint32_t)b + __umulhi(key << (32 - kMortonBits + bits), size);
 }
 
-__global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
-  const int32_t block = block_id();
-  __shared__ SortLds<false> s;
-  __shared__ int32_t s_range[2];
-  if (*a.status != INT_MAX) return;
-  if (block >= a.plan[a.n_meshes].tunit) return;
+// Half-edge i of a mesh, in the faces' order (meshes that are sorted in one cell).
+__device__ __forceinline__ Item half_edge_item(const BuildArgs& a, const MeshPlan& p, int32_t i) {
+  const int64_t f = (int64_t)p.f0 + i / 3;
+  const int k = i % 3;
+  const uint32_t u = (uint32_t)a.faces[3 * f + k], v = (uint32_t)a.faces[3 * f + (k == 2 ? 0 : k + 1)];
+  return Item{a.ekey[3 * (int64_t)p.f0 + i], u < v ? u : v, u < v ? v : u};
+}
+
+__device__ __forceinline__ void sort_tris(const BuildArgs& a, int32_t block, SortLds<false>& s, int32_t (*s_range)[3]) {
   const int32_t m = a.tumap[block];
   const MeshPlan p = a.plan[m];
   const int bits = cell_bits(p.n);
@@ -983,51 +1166,31 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_tris(BuildArgs a) {
           [&](int32_t i, const Item& e) { a.sk[p.f0 + i] = e.k; a.sv[p.f0 + i] = e.x; });
     return;
   }
-  unit_range(a.start + p.tcell, bits, p.n, block - p.tunit, s_range);
-  const int32_t b = s_range[0], n = s_range[1] - b;
+  const UnitRange u = unit_range(a.start + p.tcell, bits, p.n, block - p.tunit, a.ctr[2] != 0, a.tfirst + p.tunit,
+                                 a.tlast + p.tunit, s_range);
+  const int32_t n = u.e - u.b;
   if (n <= 0) return;
-  uint2* const cells = a.tcells + p.f0 + b;
-  uint32_t *const sk = a.sk + p.f0 + b, *const sv = a.sv + p.f0 + b;
-  auto store = [&](int32_t i, const Item& e) {
-    sk[i] = e.k;
-    sv[i] = e.x;
+  const int64_t g0 = (int64_t)p.f0 + u.b;
+  auto item = [&](int32_t i) {
+    if (bits == 0) return Item{a.key[g0 + i], (uint32_t)(g0 + i), 0u};
+    const uint2 c = a.tcells[g0 + i];
+    return Item{c.x, c.y, 0u};
   };
-  auto bin = [&](const Item& e) { return place_bin(a.start + p.tcell, bits, p.n, b, e.k); };
-  if (n <= kUnitCap)
-    lds_sort<false, false>(
-        s, n,
-        [&](int32_t i) {
-          if (bits == 0) return Item{a.key[p.f0 + i], (uint32_t)(p.f0 + i), 0u};
-          const uint2 c = cells[i];
-          return Item{c.x, c.y, 0u};
-        },
-        bin, store);
-  else
-    split_sort<false>(
-        s, n, [&](int32_t i) { return Item{cells[i].x, cells[i].y, 0u}; },
-        [&](int32_t i, const Item& e) { cells[i] = make_uint2(e.k, e.x); },
-        // the codes' and places' arrays are free by now
-        [&](int32_t i) { return Item{a.key[p.f0 + b + i], a.rank[p.f0 + b + i], 0u}; },
-        [&](int32_t i, const Item& e) { a.key[p.f0 + b + i] = e.k; a.rank[p.f0 + b + i] = e.x; }, store);
+  auto bin = [&](const Item& x) { return place_bin(a.start + p.tcell, bits, p.n, u.b, x.k); };
+  auto store = [&](int32_t i, const Item& x) {
+    a.sk[g0 + i] = x.k;
+    a.sv[g0 + i] = x.x;
+  };
+  if ((u.parts || n > kUnitCap || lds_sort<false>(s, n, item, bin, store) < 0) && threadIdx.x == 0)
+    a.packed[atomicAdd(a.ctr + 3, 1)] = block;
 }
 
-__global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
-  const int32_t block = block_id();
-  __shared__ SortLds<true> s;
-  __shared__ int32_t s_range[2];
-  if (*a.status != INT_MAX) return;
-  if (block >= a.plan[a.n_meshes].eunit) return;
+__device__ __forceinline__ void sort_edges(const BuildArgs& a, int32_t block, SortLds<true>& s, int32_t (*s_range)[3]) {
   const int32_t m = a.emap[block];
   const MeshPlan p = a.plan[m];
   const int32_t n3 = 3 * p.n;
   const int bits = cell_bits(n3);
-  // half-edge i of the mesh, in the faces' order
-  auto face_item = [&](int32_t i) {
-    const int64_t f = (int64_t)p.f0 + i / 3;
-    const int k = i % 3;
-    const uint32_t u = (uint32_t)a.faces[3 * f + k], v = (uint32_t)a.faces[3 * f + (k == 2 ? 0 : k + 1)];
-    return Item{a.ekey[3 * (int64_t)p.f0 + i], u < v ? u : v, u < v ? v : u};
-  };
+  auto face_item = [&](int32_t i) { return half_edge_item(a, p, i); };
   if (n3 <= 64) {
     if (threadIdx.x >= 64) return;
     const int32_t kept = wave_sort<true>(n3, face_item, [&](int32_t i, const Item& e) {
@@ -1040,28 +1203,92 @@ __global__ __launch_bounds__(kLdsBlock) void k_sort_edges(BuildArgs a) {
     }
     return;
   }
-  unit_range(a.start + a.cells_t + p.ecell, bits, n3, block - p.eunit, s_range);
-  const int32_t b = s_range[0], n = s_range[1] - b;
-  const int64_t g0 = 3 * (int64_t)p.f0 + b;
+  const UnitRange u = unit_range(a.start + a.cells_t + p.ecell, bits, n3, block - p.eunit, a.ctr[2] != 0,
+                                 a.efirst + p.eunit, a.elast + p.eunit, s_range);
+  const int32_t n = u.e - u.b;
+  const int64_t g0 = 3 * (int64_t)p.f0 + u.b;
   int32_t kept = 0;
-  auto store = [&](int32_t i, const Item& e) {
-    a.ul[g0 + i] = e.x;
-    a.uh[g0 + i] = e.y;
-  };
-  auto cell_item = [&](int32_t i) { return a.ecells[g0 + i]; };
-  auto item = [&](int32_t i) { return bits != 0 ? cell_item(i) : face_item(i); };
-  auto bin = [&](const Item& e) { return place_bin(a.start + a.cells_t + p.ecell, bits, n3, b, e.k); };
-  if (n > kUnitCap)
-    kept = split_sort<true>(
-        s, n, cell_item, [&](int32_t i, const Item& e) { a.ecells[g0 + i] = e; },
-        // the codes' and places' arrays, and the output's upper half, written last
-        [&](int32_t i) { return Item{a.ekey[g0 + i], a.erank[g0 + i], a.uh[g0 + i]}; },
-        [&](int32_t i, const Item& e) { a.ekey[g0 + i] = e.k; a.erank[g0 + i] = e.x; a.uh[g0 + i] = e.y; }, store);
-  else if (n > 0)
-    kept = lds_sort<true, false>(s, n, item, bin, store);
+  if (n > 0) {
+    auto item = [&](int32_t i) { return bits != 0 ? a.ecells[g0 + i] : face_item(i); };
+    auto bin = [&](const Item& x) { return place_bin(a.start + a.cells_t + p.ecell, bits, n3, u.b, x.k); };
+    auto store = [&](int32_t i, const Item& x) {
+      a.ul[g0 + i] = x.x;
+      a.uh[g0 + i] = x.y;
+    };
+    kept = u.parts || n > kUnitCap ? -1 : lds_sort<true>(s, n, item, bin, store);
+  }
   if (threadIdx.x == 0) {
-    a.ustart[block] = b;
+    a.ustart[block] = u.b;
     a.ucount[block] = kept;
+    if (kept < 0) a.packed[atomicAdd(a.ctr + 3, 1)] = block | (int)0x80000000u;
+  }
+}
+
+// The sort units: of triangles (KIND 0), of half-edges (1), or one after the
+// other (2, half-edges from block `tris` on).
+template <int KIND>
+__global__ __launch_bounds__(kLdsBlock) void k_sort(BuildArgs a, int32_t tris) {
+  __shared__ alignas(16) char s_mem[sizeof(SortLds<KIND != 0>)];
+  __shared__ int32_t s_range[2][3];
+  if (*a.status != INT_MAX) return;
+  const int32_t block = block_id();
+  if (KIND == 0 || (KIND == 2 && block < tris)) {
+    if (block >= a.plan[a.n_meshes].tunit) return;
+    sort_tris(a, block, *reinterpret_cast<SortLds<false>*>(s_mem), s_range);
+  } else {
+    const int32_t unit = KIND == 2 ? block - tris : block;
+    if (unit >= a.plan[a.n_meshes].eunit) return;
+    sort_edges(a, unit, *reinterpret_cast<SortLds<true>*>(s_mem), s_range);
+  }
+}
+
+// The units that k_sort leaves: parts of overfull cells, more items
+// than LDS holds, or codes packed together (a mesh that is small against its
+// box).  Every bit of the code may be equal there, so bins do not help, and
+// comparing all items of a unit takes 370 us where this network takes some 30
+// (build of 1,500 triangles of one code: 544 us by comparing, so 248 us).
+__global__ __launch_bounds__(kLdsBlock) void k_sort_packed(BuildArgs a) {
+  __shared__ SortLds<true> s;
+  __shared__ int32_t s_range[2][3];
+  if (*a.status != INT_MAX) return;
+  for (int32_t w = blockIdx.x; w < a.ctr[3]; w += gridDim.x) {
+    const bool edges = a.packed[w] < 0;
+    const int32_t unit = a.packed[w] & 0x7fffffff;
+    const MeshPlan p = a.plan[edges ? a.emap[unit] : a.tumap[unit]];
+    const int32_t n_all = edges ? 3 * p.n : p.n, bits = cell_bits(n_all);
+    const UnitRange u =
+        edges ? unit_range(a.start + a.cells_t + p.ecell, bits, n_all, unit - p.eunit, true, a.efirst + p.eunit,
+                           a.elast + p.eunit, s_range)
+              : unit_range(a.start + p.tcell, bits, n_all, unit - p.tunit, true, a.tfirst + p.tunit, a.tlast + p.tunit,
+                           s_range);
+    int32_t kept = 0;
+    // at most two rounds: the unit, or what comes before its last cell and that
+    for (int32_t b = u.b, e = u.cut; b < u.e; b = e, e = u.e) {
+      if (b == e) continue;
+      const int32_t n = e - b <= kUnitCap ? e - b : 1;  // (more than LDS holds: copies of one half-edge)
+      const int64_t g0 = (edges ? 3 : 1) * (int64_t)p.f0 + b, o0 = (edges ? 3 : 1) * (int64_t)p.f0 + u.b + kept;
+      kept += network_sort<true>(
+          s, n,
+          [&](int32_t i) {
+            if (!edges) {
+              if (bits == 0) return Item{a.key[g0 + i], (uint32_t)(g0 + i), 0u};
+              const uint2 c = a.tcells[g0 + i];
+              return Item{c.x, c.y, 0u};
+            }
+            return bits != 0 ? a.ecells[g0 + i] : half_edge_item(a, p, b + i);
+          },
+          [&](int32_t i, const Item& x) {
+            if (edges) {
+              a.ul[o0 + i] = x.x;
+              a.uh[o0 + i] = x.y;
+            } else {
+              a.sk[o0 + i] = x.k;
+              a.sv[o0 + i] = x.x;
+            }
+          });
+    }
+    if (edges && threadIdx.x == 0) a.ucount[unit] = kept;
+    __syncthreads();  // s_range is written again
   }
 }
 
@@ -1399,10 +1626,6 @@ __device__ __forceinline__ void collapse_group(const BuildArgs& a, int32_t node0
     else if (cn <= L) ch[c] = leaf_ref(f0 + cf, cn);
     else cx = node;
   }
-}
-
-__device__ __forceinline__ int lanes_before(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // Child c of the wide node at `slot` of a mesh is the one at slot `child`.
@@ -1900,6 +2123,9 @@ Layout blob_layout(int64_t M, int64_t F, int W, int L) {
 // Counting chunks: meshes of more than kUnitCap half-edges only.
 int64_t code_chunks(int64_t F) { return F / (kUnitCap / 3) + 1; }
 
+// Cells of more than kUnitCap triangles or half-edges, at most.
+int64_t over_cells(int64_t F) { return F / (kUnitCap + 1) + 3 * F / (kUnitCap + 1); }
+
 // Carves the workspace; with base == nullptr only measures.
 void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
   const int64_t E3 = 3 * F;
@@ -1935,6 +2161,12 @@ void carve_ws(Carve& cv, BuildArgs& a, int64_t M, int64_t F) {
   a.ecells = cv.take<Item>(E3);
   a.ul = cv.take<uint32_t>(E3);
   a.uh = cv.take<uint32_t>(E3);
+  a.over = cv.take<int2>(over_cells(F));
+  a.packed = cv.take<int32_t>(tu + eu);
+  a.tfirst = cv.take<int32_t>(tu);
+  a.tlast = cv.take<int32_t>(tu);
+  a.efirst = cv.take<int32_t>(eu);
+  a.elast = cv.take<int32_t>(eu);
   a.ustart = cv.take<int32_t>(eu);
   a.ucount = cv.take<int32_t>(eu);
   a.uoff = cv.take<int32_t>(eu);
@@ -2050,12 +2282,18 @@ extern "C" int build_mesh_bvh(const float* verts, const int64_t* vert_off, const
   }
   if (M > 0) PR_W(k_desc, gM, kBlock);
   if (F > 0) {
-    hipLaunchKernelGGL(k_codes, grid_of(tc), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_codes_cells, dim3((unsigned)code_chunks(F)), dim3(1024), 0, s, a);
     PR_HIP(device_exclusive_scan((const uint32_t*)a.hist, a.start, a.cells_all, a.tsum, (int64_t*)nullptr, s));
     hipLaunchKernelGGL(k_to_cells, grid_of(tc), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_tris, grid_of(tu), dim3(kLdsBlock), 0, s, a);
-    hipLaunchKernelGGL(k_sort_edges, grid_of(eu), dim3(kLdsBlock), 0, s, a);
+    const int64_t splits = over_cells(F) < 512 ? over_cells(F) : 512;
+    if (splits > 0) hipLaunchKernelGGL(k_split, dim3((unsigned)splits), dim3(kSplitBlock), 0, s, a);
+    if (tu + eu <= kSortOne) {
+      hipLaunchKernelGGL(k_sort<2>, grid_of(tu + eu), dim3(kLdsBlock), 0, s, a, (int32_t)tu);
+    } else {
+      hipLaunchKernelGGL(k_sort<0>, grid_of(tu), dim3(kLdsBlock), 0, s, a, 0);
+      hipLaunchKernelGGL(k_sort<1>, grid_of(eu), dim3(kLdsBlock), 0, s, a, 0);
+    }
+    hipLaunchKernelGGL(k_sort_packed, dim3((unsigned)(tu + eu < 1024 ? tu + eu : 1024)), dim3(kLdsBlock), 0, s, a);
     hipLaunchKernelGGL(k_tree, grid_of(tc), dim3(kTreeBlock), 0, s, a);
     const int tops = (int)(M < kTops ? M : kTops);
     hipLaunchKernelGGL(k_tree_top, dim3(tops), dim3(kTopUnits), 0, s, a);
