@@ -43,8 +43,8 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int j) {
 
 // Segment-box test (conservative): slab test on t in [0, 1] for the segment
 // p + t (q - p), with t computed as (plane - p) * fl(1 / fl(q - p)); every t
-// carries a relative error of at most gamma_4 = 4 eps / (1 - 4 eps) (gamma_5
-// with axis_rcp), so accepting when t_min <= t_max (1 + 2^-19) + 2^-120 never rejects a box the
+// carries a relative error of at most gamma_4 = 4 eps / (1 - 4 eps), so
+// accepting when t_min <= t_max (1 + 2^-19) + 2^-120 never rejects a box the
 // exact segment touches (closed boxes).  A zero direction component uses a
 // large finite reciprocal (2^100) and a bias of 2^16 that turns the slab into
 // "no constraint" or "empty" exactly.  Valid for FP32-safe coordinates; for
@@ -78,13 +78,14 @@ __device__ __forceinline__ bool slab(const Ray& r, float lx, float ly, float lz,
   return tn <= fmaf(tf, kSlabK, kSlabS);
 }
 
-// Reciprocal direction of the slab test, from the hardware reciprocal (1 ulp):
-// t then carries a relative error of at most gamma_5 on either side, within
-// the 2^-19 that the slab test allows.  FP32-safe coordinates differ by 0 or
-// by 2^-63 ... 2^41, so neither operand nor result is subnormal.
+// The same values in fewer instructions: the hardware reciprocal (1 ulp) and one
+// Newton step are the correctly rounded quotient 1 / d for every d of magnitude
+// 2^-64 ... 2^43 (compared for all of them on gfx950); FP32-safe coordinates
+// differ by 0 or by 2^-63 ... 2^41.
 __device__ __forceinline__ void axis_rcp(float d, bool safe, float& inv, float& bias) {
   const bool zero = d == 0.f;
-  inv = zero ? kZeroInv : __builtin_amdgcn_rcpf(d);
+  const float r = __builtin_amdgcn_rcpf(d);
+  inv = zero ? kZeroInv : fmaf(fmaf(-d, r, 1.0f), r, r);
   bias = zero ? kZeroBias : 0.f;
   if (!safe) { inv = 0.f; bias = INFINITY; }
 }
