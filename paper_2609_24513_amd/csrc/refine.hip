@@ -429,7 +429,8 @@ __device__ __forceinline__ void grid_tier(f3 p, f3 q, const float* tris, int32_t
 }
 
 // Wave sum of a per-lane count.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+template <typename T>
+__device__ __forceinline__ T wave_sum(T x) {
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
   return x;
 }
@@ -1619,6 +1620,13 @@ __global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(Refine
   uint64_t acc = 0;   // lane k: counter k of the wave's statistics
   uint32_t accm = 0;  // lane k: maximum k
   uint32_t n32 = 0, ngrid = 0;  // per lane: FP32-uncertain tests, those decided in place
+  auto add_uncertain = [&]() {
+    const uint64_t a = wave_sum((uint64_t)n32), g = wave_sum((uint64_t)ngrid);
+    if (lane == S_AMB32) acc += a;
+    if (lane == S_EXACT) acc += g;
+    n32 = 0;
+    ngrid = 0;
+  };
 
   // The wave's queues: its block's own first, then the others of its XCD (with
   // fewer blocks than queues: blockIdx, blockIdx + gridDim, ...).  Their fill
@@ -1758,7 +1766,8 @@ __global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(Refine
     WaveStack stk;
     stk.ref = 0; stk.mlo = 0; stk.mhi = 0;
     stk.lref = s_ref[wv]; stk.lmask = s_mask[wv]; stk.top = 0;
-    uint32_t visits = 0, leaf_tris = 0, tests = 0;
+    uint32_t visits = 0, leaf_tris = 0;  // at most one of each node and triangle
+    uint64_t tests = 0;
     int32_t from_root = 1;
     if (below) {
       // second-level nodes are the root's inner children only; a root with a
@@ -1820,7 +1829,7 @@ __global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(Refine
         const int cnt = (~ref & 7) + 1;
         const bool on = (nm >> lane) & 1ull;
         leaf_tris = (uint32_t)uni((int32_t)leaf_tris + cnt);
-        tests = (uint32_t)uni((int32_t)tests + __popcll(nm) * cnt);
+        tests = uni64(tests + (uint32_t)(__popcll(nm) * cnt));
         uint32_t hitbits = 0, ambbits = 0;
         const cptr_t<float> tp = cview(ttris) + 9 * (int64_t)first;
         // the next triangle's coordinates load while one is tested (the array
@@ -1883,9 +1892,10 @@ __global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(Refine
     }
     inc = lane_write((int32_t)visits, S_VISIT, inc);
     inc = lane_write((int32_t)leaf_tris, S_TRIF, inc);
-    inc = lane_write((int32_t)tests, S_TESTS, inc);
-    if (PREC == 1) inc = lane_write((int32_t)tests, S_EXACT, inc);
     acc += (uint32_t)inc;
+    if (lane == S_TESTS || (PREC == 1 && lane == S_EXACT)) acc += tests;
+    // (a group adds less than 2^28 to a lane's)
+    if (PREC != 1 && ballot(((n32 | ngrid) >> 24) != 0)) add_uncertain();
     int32_t mx = 0;
     mx = lane_write((int32_t)visits, S_MAXV, mx);
     mx = lane_write((int32_t)leaf_tris, S_MAXL, mx);
@@ -1895,11 +1905,7 @@ __global__ __launch_bounds__(kBlock, packet_waves(W, PREC)) void k_packet(Refine
       __hip_atomic_fetch_add(&s_share.busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   }
-  if (PREC != 1 && ballot(n32 != 0)) {
-    const uint32_t a = wave_sum(n32), g = wave_sum(ngrid);
-    if (lane == S_AMB32) acc += a;
-    if (lane == S_EXACT) acc += g;
-  }
+  if (PREC != 1 && ballot(n32 != 0)) add_uncertain();
   WaveStats st;
   st.acc = lane == S_MAXV || lane == S_MAXL ? (uint64_t)accm : acc;
   flush_stats(st, ra);
