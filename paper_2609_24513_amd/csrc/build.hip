@@ -267,9 +267,8 @@ __device__ __forceinline__ bool plan_entries(const BuildArgs& a, int64_t m, bool
       p.n = (int32_t)(f1 - f0);
     }
   }
-  const uint32_t w1 = (uint32_t)a.width - 1u, l1 = (uint32_t)a.leaf + 1u;
   const uint32_t n = (uint32_t)p.n, chunks = (n + kTreeChunk - 1) / kTreeChunk;
-  const uint32_t nodes = n == 0 ? 0u : (n <= (uint32_t)a.leaf ? 1u : (n - 1) / w1 + n / l1 + 2u);  // nodes_bound
+  const uint32_t nodes = nodes_bound(n, (uint32_t)a.width, (uint32_t)a.leaf);
   auto two = [](uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; };
   c[0] = two(chunks, (n + kUnit - 1) / kUnit);
   c[1] = two((3 * n + kUnit - 1) / kUnit, n > (uint32_t)kTreeChunk ? chunks : 0u);

@@ -93,11 +93,11 @@ __host__ __device__ inline int32_t leaf_ref(int32_t first, int32_t count) {
   return ~((first << 3) | (count - 1));
 }
 
-// Wide nodes that the build may create for a mesh of n triangles: full nodes
-// consume W-1 binary nodes of more than L triangles, partial nodes own
+// Wide nodes that the build may create for a mesh of n < 2^28 triangles: full
+// nodes consume W-1 binary nodes of more than L triangles, partial nodes own
 // disjoint subtrees of more than L triangles.
-__host__ __device__ inline int64_t nodes_bound(int64_t n, int w, int l) {
-  if (n <= 0) return 0;
+__host__ __device__ inline uint32_t nodes_bound(uint32_t n, uint32_t w, uint32_t l) {
+  if (n == 0) return 0;
   if (n <= l) return 1;
   return (n - 1) / (w - 1) + n / (l + 1) + 2;
 }
