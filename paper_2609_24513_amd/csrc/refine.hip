@@ -1308,19 +1308,12 @@ __global__ __launch_bounds__(kBlock, 7) void k_cull(RefineArgs ra) {
 // looks (far beyond any traversal) reports PR_E_DEVICE and leaves.
 constexpr uint32_t kHelpSpinLimit = 1u << 22;
 
-template <int W, int PREC>
-__device__ void block_help(const BlobView& A, const BlobView& B, const RefineArgs& ra, BlockShare* sh, const WaveLds& lds,
-                           WaveStats& st) {
+// Waits for a task of the block's list.  Returns false when no wave of the
+// block is on its queues or tracing a task and the list is drained (or, never
+// for a valid launch, after kHelpSpinLimit looks: status PR_E_DEVICE).
+__device__ bool take_task(BlockShare* sh, int32_t* status, int4& t, uint64_t& m) {
   const int lane = threadIdx.x & 63;
-  if (lane == 0) {
-    __hip_atomic_fetch_add(&sh->idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_add(&sh->active, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-  for (uint32_t spin = 0;; ++spin) {
-    if (spin >= kHelpSpinLimit) {
-      if (lane == 0) atomicMin(ra.status, (int32_t)PR_E_DEVICE);
-      break;
-    }
+  for (uint32_t spin = 0; spin < kHelpSpinLimit; ++spin) {
     const uint32_t tail = lds_load(&sh->tail), head = lds_load(&sh->head);
     const uint32_t n = tail < kBlkTasks ? tail : kBlkTasks;
     if (uni((int32_t)(head < n))) {
@@ -1330,7 +1323,7 @@ __device__ void block_help(const BlobView& A, const BlobView& B, const RefineArg
       uint32_t got = ~0u;
       if (lane == 0) {
         uint32_t h = lds_load(&sh->head);
-        for (int t = 0; t < 64; ++t) {
+        for (int k = 0; k < 64; ++k) {
           const uint32_t tl = lds_load(&sh->tail);
           if (h >= (tl < kBlkTasks ? tl : kBlkTasks)) break;
           uint32_t e = h;
@@ -1355,42 +1348,53 @@ __device__ void block_help(const BlobView& A, const BlobView& B, const RefineArg
         if (!ok) __builtin_amdgcn_s_sleep(1);
       }
       if (!ok) {
-        if (lane == 0) {
-          atomicMin(ra.status, (int32_t)PR_E_DEVICE);
-          __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        if (lane == 0) __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         break;
       }
-      const int4 t = sh->task[got];
-      const uint64_t m = sh->mask[got];
-      const int32_t pair = t.y >> 1, dir = t.y & 1;
-      const BlobView& S = dir == 0 ? A : B;
-      const BlobView& T = dir == 0 ? B : A;
-      const float tb_unused[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // the root was tested when the group started
-      TraceOpts o;
-      o.lds = lds;
-      o.start_mask = uni64(m);
-      o.sh = sh;
-      trace_core<W, PREC>(S, T, uni(t.x), uni(t.w) & 0xff, uni(t.z), tb_unused, pair, dir, (uni(t.w) & 256) != 0, ra,
-                          st, o);
-      if (lane == 0) {
-        __hip_atomic_fetch_add(&sh->idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-      spin = 0;
-      continue;
+      const int4 e = sh->task[got];
+      t = make_int4(uni(e.x), uni(e.y), uni(e.z), uni(e.w));
+      m = uni64(sh->mask[got]);
+      return true;
     }
     // nothing to take: leave once no wave of the block is on its queues or
     // tracing a task (read first) and the list is drained (read after)
     if (uni((int32_t)(__hip_atomic_load(&sh->active, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u &&
                       __hip_atomic_load(&sh->busy, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u))) {
       const uint32_t tl = lds_load(&sh->tail);
-      if (uni((int32_t)(lds_load(&sh->head) >= (tl < kBlkTasks ? tl : kBlkTasks)))) break;
+      if (uni((int32_t)(lds_load(&sh->head) >= (tl < kBlkTasks ? tl : kBlkTasks)))) return false;
     }
     __builtin_amdgcn_s_sleep(2);
   }
+  if (lane == 0) atomicMin(status, (int32_t)PR_E_DEVICE);
+  return false;
 }
 
+template <int W, int PREC>
+__device__ void block_help(const BlobView& A, const BlobView& B, const RefineArgs& ra, BlockShare* sh, const WaveLds& lds,
+                           WaveStats& st) {
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) {
+    __hip_atomic_fetch_add(&sh->idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(&sh->active, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  int4 t;
+  uint64_t m;
+  while (uni(take_task(sh, ra.status, t, m) ? 1 : 0)) {
+    const int32_t pair = t.y >> 1, dir = t.y & 1;
+    const BlobView& S = dir == 0 ? A : B;
+    const BlobView& T = dir == 0 ? B : A;
+    const float tb_unused[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // the root was tested when the group started
+    TraceOpts o;
+    o.lds = lds;
+    o.start_mask = m;
+    o.sh = sh;
+    trace_core<W, PREC>(S, T, t.x, t.w & 0xff, t.z, tb_unused, pair, dir, (t.w & 256) != 0, ra, st, o);
+    if (lane == 0) {
+      __hip_atomic_fetch_add(&sh->idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+}
 
 // Target-size buckets of the automatic schedule (triangles of the target
 // mesh: below 2^10, 2^13, 2^16, and larger) and the per-bucket limit on the
@@ -1511,67 +1515,6 @@ __global__ __launch_bounds__(kBlock, SCHED == 1 ? 6 : 5) void k_trace(RefineArgs
 // when they meet the group box).  The latency of a step is shared by its
 // nodes, but the order is no longer depth first, hits come later and twice
 // the nodes and triangles are tested (touching pairs 1.7 times the time).
-
-// Waits for a task of the block's list.  Returns false when no wave of the
-// block is on its queues or tracing a task and the list is drained (or, never
-// for a valid launch, after kHelpSpinLimit looks: status PR_E_DEVICE).
-__device__ bool take_task(BlockShare* sh, int32_t* status, int4& t, uint64_t& m) {
-  const int lane = threadIdx.x & 63;
-  for (uint32_t spin = 0; spin < kHelpSpinLimit; ++spin) {
-    const uint32_t tail = lds_load(&sh->tail), head = lds_load(&sh->head);
-    const uint32_t n = tail < kBlkTasks ? tail : kBlkTasks;
-    if (uni((int32_t)(head < n))) {
-      // announce the attempt before claiming: a wave deciding whether to
-      // leave reads the busy count before the list
-      if (lane == 0) __hip_atomic_fetch_add(&sh->busy, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-      uint32_t got = ~0u;
-      if (lane == 0) {
-        uint32_t h = lds_load(&sh->head);
-        for (int k = 0; k < 64; ++k) {
-          const uint32_t tl = lds_load(&sh->tail);
-          if (h >= (tl < kBlkTasks ? tl : kBlkTasks)) break;
-          uint32_t e = h;
-          if (__hip_atomic_compare_exchange_strong(&sh->head, &e, h + 1, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP)) {
-            got = h;
-            break;
-          }
-          h = e;
-        }
-      }
-      got = (uint32_t)uni((int32_t)got);
-      if (got == ~0u) {
-        if (lane == 0) __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        continue;
-      }
-      if (lane == 0) __hip_atomic_fetch_add(&sh->idle, ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      // the slot was reserved by a wave of this block that writes it next
-      uint32_t ok = 0;
-      for (uint32_t w = 0; w < kHelpSpinLimit && !ok; ++w) {
-        ok = (uint32_t)uni((int32_t)__hip_atomic_load(&sh->ready[got], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-        if (!ok) __builtin_amdgcn_s_sleep(1);
-      }
-      if (!ok) {
-        if (lane == 0) __hip_atomic_fetch_add(&sh->busy, ~0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        break;
-      }
-      const int4 e = sh->task[got];
-      t = make_int4(uni(e.x), uni(e.y), uni(e.z), uni(e.w));
-      m = uni64(sh->mask[got]);
-      return true;
-    }
-    // nothing to take: leave once no wave of the block is on its queues or
-    // tracing a task (read first) and the list is drained (read after)
-    if (uni((int32_t)(__hip_atomic_load(&sh->active, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u &&
-                      __hip_atomic_load(&sh->busy, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u))) {
-      const uint32_t tl = lds_load(&sh->tail);
-      if (uni((int32_t)(lds_load(&sh->head) >= (tl < kBlkTasks ? tl : kBlkTasks)))) return false;
-    }
-    __builtin_amdgcn_s_sleep(2);
-  }
-  if (lane == 0) atomicMin(status, (int32_t)PR_E_DEVICE);
-  return false;
-}
 
 // Survivors popped at a time from a queue of n entries that `waves` waves
 // drain, as a shift.  A wave holds a batch while others find the hits that
