@@ -280,38 +280,44 @@ class JoinServer:
         self._t0 = t0
         done = 0
         n = len(todo)
-        while done < n:
-            now = time.perf_counter() - t0
-            while todo and (todo[0].t_arrival <= now or not realtime):
-                r = todo.popleft()
-                if not realtime:
-                    r.t_arrival = now
-                pending.append(r)
-            progressed = False
-            for slot in self.slots:
-                if slot.phase and slot.event.query():
-                    k = len(slot.reqs)
-                    self._finish(slot, time.perf_counter() - t0)
-                    done += k
-                    progressed = True
-            for slot in self.slots:
-                if slot.phase == 0 and pending:
-                    batch = []
-                    while pending and len(batch) < self.max_req:
-                        batch.append(pending.popleft())
-                    if batch:
-                        self.in_flight_bytes += self.slot_bytes
-                        self._start(slot, batch)
-                        self.batches += 1
+        try:
+            while done < n:
+                now = time.perf_counter() - t0
+                while todo and (todo[0].t_arrival <= now or not realtime):
+                    r = todo.popleft()
+                    if not realtime:
+                        r.t_arrival = now
+                    pending.append(r)
+                progressed = False
+                for slot in self.slots:
+                    if slot.phase and slot.event.query():
+                        k = len(slot.reqs)
+                        self._finish(slot, time.perf_counter() - t0)
+                        done += k
                         progressed = True
-                    busy = sum(1 for s in self.slots if s.phase)
-                    self.max_in_flight = max(self.max_in_flight, busy)
-            if not progressed:
-                # the loop spins (yielding the interpreter lock each turn), so
-                # that arrivals and completions are picked up at once: a timed
-                # sleep would add its length and the timer slack to the
-                # latency of a request arriving meanwhile
-                time.sleep(0)
+                for slot in self.slots:
+                    if slot.phase == 0 and pending:
+                        batch = []
+                        while pending and len(batch) < self.max_req:
+                            batch.append(pending.popleft())
+                        if batch:
+                            self.in_flight_bytes += self.slot_bytes
+                            self._start(slot, batch)
+                            self.batches += 1
+                            progressed = True
+                        busy = sum(1 for s in self.slots if s.phase)
+                        self.max_in_flight = max(self.max_in_flight, busy)
+                if not progressed:
+                    # the loop spins (yielding the interpreter lock each turn), so
+                    # that arrivals and completions are picked up at once: a timed
+                    # sleep would add its length and the timer slack to the
+                    # latency of a request arriving meanwhile
+                    time.sleep(0)
+        except BaseException:
+            # batches in flight write the slots' buffers (device and pinned), which may die with the server
+            for slot in self.slots:
+                slot.stream.synchronize()
+            raise
         return list(trace)
 
     def query_alone(self, box: np.ndarray):
