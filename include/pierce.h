@@ -137,7 +137,7 @@ int blob_coord_exponents(const void* blob, int32_t* exps, void* stream);
  * closed boxes overlap on all three axes (touching boxes are candidates), and,
  * when query_box is given, whose boxes both overlap the closed query box and
  * whose common box part meets it.  Output is sorted by (i, j).
- *  query_box dev f32[6] or NULL
+ *  query_box dev f32[6] or NULL (an inverted box is empty: no pairs)
  *  pairs     dev i32[cap][2]   out: first min(total, cap) pairs
  *  dev_count dev i64[1]        out: exact total (may exceed cap; the caller
  *                              relaunches with a larger buffer, the paper's

@@ -10,9 +10,9 @@
 //     (ties by face index), and its half-edges by the Morton code of their
 //     midpoint (ties by vertex ids): a counting pass over cells (the code's
 //     top bits), then units of consecutive cells that fit LDS are sorted
-//     there.  Copies of one edge share midpoint and ids, so they end up side
-//     by side and are merged in the same kernel (Section 3.1: duplicate edges
-//     of one mesh are merged);
+//     there, cells that do not fit divided before.  Copies of one edge share
+//     midpoint and ids, so they end up side by side and are merged in the same
+//     kernel (Section 3.1: duplicate edges of one mesh are merged);
 //  4. per mesh, a binary radix tree over the sorted codes (Karras 2012,
 //     "Maximizing parallelism in the construction of BVHs, octrees, and k-d
 //     trees"; numbering of nodes from there), ties broken by position, with

@@ -5,16 +5,17 @@
 // wide BVH (Section 3.1 Steps I-II; both directions as in Section 3.2).  The
 // persistent pass first culls every group of every (pair, direction) against
 // the top of the target tree (k_cull), then persistent waves trace the
-// surviving groups (k_trace), in one of two ways:
-//  * wave-per-pair (packet): the wave walks the tree together, one segment
-//    per lane; a node is visited once for the whole wave, every still-active
+// surviving groups, in one of two ways:
+//  * wave-per-pair (packet; k_packet, or k_trace with the LDS-first stack, the
+//    continuation pass or the automatic schedule): the wave walks the tree
+//    together, one segment per lane; a node is visited once for the whole wave, every still-active
 //    lane tests its segment against all W child boxes, and children hit by
 //    any lane are pushed with the mask of lanes that hit them onto a per-wave
 //    stack (VGPR lanes, then LDS).  At a leaf the lanes of the mask test
 //    their segment against each triangle.
-//  * wave-per-segment: the lanes are W children x 64/W segment slots; each
-//    slot walks its own segment's path with its own stack in LDS, its W lanes
-//    testing the W children of its current node (or W leaf triangles) at
+//  * wave-per-segment (k_trace): the lanes are W children x 64/W segment
+//    slots; each slot walks its own segment's path with its own stack in LDS,
+//    its W lanes testing the W children of its current node (or W leaf triangles) at
 //    once.  Suited to groups with few segments near the target, whose paths
 //    diverge.
 // The automatic schedule picks per group, by how many of its segments meet
@@ -1507,14 +1508,14 @@ __global__ __launch_bounds__(kBlock, SCHED == 1 ? 6 : 5) void k_trace(RefineArgs
 // Long runs are bound by vector instructions, short ones by the chain of
 // dependent loads of a group.  Against k_trace's form of the same walk
 // everything but the tests is scalar (one traversal in the code for popped
-// groups and handed-over subtrees, no spilled pointers, no 64-bit remainder a
-// pop, no cross-lane sums a group): 50,000 mixed pairs W = 8, L = 1 cull +
+// groups and handed-over subtrees, pointers read again from the headers where
+// they are used, no 64-bit remainder a pop, no cross-lane sums a group): 50,000 mixed pairs W = 8, L = 1 cull +
 // trace 677 -> 622 us, 2,000 touching pairs 319 -> 211 us, 4,999 nested pairs
 // 323 -> 260 us, 16,727 nucleus-vessel pairs 167 -> 150 us.  Measured slower:
 // taking up to 64 / W pending nodes at once (boxes one per lane, broadcast
 // when they meet the group box).  The latency of a step is shared by its
 // nodes, but the order is no longer depth first, hits come later and twice
-// the nodes and triangles are tested (touching pairs 1.7 times the time).
+// the triangles are tested (touching pairs, a whole step: k_trace 425, so 693 us).
 
 // Survivors popped at a time from a queue of n entries that `waves` waves
 // drain, as a shift.  A wave holds a batch while others find the hits that
@@ -2218,8 +2219,8 @@ int launch(RefineArgs& ra, const pr_refine_params* prm, hipStream_t s) {
     const int cus = cu_count(dev);
     // the automatic schedule with an all-zero table is the packet traversal
     const int sched = prm->schedule == 0 && ra.seg_table == 0u ? 1 : prm->schedule;
-    // the packet traversal in batches of nodes; k_trace keeps the wave-per-pair form for
-    // the LDS-first stack and for the continuation pass
+    // k_packet, one node at a time; k_trace keeps the wave-per-pair form for the
+    // LDS-first stack and for the continuation pass
     const bool packet = sched == 1 && !ra.lds_stack && ra.budget == 0;
     const int per = packet       ? blocks_per_cu<k_packet<W, PREC>>(dev)
                     : sched == 1 ? blocks_per_cu<k_trace<W, PREC, 1>>(dev)
